@@ -7,7 +7,9 @@ namespace zipccl {
 namespace {
 
 /* The table for a given sigma by Eq.5 / Eq.2 (erf in FP64), exactly as the host builder does; a sigma that is
- * not positive and finite selects the lowest window.  One thread. */
+ * not positive and finite selects the lowest window.  Called by all 64 lanes of one wave with the same sigma: the
+ * four values of erf are independent, so lanes 0..3 take one each (one after the other in a single lane they
+ * are most of a small estimate's last microseconds). */
 __device__ void table_from_sigma(double sigma, uint8_t* table, double* sigma_out)
 {
     uint32_t e0 = 1;
@@ -15,12 +17,15 @@ __device__ void table_from_sigma(double sigma, uint8_t* table, double* sigma_out
         const double x_opt = log2(sigma) + 0.5 * log2(14.0 * log(2.0) / 16383.0);     /* Eq.5 */
         const int lo = (int)floor(x_opt), hi = (int)ceil(x_opt);
         const double s2 = sigma * sqrt(2.0);
-        const double p_lo = erf(ldexp(1.0, lo + 7) / s2) - erf(ldexp(1.0, lo) / s2);    /* Eq.2 */
-        const double p_hi = erf(ldexp(1.0, hi + 7) / s2) - erf(ldexp(1.0, hi) / s2);
+        const uint32_t l = lane_id();
+        const double v = erf(ldexp(1.0, ((l & 2u) ? hi : lo) + ((l & 1u) ? 0 : 7)) / s2);
+        const double p_lo = __shfl(v, 0, 64) - __shfl(v, 1, 64);                      /* Eq.2 */
+        const double p_hi = __shfl(v, 2, 64) - __shfl(v, 3, 64);
         int e = (p_hi > p_lo ? hi : lo) + 127;
         e = e < 1 ? 1 : (e > 248 ? 248 : e);
         e0 = (uint32_t)e;
     }
+    if (lane_id() != 0) return;
     table[0] = 0;
     for (uint32_t k = 1; k <= 7; ++k) table[k] = (uint8_t)(e0 + k - 1);
     if (sigma_out) *sigma_out = sigma;
@@ -103,7 +108,7 @@ __global__ __launch_bounds__(kThreads) void k_estimate_finish(const MomentArgs a
         if (threadIdx.x < d) { s_sum[threadIdx.x] += s_sum[threadIdx.x + d]; s_sq[threadIdx.x] += s_sq[threadIdx.x + d]; }
         __syncthreads();
     }
-    if (threadIdx.x != 0) return;
+    if (threadIdx.x >= 64) return;
     const double N = (double)a.n;
     double sigma = __longlong_as_double(0x7FF8000000000000ll);          /* NaN for fewer than two values */
     if (a.n >= 2) {
@@ -116,37 +121,86 @@ __global__ __launch_bounds__(kThreads) void k_estimate_finish(const MomentArgs a
 /*
  * Robust sigma (for Eq.5 / Eq.2 when the tensor is not the zero-mean Gaussian of section 4.1: outlier
  * channels, LayerNorm gains among matrix weights): the median of |w| over Phi^-1(3/4).  The median is taken
- * over the 15-bit magnitudes of the values' high 16-bit words, so it is a count: k_magnitude_hist builds the
- * histogram of all 32768 magnitudes (about one workgroup per compute unit, the whole histogram in its LDS, one
- * LDS atomic per value; nonzero bins are added to the chunk's 64-bit histogram in the workspace, which
- * k_clear_hist zeroed), k_robust_finish finds the bin of rank (K - 1) / 2 among the K magnitudes that are neither
- * zero nor Inf/NaN.  Integer work until the final division: the result does not depend on any order.
- * Both take several chunks at once (one histogram and one table per chunk); the whole tensor is one chunk.
+ * over the 15-bit magnitudes of the values' high 16-bit words, so it is a count: a histogram of all 32768
+ * magnitudes, in which the bin of rank (K - 1) / 2 among the K magnitudes that are neither zero nor Inf/NaN is
+ * looked for.  Integer work until the final division: the result does not depend on any order.  Two forms,
+ * each for one or more chunks at once (one histogram and one table per chunk; the whole tensor is one chunk):
+ *   large    k_clear_hist zeroes one histogram per chunk in the workspace, k_magnitude_hist (or its sampled form)
+ *            adds to it what about one workgroup per compute unit has counted in its LDS, k_robust_finish looks
+ *            for the rank.  2^24 bf16 values, one chunk: 2.0 + 11.6 + 3.7 us (2.4 of each is the launch; the
+ *            histogram kernel reads for 3.3, counts for 2.4 beyond that and flushes for 4).  With 64-bit counts
+ *            zeroed, flushed and read twice over by the finish, whose one thread then took four erf in a row, the
+ *            same three kernels were 3.0 + 13.8 + 11.2 us.
+ *   small    (at most kFusedGroups groups to count in every chunk) k_robust_chunk_fused: one workgroup per chunk
+ *            does it all in one kernel.
  */
 constexpr uint32_t kMagBins = 32768;
 constexpr uint32_t kHistThreads = 1024;
+constexpr uint32_t kHistWaves = kHistThreads / 64;
+constexpr uint32_t kFirstNonFinite = 0x7F80u;                /* magnitudes from here on are Inf / NaN */
 
-/* One workgroup per chunk's histogram, 64 stores per thread: with the same bytes spread over 16 or 32 times as many
- * workgroups the kernel took 5 us longer for 64 histograms (the launch, not the memory, was its limit). */
-constexpr uint32_t kClearThreads = 256, kClearPer = 64;  /* 16-byte stores per thread */
+/* Counts of a chunk: 32 bits unless the chunk holds 2^32 values or more (only a whole tensor can). */
+template <typename CNT> __device__ __forceinline__ CNT scan_of(CNT x);
 
+/* Inclusive prefix sum of 64-bit values over the 64 lanes of a wave, exact, without going through LDS: the four
+ * 16-bit limbs are scanned separately with DPP (each limb sum stays below 2^22) and put together again. */
+template <> __device__ __forceinline__ unsigned long long scan_of(unsigned long long x)
+{
+    unsigned long long r = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k)
+        r += (unsigned long long)wave_incl_scan((uint32_t)(x >> (16 * k)) & 0xFFFFu) << (16 * k);
+    return r;
+}
+template <> __device__ __forceinline__ uint32_t scan_of(uint32_t x) { return wave_incl_scan(x); }
+
+/* zero of the bins that do not count: 0 (zero) and 0x7F80.. (Inf / NaN) */
+__device__ __forceinline__ bool bin_counts(uint32_t b) { return b != 0u && b < kFirstNonFinite; }
+
+constexpr uint32_t kClearThreads = 1024;
+
+/* One workgroup per histogram, 8 or 16 16-byte stores per thread (spread over 16 or 32 times as many workgroups the
+ * kernel took 5 us longer for 64 histograms: the launch, not the memory, is its limit). */
+template <typename CNT>
 __global__ __launch_bounds__(kClearThreads) void k_clear_hist(unsigned long long* hist)
 {
     /* grid = chunks (the workspace is 8-byte aligned: the 16-byte stores are issued at that alignment) */
-    u32x4_a4* const p = reinterpret_cast<u32x4_a4*>(hist) + (uint64_t)blockIdx.x * (kClearPer * kClearThreads) + threadIdx.x;
+    u32x4_a4* const p = reinterpret_cast<u32x4_a4*>(hist + (uint64_t)blockIdx.x * (kHistBytes / 8)) + threadIdx.x;
     const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (uint32_t k = 0; k < kClearPer; ++k) p[k * kClearThreads] = zero;
+    for (uint32_t k = 0; k < kMagBins * sizeof(CNT) / (16u * kClearThreads); ++k) p[k * kClearThreads] = zero;
 }
 
-template <int DT>
+/* 16 bytes per thread and step: zeroes the workgroup's histogram (the caller's barrier follows) */
+__device__ __forceinline__ void zero_lds_hist(uint32_t* s_hist)
+{
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (uint32_t k = 0; k < kMagBins / (4u * kHistThreads); ++k)
+        reinterpret_cast<u32x4*>(s_hist)[k * kHistThreads + threadIdx.x] = zero;
+}
+
+/* Add what the workgroup counted to the chunk's histogram.  The workgroups start at different rows: their atomics
+ * on one line come from eight XCDs and take their turns (the flush is 4 us of a call on 2^24 values). */
+template <typename CNT>
+__device__ __forceinline__ void flush_lds_hist(const uint32_t* s_hist, unsigned long long* hist_c, uint32_t wg)
+{
+    CNT* const hist = reinterpret_cast<CNT*>(hist_c);
+    const uint32_t turn = wg * 128u;
+    for (uint32_t i = threadIdx.x; i < kMagBins; i += kHistThreads) {
+        const uint32_t b = (i + turn) & (kMagBins - 1u);
+        const uint32_t cnt = s_hist[b];
+        if (cnt) atomicAdd(&hist[b], (CNT)cnt);
+    }
+}
+
+template <int DT, typename CNT>
 __global__ __launch_bounds__(kHistThreads) void k_magnitude_hist(const HistArgs a)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
     constexpr uint32_t PER16 = 16u / ES;
-    __shared__ uint32_t s_hist[kMagBins];                  /* 128 KiB */
-    for (uint32_t i = threadIdx.x; i < kMagBins; i += kHistThreads) s_hist[i] = 0u;
-    __syncthreads();
+    constexpr uint32_t NF = 4;                               /* loads in flight per thread */
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kMagBins];     /* 128 KiB */
     /* grid = (workgroups per chunk, chunks); a chunk starts at some element of the tensor: the values in front of
        its first 16-byte boundary and behind its last one are taken one by one, the rest in 16-byte pieces */
     const uint32_t c = blockIdx.y;
@@ -170,12 +224,22 @@ __global__ __launch_bounds__(kHistThreads) void k_magnitude_hist(const HistArgs 
         atomicAdd(&s_hist[hi & 0x7FFFu], 1u);
     };
     uint64_t i = (uint64_t)blockIdx.x * kHistThreads + threadIdx.x;
-    for (; i + 3 * stride < n16; i += 4 * stride) {           /* four loads in flight per thread */
-        u32x4 v[4];
+    u32x4 v[NF];
+    auto load = [&](uint64_t at) {
 #pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) v[k] = ld_stream<u32x4>(mid + (i + k * stride) * 16);
+        for (uint32_t k = 0; k < NF; ++k) v[k] = ld_stream<u32x4>(mid + (at + k * stride) * 16);
+    };
+    /* the first loads travel while the histogram is zeroed */
+    bool more = i + (NF - 1) * stride < n16;
+    if (more) load(i);
+    zero_lds_hist(s_hist);
+    __syncthreads();
+    while (more) {
 #pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) count(v[k]);
+        for (uint32_t k = 0; k < NF; ++k) count(v[k]);
+        i += NF * stride;
+        more = i + (NF - 1) * stride < n16;
+        if (more) load(i);
     }
     for (; i < n16; i += stride) count(ld_stream<u32x4>(mid + i * 16));
     if (blockIdx.x == 0) {                                    /* head and tail: fewer than 16 bytes each */
@@ -184,11 +248,7 @@ __global__ __launch_bounds__(kHistThreads) void k_magnitude_hist(const HistArgs 
         if (done + threadIdx.x < n) count_one(done + threadIdx.x);
     }
     __syncthreads();
-    unsigned long long* __restrict__ hist = a.hist + (uint64_t)c * kMagBins;
-    for (uint32_t b = threadIdx.x; b < kMagBins; b += kHistThreads) {
-        const uint32_t cnt = s_hist[b];
-        if (cnt) atomicAdd(&hist[b], (unsigned long long)cnt);
-    }
+    flush_lds_hist<CNT>(s_hist, a.hist + (uint64_t)c * (kHistBytes / 8), blockIdx.x);
 }
 
 /*
@@ -198,15 +258,16 @@ __global__ __launch_bounds__(kHistThreads) void k_magnitude_hist(const HistArgs 
  * block to block, so the sample does not alias with the periods of the tensor itself, rows of 8 or 16 groups
  * say).  A wave takes a group at a time, 8 values per lane, several groups in flight; a group that is cut short by
  * the chunk's end, and every group of a chunk that does not start on a 16-byte boundary, is read value by value.
+ * Blocks k0, k0 + n_waves, ... below k_end are this wave's.  Zeroes s_hist first (all threads of the workgroup
+ * call this), while the first loads travel.
  */
 template <int DT, uint32_t NF>   /* NF groups in flight per wave */
 __device__ __forceinline__ void sample_into_lds(uint32_t* s_hist, const uint8_t* __restrict__ in, uint64_t n, uint32_t S,
-                                                uint32_t first_wave, uint32_t n_waves)
+                                                uint32_t k0, uint32_t k_end, uint32_t n_waves)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
     constexpr uint32_t NV = DT == ZIPCCL_BF16 ? 1u : 2u;    /* 16-byte pieces per lane and group */
     const uint64_t ng = (n + kGroup - 1) / kGroup;           /* at most 2^23 */
-    const uint32_t n_blk = (uint32_t)((ng + S - 1) / S);
     /* vector loads need a chunk that starts on a 16-byte boundary; then group 0, if whole, is an address that is
        always safe to load from */
     const bool vec = (reinterpret_cast<uintptr_t>(in) & 15u) == 0 && n >= kGroup;
@@ -221,18 +282,18 @@ __device__ __forceinline__ void sample_into_lds(uint32_t* s_hist, const uint8_t*
             }
         }
     };
-    for (uint32_t k0 = first_wave; k0 < n_blk; k0 += NF * n_waves) {
-        u32x4 v[NF][NV];
-        uint64_t first[NF];
-        bool some[NF], whole[NF];
-        /* the loads of all NF groups go out back to back: no branch between them (a group that is not there, or
-           not whole, loads group 0 instead and is not counted from it) */
+    u32x4 v[NF][NV];
+    uint64_t first[NF];
+    bool some[NF], whole[NF];
+    /* the loads of all NF groups go out back to back: no branch between them (a group that is not there, or
+       not whole, loads group 0 instead and is not counted from it) */
+    auto load = [&](uint32_t from_block) {
 #pragma unroll
         for (uint32_t u = 0; u < NF; ++u) {
-            const uint32_t k = k0 + u * n_waves;
+            const uint32_t k = from_block + u * n_waves;
             const uint64_t g = (uint64_t)k * S + (((k * 2654435761u) >> 16) & (S - 1u));
             first[u] = g * kGroup;
-            some[u] = k < n_blk && g < ng;
+            some[u] = k < k_end && g < ng;
             whole[u] = some[u] && vec && first[u] + kGroup <= n;
         }
         if (vec) {
@@ -244,6 +305,13 @@ __device__ __forceinline__ void sample_into_lds(uint32_t* s_hist, const uint8_t*
                     v[u][q] = ld_stream<u32x4>(in + (from + lane * kLaneElems) * ES + 16u * q);
             }
         }
+    };
+    const bool any = k0 < k_end;
+    if (any) load(k0);
+    zero_lds_hist(s_hist);
+    __syncthreads();
+    if (!any) return;
+    for (;;) {
 #pragma unroll
         for (uint32_t u = 0; u < NF; ++u) {
             if (whole[u]) {
@@ -262,168 +330,146 @@ __device__ __forceinline__ void sample_into_lds(uint32_t* s_hist, const uint8_t*
 #pragma unroll
         for (uint32_t u = 0; u < NF; ++u)
             if (some[u] && !whole[u]) one_by_one(first[u]);
+        k0 += NF * n_waves;
+        if (k0 >= k_end) return;
+        load(k0);
     }
+}
+
+/* blocks of S groups in a chunk of n values (at most 2^32 - 1): one group is sampled from each */
+__device__ __forceinline__ uint32_t sample_blocks(uint64_t n, uint32_t S)
+{
+    return (uint32_t)(((n + kGroup - 1) / kGroup + S - 1) / S);
 }
 
 template <int DT>
 __global__ __launch_bounds__(kHistThreads) void k_magnitude_hist_sampled(const HistArgs a)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
-    __shared__ uint32_t s_hist[kMagBins];                  /* 128 KiB */
-    for (uint32_t i = threadIdx.x; i < kMagBins; i += kHistThreads) s_hist[i] = 0u;
-    __syncthreads();
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kMagBins];     /* 128 KiB */
     /* grid = (workgroups per chunk, chunks) */
     const uint32_t c = blockIdx.y;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    sample_into_lds<DT, 4>(s_hist, a.in + a.tab.elem_off[c] * ES, a.tab.elem_off[c + 1] - a.tab.elem_off[c], a.sample_stride,
-                           blockIdx.x * (kHistThreads / 64u) + wave, gridDim.x * (kHistThreads / 64u));
+    const uint64_t n = a.tab.elem_off[c + 1] - a.tab.elem_off[c];
+    sample_into_lds<DT, 4>(s_hist, a.in + a.tab.elem_off[c] * ES, n, a.sample_stride, blockIdx.x * kHistWaves + wave,
+                           sample_blocks(n, a.sample_stride), gridDim.x * kHistWaves);
     __syncthreads();
-    unsigned long long* __restrict__ hist = a.hist + (uint64_t)c * kMagBins;
-    for (uint32_t b = threadIdx.x; b < kMagBins; b += kHistThreads) {
-        const uint32_t cnt = s_hist[b];
-        if (cnt) atomicAdd(&hist[b], (unsigned long long)cnt);
-    }
+    flush_lds_hist<uint32_t>(s_hist, a.hist + (uint64_t)c * (kHistBytes / 8), blockIdx.x);
 }
 
 /*
- * A chunk whose sample is small enough for one workgroup (at most kFusedGroups groups): histogram, rank and table
- * in one kernel, nothing outside LDS, no histogram in the workspace to clear and no second or third launch.
- * grid = chunks.  Thread t answers for bins [32 t, 32 t + 32) as in k_robust_finish; a chunk holds fewer than 2^32
- * values, so 32-bit counts do.
+ * Rank and table of one chunk by one workgroup of 1024 threads.  `bins` yields 16 bytes of counts at a time: in step k
+ * thread t holds the PER bins from (k * 1024 + t) * PER on, so a wave's step is one row of 64 * PER consecutive
+ * bins, read coalesced, and the counts never leave their registers: rows are summed by wave scans, every wave finds
+ * the row of the rank among the row sums, and the wave that holds that row finds lane and bin.  One barrier.
+ */
+template <typename CNT, typename LOAD>
+__device__ __forceinline__ void rank_and_table(LOAD bins, CNT* s_row, uint8_t* table, double* sigma)
+{
+    constexpr uint32_t PER = 16u / sizeof(CNT);
+    constexpr uint32_t STEPS = kMagBins / (kHistThreads * PER);      /* 8 (32-bit counts) or 16 */
+    constexpr uint32_t ROWS = STEPS * kHistWaves, RPL = ROWS / 64;   /* rows, and rows per lane when they are scanned */
+    const uint32_t t = threadIdx.x, lane = t & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    CNT v[STEPS][PER], inc[STEPS];
+#pragma unroll
+    for (uint32_t k = 0; k < STEPS; ++k) bins(k, v[k]);
+#pragma unroll
+    for (uint32_t k = 0; k < STEPS; ++k) {
+        CNT sum = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < PER; ++j) {
+            if (!bin_counts((k * kHistThreads + t) * PER + j)) v[k][j] = 0;
+            sum += v[k][j];
+        }
+        inc[k] = scan_of<CNT>(sum);
+        if (lane == 63u) s_row[k * kHistWaves + wave] = inc[k];
+    }
+    __syncthreads();
+    CNT row_sum[RPL], mine = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < RPL; ++r) {
+        row_sum[r] = s_row[lane * RPL + r];
+        mine += row_sum[r];
+    }
+    const CNT upto = scan_of<CNT>(mine);
+    const CNT total = __shfl(upto, 63, 64);
+    if (total == 0) {
+        if (wave == 0) table_from_sigma(__longlong_as_double(0x7FF8000000000000ll), table, sigma);
+        return;
+    }
+    const CNT rank = (total - 1) / 2;
+    /* exactly one lane's rows hold the rank */
+    const uint32_t at = (uint32_t)__builtin_ctzll(__ballot(rank >= upto - mine && rank < upto));
+    CNT before = upto - mine;
+    uint32_t row = lane * RPL;
+#pragma unroll
+    for (uint32_t r = 0; r + 1 < RPL; ++r)
+        if (row == lane * RPL + r && rank >= before + row_sum[r]) { before += row_sum[r]; ++row; }
+    row = (uint32_t)__builtin_amdgcn_readfirstlane(__shfl(row, (int)at, 64));
+    before = __shfl(before, (int)at, 64);
+    if ((row & (kHistWaves - 1u)) != wave) return;
+    const uint32_t step = row / kHistWaves;
+    CNT w[PER] = {}, winc = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < STEPS; ++k) {
+        if (k == step) {
+            winc = inc[k];
+#pragma unroll
+            for (uint32_t j = 0; j < PER; ++j) w[j] = v[k][j];
+        }
+    }
+    CNT sum = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j) sum += w[j];
+    CNT run = before + winc - sum;
+    const uint64_t owner = __ballot(rank >= run && rank < run + sum);
+    uint32_t bin = (step * kHistThreads + t) * PER;
+#pragma unroll
+    for (uint32_t j = 0; j + 1 < PER; ++j) {
+        run += w[j];
+        if (rank >= run) bin = (step * kHistThreads + t) * PER + j + 1;
+    }
+    bin = (uint32_t)__shfl((int)bin, (int)__builtin_ctzll(owner), 64);
+    const double med = (double)__uint_as_float(bin << 16);
+    table_from_sigma(med / 0.6744897501960817, table, sigma);     /* Phi^-1(3/4) */
+}
+
+/* One workgroup per chunk, after the histogram kernels: 8 (32-bit counts) or 16 loads per thread, all in flight together. */
+template <typename CNT>
+__global__ __launch_bounds__(kHistThreads) void k_robust_finish(const HistArgs a)
+{
+    constexpr uint32_t PER = 16u / sizeof(CNT);
+    __shared__ CNT s_row[kMagBins / (64u * PER)];
+    /* grid = chunks */
+    const u32x4_a4* const hist = reinterpret_cast<const u32x4_a4*>(a.hist + (uint64_t)blockIdx.x * (kHistBytes / 8)) + threadIdx.x;
+    rank_and_table<CNT>([&](uint32_t k, CNT* out) {
+        const u32x4 q = hist[k * kHistThreads];
+        __builtin_memcpy(out, &q, 16);
+    }, s_row, a.table + 8u * blockIdx.x, a.sigma ? a.sigma + blockIdx.x : nullptr);
+}
+
+/*
+ * A chunk whose sample is small enough for one workgroup: histogram, rank and table in one kernel, nothing outside LDS.
+ * grid = chunks.
  */
 template <int DT>
 __global__ __launch_bounds__(kHistThreads) void k_robust_chunk_fused(const HistArgs a)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
-    constexpr uint32_t kPer = kMagBins / kHistThreads;       /* 32 */
-    constexpr uint32_t kWaves = kHistThreads / 64;
-    constexpr uint32_t kFirstNonFinite = 0x7F80u;
-    __shared__ uint32_t s_hist[kMagBins];                  /* 128 KiB */
-    __shared__ uint32_t s_wave[kWaves];
-    for (uint32_t i = threadIdx.x; i < kMagBins; i += kHistThreads) s_hist[i] = 0u;
-    __syncthreads();
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kMagBins];     /* 128 KiB */
+    __shared__ uint32_t s_row[kMagBins / 256u];
     const uint32_t c = blockIdx.x;
-    const uint32_t t = threadIdx.x, lane = t & 63u;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t n = a.tab.elem_off[c + 1] - a.tab.elem_off[c];
     /* one workgroup per chunk has the chunk's whole latency to hide: eight groups in flight per wave */
-    sample_into_lds<DT, 8>(s_hist, a.in + a.tab.elem_off[c] * ES, a.tab.elem_off[c + 1] - a.tab.elem_off[c], a.sample_stride,
-                           wave, kWaves);
+    sample_into_lds<DT, 8>(s_hist, a.in + a.tab.elem_off[c] * ES, n, a.sample_stride, wave,
+                           sample_blocks(n, a.sample_stride), kHistWaves);
     __syncthreads();
-    uint8_t* const table = a.table + 8u * c;
-    double* const sigma = a.sigma ? a.sigma + c : nullptr;
-    auto counted = [&](uint32_t b) { return (b != 0u && b < kFirstNonFinite) ? s_hist[b] : 0u; };
-    uint32_t mine = 0;
-#pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k) mine += counted(t * kPer + ((k + t) & (kPer - 1u)));   /* rotated: no bank conflicts */
-    const uint32_t inc = wave_incl_scan(mine);
-    if (lane == 63u) s_wave[wave] = inc;
-    __syncthreads();
-    uint32_t before = 0, total = 0;
-    for (uint32_t w = 0; w < kWaves; ++w) {
-        const uint32_t cw = s_wave[w];
-        before += w < wave ? cw : 0u;
-        total += cw;
-    }
-    if (total == 0u) {
-        if (t == 0) table_from_sigma(__longlong_as_double(0x7FF8000000000000ll), table, sigma);
-        return;
-    }
-    const uint32_t rank = (total - 1u) / 2u, excl = before + inc - mine;
-    if (rank < excl || rank - excl >= mine) return;          /* exactly one thread holds the rank */
-    uint32_t run = excl, bin = 0;
-    bool found = false;
-    for (uint32_t k = 0; k < kPer; ++k) {
-        run += counted(t * kPer + k);
-        if (!found && rank < run) { found = true; bin = t * kPer + k; }
-    }
-    const double med = (double)__uint_as_float(bin << 16);
-    table_from_sigma(med / 0.6744897501960817, table, sigma);     /* Phi^-1(3/4) */
-}
-
-/* Inclusive prefix sum of 64-bit values over the 64 lanes of a wave, exact, without going through LDS: the four
- * 16-bit limbs are scanned separately with DPP (each limb sum stays below 2^22) and put together again.
- * (64-bit shuffles are two LDS permutes each, and a chain of several hundred of them took 20 us here.) */
-__device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long long x)
-{
-    unsigned long long r = 0;
-#pragma unroll
-    for (uint32_t k = 0; k < 4; ++k)
-        r += (unsigned long long)wave_incl_scan((uint32_t)(x >> (16 * k)) & 0xFFFFu) << (16 * k);
-    return r;
-}
-
-/*
- * One workgroup per chunk.  Thread t answers for the 32 consecutive bins [32 t, 32 t + 32).  The 32768 counts are read
- * with coalesced loads (thread t holds bin 1024 r + t of every row r, all loads in flight together) and handed to their
- * owners through LDS, 4096 bins at a time; every thread sums its 32 bins, one scan over the 1024 sums finds the
- * thread that holds the rank, and that thread walks its bins.  Bins 0 (zero) and 0x7F80.. (Inf / NaN) do not count.
- */
-__global__ __launch_bounds__(kHistThreads) void k_robust_finish(const HistArgs a)
-{
-    /* grid = chunks */
-    const unsigned long long* __restrict__ hist = a.hist + (uint64_t)blockIdx.x * kMagBins;
-    uint8_t* const table = a.table + 8u * blockIdx.x;
-    double* const sigma = a.sigma ? a.sigma + blockIdx.x : nullptr;
-    constexpr uint32_t kPer = kMagBins / kHistThreads;       /* 32 bins per thread, and rows of the coalesced read */
-    constexpr uint32_t kWaves = kHistThreads / 64;           /* 16 */
-    constexpr uint32_t kRound = 4096;                        /* bins handed over per round: 128 owners */
-    constexpr uint32_t kFirstNonFinite = 0x7F80u;            /* magnitudes from here on are Inf / NaN */
-    __shared__ unsigned long long s_buf[kRound + kRound / kPer];     /* one pad word per owner: bank-conflict relief */
-    __shared__ unsigned long long s_wave[kWaves];
-    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
-    unsigned long long v[kPer];
-#pragma unroll
-    for (uint32_t r = 0; r < kPer; ++r) {
-        const uint32_t b = r * kHistThreads + t;
-        v[r] = (b != 0u && b < kFirstNonFinite) ? hist[b] : 0ull;
-    }
-    unsigned long long mine = 0;
-#pragma unroll
-    for (uint32_t q = 0; q < kMagBins / kRound; ++q) {       /* 8 rounds; round q = bins [4096 q, 4096 q + 4096) */
-#pragma unroll
-        for (uint32_t j = 0; j < kRound / kHistThreads; ++j) {
-            const uint32_t e = j * kHistThreads + t;         /* bin inside the round */
-            s_buf[e + e / kPer] = v[q * (kRound / kHistThreads) + j];
-        }
-        __syncthreads();
-        if (t / (kRound / kPer) == q) {
-            const uint32_t o = (t % (kRound / kPer)) * (kPer + 1);
-#pragma unroll
-            for (uint32_t k = 0; k < kPer; ++k) mine += s_buf[o + k];
-        }
-        __syncthreads();
-    }
-    const unsigned long long inc = wave_incl_scan_u64(mine);
-    if (lane == 63u) s_wave[wave] = inc;
-    __syncthreads();
-    unsigned long long before = 0, total = 0;
-    for (uint32_t w = 0; w < kWaves; ++w) {
-        const unsigned long long c = s_wave[w];
-        before += w < wave ? c : 0ull;
-        total += c;
-    }
-    if (total == 0ull) {
-        if (t == 0) table_from_sigma(__longlong_as_double(0x7FF8000000000000ll), table, sigma);
-        return;
-    }
-    const unsigned long long rank = (total - 1ull) / 2ull, excl = before + inc - mine;
-    if (rank < excl || rank >= excl + mine) return;          /* exactly one thread holds the rank */
-    unsigned long long c[kPer];
-#pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k) {
-        const uint32_t b = t * kPer + k;
-        c[k] = (b != 0u && b < kFirstNonFinite) ? hist[b] : 0ull;
-    }
-    unsigned long long run = excl;
-    uint32_t bin = 0;
-    bool found = false;
-#pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k) {
-        run += c[k];
-        if (!found && rank < run) { found = true; bin = t * kPer + k; }
-    }
-    const double med = (double)__uint_as_float(bin << 16);
-    table_from_sigma(med / 0.6744897501960817, table, sigma);     /* Phi^-1(3/4) */
+    rank_and_table<uint32_t>([&](uint32_t k, uint32_t* out) {
+        const u32x4 q = reinterpret_cast<const u32x4*>(s_hist)[k * kHistThreads + threadIdx.x];
+        __builtin_memcpy(out, &q, 16);
+    }, s_row, a.table + 8u * c, a.sigma ? a.sigma + c : nullptr);
 }
 
 } // namespace
@@ -439,12 +485,6 @@ int launch_estimate(int dt, const MomentArgs& a, void* stream)
 }
 
 
-int launch_clear_hist(unsigned long long* hist, uint32_t n_chunks, void* stream)
-{
-    hipLaunchKernelGGL(k_clear_hist, dim3(n_chunks * (kMagBins * 8u / (16u * kClearPer * kClearThreads))), dim3(kClearThreads), 0, (hipStream_t)stream, hist);
-    return (int)hipGetLastError();
-}
-
 int launch_estimate_robust_fused(int dt, const HistArgs& a, void* stream)
 {
     const dim3 grid(a.tab.n_chunks);
@@ -453,18 +493,27 @@ int launch_estimate_robust_fused(int dt, const HistArgs& a, void* stream)
     return (int)hipGetLastError();
 }
 
+template <int DT, typename CNT>
+static int launch_large(const HistArgs& a, hipStream_t s)
+{
+    const dim3 grid(a.n_blocks, a.tab.n_chunks), chunks(a.tab.n_chunks);
+    hipLaunchKernelGGL((k_clear_hist<CNT>), chunks, dim3(kClearThreads), 0, s, a.hist);
+    if (hipGetLastError() != hipSuccess) return 1;
+    if (a.sample_stride > 1u) hipLaunchKernelGGL((k_magnitude_hist_sampled<DT>), grid, dim3(kHistThreads), 0, s, a);
+    else hipLaunchKernelGGL((k_magnitude_hist<DT, CNT>), grid, dim3(kHistThreads), 0, s, a);
+    if (hipGetLastError() != hipSuccess) return 1;
+    hipLaunchKernelGGL((k_robust_finish<CNT>), chunks, dim3(kHistThreads), 0, s, a);
+    return (int)hipGetLastError();
+}
+
 int launch_estimate_robust(int dt, const HistArgs& a, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
-    const dim3 grid(a.n_blocks, a.tab.n_chunks);
-    if (a.sample_stride > 1u) {
-        if (dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_magnitude_hist_sampled<ZIPCCL_BF16>), grid, dim3(kHistThreads), 0, s, a);
-        else hipLaunchKernelGGL((k_magnitude_hist_sampled<ZIPCCL_FP32>), grid, dim3(kHistThreads), 0, s, a);
-    } else if (dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_magnitude_hist<ZIPCCL_BF16>), grid, dim3(kHistThreads), 0, s, a);
-    else hipLaunchKernelGGL((k_magnitude_hist<ZIPCCL_FP32>), grid, dim3(kHistThreads), 0, s, a);
-    if (hipGetLastError() != hipSuccess) return 1;
-    hipLaunchKernelGGL(k_robust_finish, dim3(a.tab.n_chunks), dim3(kHistThreads), 0, s, a);
-    return (int)hipGetLastError();
+    /* 32-bit counts unless some chunk could overflow them; a sample is only taken of chunks below 2^32 values */
+    bool wide = false;
+    for (uint32_t c = 0; c < a.tab.n_chunks; ++c) wide |= a.tab.elem_off[c + 1] - a.tab.elem_off[c] > ZIPCCL_MAX_CHUNK_ELEMS;
+    if (wide) return dt == ZIPCCL_BF16 ? launch_large<ZIPCCL_BF16, unsigned long long>(a, s) : launch_large<ZIPCCL_FP32, unsigned long long>(a, s);
+    return dt == ZIPCCL_BF16 ? launch_large<ZIPCCL_BF16, uint32_t>(a, s) : launch_large<ZIPCCL_FP32, uint32_t>(a, s);
 }
 
 } // namespace zipccl

@@ -348,11 +348,10 @@ static zipccl_status_t estimate_chunk_tables_impl(const void* d_in, size_t n_ele
     if ((uint64_t)n_chunks * (32768 / 1024) > 0x7FFFFFFFull) return ZIPCCL_ERR_INVALID_ARG;
     unsigned long long* const hist = static_cast<unsigned long long*>(d_workspace);
     /* when every chunk's sample is small enough for one workgroup, one kernel does it all inside LDS: no histogram
-       in the workspace, nothing to clear */
+       in the workspace */
     uint64_t largest_of_all = 0;
     for (uint32_t c = 0; c < n_chunks; ++c) largest_of_all = std::max(largest_of_all, ce[c]);
     const bool fused = ((largest_of_all + kGroup - 1) / kGroup + sample_stride - 1) / sample_stride <= kFusedGroups;
-    if (!fused && launch_clear_hist(hist, n_chunks, stream) != 0) return ZIPCCL_ERR_DEVICE;
     const std::vector<uint64_t> no_slots(n_chunks + 1, 0);            /* slot offsets play no part here */
     HistArgs a;
     uint64_t elem_base = 0;
@@ -365,7 +364,7 @@ static zipccl_status_t estimate_chunk_tables_impl(const void* d_in, size_t n_ele
             a.n_blocks = 1;
             a.sample_stride = sample_stride;
             a.in = static_cast<const uint8_t*>(d_in) + elem_base * elem_size(dt);
-            a.hist = hist;
+            a.hist = hist + (uint64_t)c0 * (kHistBytes / 8);
             a.table = reinterpret_cast<uint8_t*>(d_tables + c0);
             a.sigma = d_sigmas ? d_sigmas + c0 : nullptr;
             if (launch_estimate_robust_fused(dt, a, stream) != 0) return ZIPCCL_ERR_DEVICE;
@@ -381,7 +380,7 @@ static zipccl_status_t estimate_chunk_tables_impl(const void* d_in, size_t n_ele
         a.sample_stride = sample_stride;
         if (largest / a.n_blocks >= 0xFFFFFFFFull) return ZIPCCL_ERR_INVALID_ARG;
         a.in = static_cast<const uint8_t*>(d_in) + elem_base * elem_size(dt);
-        a.hist = hist + (uint64_t)c0 * 32768;
+        a.hist = hist + (uint64_t)c0 * (kHistBytes / 8);
         a.table = reinterpret_cast<uint8_t*>(d_tables + c0);
         a.sigma = d_sigmas ? d_sigmas + c0 : nullptr;
         if (launch_estimate_robust(dt, a, stream) != 0) return ZIPCCL_ERR_DEVICE;
@@ -433,10 +432,9 @@ zipccl_status_t zipccl_estimate_table_robust(const void* d_in, size_t n_elems, z
     a.hist = hist;
     a.table = reinterpret_cast<uint8_t*>(d_table);
     a.sigma = d_sigma;
-    /* a tensor one workgroup can take on its own: one kernel, nothing to clear */
+    /* a tensor one workgroup can take on its own: one kernel */
     if ((whole + kGroup - 1) / kGroup <= kFusedGroups)
         return launch_estimate_robust_fused(dt, a, stream) == 0 ? ZIPCCL_OK : ZIPCCL_ERR_DEVICE;
-    if (launch_clear_hist(hist, 1, stream) != 0) return ZIPCCL_ERR_DEVICE;
     return launch_estimate_robust(dt, a, stream) == 0 ? ZIPCCL_OK : ZIPCCL_ERR_DEVICE;
 }
 

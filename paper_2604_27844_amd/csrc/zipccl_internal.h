@@ -91,11 +91,11 @@ struct MomentArgs {
 };
 
 constexpr uint32_t kHistBlocks = 256;                /* workgroups of the magnitude histogram: one per compute unit */
-constexpr uint32_t kHistBytes = 32768 * 8;           /* its workspace: one 64-bit count per 15-bit magnitude */
+constexpr uint32_t kHistBytes = 32768 * 8;           /* its workspace: one count per 15-bit magnitude, at most 64 bits each */
 
 struct HistArgs {
     const uint8_t* in;       /* first element of the launch's first chunk */
-    unsigned long long* hist;   /* 32768 counts per chunk of the launch, zeroed by the first kernel of the call */
+    unsigned long long* hist;   /* the launch's first chunk's workspace, kHistBytes per chunk */
     uint32_t n_blocks;       /* workgroups per chunk */
     uint32_t sample_stride;  /* 1: every value counts; a power of two S: one group of 512 values per S groups */
     uint8_t* table;          /* device zipccl_table_t (8 bytes) per chunk of the launch */
@@ -133,7 +133,6 @@ enum CompressMode { kModeCount = 0, kModeEmit = 1, kModeStash = 2 };
 /* launchers implemented next to their kernels (zipccl_compress.hip, zipccl_decompress.hip, zipccl_aux.hip);
  * they return a hipError_t as int */
 int launch_estimate(int dt, const MomentArgs& a, void* stream);
-int launch_clear_hist(unsigned long long* hist, uint32_t n_chunks, void* stream);
 int launch_estimate_robust(int dt, const HistArgs& a, void* stream);
 int launch_estimate_robust_fused(int dt, const HistArgs& a, void* stream);   /* chunks of at most kFusedGroups sampled groups */
 int launch_compress(int dt, int mode, const CompressArgs& a, void* stream);

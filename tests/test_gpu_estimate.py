@@ -334,3 +334,33 @@ def test_sampled_estimate_seeded_fuzz():
         got = d_sig.cpu().numpy()
         assert np.array_equal(np.isnan(got), np.isnan(sig)) and np.array_equal(got[~np.isnan(sig)], sig[~np.isnan(sig)]), case
         assert np.array_equal(d_tabs.cpu().numpy().reshape(C, 8), decs), case
+
+
+@pytest.mark.parametrize("n", [5000, 300_007])                # one kernel; histogram in the workspace
+def test_robust_rank_at_the_edges_of_the_bins(n):
+    """The rank's bin at the ends of what counts and of every unit the search works in (4 bins of a thread, 256 of a
+    wave, 4096 of a step), alone and between neighbours: sigma bit-equal to the oracle's (a count)."""
+    rng = np.random.default_rng(21)
+    for b in (1, 2, 3, 4, 5, 255, 256, 257, 1023, 1024, 4095, 4096, 4097, 0x3F80, 0x7EFF, 0x7F00, 0x7F7E, 0x7F7F):
+        for below, above in ((0, 0), (0.3, 0.1), (0.4999, 0.4999)):
+            r = rng.random(n)
+            x = np.where(r < below, max(b - 1, 1), np.where(r > 1 - above, min(b + 1, 0x7F7F), b)).astype(np.uint16)
+            x[rng.integers(0, n, n // 50)] = 0x8000
+            x[rng.integers(0, n, n // 50)] = 0x7F80
+            x ^= (rng.integers(0, 2, n).astype(np.uint16) << np.uint16(15))
+            print(f"[rank edges] n={n} bin={b:#x} below={below} above={above}", flush=True)
+            dec, s = osg.robust_table(x, z.BF16)
+            _, got_dec, got_s = _estimate_robust(to_device_words(x), n, z.BF16)
+            assert got_s == s and got_dec == list(dec), (b, below, above)
+
+
+def test_robust_counts_past_32_bits():
+    """2^32 + 7 equal values and three smaller ones: the count of their bin does not fit 32 bits.  The median is the
+    value itself, whatever else rounds."""
+    n = 2 ** 32 + 10
+    d_in = torch.full((n,), 0x3F81, dtype=torch.int16, device=DEV)            # bf16 1.0078125
+    d_in[5:8] = 0x3C00
+    print(f"[robust wide] n={n}", flush=True)
+    _, dec, s = _estimate_robust(d_in, n, z.BF16)
+    assert s == 1.0078125 / 0.6744897501960817
+    assert dec == list(bytes(z.zipccl_build_table(s).dec))
