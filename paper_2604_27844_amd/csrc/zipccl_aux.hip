@@ -1,6 +1,8 @@
 /*
  * Auxiliary kernels of libzipccl.so: the sigma estimates / table choice on the device (paper section 4.1).
  */
+#include <algorithm>
+
 #include "zipccl_device.h"
 
 namespace zipccl {
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(kThreads) void k_estimate_finish(const MomentArgs a
  * channels, LayerNorm gains among matrix weights): the median of |w| over Phi^-1(3/4).  The median is taken
  * over the 15-bit magnitudes of the values' high 16-bit words, so it is a count: a histogram of all 32768
  * magnitudes, in which the bin of rank (K - 1) / 2 among the K magnitudes that are neither zero nor Inf/NaN is
- * looked for.  Integer work until the final division: the result does not depend on any order.  Two forms,
+ * looked for.  Integer work until the final division: the result does not depend on any order.  Three forms,
  * each for one or more chunks at once (one histogram and one table per chunk; the whole tensor is one chunk):
  *   large    k_clear_hist zeroes one histogram per chunk in the workspace, k_magnitude_hist (or its sampled form)
  *            adds to it what about one workgroup per compute unit has counted in its LDS, k_robust_finish looks
@@ -131,8 +133,10 @@ __global__ __launch_bounds__(kThreads) void k_estimate_finish(const MomentArgs a
  *            histogram kernel reads for 3.3, counts for 2.4 beyond that and flushes for 4).  With 64-bit counts
  *            zeroed, flushed and read twice over by the finish, whose one thread then took four erf in a row, the
  *            same three kernels were 3.0 + 13.8 + 11.2 us.
- *   small    (at most kFusedGroups groups to count in every chunk) k_robust_chunk_fused: one workgroup per chunk
- *            does it all in one kernel.
+ *   small    (at most kFusedGroups groups to count in every chunk) k_robust_partial: a few workgroups per chunk, each
+ *            of which stores its own counts; k_robust_join adds them up and looks for the rank.  Nothing to clear, no
+ *            atomics on memory.
+ *   smaller  (or as many chunks as compute units) k_robust_chunk_fused: one workgroup per chunk, one kernel.
  */
 constexpr uint32_t kMagBins = 32768;
 constexpr uint32_t kHistThreads = 1024;
@@ -472,6 +476,99 @@ __global__ __launch_bounds__(kHistThreads) void k_robust_chunk_fused(const HistA
     }, s_row, a.table + 8u * c, a.sigma ? a.sigma + c : nullptr);
 }
 
+/*
+ * Chunks that are too large for one workgroup to count quickly (a group of 512 values takes its compute unit's LDS
+ * atomics 36 ns) and too few to fill the chip: G = gridDim.x <= 4 workgroups per chunk, each with at most 127 of
+ * its blocks, i.e. fewer than 2^16 values, so that 16 bits hold every count.  A workgroup stores the rows of 256 bins in
+ * which it counted anything, and the sum of every row, in its own 64 KiB of the chunk's workspace: the counts of the
+ * bins that never count (Inf / NaN, 128 of them) leave room for the 128 row sums.
+ */
+constexpr uint32_t kPartials = 4;
+constexpr uint32_t kPartialBytes = kMagBins * 2;
+constexpr uint32_t kPartialGroups = 127;
+static_assert(kPartials * kPartialBytes <= kHistBytes && kPartials * kPartialGroups == kFusedGroups &&
+              kPartialGroups * kGroup < 65536u && kMagBins - kFirstNonFinite == kMagBins / 256u, "layout of the partial counts");
+
+template <int DT>
+__global__ __launch_bounds__(kHistThreads) void k_robust_partial(const HistArgs a)
+{
+    constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kMagBins];     /* 128 KiB */
+    /* grid = (workgroups per chunk, chunks) */
+    const uint32_t c = blockIdx.y;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t n = a.tab.elem_off[c + 1] - a.tab.elem_off[c];
+    const uint32_t blocks = sample_blocks(n, a.sample_stride);               /* at most kFusedGroups */
+    sample_into_lds<DT, 8>(s_hist, a.in + a.tab.elem_off[c] * ES, n, a.sample_stride,
+                           blockIdx.x * blocks / gridDim.x + wave, (blockIdx.x + 1u) * blocks / gridDim.x, kHistWaves);
+    __syncthreads();
+    uint16_t* const mine = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(a.hist + (uint64_t)c * (kHistBytes / 8)) +
+                                                       blockIdx.x * kPartialBytes);
+#pragma unroll
+    for (uint32_t k = 0; k < kMagBins / (256u * kHistWaves); ++k) {
+        const uint32_t row = k * kHistWaves + wave, b = row * 256u + lane * 4u;
+        u32x4 q = *reinterpret_cast<const u32x4*>(s_hist + b);
+        if (b == 0u) q.x = 0u;
+        if (b >= kFirstNonFinite) q = u32x4{0u, 0u, 0u, 0u};
+        const uint32_t sum = __builtin_amdgcn_readlane(wave_incl_scan((q.x + q.y) + (q.z + q.w)), 63);
+        if (sum != 0u && b < kFirstNonFinite)
+            *reinterpret_cast<u32x2*>(mine + b) = u32x2{q.x | (q.y << 16), q.z | (q.w << 16)};
+        if (lane == 0) mine[kFirstNonFinite + row] = (uint16_t)sum;
+    }
+}
+
+/* One wave per chunk: the row of the rank from the row sums, then the bin from that row of every partial. */
+__global__ __launch_bounds__(64) void k_robust_join(const HistArgs a)
+{
+    /* grid = chunks; a.n_blocks partials each */
+    const uint32_t c = blockIdx.x, lane = lane_id();
+    const uint8_t* const part = reinterpret_cast<const uint8_t*>(a.hist + (uint64_t)c * (kHistBytes / 8));
+    uint8_t* const table = a.table + 8u * c;
+    double* const sigma = a.sigma ? a.sigma + c : nullptr;
+    uint32_t sums[kPartials];                                  /* of rows 2 lane (low half) and 2 lane + 1 */
+#pragma unroll
+    for (uint32_t g = 0; g < kPartials; ++g)
+        sums[g] = g < a.n_blocks ? *reinterpret_cast<const uint32_t*>(part + g * kPartialBytes + 2u * (kFirstNonFinite + 2u * lane)) : 0u;
+    uint32_t even = 0, odd = 0;
+#pragma unroll
+    for (uint32_t g = 0; g < kPartials; ++g) { even += sums[g] & 0xFFFFu; odd += sums[g] >> 16; }
+    const uint32_t upto = wave_incl_scan(even + odd);
+    const uint32_t total = __builtin_amdgcn_readlane(upto, 63);
+    if (total == 0u) {
+        table_from_sigma(__longlong_as_double(0x7FF8000000000000ll), table, sigma);
+        return;
+    }
+    const uint32_t rank = (total - 1u) / 2u;
+    uint32_t before = upto - even - odd;
+    const uint32_t at = (uint32_t)__builtin_ctzll(__ballot(rank >= before && rank < upto));
+    uint32_t row = 2u * lane;
+    if (rank >= before + even) { before += even; ++row; }
+    row = __builtin_amdgcn_readlane(row, at);
+    before = __builtin_amdgcn_readlane(before, at);
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (uint32_t g = 0; g < kPartials; ++g) {
+        const uint32_t of_row = __builtin_amdgcn_readlane(sums[g], at) >> (16u * (row & 1u)) & 0xFFFFu;
+        if (of_row != 0u && row * 256u + lane * 4u < kFirstNonFinite) {      /* rows without counts were not stored */
+            const u32x2 q = *reinterpret_cast<const u32x2*>(part + g * kPartialBytes + 2u * (row * 256u + lane * 4u));
+            w[0] += q.x & 0xFFFFu; w[1] += q.x >> 16; w[2] += q.y & 0xFFFFu; w[3] += q.y >> 16;
+        }
+    }
+    const uint32_t sum = (w[0] + w[1]) + (w[2] + w[3]);
+    uint32_t run = before + wave_incl_scan(sum) - sum;
+    const uint64_t owner = __ballot(rank >= run && rank < run + sum);
+    uint32_t bin = row * 256u + lane * 4u;
+#pragma unroll
+    for (uint32_t j = 0; j < 3; ++j) {
+        run += w[j];
+        if (rank >= run) bin = row * 256u + lane * 4u + j + 1u;
+    }
+    bin = __builtin_amdgcn_readlane(bin, (uint32_t)__builtin_ctzll(owner));
+    const double med = (double)__uint_as_float(bin << 16);
+    table_from_sigma(med / 0.6744897501960817, table, sigma);     /* Phi^-1(3/4) */
+}
+
 } // namespace
 
 int launch_estimate(int dt, const MomentArgs& a, void* stream)
@@ -485,11 +582,32 @@ int launch_estimate(int dt, const MomentArgs& a, void* stream)
 }
 
 
+/* Several workgroups per chunk and a second kernel from this many groups in the largest chunk on, as long as there are
+ * no more of them than compute units (a compute unit's LDS holds one at a time).  Measured, us, bf16, one workgroup
+ * against several: 64 chunks of 128 groups 10.2 / 11.2, of 192 13.1 / 11.9, of 448 21.9 / 14.0; one chunk of 128
+ * groups 9.4 / 9.7, of 500 20.9 / 12.4; 128 chunks of 192 (two workgroups each) 13.4 / 12.5, and of 256, where two
+ * workgroups per chunk cannot hold them, 15.5 / 15.9.  fp32: 64 chunks of 448 38.1 / 20.5. */
+constexpr uint32_t kPartialFrom = 160;
+
 int launch_estimate_robust_fused(int dt, const HistArgs& a, void* stream)
 {
-    const dim3 grid(a.tab.n_chunks);
-    if (dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_robust_chunk_fused<ZIPCCL_BF16>), grid, dim3(kHistThreads), 0, (hipStream_t)stream, a);
-    else hipLaunchKernelGGL((k_robust_chunk_fused<ZIPCCL_FP32>), grid, dim3(kHistThreads), 0, (hipStream_t)stream, a);
+    hipStream_t s = (hipStream_t)stream;
+    uint64_t largest = 0;
+    for (uint32_t c = 0; c < a.tab.n_chunks; ++c) largest = std::max(largest, a.tab.elem_off[c + 1] - a.tab.elem_off[c]);
+    const uint64_t groups = ((largest + kGroup - 1) / kGroup + a.sample_stride - 1) / a.sample_stride;
+    const uint32_t chunks = a.tab.n_chunks;
+    HistArgs b = a;
+    b.n_blocks = (uint32_t)std::max<uint64_t>(std::min(kHistBlocks / chunks, kPartials), (groups + kPartialGroups - 1) / kPartialGroups);
+    if (groups >= kPartialFrom && b.n_blocks * chunks <= kHistBlocks) {
+        const dim3 grid(b.n_blocks, chunks);
+        if (dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_robust_partial<ZIPCCL_BF16>), grid, dim3(kHistThreads), 0, s, b);
+        else hipLaunchKernelGGL((k_robust_partial<ZIPCCL_FP32>), grid, dim3(kHistThreads), 0, s, b);
+        if (hipGetLastError() != hipSuccess) return 1;
+        hipLaunchKernelGGL(k_robust_join, dim3(chunks), dim3(64), 0, s, b);
+        return (int)hipGetLastError();
+    }
+    if (dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_robust_chunk_fused<ZIPCCL_BF16>), dim3(chunks), dim3(kHistThreads), 0, s, a);
+    else hipLaunchKernelGGL((k_robust_chunk_fused<ZIPCCL_FP32>), dim3(chunks), dim3(kHistThreads), 0, s, a);
     return (int)hipGetLastError();
 }
 

@@ -364,3 +364,25 @@ def test_robust_counts_past_32_bits():
     _, dec, s = _estimate_robust(d_in, n, z.BF16)
     assert s == 1.0078125 / 0.6744897501960817
     assert dec == list(bytes(z.zipccl_build_table(s).dec))
+
+
+@pytest.mark.parametrize("dtype", [z.BF16, z.FP32])
+def test_estimate_of_chunks_shared_by_a_few_workgroups(dtype):
+    """Chunks on either side of the sizes at which the number of workgroups per chunk changes (one below 160 groups to
+    count, up to four below 509, then a histogram in the workspace), a workgroup's counts all in one bin (127 groups of
+    equal values: the largest 16-bit count), ragged and element-aligned chunks beside empty ones: bit-equal to the oracle."""
+    rng = np.random.default_rng(31)
+    G = 512
+    for stride, groups in ((1, (159, 160, 161, 254, 255)), (1, (381, 382, 507, 508)), (1, (509, 3)), (4, (4 * 160, 4 * 508 - 1, 4 * 508))):
+        ce = np.array([g * G for g in groups] + [0, 5, 160 * G - 7], dtype=np.uint64)
+        x = np.concatenate([rng.standard_normal(int(k), dtype=np.float32) * np.float32(np.exp(rng.uniform(-8, 4))) for k in ce])
+        x = W.f32_to_bf16_words(x) if dtype == z.BF16 else x.view(np.uint32).copy()
+        _sampled_case(x, dtype, ce, stride, f"sizes {groups} dtype={dtype}")
+        _sampled_case(x[1:], dtype, np.concatenate([[ce[0] - 1], ce[1:]]).astype(np.uint64), stride, f"sizes {groups} skewed dtype={dtype}")
+    for word in (0x3F80, 0x0000, 0x7F7F, 0x0001):                    # all counts in one bin, or in none
+        x = np.full(508 * G, word, dtype=np.uint16) if dtype == z.BF16 else np.full(508 * G, word << 16, dtype=np.uint32)
+        x[7], x[1000] = 0, 0
+        _sampled_case(x, dtype, np.array([x.size], dtype=np.uint64), 1, f"one value {word:#x} dtype={dtype}")
+    many = rng.standard_normal(100 * 200 * G, dtype=np.float32)      # 100 chunks: two workgroups each
+    _sampled_case(W.f32_to_bf16_words(many) if dtype == z.BF16 else many.view(np.uint32).copy(), dtype,
+                  np.full(100, 200 * G, dtype=np.uint64), 1, f"100 chunks dtype={dtype}")
