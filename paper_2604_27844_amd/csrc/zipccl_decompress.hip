@@ -122,9 +122,7 @@ __device__ __forceinline__ void decode_fetch_list(const uint8_t* __restrict__ sl
 }
 
 /* Phase 1b: the lane's SM bytes, plane bytes and (fp32) low words. */
-/* WORDS: b0..b2 receive the aligned 32-bit word holding the lane's plane byte (see plane_bytes_of_words)
- * instead of the byte itself. */
-template <int DT, bool FAST, bool WORDS = false, bool QUAD = false>
+template <int DT, bool FAST, bool QUAD = false>
 __device__ __forceinline__ void decode_load(const uint8_t* __restrict__ slot, const SlotLayout& L, uint64_t n,
                                             uint64_t gstart, uint32_t lane, DecIn& r)
 {
@@ -159,15 +157,9 @@ __device__ __forceinline__ void decode_load(const uint8_t* __restrict__ slot, co
     const uint64_t pb = e >> 3;
     if (FAST || pb < L.plane_bytes) {
         const uint8_t* pl = slot + L.p0 + (gstart >> 3);     /* 64-byte aligned: a group's 64 plane bytes */
-        if (WORDS) {
-            r.b0 = ld_stream<uint32_t>(pl + (lane & ~3u));
-            r.b1 = ld_stream<uint32_t>((pl + L.plane_bytes) + (lane & ~3u));
-            r.b2 = ld_stream<uint32_t>((pl + 2 * L.plane_bytes) + (lane & ~3u));
-        } else {
-            r.b0 = ld_stream<uint8_t>(pl + lane);
-            r.b1 = ld_stream<uint8_t>((pl + L.plane_bytes) + lane);
-            r.b2 = ld_stream<uint8_t>((pl + 2 * L.plane_bytes) + lane);
-        }
+        r.b0 = ld_stream<uint8_t>(pl + lane);
+        r.b1 = ld_stream<uint8_t>((pl + L.plane_bytes) + lane);
+        r.b2 = ld_stream<uint8_t>((pl + 2 * L.plane_bytes) + lane);
     }
     if (DT == ZIPCCL_FP32) {
         if (FAST || 2 * e < pad128(2 * n)) {
@@ -177,15 +169,6 @@ __device__ __forceinline__ void decode_load(const uint8_t* __restrict__ slot, co
     }
     r.vmask = 0xFFu;
     if (!FAST) r.vmask = e >= n ? 0u : (n - e >= 8 ? 0xFFu : ((1u << (uint32_t)(n - e)) - 1u));
-}
-
-/* After decode_load<.., WORDS = true>: the lane's plane bytes out of the words that hold them. */
-__device__ __forceinline__ void plane_bytes_of_words(DecIn& r, uint32_t lane)
-{
-    const uint32_t sh = 8u * (lane & 3u);
-    r.b0 = __builtin_amdgcn_ubfe(r.b0, sh, 8u);
-    r.b1 = __builtin_amdgcn_ubfe(r.b1, sh, 8u);
-    r.b2 = __builtin_amdgcn_ubfe(r.b2, sh, 8u);
 }
 
 /* After decode_load<.., QUAD = true>: from the plane bytes shared by a pair of lanes to each lane's own
@@ -418,7 +401,7 @@ void k_decompress(const DecompressArgs a)
 #pragma unroll
         for (uint32_t u = 0; u < GPW; ++u) {
             const uint64_t gstart = ts + (uint64_t)(u * kWavesPerBlock + wave) * kGroup;
-            decode_load<DT, true, false, DT == ZIPCCL_FP32>(slot, L, n, gstart, lane, in[u]);
+            decode_load<DT, true, DT == ZIPCCL_FP32>(slot, L, n, gstart, lane, in[u]);
             const uint64_t g = gstart / kGroup;
             const uint32_t* __restrict__ idx = reinterpret_cast<const uint32_t*>(slot + L.idx);
             in[u].base = idx[g];
@@ -587,9 +570,11 @@ __device__ __forceinline__ void reduce_stages(const ReduceArgs& a, const SlotLay
             }
         }
     };
-    /* issue every vector load of the stage r.pre_* describes.  FAST: the lanes' offsets inside a slot
+    /* issue every vector load of the stage r.pre_* describes.  The lanes' offsets inside a slot
        (section + group + lane) are kept in vector registers and renewed when the group changes, so that
-       a stage adds nothing but the slot's address. */
+       a stage adds nothing but the slot's address.  FAST = false differs in them, in the mask of the lane's
+       values that exist and in the stores: loads under a condition would be waited for one by one (a shard of
+       1 000 003 values took 10.8 us with them, one of 2^20 without any 7.8). */
     uint32_t g_iss = 0xFFFFFFFFu;
     uint64_t v_sm = 0, v_pl = 0, v_lo = 0;
     auto issue = [&](StageBuf& r) {
@@ -598,35 +583,32 @@ __device__ __forceinline__ void reduce_stages(const ReduceArgs& a, const SlotLay
         const uint32_t next = r.pre_g + 1u < ng ? r.pre_next : r.pre_nesc;
         r.in.base = r.pre_base;
         check_index(r.in, next, r.pre_nesc);
-        if (FAST) {
-            if (r.pre_g != g_iss) {
-                g_iss = r.pre_g;
-                const uint64_t gs = (uint64_t)g_iss * kGroup;
-                v_sm = L.sm + gs + lane * 8u;
-                /* the group's 3 x 64 plane bytes in one load: lanes 0..15 fetch the words of plane 0,
-                   16..31 those of plane 1, 32..47 (and again 48..63) those of plane 2 */
-                v_pl = L.p0 + (gs >> 3) + (lane & 15u) * 4u + (uint64_t)min(lane >> 4, 2u) * L.plane_bytes;
-                v_lo = L.lo + 2 * gs + lane * 16u;
-            }
-            /* the list as in decode_fetch_list, relative to 16 bytes before it */
-            const uint32_t end = r.in.count != 0u ? next : 0u;
-            const uint32_t a16 = (r.in.base & ~15u) + 16u * lane;
-            r.lv = *reinterpret_cast<const u32x4*>((slot + (L.esc - 16)) + (a16 < end ? a16 + 16u : 0u));
-            const u32x2 sm = ld_stream<u32x2>(slot + v_sm);
-            r.in.sm0 = sm.x; r.in.sm1 = sm.y;
-            /* a plain load, not a streaming one: a group's 64 bytes of a plane are half a cache line, and the
-               other half is the neighbouring group's, which another wave decodes at another time (streamed,
-               such lines came from memory twice: 13 % more bytes fetched and 204 instead of 179 us for
-               8 x 2^26 values) */
-            r.in.b0 = *reinterpret_cast<const uint32_t*>(slot + v_pl);
-            if (DT == ZIPCCL_FP32) {
-                const u32x4 lo = ld_stream<u32x4>(slot + v_lo);
-                r.in.lo[0] = lo.x; r.in.lo[1] = lo.y; r.in.lo[2] = lo.z; r.in.lo[3] = lo.w;
-            }
-            r.in.vmask = 0xFFu;
-        } else {
-            decode_fetch_list(slot, L, r.in, next, lane, r.lv);
-            decode_load<DT, false, true>(slot, L, n, (uint64_t)r.pre_g * kGroup, lane, r.in);
+        if (!FAST || r.pre_g != g_iss) {
+            g_iss = r.pre_g;
+            const uint64_t gs = (uint64_t)g_iss * kGroup, e = gs + lane * kLaneElems;
+            /* lanes past the end of the shard read the sections' first bytes instead; the planes of a group that
+               has any value are there as a whole */
+            const bool some = FAST || e < n;
+            v_sm = L.sm + (some ? e : 0u);
+            /* the group's 3 x 64 plane bytes in one load: lanes 0..15 fetch the words of plane 0,
+               16..31 those of plane 1, 32..47 (and again 48..63) those of plane 2 */
+            v_pl = L.p0 + (gs >> 3) + (lane & 15u) * 4u + (uint64_t)min(lane >> 4, 2u) * L.plane_bytes;
+            v_lo = L.lo + (some ? 2 * e : 0u);
+        }
+        /* the list as in decode_fetch_list, relative to 16 bytes before it */
+        const uint32_t end = r.in.count != 0u ? next : 0u;
+        const uint32_t a16 = (r.in.base & ~15u) + 16u * lane;
+        r.lv = *reinterpret_cast<const u32x4*>((slot + (L.esc - 16)) + (a16 < end ? a16 + 16u : 0u));
+        const u32x2 sm = ld_stream<u32x2>(slot + v_sm);
+        r.in.sm0 = sm.x; r.in.sm1 = sm.y;
+        /* a plain load, not a streaming one: a group's 64 bytes of a plane are half a cache line, and the
+           other half is the neighbouring group's, which another wave decodes at another time (streamed,
+           such lines came from memory twice: 13 % more bytes fetched and 204 instead of 179 us for
+           8 x 2^26 values) */
+        r.in.b0 = *reinterpret_cast<const uint32_t*>(slot + v_pl);
+        if (DT == ZIPCCL_FP32) {
+            const u32x4 lo = ld_stream<u32x4>(slot + v_lo);
+            r.in.lo[0] = lo.x; r.in.lo[1] = lo.y; r.in.lo[2] = lo.z; r.in.lo[3] = lo.w;
         }
     };
     /* decode the stage in r and add it; after a group's last peer the sums are stored */
@@ -634,14 +616,16 @@ __device__ __forceinline__ void reduce_stages(const ReduceArgs& a, const SlotLay
         /* nothing that uses the stage's loaded words may be scheduled before this point (among the loads
            of the next stage, where it would wait for them to land as well) */
         __builtin_amdgcn_sched_barrier(0);
-        if (FAST) {
-            /* the word holding the lane's byte of plane k sits in lane 16 k + lane / 4 */
-            const uint32_t w = r.in.b0, from = (lane >> 2) * 4u;
-            r.in.b0 = __builtin_amdgcn_ds_bpermute(from, w);
-            r.in.b1 = __builtin_amdgcn_ds_bpermute(from + 64u, w);
-            r.in.b2 = __builtin_amdgcn_ds_bpermute(from + 128u, w);
+        /* the word holding the lane's byte of plane k sits in lane 16 k + lane / 4 */
+        r.in.vmask = 0xFFu;
+        if (!FAST) {
+            const uint64_t e = (uint64_t)r.cur_g * kGroup + lane * kLaneElems;
+            r.in.vmask = e >= n ? 0u : (n - e >= kLaneElems ? 0xFFu : (1u << (uint32_t)(n - e)) - 1u);
         }
-        plane_bytes_of_words(r.in, lane);
+        const uint32_t w = r.in.b0, from = (lane >> 2) * 4u, sh = 8u * (lane & 3u);
+        r.in.b0 = __builtin_amdgcn_ubfe(__builtin_amdgcn_ds_bpermute(from, w), sh, 8u);
+        r.in.b1 = __builtin_amdgcn_ubfe(__builtin_amdgcn_ds_bpermute(from + 64u, w), sh, 8u);
+        r.in.b2 = __builtin_amdgcn_ubfe(__builtin_amdgcn_ds_bpermute(from + 128u, w), sh, 8u);
         /* park the slice; the wave's region holds 64 x 16 bytes, so every lane writes what it fetched and the
            store needs no predicate (lanes past the slice hold bytes that no lane picks) */
         *reinterpret_cast<u32x4*>(lds + 16u * lane) = r.lv;
@@ -758,23 +742,220 @@ __device__ __forceinline__ void reduce_stages(const ReduceArgs& a, const SlotLay
     }
 }
 
+/* What a wave has in flight of one peer's copy of a pair of groups; everything but the loaded words is wave-uniform. */
+struct PairBuf {
+    u32x4 sm;                         /* 16 sign+mantissa bytes */
+    uint32_t p0, p1, p2;              /* 16 code bits of each plane */
+    u32x4 lv;
+    const uint8_t* pre_slot;          /* next stage: its slot, */
+    uint32_t pre_base, pre_mid, pre_next;    /* the index entries of the two groups and the following one, */
+    uint32_t pre_nesc, pre_dec;       /* the slot's zero-point count and header word holding dec[0..3] */
+    const uint8_t* list;              /* 16 bytes in front of the aligned start of the pair's slice of the list */
+    uint32_t e0, mis, count_a, count_b, idx_bad;
+};
+
+/* Bytes of LDS per wave: the slice of two groups at any alignment (1024 + 15) and the words a lane may read past
+ * the last position it can be sent to; 2 KiB of sums on their way out. */
+constexpr uint32_t kPairRegion = 2048;
+static_assert(kPairRegion >= 2 * kGroup + 15 + 8 + 12, "a lane's words stay inside the region");
+
+/*
+ * The same for bf16 and whole tiles, two neighbouring groups (1024 values, 16 consecutive ones per lane) at a time and
+ * one such pair per wave: a stage is a peer.  The kernel is bound by instruction issue, and much of a stage does not
+ * depend on how many values a lane holds: one scan locates the zero-points of both groups (group a is lanes 0..31), one
+ * fetch brings their slices, which are adjacent, and the walk over slots and index entries is paid once.  A lane's
+ * plane bits are two bytes of a whole cache line per plane, loaded directly.  Addresses are scalar bases with the
+ * lane's constant offset: the scalar unit has the room now that a stage is twice as large.
+ * 8 x 2^25 bf16 -> FP32: 96.4 -> 84.6 us (6.1 TB/s of the 520 MB it cannot do without), 8 x 2^26: 187.6 -> 165.3.  More
+ * than one pair per wave is slower (2^25: 89.0 with two, 102.7 with four; 2 peers: 40.0, 41.1, 45.5).
+ */
+template <int ODT>
+__device__ __forceinline__ void reduce_pair(const ReduceArgs& a, const SlotLayout& L, uint64_t gs, uint32_t n_acc, uint32_t lane,
+                                            uint8_t* lds, const DecTables& tab, const uint32_t* s_peer, bool all_ok, uint32_t& bad)
+{
+    constexpr uint32_t OES = ODT == ZIPCCL_BF16 ? 2u : 4u;
+    const uint32_t ng = (uint32_t)((a.n + kGroup - 1) / kGroup), g = (uint32_t)(gs / kGroup);
+    const bool last_pair = g + 2u >= ng;
+    const uint64_t o_idx = L.idx + 4u * (uint64_t)g, o_sm = L.sm + gs, o_pl = L.p0 + (gs >> 3);      /* in a slot */
+    const uint32_t lane16 = lane * 16u;
+    float acc[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) acc[j] = -0.0f;
+
+    uint32_t jf = 0;
+    const uint8_t* slot_f = a.comp;                            /* all slots accepted: slot jf */
+    auto front = [&](PairBuf& r) {
+        /* some slot rejected: the j-th accepted one is not slot j */
+        r.pre_slot = all_ok ? slot_f : a.comp + (uint64_t)__builtin_amdgcn_readfirstlane(s_peer[jf]) * a.slot_cap;
+        r.pre_nesc = load_const_u32(r.pre_slot + 24);
+        r.pre_dec = load_const_u32(r.pre_slot + 40);
+        r.pre_base = load_const_u32(r.pre_slot + o_idx);
+        r.pre_mid = load_const_u32(r.pre_slot + o_idx + 4);
+        r.pre_next = load_const_u32(r.pre_slot + o_idx + (last_pair ? 4u : 8u));
+        if (jf + 1u < n_acc) {
+            ++jf;
+            slot_f += a.slot_cap;
+        }
+    };
+    auto issue = [&](PairBuf& r) {
+        r.e0 = (r.pre_dec >> 8) & 0xFFu;
+        const uint32_t next = last_pair ? r.pre_nesc : r.pre_next;
+        /* the two groups' entries must ascend, by at most 512 each, to an end inside the list */
+        r.count_a = r.pre_mid - r.pre_base;
+        r.count_b = next - r.pre_mid;
+        r.idx_bad = (uint32_t)(r.count_a > kGroup) | (uint32_t)(r.count_b > kGroup) | (uint32_t)(next > r.pre_nesc);
+        const uint32_t from = r.idx_bad ? 0u : r.pre_base & ~15u;
+        const uint32_t span = r.idx_bad || r.count_a + r.count_b == 0u ? 0u : next - from;   /* bytes of the list from there on */
+        r.mis = r.idx_bad ? 0u : r.pre_base & 15u;
+        r.list = r.pre_slot + (L.esc - 16u) + from;
+        r.lv = *reinterpret_cast<const u32x4*>(r.list + (lane16 < span ? lane16 + 16u : 0u));
+        r.sm = ld_stream<u32x4>((r.pre_slot + o_sm) + lane16);
+        const uint8_t* const pl = r.pre_slot + o_pl;
+        r.p0 = ld_stream<uint16_t>(pl + 2u * lane);
+        r.p1 = ld_stream<uint16_t>((pl + L.plane_bytes) + 2u * lane);
+        r.p2 = ld_stream<uint16_t>((pl + 2u * L.plane_bytes) + 2u * lane);
+    };
+    auto consume = [&](PairBuf& r) {
+        /* nothing that uses the stage's loaded words may be scheduled before this point */
+        __builtin_amdgcn_sched_barrier(0);
+        *reinterpret_cast<u32x4*>(lds + lane16) = r.lv;
+        if (__builtin_expect(!r.idx_bad && r.mis + r.count_a + r.count_b > 64u * 16u, 0)) {
+            /* a slice that no 64 aligned pieces cover: all but a few of the 1024 values are zero-points */
+            if (lane == 0) *reinterpret_cast<u32x4*>(lds + 64u * 16u) = *reinterpret_cast<const u32x4*>(r.list + 16u + 64u * 16u);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const uint32_t m = ((r.p0 | r.p1 | r.p2) ^ 0xFFFFu) & 0xFFFFu;
+        const uint32_t cnt = __popc(m);
+        const uint32_t inc = wave_incl_scan(cnt);
+        const uint32_t tot_a = __builtin_amdgcn_readlane(inc, 31), tot = __builtin_amdgcn_readlane(inc, 63);
+        bad |= r.idx_bad | (tot_a ^ r.count_a) | ((tot - tot_a) ^ r.count_b);      /* planes and IDX must agree */
+        /* the lane's zero-point exponents, those of its first eight values in front (clamped, so that a corrupt stream
+           still reads inside the region) */
+        const uint32_t first = min(r.mis + (inc - cnt), 2u * kGroup + 15u);
+        const uint32_t at[2] = {first, first + (uint32_t)__popc(m & 0xFFu)};
+        float x[16];
+#pragma unroll
+        for (uint32_t h = 0; h < 2; ++h) {
+            const uint32_t* w = reinterpret_cast<const uint32_t*>(lds + (at[h] & ~3u));
+            DecEsc es;
+            es.m = h ? m >> 8 : m & 0xFFu;
+            es.l8 = __builtin_amdgcn_alignbyte(w[1], w[0], at[h] & 3u);
+            es.h8 = __builtin_amdgcn_alignbyte(w[2], w[1], at[h] & 3u);
+            DecIn in;
+            in.sm0 = h ? r.sm.z : r.sm.x; in.sm1 = h ? r.sm.w : r.sm.y;
+            in.b0 = h ? r.p0 >> 8 : r.p0 & 0xFFu;
+            in.b1 = h ? r.p1 >> 8 : r.p1 & 0xFFu;
+            in.b2 = h ? r.p2 >> 8 : r.p2 & 0xFFu;
+            uint32_t lA, hA, lB, hB;
+            decode_bytes(in, es, r.e0, tab, lA, hA, lB, hB);
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {    /* value j as FP32 bits: high byte, low byte, 16 zero bits */
+                const uint32_t sel = ((4u + j) << 24) | (j << 16) | 0x0C0Cu;
+                x[8 * h + j] = __uint_as_float(perm(hA, lA, sel));
+                x[8 * h + 4 + j] = __uint_as_float(perm(hB, lB, sel));
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc[j] += x[j];
+        /* the additions happen here: put off past the next stage's loads, the decoded values cost more registers
+           than there are */
+        asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]), "+v"(acc[7]),
+                          "+v"(acc[8]), "+v"(acc[9]), "+v"(acc[10]), "+v"(acc[11]), "+v"(acc[12]), "+v"(acc[13]), "+v"(acc[14]), "+v"(acc[15]));
+    };
+
+    /* the pipeline of reduce_stages, stage k = accepted slot k */
+    PairBuf bufA, bufB;
+    front(bufA);
+    front(bufB);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  /* lgkmcnt(0): nothing pending when the loop is entered */
+    issue(bufA);
+    uint32_t k = 0;                      /* stage whose loads bufA holds */
+    while (k + 2u < n_acc) {             /* two stages, each with a real stage to look ahead to */
+        front(bufA);
+        asm volatile("" ::: "memory");
+        issue(bufB);
+        consume(bufA);
+        front(bufB);
+        asm volatile("" ::: "memory");
+        issue(bufA);
+        consume(bufB);
+        k += 2u;
+    }
+    if (k + 2u == n_acc) {               /* two stages left */
+        issue(bufB);
+        consume(bufA);
+        consume(bufB);
+    } else {
+        consume(bufA);
+    }
+
+    uint8_t* __restrict__ og = a.out + gs * OES;
+    bool any_nan = false;
+#pragma unroll
+    for (int j = 0; j < 16; j += 2) any_nan |= acc[j] != acc[j] || acc[j + 1] != acc[j + 1];
+    if (__builtin_expect(__ballot(any_nan) != 0ull, 0)) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc[j] = __uint_as_float(sum_bits(acc[j]));
+    }
+    /* The lane's 16 sums are 64 (bf16: 32) contiguous bytes; they leave through the wave's LDS region as 16
+       contiguous bytes per lane, 2 KiB at a time. */
+    constexpr uint32_t PIECES = 16u * OES / 16u, ROUNDS = PIECES / 2u;       /* 16-byte pieces per lane */
+    u32x4 piece[PIECES];
+    if (ODT == ZIPCCL_FP32) {
+#pragma unroll
+        for (uint32_t q = 0; q < PIECES; ++q)
+            piece[q] = u32x4{__float_as_uint(acc[4 * q]), __float_as_uint(acc[4 * q + 1]),
+                             __float_as_uint(acc[4 * q + 2]), __float_as_uint(acc[4 * q + 3])};
+    } else {
+#pragma unroll
+        for (uint32_t q = 0; q < PIECES; ++q) {
+            uint32_t o[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k)
+                o[k] = f32_bits_to_bf16_bits(__float_as_uint(acc[8 * q + 2 * k])) |
+                       (f32_bits_to_bf16_bits(__float_as_uint(acc[8 * q + 2 * k + 1])) << 16);
+            piece[q] = u32x4{o[0], o[1], o[2], o[3]};
+        }
+    }
+    constexpr uint32_t LANES = 64u / ROUNDS;                                 /* lanes that hand over per round */
+#pragma unroll
+    for (uint32_t h = 0; h < ROUNDS; ++h) {
+        if (lane / LANES == h) {
+#pragma unroll
+            for (uint32_t q = 0; q < PIECES; ++q)
+                *reinterpret_cast<u32x4*>(lds + ((lane % LANES) * PIECES + q) * 16u) = piece[q];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const u32x4 r0 = *reinterpret_cast<const u32x4*>(lds + lane16);
+        const u32x4 r1 = *reinterpret_cast<const u32x4*>(lds + 1024u + lane16);
+        __builtin_amdgcn_wave_barrier();
+        st_stream_a4((og + h * 2048u) + lane16, r0);
+        st_stream_a4((og + h * 2048u + 1024u) + lane16, r1);
+    }
+}
+
 /*
  * One launch covers a call: workgroups 0 .. a.n_full - 1 take whole tiles of a.gpw groups per wave (every group
  * complete, the output dword-aligned: the form without bounds checks), the workgroups after them the rest of the
  * shard in tiles of a.gpw_rest groups per wave through the general form.  Groups per wave: the larger, the fewer
  * workgroups pay for the header checks and the table build; 1 for small shards, and for the rest behind whole
- * tiles, so that there are enough workgroups to fill the chip.  REST = false: the launch holds whole tiles only
- * (the general form is compiled out: it costs the whole-tile workgroups a few per cent of vector instructions
- * to share a kernel with it).  Dynamic LDS: one 32-bit word per peer.
+ * tiles, so that there are enough workgroups to fill the chip.  PAIR: whole tiles are taken by reduce_pair
+ * (a.gpw = 2).  REST = false: the launch holds whole tiles only (the general form is compiled out: it costs the
+ * whole-tile workgroups registers to share a kernel with it).  Dynamic LDS: one 32-bit word per peer.
  */
-template <int DT, int ODT, bool REST>
-__global__ __launch_bounds__(kThreads, DT == ZIPCCL_BF16 ? 8 : 6) void k_decompress_reduce(const ReduceArgs a)
+template <int DT, int ODT, bool REST, bool PAIR>
+__global__ __launch_bounds__(kThreads, DT == ZIPCCL_BF16 ? (REST ? 7 : 8) : 6) void k_decompress_reduce(const ReduceArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];
     uint32_t* s_peer = reinterpret_cast<uint32_t*>(s_dyn);     /* the accepted slots, in slot order */
     __shared__ DecTables s_tab;
-    /* per wave: the zero-point slice of the group being decoded, or half a group of FP32 sums on their way out */
-    constexpr uint32_t kRegion = kEscRegion > 1024u ? kEscRegion : 1024u;
+    /* per wave: the zero-point slice of the group or pair being decoded, or sums on their way out */
+    constexpr uint32_t kRegion = PAIR ? kPairRegion : (kEscRegion > 1024u ? kEscRegion : 1024u);
     __shared__ __attribute__((aligned(16))) uint8_t s_esc[kWavesPerBlock][kRegion];
     __shared__ uint32_t s_wcnt[kWavesPerBlock];
     build_tables(s_tab);
@@ -817,13 +998,20 @@ __global__ __launch_bounds__(kThreads, DT == ZIPCCL_BF16 ? 8 : 6) void k_decompr
     n_acc = __builtin_amdgcn_readfirstlane(n_acc);
     uint32_t bad = n_acc != a.n_peers;
 
+    if (PAIR && whole) {                /* whole tiles of 8 groups: two neighbouring ones per wave */
+        if (n_acc != 0u) {
+            reduce_pair<ODT>(a, L, ts + (uint64_t)wave * (2 * kGroup), n_acc, lane, s_esc[wave], s_tab, s_peer, n_acc == a.n_peers, bad);
+            if (bad && a.status) atomicOr(a.status, (uint32_t)ZIPCCL_ERR_CORRUPT);
+            return;
+        }
+    }
     /* this wave's groups start at gs0, gs0 + 2048, ...; those that begin inside n count */
     const uint64_t gs0 = ts + (uint64_t)wave * kGroup;
     uint32_t n_groups = gpw;
     if (!whole) n_groups = gs0 >= n ? 0u : (uint32_t)min((uint64_t)gpw, (n - gs0 + kGroupStride - 1) / kGroupStride);
     if (n_groups != 0u) {
         if (n_acc != 0u) {
-            if (whole) reduce_stages<DT, ODT, true>(a, L, gs0, n_groups, n_acc, lane, s_esc[wave], s_tab, s_peer, n_acc == a.n_peers, bad);
+            if (!PAIR && whole) reduce_stages<DT, ODT, true>(a, L, gs0, n_groups, n_acc, lane, s_esc[wave], s_tab, s_peer, n_acc == a.n_peers, bad);
             else if (REST) reduce_stages<DT, ODT, false>(a, L, gs0, n_groups, n_acc, lane, s_esc[wave], s_tab, s_peer, n_acc == a.n_peers, bad);
         } else {
             /* no slot accepted: the sum of nothing */
@@ -874,18 +1062,18 @@ int launch_decompress(int dt, const DecompressArgs& a, void* stream)
 
 
 /*
- * Groups per wave of the fused reduce, from timings on MI355X over shards of 2^22 to 2^27 values.  One group per
- * wave while the shard gives the chip's resident workgroups (256 CUs x 8, or x 6 for fp32) too little to do
- * for a second group to pay; two from there on; four only for bf16 shards that fill the chip a whole number of
- * times with four (2048 workgroups at once), where the last round leaves no compute unit idle: 3 % faster than two
- * at 2^26 values, while between such sizes two groups per wave are 1-6 % faster than four.
+ * Groups per wave of the fused reduce, from timings on MI355X over shards of 2^18 to 2^27 values, 2 to 64 peers.  One
+ * group per wave while the shard gives the chip's resident workgroups too little to do for a second group to pay, two
+ * from there on: for bf16 as a pair of neighbours (reduce_pair), where more peers make a longer chain per wave and want
+ * more waves.  us, one group against a pair, 128 / 256 / 384 / 512 tiles of 8192 values: 8 peers 7.8 / 9.1, 10.3 / 10.5,
+ * 13.0 / 12.7, 15.1 / 15.1, then 18.8 / 17.1 at 640; 2 peers 7.1 / 6.1 at 384; 16 peers 21.3 / 21.4 at 384; 64 peers
+ * 69.9 / 78.5 at 384, 88.8 / 89.2 at 512.
  */
-static uint32_t reduce_groups_per_wave(uint64_t n, int dt)
+static uint32_t reduce_groups_per_wave(uint64_t n, int dt, uint32_t n_peers)
 {
     const uint64_t tiles = n / kTile;
     if (dt == ZIPCCL_FP32) return tiles < 2560u ? 1u : 2u;
-    if (tiles < 640u) return 1u;
-    return tiles % 2048u == 0 ? 4u : 2u;
+    return tiles < (n_peers <= 16u ? 384u : 512u) ? 1u : 2u;
 }
 
 int launch_decompress_reduce(int dt, int out_dt, const ReduceArgs& a, void* stream)
@@ -893,7 +1081,7 @@ int launch_decompress_reduce(int dt, int out_dt, const ReduceArgs& a, void* stre
     hipStream_t s = (hipStream_t)stream;
     const dim3 block(kThreads);
     ReduceArgs b = a;
-    b.gpw = reduce_groups_per_wave(a.n, dt);
+    b.gpw = reduce_groups_per_wave(a.n, dt, a.n_peers);
     const uint64_t per = (uint64_t)kGroup * kWavesPerBlock * b.gpw;
     /* whole tiles with a dword-aligned output go through the form without bounds checks, the rest (under one
        tile, or everything when the output is only 2-byte aligned) through the general one, in the same launch */
@@ -907,19 +1095,18 @@ int launch_decompress_reduce(int dt, int out_dt, const ReduceArgs& a, void* stre
     uint64_t n_rest = (rest + per_rest - 1) / per_rest;
     if (a.n == 0) n_rest = 1;           /* one workgroup that only checks the headers */
     const dim3 grid((uint32_t)(full + n_rest));
-#define ZIPCCL_REDUCE(REST)                                                                                            \
+#define ZIPCCL_REDUCE(DT, ODT, PAIR)                                                                                   \
     do {                                                                                                               \
-        if (dt == ZIPCCL_BF16 && out_dt == ZIPCCL_FP32)                                                                \
-            hipLaunchKernelGGL((k_decompress_reduce<ZIPCCL_BF16, ZIPCCL_FP32, REST>), grid, block, lds_bytes, s, b);   \
-        else if (dt == ZIPCCL_BF16)                                                                                    \
-            hipLaunchKernelGGL((k_decompress_reduce<ZIPCCL_BF16, ZIPCCL_BF16, REST>), grid, block, lds_bytes, s, b);   \
-        else if (out_dt == ZIPCCL_FP32)                                                                                \
-            hipLaunchKernelGGL((k_decompress_reduce<ZIPCCL_FP32, ZIPCCL_FP32, REST>), grid, block, lds_bytes, s, b);   \
-        else                                                                                                           \
-            hipLaunchKernelGGL((k_decompress_reduce<ZIPCCL_FP32, ZIPCCL_BF16, REST>), grid, block, lds_bytes, s, b);   \
+        if (n_rest) hipLaunchKernelGGL((k_decompress_reduce<DT, ODT, true, PAIR>), grid, block, lds_bytes, s, b);      \
+        else hipLaunchKernelGGL((k_decompress_reduce<DT, ODT, false, PAIR>), grid, block, lds_bytes, s, b);            \
     } while (0)
-    if (n_rest) ZIPCCL_REDUCE(true);
-    else ZIPCCL_REDUCE(false);
+    const bool pair = dt == ZIPCCL_BF16 && b.gpw == 2u;
+    if (pair && out_dt == ZIPCCL_FP32) ZIPCCL_REDUCE(ZIPCCL_BF16, ZIPCCL_FP32, true);
+    else if (pair) ZIPCCL_REDUCE(ZIPCCL_BF16, ZIPCCL_BF16, true);
+    else if (dt == ZIPCCL_BF16 && out_dt == ZIPCCL_FP32) ZIPCCL_REDUCE(ZIPCCL_BF16, ZIPCCL_FP32, false);
+    else if (dt == ZIPCCL_BF16) ZIPCCL_REDUCE(ZIPCCL_BF16, ZIPCCL_BF16, false);
+    else if (out_dt == ZIPCCL_FP32) ZIPCCL_REDUCE(ZIPCCL_FP32, ZIPCCL_FP32, false);
+    else ZIPCCL_REDUCE(ZIPCCL_FP32, ZIPCCL_BF16, false);
 #undef ZIPCCL_REDUCE
     return (int)hipGetLastError();
 }

@@ -337,3 +337,68 @@ def test_reduce_of_the_largest_peer_count_with_rejected_slots_in_every_round():
     torch.cuda.synchronize()
     assert int(d_st.item()) == 4
     assert np.array_equal(d_out.cpu().numpy().view(np.uint32), want)
+
+
+def _uneven(rng, n, p):
+    """bf16 values whose zero-points (exponents outside the window of sigma 0.02) come in runs: pairs of groups that
+    hold none, nearly all or only zero-points, behind prefixes that shift their slices to every alignment."""
+    x = W.f32_to_bf16_words(rng.standard_normal(n, dtype=np.float32) * np.float32(0.02))
+    for k in range(0, n // 1024, 3):
+        s = 1024 * k
+        dense = 1024 - (k // 3 + 5 * p) % 20                       # 1005 .. 1024 zero-points in the pair
+        where = rng.permutation(1024)[:dense]
+        x[s:s + 1024] = 0x3C12
+        x[s + where] = 0x4F00 + rng.integers(0, 127, dense).astype(np.uint16)
+        x[s + 1024 + rng.integers(0, 1024, (k + p) % 17)] = 0x0000
+    return x
+
+
+@pytest.mark.parametrize("tail", [0, 1, 511, 513, 4095, 4096 + 1536])
+def test_reduce_pairs_of_groups(tail):
+    """bf16 shards from the size on at which a wave takes two neighbouring groups (384 tiles), with every kind of rest
+    behind the whole tiles, one to five peers (odd and even lengths of the pipeline), slices of the zero-point list
+    up to the full 1024 bytes at any alignment, both outputs: bit-equal to the oracle."""
+    rng = np.random.default_rng(50 + tail)
+    n = 384 * 8192 + tail
+    for P in (1, 2, 5) if tail in (0, 4095) else (2,):
+        print(f"[reduce pairs] n={n} P={P}", flush=True)
+        peers = [_uneven(rng, n, p) for p in range(P)]
+        for out_dt in (z.FP32, z.BF16):
+            _check(peers, z.BF16, [0.02], out_dt, f"pairs n={n} P={P} out={out_dt}")
+
+
+def test_reduce_pairs_flag_damage_and_leave_rejected_slots_out():
+    """In a shard that is taken in pairs: each index entry of a pair checked on its own (first, middle, last of the chunk),
+    plane bits, a rejected header; an intact call stays clean."""
+    rng = np.random.default_rng(60)
+    P, n = 3, 384 * 8192
+    peers = _peers(rng, P, n, z.BF16, [0.02])
+    buf = _receive_buffer(peers, z.BF16, [0.02])
+    cap1 = z.zipccl_max_compressed_size(n, z.BF16, 1)
+    idx = 128 + n + 3 * (n // 8)                                   # n is a multiple of 1024: no padding in front
+    d_out = torch.zeros(n, dtype=torch.int32, device=DEV)
+
+    def run(b):
+        d_st = torch.zeros(1, dtype=torch.int32, device=DEV)
+        z.zipccl_decompress_reduce(b, d_out, n, z.BF16, P, z.FP32, d_st)
+        torch.cuda.synchronize()
+        return int(d_st.item())
+
+    assert run(buf) == 0
+    last = n // 512 - 1
+    for g in (0, 1, 2, 1001, 1002, last - 1, last):
+        for delta in (1, 255):                                     # one more, one less (mod 256)
+            bad = buf.clone()
+            at = cap1 + idx + 4 * g
+            bad[at] = (int(bad[at]) + delta) % 256
+            assert run(bad) == 4, (g, delta)
+    bad = buf.clone()                                              # 8 values of the last peer become zero-points
+    for k in range(3):
+        bad[2 * cap1 + 128 + n + k * (n // 8) + 77] = 0
+    assert run(bad) == 4
+    bad = buf.clone()
+    bad[cap1 + 2] = 0x00                                           # the middle slot's magic
+    assert run(bad) == 4
+    rest = _receive_buffer([peers[0], peers[2]], z.BF16, [0.02])
+    want = oracle.decompress_reduce(rest.cpu().numpy(), n, z.BF16, 2, z.FP32)
+    assert np.array_equal(d_out.cpu().numpy().view(np.uint32), want)
