@@ -7,6 +7,8 @@
  * lane); decoding is SWAR on packed bytes (table-driven bit spread, v_perm_b32 / v_bfi_b32
  * recombination) with a DPP wave scan to locate each lane's zero-point exponents.
  */
+#include <type_traits>
+
 #include "zipccl_device.h"
 
 namespace zipccl {
@@ -97,17 +99,6 @@ __device__ __forceinline__ void check_index(DecIn& r, uint32_t next, uint32_t n_
     r.count = r.idx_bad ? 0u : d;
 }
 
-/* Phase 0: the group's slice of the zero-point list by IDX alone (scalar loads). */
-__device__ __forceinline__ void decode_index(const uint8_t* __restrict__ slot, const SlotLayout& L, uint64_t n,
-                                             uint32_t n_esc, uint64_t gstart, DecIn& r, uint32_t& next)
-{
-    const uint64_t g = gstart / kGroup, ng = (n + kGroup - 1) / kGroup;
-    const uint32_t* __restrict__ idx = reinterpret_cast<const uint32_t*>(slot + L.idx);
-    r.base = idx[g];
-    next = g + 1 < ng ? idx[g + 1] : n_esc;
-    check_index(r, next, n_esc);
-}
-
 /* Phase 1a: fetch the slice [base, base + count): 16 aligned bytes per lane by the first 33 lanes, which
  * covers 512 bytes at any alignment.  Aligned reads stay inside pad128(n_esc); lanes past the slice read
  * the 16 bytes in front of the list instead (the end of the static part), so the load needs no predicate
@@ -121,57 +112,59 @@ __device__ __forceinline__ void decode_fetch_list(const uint8_t* __restrict__ sl
     v = *reinterpret_cast<const u32x4*>(esc + (a < end ? (int64_t)a : (int64_t)-16));
 }
 
-/* Phase 1b: the lane's SM bytes, plane bytes and (fp32) low words. */
-template <int DT, bool FAST, bool QUAD = false>
+/* Which of the lane's 8 values of the group at gs exist (bit j = value j): bf16: 8 consecutive ones; fp32: two quads,
+ * [4 lane, 4 lane + 4) of the group's first half and of its second. */
+template <int DT>
+__device__ __forceinline__ uint32_t value_mask(uint64_t n, uint64_t gs, uint32_t lane)
+{
+    const uint32_t left = gs >= n ? 0u : (uint32_t)min(n - gs, (uint64_t)kGroup);      /* values of the group */
+    if (DT == ZIPCCL_BF16) {
+        const uint32_t e = lane * kLaneElems;
+        return e >= left ? 0u : (1u << min(left - e, 8u)) - 1u;
+    }
+    const uint32_t a = lane * 4u, b = a + kGroup / 2;
+    return (a >= left ? 0u : (1u << min(left - a, 4u)) - 1u) | ((b >= left ? 0u : (1u << min(left - b, 4u)) - 1u) << 4);
+}
+
+/*
+ * Phase 1b: the lane's SM bytes, plane bytes and (fp32) low words.  Every output row of 1 KiB is 16 contiguous bytes per
+ * lane, so fp32 lanes hold two quads (value_mask).  FAST: a whole group.  Otherwise lanes without values read the
+ * first bytes of the group's part of the section instead, and a group past the end reads group 0's (the chunk is not
+ * empty): no load is under a condition, so all groups' loads are in flight together.  The planes of a group that has
+ * any value are there as a whole.
+ */
+template <int DT, bool FAST>
 __device__ __forceinline__ void decode_load(const uint8_t* __restrict__ slot, const SlotLayout& L, uint64_t n,
                                             uint64_t gstart, uint32_t lane, DecIn& r)
 {
-    if (QUAD) {
-        /* fp32, whole groups: the lane's 8 values are two quads, [4 lane, 4 lane + 4) of the group's first
-           and of its second half, so that its 32 output bytes are two contiguous 16-byte stores per wave row.
-           The lane fetches one plane byte per plane, the one it shares with its neighbour: even lanes that
-           of the first half, odd lanes that of the second (quad_plane_bytes sorts the nibbles out). */
-        const uint8_t* __restrict__ sm = slot + L.sm + gstart;
-        r.sm0 = ld_stream<uint32_t>(sm + lane * 4u);
-        r.sm1 = ld_stream<uint32_t>((sm + kGroup / 2) + lane * 4u);
-        const uint8_t* pl = slot + L.p0 + (gstart >> 3);
-        const uint32_t pi = (lane >> 1) + 32u * (lane & 1u);
-        r.b0 = ld_stream<uint8_t>(pl + pi);
-        r.b1 = ld_stream<uint8_t>((pl + L.plane_bytes) + pi);
-        r.b2 = ld_stream<uint8_t>((pl + 2 * L.plane_bytes) + pi);
-        const uint8_t* __restrict__ lo = slot + L.lo + 2 * gstart;
-        const u32x2 la = ld_stream<u32x2>(lo + lane * 8u);
-        const u32x2 lb = ld_stream<u32x2>((lo + kGroup) + lane * 8u);
-        r.lo[0] = la.x; r.lo[1] = la.y; r.lo[2] = lb.x; r.lo[3] = lb.y;
-        r.vmask = 0xFFu;
-        return;
-    }
-    /* gstart is wave-uniform: uniform 64-bit base + 32-bit lane offset */
-    const uint64_t e = gstart + lane * kLaneElems;
-    r.sm0 = r.sm1 = r.b0 = r.b1 = r.b2 = 0;
-    r.lo[0] = r.lo[1] = r.lo[2] = r.lo[3] = 0;
-    if (FAST || e < pad128(n)) {
-        const u32x2 v = ld_stream<u32x2>((slot + L.sm + gstart) + lane * 8u);
+    r.vmask = FAST ? 0xFFu : value_mask<DT>(n, gstart, lane);
+    const uint64_t gs = FAST || gstart < n ? gstart : 0u;
+    /* wave-uniform 64-bit bases + 32-bit lane offsets */
+    const uint8_t* __restrict__ sm = slot + L.sm + gs;
+    const uint8_t* __restrict__ pl = slot + L.p0 + (gs >> 3);     /* 64-byte aligned: a group's 64 plane bytes */
+    uint32_t pi = lane;
+    if (DT == ZIPCCL_BF16) {
+        const u32x2 v = ld_stream<u32x2>(sm + (FAST || r.vmask ? lane * 8u : 0u));
         r.sm0 = v.x; r.sm1 = v.y;
+        r.lo[0] = r.lo[1] = r.lo[2] = r.lo[3] = 0;
+    } else {
+        /* The lane fetches one plane byte per plane, the one it shares with its neighbour: even lanes that
+           of the first half, odd lanes that of the second (quad_plane_bytes sorts the nibbles out). */
+        const uint32_t ia = FAST || (r.vmask & 15u) ? lane * 4u : 0u, ib = FAST || (r.vmask >> 4) ? kGroup / 2 + lane * 4u : 0u;
+        r.sm0 = ld_stream<uint32_t>(sm + ia);
+        r.sm1 = ld_stream<uint32_t>(sm + ib);
+        pi = (lane >> 1) + 32u * (lane & 1u);
+        const uint8_t* __restrict__ lo = slot + L.lo + 2 * gs;
+        const u32x2 la = ld_stream<u32x2>(lo + 2u * ia);
+        const u32x2 lb = ld_stream<u32x2>(lo + 2u * ib);
+        r.lo[0] = la.x; r.lo[1] = la.y; r.lo[2] = lb.x; r.lo[3] = lb.y;
     }
-    const uint64_t pb = e >> 3;
-    if (FAST || pb < L.plane_bytes) {
-        const uint8_t* pl = slot + L.p0 + (gstart >> 3);     /* 64-byte aligned: a group's 64 plane bytes */
-        r.b0 = ld_stream<uint8_t>(pl + lane);
-        r.b1 = ld_stream<uint8_t>((pl + L.plane_bytes) + lane);
-        r.b2 = ld_stream<uint8_t>((pl + 2 * L.plane_bytes) + lane);
-    }
-    if (DT == ZIPCCL_FP32) {
-        if (FAST || 2 * e < pad128(2 * n)) {
-            const u32x4 v = ld_stream<u32x4>((slot + L.lo + 2 * gstart) + lane * 16u);
-            r.lo[0] = v.x; r.lo[1] = v.y; r.lo[2] = v.z; r.lo[3] = v.w;
-        }
-    }
-    r.vmask = 0xFFu;
-    if (!FAST) r.vmask = e >= n ? 0u : (n - e >= 8 ? 0xFFu : ((1u << (uint32_t)(n - e)) - 1u));
+    r.b0 = ld_stream<uint8_t>(pl + pi);
+    r.b1 = ld_stream<uint8_t>((pl + L.plane_bytes) + pi);
+    r.b2 = ld_stream<uint8_t>((pl + 2 * L.plane_bytes) + pi);
 }
 
-/* After decode_load<.., QUAD = true>: from the plane bytes shared by a pair of lanes to each lane's own
+/* After decode_load of fp32: from the plane bytes shared by a pair of lanes to each lane's own
  * byte (bits 0..3 = its first quad, bits 4..7 = its second), the three planes at once. */
 __device__ __forceinline__ void quad_plane_bytes(DecIn& r, uint32_t lane)
 {
@@ -217,7 +210,7 @@ __device__ __forceinline__ DecEsc decode_locate(const DecIn& in, const uint8_t* 
 __device__ __forceinline__ DecEsc decode_locate_quad(const DecIn& in, const uint8_t* lds)
 {
     DecEsc r;
-    r.m = (in.b0 | in.b1 | in.b2) ^ 0xFFu;
+    r.m = ((in.b0 | in.b1 | in.b2) ^ 0xFFu) & in.vmask;
     const uint32_t cA = __popc(r.m & 15u), cB = __popc(r.m >> 4);
     const uint32_t inc = wave_incl_scan(cA | (cB << 16));
     const uint32_t tot = __builtin_amdgcn_readlane(inc, 63);
@@ -271,54 +264,43 @@ __device__ __forceinline__ void decode_values(const DecIn& in, const DecEsc& es,
     hp[3] = perm(hB, lB, 0x07030602u);
 }
 
-/* Rebuild the 8 values and store them. */
-template <int DT, bool FAST>
-__device__ __forceinline__ void decode_store(uint8_t* __restrict__ cout, const DecIn& in, const DecEsc& es,
-                                             uint64_t gstart, uint32_t e0, uint32_t lane, const DecTables& tab,
-                                             bool skew = false)
+/* Rebuild the lane's 8 values as they are stored, 16 bytes per row of 1 KiB: bf16: one row; fp32: one of the group's
+ * first half and one of its second. */
+template <int DT>
+__device__ __forceinline__ void decode_rows(const DecIn& in, const DecEsc& es, uint32_t e0, const DecTables& tab,
+                                            u32x4 row[DT == ZIPCCL_BF16 ? 1 : 2])
 {
-    const uint64_t e = gstart + lane * kLaneElems;
     uint32_t hp[4];
-    decode_values<DT == ZIPCCL_FP32 && FAST>(in, es, e0, tab, hp);
-    if (FAST) {
-        if (DT == ZIPCCL_BF16) {
-            uint8_t* __restrict__ p = (cout + gstart * 2) + lane * 16u;
-            if (!skew) {
-                st_stream_a4(p, u32x4{hp[0], hp[1], hp[2], hp[3]});
-            } else {
-                /* the chunk starts at an odd element of the tensor (bytes 2 but not 4-byte aligned):
-                   halfword + three dwords + halfword */
-                st_stream<uint16_t>(p, (uint16_t)hp[0]);
-                __builtin_nontemporal_store(u32x3{__builtin_amdgcn_alignbyte(hp[1], hp[0], 2u),
-                                                  __builtin_amdgcn_alignbyte(hp[2], hp[1], 2u),
-                                                  __builtin_amdgcn_alignbyte(hp[3], hp[2], 2u)},
-                                            reinterpret_cast<u32x3_a4*>(p + 2));
-                st_stream<uint16_t>(p + 14, (uint16_t)(hp[3] >> 16));
-            }
-        } else {
-            /* two quads per lane (decode_load<.., QUAD>): values 0..3 belong to the group's first half,
-               4..7 to its second; each store is 16 contiguous bytes per lane */
-            uint32_t x[8];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                x[2 * k] = perm(hp[k], in.lo[k], 0x05040100u);
-                x[2 * k + 1] = perm(hp[k], in.lo[k], 0x07060302u);
-            }
-            st_stream_a4((cout + gstart * 4) + lane * 16u, u32x4{x[0], x[1], x[2], x[3]});
-            st_stream_a4((cout + gstart * 4 + 2 * kGroup) + lane * 16u, u32x4{x[4], x[5], x[6], x[7]});
-        }
+    decode_values<DT == ZIPCCL_FP32>(in, es, e0, tab, hp);
+    if (DT == ZIPCCL_BF16) {
+        row[0] = u32x4{hp[0], hp[1], hp[2], hp[3]};
     } else {
+        uint32_t x[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if ((in.vmask >> j) & 1u) {
-                const uint32_t h = (hp[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
-                if (DT == ZIPCCL_BF16) {
-                    *reinterpret_cast<uint16_t*>(cout + (e + j) * 2) = (uint16_t)h;
-                } else {
-                    const uint32_t l = (in.lo[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
-                    *reinterpret_cast<uint32_t*>(cout + (e + j) * 4) = (h << 16) | l;
-                }
-            }
+        for (int k = 0; k < 4; ++k) {
+            x[2 * k] = perm(hp[k], in.lo[k], 0x05040100u);
+            x[2 * k + 1] = perm(hp[k], in.lo[k], 0x07060302u);
+        }
+        row[0] = u32x4{x[0], x[1], x[2], x[3]};
+        row[DT == ZIPCCL_BF16 ? 0 : 1] = u32x4{x[4], x[5], x[6], x[7]};
+    }
+}
+
+/* The existing ones of a lane's 16 bytes (bit j of mask = value j exists). */
+template <int DT>
+__device__ __forceinline__ void store_masked(uint8_t* p, const u32x4& v, uint32_t mask)
+{
+    constexpr uint32_t N = DT == ZIPCCL_BF16 ? 8u : 4u;
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    if (mask == (1u << N) - 1u) {
+        st_stream_a2(p, v);
+        return;
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < N; ++j) {
+        if ((mask >> j) & 1u) {
+            if (DT == ZIPCCL_BF16) reinterpret_cast<uint16_t*>(p)[j] = (uint16_t)(w[j >> 1] >> (16u * (j & 1u)));
+            else reinterpret_cast<uint32_t*>(p)[j] = w[j];
         }
     }
 }
@@ -364,7 +346,7 @@ __device__ __forceinline__ bool check_header(const HeaderWords& hdr, const SlotL
     return ok;
 }
 
-/* GPW groups per wave: a workgroup decodes a tile of 4 * GPW groups.  The compressed format does not know
+/* GPW (1, 2 or 4) groups per wave: a workgroup decodes a tile of 4 * GPW groups.  The compressed format does not know
  * tiles (groups are located through IDX alone), so this is free to differ from the compress side's tile. */
 template <int DT, uint32_t GPW>
 __global__ __launch_bounds__(kThreads, DT == ZIPCCL_BF16 ? 8 : 6)   /* waves per SIMD: <= 64 VGPRs for bf16, <= 80 for fp32 */
@@ -378,18 +360,27 @@ void k_decompress(const DecompressArgs a)
     /* grid = (tiles of the largest chunk, chunks) */
     const uint32_t c = blockIdx.y;
     const uint64_t n = a.tab.elem_off[c + 1] - a.tab.elem_off[c];
-    if (blockIdx.x >= (n == 0 ? 1u : (n + TILE - 1) / TILE)) return;   /* an empty chunk still has its header checked */
+    const uint32_t tiles = n == 0 ? 1u : (uint32_t)((n + TILE - 1) / TILE);    /* an empty chunk still has its header checked */
+    if (blockIdx.x >= tiles) return;
     const uint64_t ts = (uint64_t)blockIdx.x * TILE;
     const uint8_t* __restrict__ slot = a.comp + a.tab.slot_off[c];
     uint8_t* __restrict__ cout = a.out + a.tab.elem_off[c] * ES;
     const SlotLayout L = slot_layout(n, DT);
-    /* whole tiles take the vector path; a chunk of the tensor starts at some element of it, so its bytes are
-       dword-aligned or (bf16, odd element) skewed by one halfword */
+    /* whole tiles need no masks */
     const bool fast = ts + TILE <= n;
-    const bool skew = (reinterpret_cast<uintptr_t>(cout) & 2u) != 0;
     const uint32_t lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   /* scalar: group addresses and index entries stay out of the vector registers */
-    const uint64_t ng = (n + kGroup - 1) / kGroup;
+    const uint32_t ng = (uint32_t)((n + kGroup - 1) / kGroup);                /* at most 2^23 */
+    /* A chunk of the tensor starts at some element of it, so that rows of 1 KiB may share cache lines with their
+       neighbours.  One or two groups per wave are neighbours: the pieces of a shared line come from one wave, one after
+       the other (from two waves of a tile, each half a line at its own time, they took twice as long: 64 chunks of
+       262 139 values, bf16 29.1 -> 12.4 us, fp32 49.1 -> 23.5; 11.5 and 22.9 on line boundaries).  Four groups per
+       wave, for chunks on line boundaries only, are four apart, which shares a short tile evenly among the waves
+       (2^24 bf16 values: 11.7 us, 12.1 with neighbours). */
+    constexpr bool NEIGHBOURS = GPW <= 2u;
+    constexpr uint32_t step = NEIGHBOURS ? 1u : kWavesPerBlock;
+    const uint32_t g0 = (uint32_t)(ts / kGroup) + (NEIGHBOURS ? wave * GPW : wave);
+    const uint64_t gs0 = (uint64_t)g0 * kGroup;
 
     /* What does not depend on the header or on IDX goes out first (the static part is readable: the host
        checked it): SM, planes and low words of the wave's groups, and the groups' index entries.
@@ -397,15 +388,20 @@ void k_decompress(const DecompressArgs a)
     const HeaderWords hdr = load_header(slot);
     DecIn in[GPW];
     uint32_t next[GPW];
-    if (fast) {
+    if (n != 0) {
+        const uint32_t* __restrict__ idx = reinterpret_cast<const uint32_t*>(slot + L.idx);
+        if (fast) {
+#pragma unroll
+            for (uint32_t u = 0; u < GPW; ++u) decode_load<DT, true>(slot, L, n, gs0 + (uint64_t)(u * step) * kGroup, lane, in[u]);
+        } else {
+#pragma unroll
+            for (uint32_t u = 0; u < GPW; ++u) decode_load<DT, false>(slot, L, n, gs0 + (uint64_t)(u * step) * kGroup, lane, in[u]);
+        }
 #pragma unroll
         for (uint32_t u = 0; u < GPW; ++u) {
-            const uint64_t gstart = ts + (uint64_t)(u * kWavesPerBlock + wave) * kGroup;
-            decode_load<DT, true, DT == ZIPCCL_FP32>(slot, L, n, gstart, lane, in[u]);
-            const uint64_t g = gstart / kGroup;
-            const uint32_t* __restrict__ idx = reinterpret_cast<const uint32_t*>(slot + L.idx);
-            in[u].base = idx[g];
-            next[u] = idx[g + 1 < ng ? g + 1 : g];
+            const uint32_t g = g0 + u * step;
+            in[u].base = idx[min(g, ng - 1)];
+            next[u] = idx[min(g + 1, ng - 1)];
         }
     }
     build_tables(s_tab);
@@ -417,15 +413,22 @@ void k_decompress(const DecompressArgs a)
         if (threadIdx.x == 0 && a.status) atomicOr(a.status, (uint32_t)ZIPCCL_ERR_CORRUPT);
         return;
     }
+    if (n == 0) return;
 
     uint32_t bad = 0;
-    if (fast) {
-        /* phases over the wave's groups, so that each phase's loads are all in flight together */
-        DecEsc es[GPW];
+    constexpr uint32_t ROWS = DT == ZIPCCL_BF16 ? 1u : 2u;
+    uint8_t* __restrict__ dst = cout + gs0 * ES;
+    DecEsc es[GPW];
+    /* phases over the wave's groups, so that each phase's loads are all in flight together; a group past the end
+       has an empty slice */
+    auto locate = [&](auto whole_tile) {
+        constexpr bool FAST = decltype(whole_tile)::value;
         u32x4 lv[GPW];
 #pragma unroll
         for (uint32_t u = 0; u < GPW; ++u) {
-            const uint64_t g = (ts + (uint64_t)(u * kWavesPerBlock + wave) * kGroup) / kGroup;
+            const uint32_t g = g0 + u * step;
+            if (FAST) in[u].vmask = 0xFFu;
+            else if (g >= ng) in[u].base = n_esc;
             if (g + 1 >= ng) next[u] = n_esc;
             check_index(in[u], next[u], n_esc);
         }
@@ -444,31 +447,30 @@ void k_decompress(const DecompressArgs a)
             } else {
                 es[u] = decode_locate(in[u], s_esc[wave][u]);
             }
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < GPW; ++u) {
-            decode_store<DT, true>(cout, in[u], es[u], ts + (uint64_t)(u * kWavesPerBlock + wave) * kGroup, e0, lane, s_tab,
-                                   DT == ZIPCCL_BF16 && skew);
             bad |= es[u].bad;
         }
-    } else {
+    };
+    if (fast) {
+        locate(std::true_type{});
+#pragma unroll
         for (uint32_t u = 0; u < GPW; ++u) {
-            const uint64_t gstart = ts + (uint64_t)(u * kWavesPerBlock + wave) * kGroup;
-            if (gstart < n) {
-                DecIn r;
-                uint32_t nx;
-                u32x4 lv;
-                decode_index(slot, L, n, n_esc, gstart, r, nx);
-                decode_fetch_list(slot, L, r, nx, lane, lv);
-                decode_load<DT, false>(slot, L, n, gstart, lane, r);
-                decode_park_list(s_esc[wave][u], lane, lv);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                const DecEsc es = decode_locate(r, s_esc[wave][u]);
-                decode_store<DT, false>(cout, r, es, gstart, e0, lane, s_tab);
-                bad |= es.bad;
-            }
+            u32x4 row[ROWS];
+            decode_rows<DT>(in[u], es[u], e0, s_tab, row);
+#pragma unroll
+            for (uint32_t q = 0; q < ROWS; ++q) st_stream_a2((dst + (u * step * ROWS + q) * 1024u) + lane * 16u, row[q]);
+        }
+    } else {
+        locate(std::false_type{});
+#pragma unroll
+        for (uint32_t u = 0; u < GPW; ++u) {
+            const uint64_t gs = gs0 + (uint64_t)u * step * kGroup;
+            if (gs >= n) break;
+            u32x4 row[ROWS];
+            decode_rows<DT>(in[u], es[u], e0, s_tab, row);
+#pragma unroll
+            for (uint32_t q = 0; q < ROWS; ++q)
+                store_masked<DT>((dst + (u * step * ROWS + q) * 1024u) + lane * 16u, row[q],
+                                 DT == ZIPCCL_BF16 ? in[u].vmask : (in[u].vmask >> (4u * q)) & 15u);
         }
     }
     if (bad && a.status) atomicOr(a.status, (uint32_t)ZIPCCL_ERR_CORRUPT);
@@ -1032,11 +1034,8 @@ __global__ __launch_bounds__(kThreads, DT == ZIPCCL_BF16 ? (REST ? 7 : 8) : 6) v
 
 } // namespace
 
-/* launches that write at least this many bytes decode in tiles of 8 groups, smaller ones in tiles of 16 */
-constexpr uint64_t kDecSmallTileFrom = 64ull << 20;
-
-template <uint32_t GPW>
-static int launch_decompress_gpw(int dt, const DecompressArgs& a, void* stream)
+template <int DT, uint32_t GPW>
+static int launch_decompress_gpw(const DecompressArgs& a, hipStream_t s)
 {
     constexpr uint64_t TILE = (uint64_t)kGroup * kWavesPerBlock * GPW;
     uint64_t tiles = 1;
@@ -1045,19 +1044,30 @@ static int launch_decompress_gpw(int dt, const DecompressArgs& a, void* stream)
         tiles = t > tiles ? t : tiles;
     }
     const dim3 grid((uint32_t)tiles, a.tab.n_chunks), block(kThreads);
-    if (dt == ZIPCCL_BF16)
-        hipLaunchKernelGGL((k_decompress<ZIPCCL_BF16, GPW>), grid, block, 0, (hipStream_t)stream, a);
-    else
-        hipLaunchKernelGGL((k_decompress<ZIPCCL_FP32, GPW>), grid, block, 0, (hipStream_t)stream, a);
+    hipLaunchKernelGGL((k_decompress<DT, GPW>), grid, block, 0, s, a);
     return (int)hipGetLastError();
 }
 
+/*
+ * Groups per wave by the values of the launch, from timings on MI355X (us in a graph, 1 / 2 / 4 groups).  bf16: 2^18
+ * values 2.9 / 3.2 / 3.9, 2^20 3.4 / 3.4 / 4.1, 2^21 4.2 / 3.9 / 4.2, 5 * 2^20 7.0 / 5.4 / 5.6, 6 * 2^20 7.7 / 6.4 / 5.7,
+ * 2^23 9.4 / 7.4 / 6.4, 2^24 15.2 / 11.9 / 11.8, 24 * 2^20 21.0 / 16.3 / 17.1; 2^28 72.6 with two, 74.4 with four.  fp32:
+ * 2^18 3.3 / 3.7 / 4.6, 2^20 4.2 / 4.4 / 5.4, 2^21 5.0 / 5.0 / 5.9, 2^22 7.3 / 6.5 / 7.1, 2^24 23.0 / 23.1 / 24.2; four
+ * win only about 6 * 2^20 (10.7 / 10.1 / 8.6) and are not built.  In small launches fewer groups per wave mean more
+ * waves that share one chain of latencies; in launches of about one round of resident workgroups four mean one round
+ * instead of a second, almost empty one (only where the chunks start on line boundaries: 64 chunks of 131 073 bf16
+ * values 7.9 us with two neighbouring groups, 8.3 with four).
+ */
 int launch_decompress(int dt, const DecompressArgs& a, void* stream)
 {
-    /* Measured on MI355X: tiles of 8 groups (4096 values) decode 2-3 % faster than tiles of 16 once the launch
-       holds many workgroups per compute unit; a launch of about one round of workgroups is faster with 16. */
-    const uint64_t total = (a.tab.elem_off[a.tab.n_chunks] - a.tab.elem_off[0]) * (dt == ZIPCCL_BF16 ? 2u : 4u);
-    return total >= kDecSmallTileFrom ? launch_decompress_gpw<2>(dt, a, stream) : launch_decompress_gpw<kGroupsPerWave>(dt, a, stream);
+    const uint64_t n = a.tab.elem_off[a.tab.n_chunks] - a.tab.elem_off[0];
+    hipStream_t s = (hipStream_t)stream;
+    if (dt == ZIPCCL_FP32) return n < (2ull << 20) ? launch_decompress_gpw<ZIPCCL_FP32, 1>(a, s) : launch_decompress_gpw<ZIPCCL_FP32, 2>(a, s);
+    if (n < (1ull << 20)) return launch_decompress_gpw<ZIPCCL_BF16, 1>(a, s);
+    uint64_t starts = reinterpret_cast<uintptr_t>(a.out);
+    for (uint32_t c = 0; c < a.tab.n_chunks; ++c) starts |= 2u * a.tab.elem_off[c];
+    if (starts % 128u == 0 && n >= (11ull << 19) && n < (20ull << 20)) return launch_decompress_gpw<ZIPCCL_BF16, 4>(a, s);
+    return launch_decompress_gpw<ZIPCCL_BF16, 2>(a, s);
 }
 
 

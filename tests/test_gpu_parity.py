@@ -361,3 +361,33 @@ def test_compress_and_decompress_replay_inside_a_hip_graph():
             assert np.array_equal(got[a:b], ref[a:b]), (rep, c)
         assert int(d_st.item()) == 0
         assert np.array_equal(d_back.cpu().numpy().view(np.uint16), data), rep
+
+
+@pytest.mark.parametrize("dtype", [z.BF16, z.FP32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("n", [(1 << 20) - 1, 1 << 20, (1 << 21) - 1, 1 << 21, (11 << 19) - 1, 11 << 19, (20 << 20) - 1, 20 << 20])
+def test_decode_on_either_side_of_every_tile_size(dtype, n):
+    """Launches on either side of the sizes at which the decoder's groups per wave change: one chunk; ragged chunks that
+    start at every alignment and end in every kind of rest; outputs that start 0 to 7 elements into an allocation.
+    Exact words back, and nothing written in front of or behind the output."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + dtype)
+    x = torch.empty(n, dtype=torch.float32, device=DEV).normal_(0.0, 0.02, generator=g)
+    x[::37] = 0.0
+    x[5000:9000] = 3.0e5                                               # groups of nothing but zero-points
+    x = x.to(torch.bfloat16).view(torch.int16) if dtype == z.BF16 else x.view(torch.int32)
+    rest = [1, 511, 513, 4095, 8191, 12 * 512 + 3, 2 * 8192 + 1027]
+    split = np.array(rest + [n - sum(rest)], dtype=np.uint64)
+    table = z.zipccl_build_table(0.02, dtype)
+    for ce, off in ((None, 0), (split, 0), (split, 1), (split, 3), (split[::-1].copy(), 6)):
+        C = 1 if ce is None else len(ce)
+        _say(f"[tile sizes] dtype={dtype} n={n} chunks={C} offset={off}")
+        out = torch.empty(z.zipccl_max_compressed_size(n, dtype, C, ce), dtype=torch.uint8, device=DEV)
+        ws = torch.empty(z.zipccl_compress_workspace_size(n, dtype, C, ce), dtype=torch.uint8, device=DEV)
+        z.zipccl_compress(x, n, dtype, C, ce, table, out, None, ws)
+        back = torch.full((n + 32,), 0x5B5B, dtype=x.dtype, device=DEV)
+        st = torch.zeros(1, dtype=torch.int32, device=DEV)
+        z.zipccl_decompress(out, back[off:off + n], n, dtype, C, ce, st)
+        torch.cuda.synchronize()
+        assert int(st.item()) == 0
+        assert torch.equal(back[off:off + n], x)
+        assert bool((back[:off] == 0x5B5B).all()) and bool((back[off + n:] == 0x5B5B).all())
