@@ -36,70 +36,86 @@ namespace {
  */
 static __device__ __align__(256) uint8_t scratch[ZIPCCL_STATIC_SCRATCH_BYTES];
 
+/* How a tile's values are read: every group whole; cut short by the end of a chunk of at least 8 values; a chunk of
+ * fewer than 8. */
+enum LoadForm { kWhole, kRest, kTiny };
+
 /*
- * Load the lane's 8 consecutive values starting at chunk-relative element e.
- * hp[k] packs the high 16-bit words of values 2k (low half) and 2k+1 (high half);
- * lp[k] the low words (fp32 only).  vmask bit j = value j exists (e + j < n).
- * Values that do not exist read as 0.
+ * Load the lane's 8 values of the group at chunk-relative element gbase: bf16: 8 consecutive ones; fp32: two quads,
+ * [4 lane, 4 lane + 4) of the group's first half and of its second, so that each load is 16 contiguous bytes per
+ * lane (32 contiguous bytes per lane cost ~7 % of the bandwidth, measured).
+ * hp[k] packs the high 16-bit words of values 2k (low half) and 2k+1 (high half); lp[k] the low words (fp32 only).
+ * vmask bit j = value j exists; values that do not exist read as 0.  kRest: no load is under a condition, so that all
+ * groups' loads are in flight together: a lane (or quad) that the chunk's end cuts short loads the 16 bytes that end
+ * there and moves them down, one without values loads 16 bytes that exist.  With eight loads under conditions per lane,
+ * each waited for, the tile behind the last whole one was what a call ended with: 8191 bf16 values 9.4 -> 7.7 us, 8 chunks
+ * of 2 097 147 22.8 -> 17.1 us, fp32 37.3 -> 27.6.
  */
-/* FAST, bf16: `skew` says that the chunk starts at an odd element of the tensor, i.e. its bytes are 2 but
- * not 4-byte aligned; the lane's 16 bytes then come as halfword + three dwords + halfword. */
-template <int DT, bool FAST>
+template <int DT, int FORM>
 __device__ __forceinline__ void load_lane(const uint8_t* __restrict__ cin, uint64_t gbase, uint32_t lane, uint64_t n,
-                                          uint32_t hp[4], uint32_t lp[4], uint32_t& vmask, bool skew = false)
+                                          uint32_t hp[4], uint32_t lp[4], uint32_t& vmask)
 {
-    /* gbase (first value of the group) is wave-uniform: uniform 64-bit base + 32-bit lane offset */
-    const uint64_t e = gbase + lane * kLaneElems;
-    if (FAST) {
+    constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u, PER16 = 16u / ES, NQ = DT == ZIPCCL_BF16 ? 1u : 2u;
+    u32x4 v[NQ];
+    /* gbase is wave-uniform: uniform 64-bit base + 32-bit lane offset */
+    if (FORM == kWhole) {
+        const uint8_t* __restrict__ p = cin + gbase * ES;
         vmask = 0xFFu;
-        if (DT == ZIPCCL_BF16) {
-            const uint8_t* __restrict__ p = (cin + gbase * 2) + lane * 16u;
-            if (!skew) {
-                const u32x4 v = ld_stream_a4(p);
-                hp[0] = v.x; hp[1] = v.y; hp[2] = v.z; hp[3] = v.w;
-            } else {
-                const uint32_t h0 = ld_stream<uint16_t>(p);
-                const u32x3 d = __builtin_nontemporal_load(reinterpret_cast<const u32x3_a4*>(p + 2));
-                const uint32_t h7 = ld_stream<uint16_t>(p + 14);
-                hp[0] = h0 | (d.x << 16);
-                hp[1] = __builtin_amdgcn_alignbyte(d.y, d.x, 2u);
-                hp[2] = __builtin_amdgcn_alignbyte(d.z, d.y, 2u);
-                hp[3] = (d.z >> 16) | (h7 << 16);
-            }
-            lp[0] = lp[1] = lp[2] = lp[3] = 0;
-        } else {
-            /* fp32, whole groups: the lane's 8 values are two quads, [4 lane, 4 lane + 4) of the group's first
-               half and of its second half, so that each load is 16 contiguous bytes per lane (32 contiguous
-               bytes per lane cost ~7 % of the bandwidth, measured).  Values 0..3 = first quad, 4..7 = second. */
-            const u32x4 a = ld_stream_a4((cin + gbase * 4) + lane * 16u);
-            const u32x4 b = ld_stream_a4((cin + gbase * 4 + 2 * kGroup) + lane * 16u);
-            const uint32_t x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                hp[k] = perm(x[2 * k + 1], x[2 * k], 0x07060302u);
-                lp[k] = perm(x[2 * k + 1], x[2 * k], 0x05040100u);
-            }
-        }
+        for (uint32_t q = 0; q < NQ; ++q) v[q] = ld_stream_a2(p + q * 1024u + lane * 16u);
     } else {
+        const uint32_t left = gbase >= n ? 0u : (uint32_t)min(n - gbase, (uint64_t)kGroup);      /* values of the group */
+        const int64_t base = left != 0u ? (int64_t)gbase : 0;                    /* a group past the end: the chunk's first */
         vmask = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) { hp[k] = 0; lp[k] = 0; }
+        for (uint32_t q = 0; q < NQ; ++q) {
+            const uint32_t e = lane * PER16 + q * (kGroup / 2);
+            const uint32_t here = e >= left ? 0u : min(left - e, PER16);         /* values of these 16 bytes */
+            vmask |= ((1u << here) - 1u) << (4u * q);
+            uint32_t w[4];
+            if (FORM == kRest) {
+                /* one with none loads from where the group has 16 bytes, or from the 16 bytes the chunk ends with */
+                const int32_t none = left != 0u && left < PER16 ? (int32_t)left - (int32_t)PER16 : 0;
+                const int32_t at = here != 0u ? (int32_t)e - (int32_t)(PER16 - here) : none;
+                const u32x4 t = ld_stream_a2(cin + (base + at) * (int64_t)ES);
+                w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+                const uint32_t down = here != 0u ? PER16 - here : 0u;            /* values that belong to the 16 bytes before */
+                const uint32_t dw = ES * down / 4u;                              /* whole words of them, 0 .. 3 */
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint64_t i = e + j;
-            if (i < n) {
-                uint32_t hi16, lo16 = 0;
-                if (DT == ZIPCCL_BF16) {
-                    hi16 = *reinterpret_cast<const uint16_t*>(cin + i * 2);
-                } else {
-                    const uint32_t x = *reinterpret_cast<const uint32_t*>(cin + i * 4);
-                    hi16 = x >> 16;
-                    lo16 = x & 0xFFFFu;
+                for (uint32_t bit = 0; bit < 2u; ++bit) {
+                    if ((dw >> bit) & 1u) {
+#pragma unroll
+                        for (uint32_t k = 0; k < 4u; ++k) w[k] = k + (1u << bit) < 4u ? w[(k + (1u << bit)) & 3u] : 0u;
+                    }
                 }
-                hp[j >> 1] |= hi16 << (16 * (j & 1));
-                lp[j >> 1] |= lo16 << (16 * (j & 1));
-                vmask |= 1u << j;
+                if (DT == ZIPCCL_BF16 && (down & 1u)) {
+#pragma unroll
+                    for (uint32_t k = 0; k < 4u; ++k) w[k] = (w[k] >> 16) | (k < 3u ? w[(k + 1u) & 3u] << 16 : 0u);
+                }
+                if (here == 0u) w[0] = w[1] = w[2] = w[3] = 0u;
+            } else {
+                w[0] = w[1] = w[2] = w[3] = 0u;
+#pragma unroll
+                for (uint32_t j = 0; j < PER16; ++j) {
+                    if (j < here) {
+                        if (DT == ZIPCCL_BF16) w[j >> 1] |= (uint32_t)reinterpret_cast<const uint16_t*>(cin)[e + j] << (16u * (j & 1u));
+                        else w[j & 3u] = reinterpret_cast<const uint32_t*>(cin)[e + j];
+                    }
+                }
             }
+            v[q] = u32x4{w[0], w[1], w[2], w[3]};
+        }
+    }
+    if (DT == ZIPCCL_BF16) {
+        hp[0] = v[0].x; hp[1] = v[0].y; hp[2] = v[0].z; hp[3] = v[0].w;
+        lp[0] = lp[1] = lp[2] = lp[3] = 0;
+    } else {
+        const u32x4 a = v[0], b = v[NQ - 1];
+        const uint32_t x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            hp[k] = perm(x[2 * k + 1], x[2 * k], 0x07060302u);
+            lp[k] = perm(x[2 * k + 1], x[2 * k], 0x05040100u);
         }
     }
 }
@@ -148,6 +164,10 @@ __device__ __forceinline__ LaneEnc encode8(const uint32_t w[4], uint32_t k7)
     return r;
 }
 
+/* The groups of a wave are four apart in the tile, which shares a short tile evenly among the waves (neighbours instead:
+ * 64 chunks of 65 531 bf16 values 12.0 against 10.6 us, whole tiles 1 % slower). */
+__device__ __forceinline__ uint32_t group_of(uint32_t wave, uint32_t u) { return u * kWavesPerBlock + wave; }
+
 struct CompressShared {
     uint8_t planes[3][kTile / 8];          /* plane bytes of the tile, natural order */
     uint8_t esc[kGroupsPerTile][kGroup];   /* zero-point exponents, one region per group */
@@ -166,16 +186,18 @@ __device__ __forceinline__ void compress_group(uint8_t* __restrict__ slot, const
     const uint64_t e = gbase + lane * kLaneElems;
     const LaneEnc r = encode8(hp, k7);
     const uint32_t m = r.m & vmask;
-    if (DT == ZIPCCL_FP32 && FAST) {
+    if (DT == ZIPCCL_FP32) {
         /* two quads per lane (see load_lane): bits 0..3 of the plane bytes and of m belong to values
            [4 lane, 4 lane + 4) of the group, bits 4..7 to the same values of its second half */
         if (STORE) {
+            /* the sections' padding is written along (as zeros: values that do not exist read as 0) */
+            const uint64_t ea = gbase + lane * 4u, eb = ea + kGroup / 2;
             uint8_t* __restrict__ sm = slot + L.sm + gbase;
-            st_stream<uint32_t>(sm + lane * 4u, r.sm0);
-            st_stream<uint32_t>((sm + kGroup / 2) + lane * 4u, r.sm1);
+            if (FAST || ea < pad128(n)) st_stream<uint32_t>(sm + lane * 4u, r.sm0);
+            if (FAST || eb < pad128(n)) st_stream<uint32_t>((sm + kGroup / 2) + lane * 4u, r.sm1);
             uint8_t* __restrict__ lo = slot + L.lo + 2 * gbase;
-            st_stream<u32x2>(lo + lane * 8u, u32x2{lp[0], lp[1]});
-            st_stream<u32x2>((lo + kGroup) + lane * 8u, u32x2{lp[2], lp[3]});
+            if (FAST || 2 * ea < pad128(2 * n)) st_stream<u32x2>(lo + lane * 8u, u32x2{lp[0], lp[1]});
+            if (FAST || 2 * eb < pad128(2 * n)) st_stream<u32x2>((lo + kGroup) + lane * 8u, u32x2{lp[2], lp[3]});
             /* a plane byte = the nibbles of two neighbouring lanes: even lanes assemble the byte of the
                first half, odd lanes that of the second (three planes at once, one byte each) */
             const uint32_t p3 = r.b0 | (r.b1 << 8) | (r.b2 << 16);
@@ -213,10 +235,6 @@ __device__ __forceinline__ void compress_group(uint8_t* __restrict__ slot, const
     }
     if (STORE) {
         if (FAST || e < pad128(n)) st_stream<u32x2>((slot + L.sm + gbase) + lane * 8u, u32x2{r.sm0, r.sm1});
-        if (DT == ZIPCCL_FP32) {
-            if (FAST || 2 * e < pad128(2 * n))
-                st_stream<u32x4>((slot + L.lo + 2 * gbase) + lane * 16u, u32x4{lp[0], lp[1], lp[2], lp[3]});
-        }
         const uint32_t pi = gi * 64u + lane;
         sh.planes[0][pi] = (uint8_t)r.b0;
         sh.planes[1][pi] = (uint8_t)r.b1;
@@ -297,10 +315,7 @@ __global__ __launch_bounds__(kThreads) void k_compress(const CompressArgs a)
     const uint8_t* __restrict__ cin = a.in + a.tab.elem_off[c] * ES;
     uint8_t* __restrict__ slot = a.out + a.tab.slot_off[c];
     const SlotLayout L = slot_layout(n, DT);
-    /* whole tiles take the vector path; a chunk of the tensor starts at some element of it, so its bytes are
-       dword-aligned or (bf16, odd element) skewed by one halfword */
-    const bool fast = ts + kTile <= n;
-    const bool skew = (reinterpret_cast<uintptr_t>(cin) & 2u) != 0;
+    const bool fast = ts + kTile <= n;                      /* a whole tile */
     const uint32_t lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   /* keep wave-derived math scalar */
     /* the table is a kernel argument, or (estimated on the device) two words in device memory */
@@ -310,24 +325,29 @@ __global__ __launch_bounds__(kThreads) void k_compress(const CompressArgs a)
     const uint32_t e0 = a.d_table ? (dec_lo >> 8) & 0xFFu : a.e0;
     const uint32_t k7 = ((e0 - 1u) << 7) * 0x00010001u;
 
+    /* all four groups' loads go out before the first is encoded: four times the bytes in flight per
+       wave, and no wait for a load ever includes the stores of the group before */
+    uint32_t hp[kGroupsPerWave][4], lp[kGroupsPerWave][4], vm[kGroupsPerWave];
     if (fast) {
-        /* all four groups' loads go out before the first is encoded: four times the bytes in flight per
-           wave, and no wait for a load ever includes the stores of the group before */
-        uint32_t hp[kGroupsPerWave][4], lp[kGroupsPerWave][4], vm[kGroupsPerWave];
 #pragma unroll
         for (uint32_t u = 0; u < kGroupsPerWave; ++u)
-            load_lane<DT, true>(cin, ts + (uint64_t)(u * kWavesPerBlock + wave) * kGroup, lane, n, hp[u], lp[u], vm[u], skew);
+            load_lane<DT, kWhole>(cin, ts + (uint64_t)group_of(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u]);
 #pragma unroll
         for (uint32_t u = 0; u < kGroupsPerWave; ++u)
-            compress_group<DT, true, STORE>(slot, L, n, ts, u * kWavesPerBlock + wave, k7, lane, sh, hp[u], lp[u], vm[u]);
+            compress_group<DT, true, STORE>(slot, L, n, ts, group_of(wave, u), k7, lane, sh, hp[u], lp[u], vm[u]);
     } else {
+        if (n >= 8u) {
 #pragma unroll
-        for (uint32_t u = 0; u < kGroupsPerWave; ++u) {
-            const uint32_t gi = u * kWavesPerBlock + wave;
-            uint32_t hp[4], lp[4], vm;
-            load_lane<DT, false>(cin, ts + (uint64_t)gi * kGroup, lane, n, hp, lp, vm);
-            compress_group<DT, false, STORE>(slot, L, n, ts, gi, k7, lane, sh, hp, lp, vm);
+            for (uint32_t u = 0; u < kGroupsPerWave; ++u)
+                load_lane<DT, kRest>(cin, ts + (uint64_t)group_of(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u]);
+        } else {
+#pragma unroll
+            for (uint32_t u = 0; u < kGroupsPerWave; ++u)
+                load_lane<DT, kTiny>(cin, ts + (uint64_t)group_of(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u]);
         }
+#pragma unroll
+        for (uint32_t u = 0; u < kGroupsPerWave; ++u)
+            compress_group<DT, false, STORE>(slot, L, n, ts, group_of(wave, u), k7, lane, sh, hp[u], lp[u], vm[u]);
     }
     __syncthreads();
 
@@ -363,7 +383,7 @@ __global__ __launch_bounds__(kThreads) void k_compress(const CompressArgs a)
     /* zero-point exponents: every wave copies the segments of its own groups, in element order */
 #pragma unroll
     for (uint32_t u = 0; u < kGroupsPerWave; ++u) {
-        const uint32_t gi = u * kWavesPerBlock + wave;
+        const uint32_t gi = group_of(wave, u);
         const uint32_t cnt = __builtin_amdgcn_readlane(gc, gi);
         uint8_t* dst = esc + __builtin_amdgcn_readlane(gex, gi);
 #pragma unroll 1

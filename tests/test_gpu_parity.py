@@ -391,3 +391,18 @@ def test_decode_on_either_side_of_every_tile_size(dtype, n):
         assert int(st.item()) == 0
         assert torch.equal(back[off:off + n], x)
         assert bool((back[:off] == 0x5B5B).all()) and bool((back[off + n:] == 0x5B5B).all())
+
+
+@pytest.mark.parametrize("dtype", [z.BF16, z.FP32], ids=["bf16", "fp32"])
+def test_chunks_of_every_rest(dtype, compress_path):
+    """Chunks of 1 to 33 values, of one to three groups and of one tile, each plus or minus up to 9 values, one behind
+    the other, so that every length of a last 16 bytes meets every alignment; the lowest window too, whose first code is
+    exponent 1 beside the zeros that pad a rest."""
+    rng = np.random.default_rng(70 + dtype)
+    sizes = list(range(1, 34)) + [m + d for m in (512, 1024, 1536, 8192) for d in range(-9, 10)] + [0, 8192 + 4096 + 5]
+    ce = np.array(sizes, dtype=np.uint64)
+    for sigma in (0.02, 1e-38):
+        f = rng.standard_normal(int(ce.sum()), dtype=np.float32) * np.float32(sigma)
+        data = W.f32_to_bf16_words(f) if dtype == z.BF16 else f.view(np.uint32).copy()
+        _say(f"[rests] dtype={dtype} sigma={sigma} path={compress_path}")
+        check_parity(data, dtype, sigma, len(sizes), ce, label=f"rests sigma={sigma}", reread=compress_path)
