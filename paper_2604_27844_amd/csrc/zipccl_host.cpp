@@ -179,6 +179,19 @@ size_t zipccl_compress_min_workspace_size(size_t n_elems, zipccl_dtype_t dt, uin
 
 namespace {
 
+/*
+ * Whether a launch of `tiles` tiles in chunks of at most max_tiles compresses in one kernel, whose workgroups read their
+ * chunk's tiles before their own once more, or in two, from timings on MI355X (us in a graph, one kernel / two).  bf16:
+ * 1 chunk of 1 tile 4.0 / 6.6, of 4 5.2 / 7.5, of 8 6.2 / 7.7, of 16 8.2 / 7.8; 8 chunks of 2 4.8 / 8.4, of 8 6.6 / 8.3; 64
+ * of 2 5.4 / 8.6, of 4 6.7 / 8.8, of 8 12.5 / 9.5; 128 of 4 9.2 / 9.4.  fp32: 1 chunk of 4 7.5 / 8.5, of 8 9.1 / 8.1; 8
+ * chunks of 4 6.8 / 8.7; 64 of 2 6.3 / 9.2, of 4 9.5 / 9.6; 128 of 4 28 / 23 with 72 more behind them.
+ */
+bool direct_pays(zipccl_dtype_t dt, uint32_t max_tiles, uint32_t tiles)
+{
+    if (dt == ZIPCCL_FP32) return max_tiles <= 4 && tiles <= 128;
+    return max_tiles <= 4 ? tiles <= 512 : max_tiles <= 8 && tiles <= 64;
+}
+
 /* compress with the table either on the host (checked here) or in device memory (d_table) */
 zipccl_status_t compress_impl(const void* d_in, size_t n_elems, zipccl_dtype_t dt,
                               uint32_t n_chunks, const uint64_t* chunk_elems,
@@ -232,9 +245,11 @@ zipccl_status_t compress_impl(const void* d_in, size_t n_elems, zipccl_dtype_t d
         a.tile_total = reinterpret_cast<uint32_t*>(ws + wp.total_off) + tile_base;
         a.tile_prefix = reinterpret_cast<uint32_t*>(ws + wp.prefix_off) + tile_base;
         a.stash = stash ? ws + wp.stash_off + elem_base : nullptr;
-        if (stash) {
-            uint32_t max_tiles = 0;
-            for (uint32_t c = 0; c < nb; ++c) max_tiles = std::max(max_tiles, a.tab.tile_start[c + 1] - a.tab.tile_start[c]);
+        uint32_t max_tiles = 0;
+        for (uint32_t c = 0; c < nb; ++c) max_tiles = std::max(max_tiles, a.tab.tile_start[c + 1] - a.tab.tile_start[c]);
+        if (direct_pays(dt, max_tiles, nt)) {
+            if (launch_compress(dt, kModeDirect, a, stream) != 0) return ZIPCCL_ERR_DEVICE;
+        } else if (stash) {
             const bool fused_scan = max_tiles <= kPlaceScanTiles;
             if (launch_compress(dt, kModeStash, a, stream) != 0) return ZIPCCL_ERR_DEVICE;
             if (!fused_scan && launch_tile_scan(a, stream) != 0) return ZIPCCL_ERR_DEVICE;

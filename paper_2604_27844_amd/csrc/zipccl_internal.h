@@ -113,7 +113,8 @@ struct DecompressArgs {
 
 /* kModeStash: single pass over the input; zero-point exponents go to a stash at a position that
  * does not depend on other tiles, and k_place moves them once the tile prefixes are known.
- * kModeCount + kModeEmit: the same without a stash, reading the input twice. */
+ * kModeCount + kModeEmit: the same without a stash, reading the input twice.
+ * kModeDirect: one launch for small chunks; every workgroup counts the zero-points of its chunk's tiles before its own. */
 struct ReduceArgs {
     const uint8_t* comp;     /* n_peers slots of n values each, back to back */
     uint64_t comp_capacity;  /* readable bytes from comp */
@@ -128,7 +129,7 @@ struct ReduceArgs {
     uint32_t gpw_rest;       /* groups per wave in the workgroups after them, which take the rest of the shard */
 };
 
-enum CompressMode { kModeCount = 0, kModeEmit = 1, kModeStash = 2 };
+enum CompressMode { kModeCount = 0, kModeEmit = 1, kModeStash = 2, kModeDirect = 3 };
 
 /* launchers implemented next to their kernels (zipccl_compress.hip, zipccl_decompress.hip, zipccl_aux.hip);
  * they return a hipError_t as int */

@@ -406,3 +406,23 @@ def test_chunks_of_every_rest(dtype, compress_path):
         data = W.f32_to_bf16_words(f) if dtype == z.BF16 else f.view(np.uint32).copy()
         _say(f"[rests] dtype={dtype} sigma={sigma} path={compress_path}")
         check_parity(data, dtype, sigma, len(sizes), ce, label=f"rests sigma={sigma}", reread=compress_path)
+
+
+@pytest.mark.parametrize("dtype", [z.BF16, z.FP32], ids=["bf16", "fp32"])
+def test_small_chunks_on_either_side_of_the_one_launch_form(dtype, compress_path):
+    """Calls on either side of the sizes up to which a compress is one launch (chunks of 4 and 8 tiles; 64, 128 and 512
+    tiles in all), with zero-points that are dense in early tiles, absent, or in the last tile only, ragged last
+    tiles and empty chunks, more chunks than one launch holds: bytes equal to the oracle's."""
+    rng = np.random.default_rng(80 + dtype)
+    T = 8192
+    for ce in ([T], [4 * T], [4 * T + 1], [8 * T], [8 * T + 1], [8 * T - 5] * 8, [8 * T] * 8 + [3], [3 * T + 9, 0, 4 * T, 1, T - 1],
+               [4 * T] * 32, [4 * T] * 32 + [7], [4 * T] * 127 + [4 * T - 3], [4 * T - 1] * 128 + [T]):
+        ce = np.array(ce, dtype=np.uint64)
+        n = int(ce.sum())
+        f = rng.standard_normal(n, dtype=np.float32) * np.float32(0.02)
+        f[:T // 2] = 1e9                                               # all zero-points, then none, then a few
+        f[T:2 * T] = 0.02
+        f[-3:] = 0.0
+        data = W.f32_to_bf16_words(f) if dtype == z.BF16 else f.view(np.uint32).copy()
+        _say(f"[one launch] dtype={dtype} chunks={len(ce)} n={n} path={compress_path}")
+        check_parity(data, dtype, 0.02, len(ce), ce, label=f"chunks={len(ce)} n={n}", reread=compress_path)
