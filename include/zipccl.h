@@ -111,6 +111,8 @@ zipccl_status_t zipccl_chunk_static_bytes(size_t n_elems, zipccl_dtype_t dt, uin
  * in the scratch until the per-chunk prefix of section 4.2.3 is known.  With less, but at least
  * zipccl_compress_min_workspace_size bytes (8 bytes per 8192 elements), it reads the input twice
  * (count, prefix, emit): workspace_bytes alone selects the form, call by call, and both write the same bytes.
+ * Calls on chunks of a few tiles of 8192 values take neither: one kernel, which needs no scratch (the minimum is still
+ * asked for).
  * Both return 0 on invalid arguments. */
 size_t zipccl_compress_workspace_size(size_t n_elems, zipccl_dtype_t dt, uint32_t n_chunks,
                                       const uint64_t* chunk_elems);
