@@ -142,26 +142,28 @@ __device__ __forceinline__ void decode_load(const uint8_t* __restrict__ slot, co
     /* wave-uniform 64-bit bases + 32-bit lane offsets */
     const uint8_t* __restrict__ sm = slot + L.sm + gs;
     const uint8_t* __restrict__ pl = slot + L.p0 + (gs >> 3);     /* 64-byte aligned: a group's 64 plane bytes */
-    uint32_t pi = lane;
+    /* fp32: the lane fetches one plane byte per plane, the one it shares with its neighbour: even lanes that of the
+       first half, odd lanes that of the second (quad_plane_bytes sorts the nibbles out) */
+    const uint32_t pi = DT == ZIPCCL_BF16 ? lane : (lane >> 1) + 32u * (lane & 1u);
+    const uint32_t ia = FAST || (r.vmask & 15u) ? lane * 4u : 0u, ib = FAST || (r.vmask >> 4) ? kGroup / 2 + lane * 4u : 0u;
     if (DT == ZIPCCL_BF16) {
         const u32x2 v = ld_stream<u32x2>(sm + (FAST || r.vmask ? lane * 8u : 0u));
         r.sm0 = v.x; r.sm1 = v.y;
-        r.lo[0] = r.lo[1] = r.lo[2] = r.lo[3] = 0;
     } else {
-        /* The lane fetches one plane byte per plane, the one it shares with its neighbour: even lanes that
-           of the first half, odd lanes that of the second (quad_plane_bytes sorts the nibbles out). */
-        const uint32_t ia = FAST || (r.vmask & 15u) ? lane * 4u : 0u, ib = FAST || (r.vmask >> 4) ? kGroup / 2 + lane * 4u : 0u;
         r.sm0 = ld_stream<uint32_t>(sm + ia);
         r.sm1 = ld_stream<uint32_t>(sm + ib);
-        pi = (lane >> 1) + 32u * (lane & 1u);
+    }
+    /* the planes before the low words: they are wanted first, and loads are waited for in order */
+    r.b0 = ld_stream<uint8_t>(pl + pi);
+    r.b1 = ld_stream<uint8_t>((pl + L.plane_bytes) + pi);
+    r.b2 = ld_stream<uint8_t>((pl + 2 * L.plane_bytes) + pi);
+    r.lo[0] = r.lo[1] = r.lo[2] = r.lo[3] = 0;
+    if (DT == ZIPCCL_FP32) {
         const uint8_t* __restrict__ lo = slot + L.lo + 2 * gs;
         const u32x2 la = ld_stream<u32x2>(lo + 2u * ia);
         const u32x2 lb = ld_stream<u32x2>(lo + 2u * ib);
         r.lo[0] = la.x; r.lo[1] = la.y; r.lo[2] = lb.x; r.lo[3] = lb.y;
     }
-    r.b0 = ld_stream<uint8_t>(pl + pi);
-    r.b1 = ld_stream<uint8_t>((pl + L.plane_bytes) + pi);
-    r.b2 = ld_stream<uint8_t>((pl + 2 * L.plane_bytes) + pi);
 }
 
 /* After decode_load of fp32: from the plane bytes shared by a pair of lanes to each lane's own
@@ -349,7 +351,7 @@ __device__ __forceinline__ bool check_header(const HeaderWords& hdr, const SlotL
 /* GPW (1, 2 or 4) groups per wave: a workgroup decodes a tile of 4 * GPW groups.  The compressed format does not know
  * tiles (groups are located through IDX alone), so this is free to differ from the compress side's tile. */
 template <int DT, uint32_t GPW>
-__global__ __launch_bounds__(kThreads, DT == ZIPCCL_BF16 ? 8 : 6)   /* waves per SIMD: <= 64 VGPRs for bf16, <= 80 for fp32 */
+__global__ __launch_bounds__(kThreads, 8)   /* waves per SIMD: <= 64 VGPRs */
 void k_decompress(const DecompressArgs a)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
