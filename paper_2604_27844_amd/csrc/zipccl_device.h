@@ -19,15 +19,12 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
  * at any element (the hardware takes multi-dword accesses at any alignment; the type tells the compiler) */
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
-typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
-typedef u32x3 u32x3_a4 __attribute__((aligned(4)));
 
 /* streaming accesses: every tensor byte is touched once, so keep it out of the way of the caches */
 template <typename T>
 __device__ __forceinline__ T ld_stream(const void* p) { return __builtin_nontemporal_load(static_cast<const T*>(p)); }
 template <typename T>
 __device__ __forceinline__ void st_stream(void* p, T v) { __builtin_nontemporal_store(v, static_cast<T*>(p)); }
-__device__ __forceinline__ u32x4 ld_stream_a4(const void* p) { return __builtin_nontemporal_load(static_cast<const u32x4_a4*>(p)); }
 __device__ __forceinline__ void st_stream_a4(void* p, u32x4 v) { __builtin_nontemporal_store(v, static_cast<u32x4_a4*>(p)); }
 __device__ __forceinline__ u32x4 ld_stream_a2(const void* p) { return __builtin_nontemporal_load(static_cast<const u32x4_a2*>(p)); }
 __device__ __forceinline__ void st_stream_a2(void* p, u32x4 v) { __builtin_nontemporal_store(v, static_cast<u32x4_a2*>(p)); }
