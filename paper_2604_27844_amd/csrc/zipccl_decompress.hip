@@ -755,7 +755,8 @@ struct PairBuf {
     uint32_t pre_base, pre_mid, pre_next;    /* the index entries of the two groups and the following one, */
     uint32_t pre_nesc, pre_dec;       /* the slot's zero-point count and header word holding dec[0..3] */
     const uint8_t* list;              /* 16 bytes in front of the aligned start of the pair's slice of the list */
-    uint32_t e0, mis, count_a, count_b, idx_bad;
+    PairSlices sl;
+    uint32_t e0;
 };
 
 /* Bytes of LDS per wave: the slice of two groups at any alignment (1024 + 15) and the words a lane may read past
@@ -804,15 +805,9 @@ __device__ __forceinline__ void reduce_pair(const ReduceArgs& a, const SlotLayou
     auto issue = [&](PairBuf& r) {
         r.e0 = (r.pre_dec >> 8) & 0xFFu;
         const uint32_t next = last_pair ? r.pre_nesc : r.pre_next;
-        /* the two groups' entries must ascend, by at most 512 each, to an end inside the list */
-        r.count_a = r.pre_mid - r.pre_base;
-        r.count_b = next - r.pre_mid;
-        r.idx_bad = (uint32_t)(r.count_a > kGroup) | (uint32_t)(r.count_b > kGroup) | (uint32_t)(next > r.pre_nesc);
-        const uint32_t from = r.idx_bad ? 0u : r.pre_base & ~15u;
-        const uint32_t span = r.idx_bad || r.count_a + r.count_b == 0u ? 0u : next - from;   /* bytes of the list from there on */
-        r.mis = r.idx_bad ? 0u : r.pre_base & 15u;
-        r.list = r.pre_slot + (L.esc - 16u) + from;
-        r.lv = *reinterpret_cast<const u32x4*>(r.list + (lane16 < span ? lane16 + 16u : 0u));
+        r.sl = pair_slices(r.pre_base, r.pre_mid, next, r.pre_nesc);
+        r.list = r.pre_slot + (L.esc - 16u) + r.sl.from;
+        r.lv = *reinterpret_cast<const u32x4*>(r.list + pair_list_offset(r.sl, lane));
         r.sm = ld_stream<u32x4>((r.pre_slot + o_sm) + lane16);
         const uint8_t* const pl = r.pre_slot + o_pl;
         r.p0 = ld_stream<uint16_t>(pl + 2u * lane);
@@ -823,9 +818,8 @@ __device__ __forceinline__ void reduce_pair(const ReduceArgs& a, const SlotLayou
         /* nothing that uses the stage's loaded words may be scheduled before this point */
         __builtin_amdgcn_sched_barrier(0);
         *reinterpret_cast<u32x4*>(lds + lane16) = r.lv;
-        if (__builtin_expect(!r.idx_bad && r.mis + r.count_a + r.count_b > 64u * 16u, 0)) {
-            /* a slice that no 64 aligned pieces cover: all but a few of the 1024 values are zero-points */
-            if (lane == 0) *reinterpret_cast<u32x4*>(lds + 64u * 16u) = *reinterpret_cast<const u32x4*>(r.list + 16u + 64u * 16u);
+        if (__builtin_expect(pair_has_last_piece(r.sl), 0)) {
+            if (lane == 0) *reinterpret_cast<u32x4*>(lds + kPairLastPiece) = *reinterpret_cast<const u32x4*>(r.list + 16u + kPairLastPiece);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -834,10 +828,10 @@ __device__ __forceinline__ void reduce_pair(const ReduceArgs& a, const SlotLayou
         const uint32_t cnt = __popc(m);
         const uint32_t inc = wave_incl_scan(cnt);
         const uint32_t tot_a = __builtin_amdgcn_readlane(inc, 31), tot = __builtin_amdgcn_readlane(inc, 63);
-        bad |= r.idx_bad | (tot_a ^ r.count_a) | ((tot - tot_a) ^ r.count_b);      /* planes and IDX must agree */
+        bad |= r.sl.bad | (tot_a ^ r.sl.count_a) | ((tot - tot_a) ^ r.sl.count_b);      /* planes and IDX must agree */
         /* the lane's zero-point exponents, those of its first eight values in front (clamped, so that a corrupt stream
            still reads inside the region) */
-        const uint32_t first = min(r.mis + (inc - cnt), 2u * kGroup + 15u);
+        const uint32_t first = min(r.sl.mis + (inc - cnt), 2u * kGroup + 15u);
         const uint32_t at[2] = {first, first + (uint32_t)__popc(m & 0xFFu)};
         float x[16];
 #pragma unroll

@@ -54,6 +54,39 @@ ZIPCCL_HD SlotLayout slot_layout(uint64_t n, int dt)
     return L;
 }
 
+/*
+ * The slices of the zero-point list that three consecutive index entries give two neighbouring groups, and how a wave
+ * fetches both: lane l reads the 16 bytes at pair_list_offset(s, l) behind the 16 bytes in front of the list.  Entries
+ * that are not base <= mid <= next <= n_esc, 512 apart at most, are bad: nothing of the list is fetched then.  The
+ * positions themselves are compared, and not only their differences, which wrap: a base just below 2^32 is as
+ * little ahead of a small next as a good one.
+ */
+struct PairSlices {
+    uint32_t count_a, count_b;   /* zero-points of the two groups (meaningless if bad) */
+    uint32_t from;               /* base rounded down to 16, */
+    uint32_t mis;                /* base - from, */
+    uint32_t span;               /* and bytes from there to next, 0 for empty slices */
+    uint32_t bad;
+};
+
+ZIPCCL_HD PairSlices pair_slices(uint32_t base, uint32_t mid, uint32_t next, uint32_t n_esc)
+{
+    PairSlices s;
+    s.count_a = mid - base;
+    s.count_b = next - mid;
+    s.bad = (uint32_t)(s.count_a > kGroup) | (uint32_t)(s.count_b > kGroup) | (uint32_t)(next > n_esc) | (uint32_t)(base > next);
+    s.from = s.bad ? 0u : base & ~15u;
+    s.mis = s.bad ? 0u : base & 15u;
+    s.span = s.bad || s.count_a + s.count_b == 0u ? 0u : next - s.from;
+    return s;
+}
+
+ZIPCCL_HD uint32_t pair_list_offset(const PairSlices& s, uint32_t lane) { return 16u * lane < s.span ? 16u * lane + 16u : 0u; }
+
+/* a slice of more than 64 aligned pieces (all but a few of the 1024 values are zero-points): one more, behind those */
+constexpr uint32_t kPairLastPiece = 64u * 16u;
+ZIPCCL_HD bool pair_has_last_piece(const PairSlices& s) { return !s.bad && s.mis + s.count_a + s.count_b > kPairLastPiece; }
+
 ZIPCCL_HD uint64_t tiles_of(uint64_t n) { return n == 0 ? 1 : (n + kTile - 1) / kTile; }
 
 /* Per-launch chunk table, passed by value in the kernel argument segment. */

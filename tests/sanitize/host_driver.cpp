@@ -60,11 +60,47 @@ int static_scratch(void** ptr, size_t* bytes)
     return 0;
 }
 
+/* What a wave of the fused reduce fetches of a slot's zero-point list for three consecutive index entries, whatever a
+ * damaged stream holds in their place: every 16-byte read of the 64 lanes (and the last piece) lies between the 16
+ * bytes in front of the list and its padded end, and entries that are not ascending positions of the list, at most a
+ * group apart, are bad. */
+static void check_pair_slices()
+{
+    const uint32_t ends[] = {0u, 1u, 13u, 30u, 512u, 1024u, 1040u, 100000u, 0x7FFFFFFFu, 0xFFFFFFFFu};
+    const int64_t near[] = {0, 1, 14, 15, 16, 17, 511, 512, 513, 1007, 1008, 1009, 1023, 1024, 1025, 1040};
+    for (uint32_t n_esc : ends) {
+        std::vector<uint32_t> at;                     /* entries around 0, around n_esc and just below 2^32 */
+        for (int64_t d : near)
+            for (int64_t v : {d, (int64_t)n_esc - d, (int64_t)n_esc + d, ((int64_t)1 << 32) - 1 - d})
+                if (v >= 0 && v <= 0xFFFFFFFFll) at.push_back((uint32_t)v);
+        const int64_t list_end = (int64_t)pad128(n_esc);
+        for (uint32_t base : at) {
+            for (uint32_t mid : at) {
+                for (uint32_t next : at) {
+                    const PairSlices s = pair_slices(base, mid, next, n_esc);
+                    const bool good = base <= mid && mid <= next && next <= n_esc && mid - base <= kGroup && next - mid <= kGroup;
+                    CHECK((s.bad == 0u) == good);
+                    for (uint32_t lane = 0; lane < 64; ++lane) {
+                        const int64_t off = -16 + (int64_t)s.from + (int64_t)pair_list_offset(s, lane);
+                        CHECK(off >= -16 && off % 16 == 0 && off + 16 <= (list_end > 0 ? list_end : 0));
+                    }
+                    if (pair_has_last_piece(s)) CHECK((int64_t)s.from + kPairLastPiece + 16 <= list_end);
+                    if (!good) continue;              /* the lanes' pieces cover the slice */
+                    const uint32_t fetched = pair_has_last_piece(s) ? kPairLastPiece + 16u : kPairLastPiece;
+                    CHECK(s.mis + s.count_a + s.count_b <= fetched && s.from + s.mis == base && s.count_a + s.count_b == next - base);
+                    if (next != base) CHECK(s.span == next - s.from);
+                }
+            }
+        }
+    }
+}
+
 } // namespace zipccl
 
 int main()
 {
     using namespace zipccl;
+    check_pair_slices();
     /* table builder over a wide sigma range, clamps and rejections */
     zipccl_table_t t;
     for (int k = -1100; k <= 1100; ++k) {

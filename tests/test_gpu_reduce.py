@@ -402,3 +402,34 @@ def test_reduce_pairs_flag_damage_and_leave_rejected_slots_out():
     rest = _receive_buffer([peers[0], peers[2]], z.BF16, [0.02])
     want = oracle.decompress_reduce(rest.cpu().numpy(), n, z.BF16, 2, z.FP32)
     assert np.array_equal(d_out.cpu().numpy().view(np.uint32), want)
+
+
+def test_reduce_pairs_flag_whole_index_words_and_stay_inside_the_list():
+    """Whole index entries overwritten in a shard that is taken in pairs, the first, an inner and the last one, with
+    positions just below 2^32 (whose distance to a small following entry wraps to a small number), far outside the
+    list, and behind the entry that follows: each is flagged, and the intact buffer still sums to the oracle's bits.
+    (What is read of the list for such entries is checked on the host, over all of them, in the sanitizer driver.)"""
+    rng = np.random.default_rng(61)
+    P, n = 2, 384 * 8192 + 512
+    peers = _peers(rng, P, n, z.BF16, [0.02])
+    buf = _receive_buffer(peers, z.BF16, [0.02])
+    cap1 = z.zipccl_max_compressed_size(n, z.BF16, 1)
+    pad = lambda x: (x + 127) // 128 * 128
+    idx = cap1 + 128 + pad(n) + 3 * pad((n + 7) // 8)              # of the second slot
+    d_out = torch.zeros(n, dtype=torch.int32, device=DEV)
+
+    def run(b):
+        d_st = torch.zeros(1, dtype=torch.int32, device=DEV)
+        z.zipccl_decompress_reduce(b, d_out, n, z.BF16, P, z.FP32, d_st)
+        torch.cuda.synchronize()
+        return int(d_st.item())
+
+    for g in (0, 1000, 1001, n // 512 - 2, n // 512 - 1):
+        for word in (0xFFFFFFFF, 0xFFFFFFF0, 0xFFFFFC00, 0x80000000, n):
+            print(f"[reduce pairs] entry {g} = {word:#x}", flush=True)
+            bad = buf.clone()
+            bad[idx + 4 * g:idx + 4 * g + 4] = torch.tensor(list(word.to_bytes(4, "little")), dtype=torch.uint8, device=DEV)
+            assert run(bad) == 4, (g, hex(word))
+    assert run(buf) == 0
+    assert np.array_equal(d_out.cpu().numpy().view(np.uint32),
+                          oracle.decompress_reduce(buf.cpu().numpy(), n, z.BF16, P, z.FP32))
