@@ -702,6 +702,10 @@ __device__ __forceinline__ void reduce_stages(const ReduceArgs& a, const SlotLay
                     st_stream_a4(og + lane * 16u, u32x4{o[0], o[1], o[2], o[3]});
                 }
             } else {
+                /* the sums are finished here: sunk into the branches below, what is left of them waits for the stage's
+                   low words there, and such a wait includes the store of the branch before (eight stores one after
+                   the other: 200 003 fp32 values of two peers 4.7 -> 4.1 us) */
+                asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]), "+v"(acc[7]));
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     if ((r.in.vmask >> j) & 1u) {
