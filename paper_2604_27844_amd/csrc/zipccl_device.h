@@ -19,6 +19,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
  * at any element (the hardware takes multi-dword accesses at any alignment; the type tells the compiler) */
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
+typedef uint32_t u32_a2 __attribute__((aligned(2)));
 
 /* streaming accesses: every tensor byte is touched once, so keep it out of the way of the caches */
 template <typename T>
