@@ -365,7 +365,8 @@ __device__ __forceinline__ bool check_header(const HeaderWords& hdr, const SlotL
 /* GPW (1, 2 or 4) groups per wave: a workgroup decodes a tile of 4 * GPW groups.  The compressed format does not know
  * tiles (groups are located through IDX alone), so this is free to differ from the compress side's tile. */
 template <int DT, uint32_t GPW>
-__global__ __launch_bounds__(kThreads, 8)   /* waves per SIMD: <= 64 VGPRs */
+/* waves per SIMD: 8 (<= 64 VGPRs); launches with four fp32 groups per wave hold no more than 4 */
+__global__ __launch_bounds__(kThreads, DT == ZIPCCL_FP32 && GPW == 4u ? 4 : 8)
 void k_decompress(const DecompressArgs a)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
@@ -1071,24 +1072,36 @@ static int launch_decompress_gpw(const DecompressArgs& a, hipStream_t s)
 
 /*
  * Groups per wave by the values of the launch, from timings on MI355X (us in a graph, 1 / 2 / 4 groups).  bf16: 2^18
- * values 2.9 / 3.2 / 3.9, 2^20 3.4 / 3.4 / 4.1, 2^21 4.2 / 3.9 / 4.2, 5 * 2^20 7.0 / 5.4 / 5.6, 6 * 2^20 7.7 / 6.4 / 5.7,
- * 2^23 9.4 / 7.4 / 6.4, 2^24 15.2 / 11.9 / 11.8, 24 * 2^20 21.0 / 16.3 / 17.1; 2^28 72.6 with two, 74.4 with four.  fp32:
- * 2^18 3.3 / 3.7 / 4.6, 2^20 4.2 / 4.4 / 5.4, 2^21 5.0 / 5.0 / 5.9, 2^22 7.3 / 6.5 / 7.1, 2^24 23.0 / 23.1 / 24.2; four
- * win only about 6 * 2^20 (10.7 / 10.1 / 8.6) and are not built.  In small launches fewer groups per wave mean more
- * waves that share one chain of latencies; in launches of about one round of resident workgroups four mean one round
- * instead of a second, almost empty one (only where the chunks start on line boundaries: 64 chunks of 131 073 bf16
- * values 7.9 us with two neighbouring groups, 8.3 with four).
+ * values 2.9 / 3.2 / 3.9, 2^20 3.4 / 3.4 / 4.1, 2^21 4.2 / 3.7 / 4.2, 2^22 - / 4.5 / 4.6, 4.5 * 2^20 - / 5.6 / 5.3, 5.25 *
+ * 2^20 - / 6.0 / 5.3, 2^23 9.4 / 7.4 / 6.0, 2^24 15.2 / 11.9 / 11.8, 24 * 2^20 21.0 / 16.3 / 17.1; 2^28 72.6 with two, 74.4
+ * with four.  fp32: 2^18 3.3 / 3.7 / 4.6, 2^20 4.2 / 4.4 / 5.4, 2^21 5.0 / 5.0 / 5.9, 2^22 7.3 / 6.5 / 7.6, 5 * 2^20 - / 8.0
+ * / 8.9, 5.25 * 2^20 - / 9.9 / 8.7, 6 * 2^20 - / 9.9 / 8.7, 6.25 * 2^20 - / 11.1 / 12.5, 7.25 * 2^20 - / 12.9 / 12.9, 2^23 - /
+ * 13.5 / 12.6, 8.1 * 2^20 - / 13.9 / 15.1.  In small launches fewer groups per wave mean more waves that share one chain
+ * of latencies.  Launches of a few workgroups per compute unit take the time of the fullest unit: in steps of 2^21
+ * values (256 workgroups of 8192) with four, of 2^20 with two, so that four win towards the upper end of their steps; for
+ * fp32 these are the ones that end at 6 and at 8 * 2^20.  Four only where the chunks start on line boundaries (64 chunks of
+ * 131 073 bf16 values 7.9 us with two neighbouring groups, 8.3 with four), and below 5 * 2^20 bf16 values not for many
+ * chunks with rests (128 chunks of 37 824 values 6 % slower with four).
  */
 int launch_decompress(int dt, const DecompressArgs& a, void* stream)
 {
     const uint64_t n = a.tab.elem_off[a.tab.n_chunks] - a.tab.elem_off[0];
     hipStream_t s = (hipStream_t)stream;
-    if (dt == ZIPCCL_FP32) return n < (2ull << 20) ? launch_decompress_gpw<ZIPCCL_FP32, 1>(a, s) : launch_decompress_gpw<ZIPCCL_FP32, 2>(a, s);
+    uint64_t starts = reinterpret_cast<uintptr_t>(a.out), ends = 0;
+    for (uint32_t c = 0; c < a.tab.n_chunks; ++c) {
+        starts |= elem_size(dt) * a.tab.elem_off[c];
+        ends |= a.tab.elem_off[c + 1];
+    }
+    const bool lines = starts % 128u == 0;
+    if (dt == ZIPCCL_FP32) {
+        if (n < (2ull << 20)) return launch_decompress_gpw<ZIPCCL_FP32, 1>(a, s);
+        const bool four = (n > (5ull << 20) && n <= (6ull << 20)) || (n > (29ull << 18) && n <= (8ull << 20));
+        return lines && four ? launch_decompress_gpw<ZIPCCL_FP32, 4>(a, s) : launch_decompress_gpw<ZIPCCL_FP32, 2>(a, s);
+    }
     if (n < (1ull << 20)) return launch_decompress_gpw<ZIPCCL_BF16, 1>(a, s);
-    uint64_t starts = reinterpret_cast<uintptr_t>(a.out);
-    for (uint32_t c = 0; c < a.tab.n_chunks; ++c) starts |= 2u * a.tab.elem_off[c];
-    if (starts % 128u == 0 && n >= (11ull << 19) && n < (20ull << 20)) return launch_decompress_gpw<ZIPCCL_BF16, 4>(a, s);
-    return launch_decompress_gpw<ZIPCCL_BF16, 2>(a, s);
+    const bool few_rests = a.tab.n_chunks <= 64u || ends % kTile == 0;
+    const bool four = n < (20ull << 20) && (n > (5ull << 20) || (n > (4ull << 20) && few_rests));
+    return lines && four ? launch_decompress_gpw<ZIPCCL_BF16, 4>(a, s) : launch_decompress_gpw<ZIPCCL_BF16, 2>(a, s);
 }
 
 

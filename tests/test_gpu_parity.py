@@ -364,7 +364,9 @@ def test_compress_and_decompress_replay_inside_a_hip_graph():
 
 
 @pytest.mark.parametrize("dtype", [z.BF16, z.FP32], ids=["bf16", "fp32"])
-@pytest.mark.parametrize("n", [(1 << 20) - 1, 1 << 20, (1 << 21) - 1, 1 << 21, (11 << 19) - 1, 11 << 19, (20 << 20) - 1, 20 << 20])
+@pytest.mark.parametrize("n", [(1 << 20) - 1, 1 << 20, (1 << 21) - 1, 1 << 21, 1 << 22, (1 << 22) + 1, 5 << 20, (5 << 20) + 1,
+                               (11 << 19) - 1, 11 << 19, 6 << 20, (6 << 20) + 1, 29 << 18, (29 << 18) + 1, 1 << 23, (1 << 23) + 1,
+                               (20 << 20) - 1, 20 << 20])
 def test_decode_on_either_side_of_every_tile_size(dtype, n):
     """Launches on either side of the sizes at which the decoder's groups per wave change: one chunk; ragged chunks that
     start at every alignment and end in every kind of rest; outputs that start 0 to 7 elements into an allocation.
@@ -391,6 +393,46 @@ def test_decode_on_either_side_of_every_tile_size(dtype, n):
         assert int(st.item()) == 0
         assert torch.equal(back[off:off + n], x)
         assert bool((back[:off] == 0x5B5B).all()) and bool((back[off + n:] == 0x5B5B).all())
+
+
+@pytest.mark.parametrize("dtype,n", [(z.BF16, (9 << 19) + 64), (z.BF16, (21 << 18) + 192), (z.FP32, (11 << 19) + 64), (z.FP32, 15 << 19)])
+def test_decode_of_chunks_on_line_boundaries_with_rests(dtype, n):
+    """Launches in which a wave takes four groups, several chunks that start on cache lines and end in every kind of
+    rest (whole groups, part of one, a single line, a tile less or more a line): exact words back, nothing written in
+    front of or behind the output; a damaged index entry of a tail and of a whole tile is flagged."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + dtype)
+    x = torch.empty(n, dtype=torch.float32, device=DEV).normal_(0.0, 0.02, generator=g)
+    x[::41] = 0.0
+    x[7000:11000] = 3.0e5
+    x = x.to(torch.bfloat16).view(torch.int16) if dtype == z.BF16 else x.view(torch.int32)
+    head = [64, 512, 576, 4096 + 64, 8192 - 64, 0, 8192, 8192 + 64, 8192 + 5 * 512 + 64, 3 * 8192 + 3 * 1024, 20 * 8192 + 13 * 512]
+    ce = np.array(head + [n - sum(head)], dtype=np.uint64)
+    C = len(ce)
+    out = torch.empty(z.zipccl_max_compressed_size(n, dtype, C, ce), dtype=torch.uint8, device=DEV)
+    ws = torch.empty(z.zipccl_compress_workspace_size(n, dtype, C, ce), dtype=torch.uint8, device=DEV)
+    z.zipccl_compress(x, n, dtype, C, ce, z.zipccl_build_table(0.02, dtype), out, None, ws)
+    back = torch.full((n + 128,), 0x5B5B, dtype=x.dtype, device=DEV)
+
+    def run(comp):
+        st = torch.zeros(1, dtype=torch.int32, device=DEV)
+        z.zipccl_decompress(comp, back[64:64 + n], n, dtype, C, ce, st)
+        torch.cuda.synchronize()
+        return int(st.item())
+
+    assert run(out) == 0
+    assert torch.equal(back[64:64 + n], x)
+    assert bool((back[:64] == 0x5B5B).all()) and bool((back[64 + n:] == 0x5B5B).all())
+    off = z.zipccl_chunk_slot_offsets(n, dtype, C, ce)
+    static = z.zipccl_chunk_static_bytes(n, dtype, C, ce)
+    for c, entry in ((8, 20), (10, 5), (10, 330)):                     # the index is what the static part ends with
+        groups = (int(ce[c]) + 511) // 512
+        pos = int(off[c]) + int(static[c]) - (4 * groups + 127) // 128 * 128 + 4 * entry
+        assert entry < groups
+        _say(f"[line boundaries] dtype={dtype} n={n} damaged entry {entry} of chunk {c}")
+        bad = out.clone()
+        bad[pos:pos + 4] = torch.tensor([0xFF, 0xFF, 0xFF, 0x7F], dtype=torch.uint8, device=DEV)
+        assert run(bad) == 4
 
 
 @pytest.mark.parametrize("dtype", [z.BF16, z.FP32], ids=["bf16", "fp32"])
