@@ -1110,14 +1110,17 @@ int launch_decompress(int dt, const DecompressArgs& a, void* stream)
  * group per wave while the shard gives the chip's resident workgroups too little to do for a second group to pay, two
  * from there on: for bf16 as a pair of neighbours (reduce_pair), where more peers make a longer chain per wave and want
  * more waves.  us, one group against a pair, 128 / 256 / 384 / 512 tiles of 8192 values: 8 peers 7.8 / 9.1, 10.3 / 10.5,
- * 13.0 / 12.7, 15.1 / 15.1, then 18.8 / 17.1 at 640; 2 peers 7.1 / 6.1 at 384; 16 peers 21.3 / 21.4 at 384; 64 peers
- * 69.9 / 78.5 at 384, 88.8 / 89.2 at 512.
+ * 13.2 / 13.6, 15.6 / 15.4, then 18.8 / 17.1 at 640; 2 peers 7.1 / 6.1 at 384; 16 peers 20.8 / 21.3 at 384, 22.6 / 23.5 at
+ * 448 (the last whole number of one-group workgroups per compute unit), 25.0 / 24.0 at 456; 64 peers 69.9 / 78.5 at 384, 88.8
+ * / 89.2 at 512.  bf16 sums, and shards with a rest, whose kernel leaves room for fewer waves, are no worse off as
+ * pairs from 384 tiles on (16 peers, 448 tiles and 1000 values: one group 11 % slower).
  */
-static uint32_t reduce_groups_per_wave(uint64_t n, int dt, uint32_t n_peers)
+static uint32_t reduce_groups_per_wave(uint64_t n, int dt, int out_dt, uint32_t n_peers)
 {
     const uint64_t tiles = n / kTile;
     if (dt == ZIPCCL_FP32) return tiles < 2560u ? 1u : 2u;
-    return tiles < (n_peers <= 16u ? 384u : 512u) ? 1u : 2u;
+    const uint32_t from = n_peers > 16u ? 512u : (n_peers > 6u && out_dt == ZIPCCL_FP32 && n % kTile == 0 ? 449u : 384u);
+    return tiles < from ? 1u : 2u;
 }
 
 int launch_decompress_reduce(int dt, int out_dt, const ReduceArgs& a, void* stream)
@@ -1125,7 +1128,7 @@ int launch_decompress_reduce(int dt, int out_dt, const ReduceArgs& a, void* stre
     hipStream_t s = (hipStream_t)stream;
     const dim3 block(kThreads);
     ReduceArgs b = a;
-    b.gpw = reduce_groups_per_wave(a.n, dt, a.n_peers);
+    b.gpw = reduce_groups_per_wave(a.n, dt, out_dt, a.n_peers);
     const uint64_t per = (uint64_t)kGroup * kWavesPerBlock * b.gpw;
     /* whole tiles with a dword-aligned output go through the form without bounds checks, the rest (under one
        tile, or everything when the output is only 2-byte aligned) through the general one, in the same launch */

@@ -367,6 +367,15 @@ def test_reduce_pairs_of_groups(tail):
             _check(peers, z.BF16, [0.02], out_dt, f"pairs n={n} P={P} out={out_dt}")
 
 
+@pytest.mark.parametrize("P,n", [(7, 448 * 8192), (7, 448 * 8192 + 512), (7, 449 * 8192)])
+def test_reduce_on_either_side_of_the_size_from_which_more_peers_go_in_pairs(P, n):
+    """FP32 sums of more than 6 peers: whole tiles one group per wave up to 448 of them, pairs behind that and wherever
+    the shard has a rest."""
+    rng = np.random.default_rng(P * n)
+    peers = _peers(rng, P, n, z.BF16, [0.02, 0.5])
+    _check(peers, z.BF16, [0.02, 0.5], z.FP32, f"P={P} n={n}")
+
+
 def test_reduce_pairs_flag_damage_and_leave_rejected_slots_out():
     """In a shard that is taken in pairs: each index entry of a pair checked on its own (first, middle, last of the chunk),
     plane bits, a rejected header; an intact call stays clean."""
