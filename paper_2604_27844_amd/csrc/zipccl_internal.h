@@ -55,11 +55,21 @@ ZIPCCL_HD SlotLayout slot_layout(uint64_t n, int dt)
 }
 
 /*
+ * Nonzero unless base <= next <= n_esc and next - base <= 512: what two consecutive index entries must be to bound a
+ * group's slice of a list of n_esc zero-points.  The difference alone does not say that they ascend: it wraps, and a base
+ * just below 2^32 is as little ahead of a small next as a good one.  A decoder of a whole chunk need ask so (`ascend`) of
+ * the first group only: a later group's base is the next of the group before, inside the list, and if every group's
+ * difference is its count of zero-points, the entries are the first one plus sums that stay below 2^32.
+ */
+ZIPCCL_HD uint32_t slice_bad(uint32_t base, uint32_t next, uint32_t n_esc, bool ascend)
+{
+    return (uint32_t)(next - base > kGroup) | (uint32_t)(next > n_esc) | (uint32_t)(ascend && base > next);
+}
+
+/*
  * The slices of the zero-point list that three consecutive index entries give two neighbouring groups, and how a wave
  * fetches both: lane l reads the 16 bytes at pair_list_offset(s, l) behind the 16 bytes in front of the list.  Entries
- * that are not base <= mid <= next <= n_esc, 512 apart at most, are bad: nothing of the list is fetched then.  The
- * positions themselves are compared, and not only their differences, which wrap: a base just below 2^32 is as
- * little ahead of a small next as a good one.
+ * that are not base <= mid <= next <= n_esc, 512 apart at most, are bad: nothing of the list is fetched then.
  */
 struct PairSlices {
     uint32_t count_a, count_b;   /* zero-points of the two groups (meaningless if bad) */

@@ -60,7 +60,7 @@ int static_scratch(void** ptr, size_t* bytes)
     return 0;
 }
 
-/* What a wave of the fused reduce fetches of a slot's zero-point list for three consecutive index entries, whatever a
+/* The check of a group's two index entries; and what a wave of the fused reduce fetches of a slot's zero-point list for three consecutive index entries, whatever a
  * damaged stream holds in their place: every 16-byte read of the 64 lanes (and the last piece) lies between the 16
  * bytes in front of the list and its padded end, and entries that are not ascending positions of the list, at most a
  * group apart, are bad. */
@@ -73,6 +73,12 @@ static void check_pair_slices()
         for (int64_t d : near)
             for (int64_t v : {d, (int64_t)n_esc - d, (int64_t)n_esc + d, ((int64_t)1 << 32) - 1 - d})
                 if (v >= 0 && v <= 0xFFFFFFFFll) at.push_back((uint32_t)v);
+        for (uint32_t base : at) {
+            for (uint32_t next : at) {
+                CHECK((slice_bad(base, next, n_esc, true) == 0u) == (base <= next && next <= n_esc && next - base <= kGroup));
+                if (base <= next) CHECK(slice_bad(base, next, n_esc, false) == slice_bad(base, next, n_esc, true));
+            }
+        }
         const int64_t list_end = (int64_t)pad128(n_esc);
         for (uint32_t base : at) {
             for (uint32_t mid : at) {

@@ -245,6 +245,38 @@ def test_decoder_flags_corrupt_streams_without_leaving_buffers():
     assert ei.value.code == 3
 
 
+@pytest.mark.parametrize("dtype", [z.BF16, z.FP32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("n", [700, 5 * 8192])
+def test_decoder_flags_an_index_that_starts_in_front_of_the_list(dtype, n):
+    """Every index entry, the count and the size moved down by the same small number: the entries then agree with the
+    planes and with each other modulo 2^32, but the first group's slice starts in front of the list.  Flagged by
+    the decoder and by the fused reduce (all reads stay inside the buffer: positions are compared before they are used)."""
+    rng = np.random.default_rng(n + dtype)
+    f = rng.standard_normal(n, dtype=np.float32) * np.float32(0.02)
+    f[::16] = 0.0                                           # 32 zero-points a group and more
+    data = W.f32_to_bf16_words(f) if dtype == z.BF16 else f.view(np.uint32).copy()
+    stream, _, _ = oracle.compress(data, dtype, oracle.build_table(0.02), 1)
+    stream = stream.copy()
+    pad = lambda x: (x + 127) // 128 * 128
+    groups = (n + 511) // 512
+    static = int(z.zipccl_chunk_static_bytes(n, dtype, 1)[0])
+    idx = stream[static - pad(4 * groups):][:4 * groups].view(np.uint32)
+    n_esc = int(stream[24:32].view(np.uint64)[0])
+    down = 5
+    assert idx[0] == 0 and idx[1] > down
+    idx -= np.uint32(down)
+    stream[24:32].view(np.uint64)[0] = n_esc - down
+    stream[32:40].view(np.uint64)[0] = static + pad(n_esc - down)
+    d = torch.from_numpy(stream).to(DEV)
+    _, st = gpu_decompress(d, n, dtype)
+    assert st == 4
+    out = torch.zeros(n, dtype=torch.int32, device=DEV)
+    d_st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    z.zipccl_decompress_reduce(torch.cat([d, d]), out, n, dtype, 2, z.FP32, d_st)
+    torch.cuda.synchronize()
+    assert int(d_st.item()) == 4
+
+
 def test_runs_on_a_side_stream():
     w = W.make("c2", 1 / 16)
     s = torch.cuda.Stream()
