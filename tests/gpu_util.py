@@ -15,9 +15,38 @@ def to_device_words(data):
     return torch.from_numpy(np.ascontiguousarray(data).view(signed)).to(DEV)
 
 
+FORMS = ("by_rule", "stash", "reread")
+TILE = 8192
+
+
+def split_for_form(data, n_chunks, chunk_elems, form):
+    """zipccl_compress takes a launch (128 chunks) whose chunks all hold a few tiles in one kernel, whatever the workspace.
+    by_rule: the call as it is.  stash / reread: a chunk of more tiles than that form takes is put behind every 100
+    chunks that have none, so that the launch goes through the two-kernel form with a stash, or the one that reads its
+    input twice (which of them, the workspace selects).  Returns (data, n_chunks, chunk_elems)."""
+    if form == "by_rule":
+        return data, n_chunks, chunk_elems
+    n, extra = int(data.size), 8 * TILE + 1
+    ce = [n // n_chunks] * n_chunks if chunk_elems is None else [int(k) for k in chunk_elems]
+    filler = np.resize(data, extra) if n else np.full(extra, 0x3F80 if data.dtype == np.uint16 else 0x3F800000, dtype=data.dtype)
+    parts, split, start, added = [], [], 0, False
+    for c in range(0, n_chunks, 100):
+        block = ce[c:c + 100]
+        parts.append(data[start:start + sum(block)])
+        start += sum(block)
+        split += block
+        if max(block) < extra:
+            parts.append(filler)
+            split.append(extra)
+            added = True
+    if not added:
+        return data, n_chunks, chunk_elems
+    return np.concatenate(parts), len(split), np.array(split, dtype=np.uint64)
+
+
 def gpu_compress(data, dtype, sigma, n_chunks=1, chunk_elems=None, table=None, d_in=None, reread=False):
     """reread: hand zipccl_compress only its minimum workspace, which selects the form that reads the input
-    twice (count, prefix, emit) instead of the single pass with a stash."""
+    twice (count, prefix, emit) instead of the single pass with a stash (calls on small chunks take neither)."""
     n = int(data.size)
     table = table if table is not None else z.zipccl_build_table(sigma, dtype)
     cap = z.zipccl_max_compressed_size(n, dtype, n_chunks, chunk_elems)
@@ -43,12 +72,13 @@ def gpu_decompress(d_comp, n, dtype, n_chunks=1, chunk_elems=None, comp_capacity
     return d_back.cpu().numpy().view(words), int(d_st.item())
 
 
-def check_parity(data, dtype, sigma, n_chunks=1, chunk_elems=None, label="", reread=False):
-    """GPU compressed bytes, chunk sizes and decoded words must equal the oracle's."""
+def check_parity(data, dtype, sigma, n_chunks=1, chunk_elems=None, label="", form="by_rule"):
+    """GPU compressed bytes, chunk sizes and decoded words must equal the oracle's; form: see split_for_form."""
+    data, n_chunks, chunk_elems = split_for_form(data, n_chunks, chunk_elems, form)
     n = int(data.size)
     dec = oracle.build_table(sigma)
     ref, ref_cb, off = oracle.compress(data, dtype, dec, n_chunks, chunk_elems)
-    d_out, d_cb, table = gpu_compress(data, dtype, sigma, n_chunks, chunk_elems, reread=reread)
+    d_out, d_cb, table = gpu_compress(data, dtype, sigma, n_chunks, chunk_elems, reread=form == "reread")
     assert list(bytes(table.dec)) == list(dec), f"{label}: table differs"
     got = d_out.cpu().numpy()
     got_cb = d_cb.cpu().numpy().astype(np.uint64)

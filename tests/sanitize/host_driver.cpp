@@ -32,7 +32,6 @@ static void check_tab(const ChunkTab& t)
 }
 
 int launch_estimate(int, const MomentArgs& a, void*) { CHECK(a.n_blocks >= 1 && a.n_blocks <= kMomentBlocks); ++g_launches; return 0; }
-int launch_clear_hist(unsigned long long* hist, uint32_t n_chunks, void*) { CHECK(hist != nullptr && n_chunks >= 1); ++g_launches; return 0; }
 int launch_estimate_robust(int, const HistArgs& a, void*)
 {
     CHECK(a.n_blocks >= 1 && a.n_blocks <= kHistBlocks && a.tab.n_chunks >= 1 && a.tab.n_chunks <= kMaxBatch);
@@ -47,7 +46,19 @@ int launch_estimate_robust_fused(int dt, const HistArgs& a, void* s)
         CHECK(((a.tab.elem_off[c + 1] - a.tab.elem_off[c] + kGroup - 1) / kGroup + a.sample_stride - 1) / a.sample_stride <= kFusedGroups);
     return launch_estimate_robust(dt, a, s);
 }
-int launch_compress(int, int, const CompressArgs& a, void*) { check_tab(a.tab); ++g_launches; return 0; }
+/* kModeDirect has no workgroup wait for another: every one counts the tiles before its own, so they have to be few */
+static int g_by_mode[4];
+int launch_compress(int dt, int mode, const CompressArgs& a, void*)
+{
+    check_tab(a.tab);
+    if (mode == kModeDirect)
+        for (uint32_t c = 0; c < a.tab.n_chunks; ++c)
+            CHECK(a.tab.tile_start[c + 1] - a.tab.tile_start[c] <= (dt == ZIPCCL_BF16 ? 8u : 4u));
+    if (mode == kModeStash) CHECK(a.stash != nullptr);
+    ++g_by_mode[mode];
+    ++g_launches;
+    return 0;
+}
 int launch_tile_scan(const CompressArgs& a, void*) { check_tab(a.tab); ++g_launches; return 0; }
 int launch_place(int, bool, const CompressArgs& a, void*) { check_tab(a.tab); ++g_launches; return 0; }
 int launch_decompress(int, const DecompressArgs& a, void*) { check_tab(a.tab); ++g_launches; return 0; }
@@ -169,6 +180,34 @@ int main()
     CHECK(zipccl_compress(in, n, ZIPCCL_FP32, C, ce.data(), &t, out, big, nullptr, ws,
                           zipccl_compress_min_workspace_size(n, ZIPCCL_FP32, C, ce.data()), nullptr) == ZIPCCL_OK);
     CHECK(zipccl_compress_static(in, n, ZIPCCL_FP32, C, ce.data(), &t, out, big, nullptr, nullptr) == ZIPCCL_OK);
+    /* which form a compress takes: small chunks one kernel whatever the workspace, launch by launch; a chunk of more tiles
+       the stash or, in the minimum workspace, two reads */
+    auto forms = [&](zipccl_dtype_t dt, std::vector<uint64_t> split, bool least, int direct, int stash_launches, int emit) {
+        uint64_t total = 0;
+        for (uint64_t k : split) total += k;
+        for (int& m : g_by_mode) m = 0;
+        const uint32_t k = (uint32_t)split.size();
+        const size_t ws_bytes = least ? zipccl_compress_min_workspace_size(total, dt, k, split.data()) : big;
+        CHECK(zipccl_compress(in, total, dt, k, split.data(), &t, out, big, nullptr, ws, ws_bytes, nullptr) == ZIPCCL_OK);
+        CHECK(g_by_mode[kModeDirect] == direct && g_by_mode[kModeStash] == stash_launches);
+        CHECK(g_by_mode[kModeCount] == emit && g_by_mode[kModeEmit] == emit);
+    };
+    const uint64_t T = kTile;
+    for (bool least : {false, true}) {
+        const int s = least ? 0 : 1, e = least ? 1 : 0;
+        forms(ZIPCCL_BF16, {8 * T}, least, 1, 0, 0);
+        forms(ZIPCCL_BF16, {8 * T + 1}, least, 0, s, e);
+        forms(ZIPCCL_FP32, {4 * T, 0, 1}, least, 1, 0, 0);
+        forms(ZIPCCL_FP32, {4 * T + 1}, least, 0, s, e);
+        forms(ZIPCCL_BF16, std::vector<uint64_t>(8, 8 * T), least, 1, 0, 0);
+        forms(ZIPCCL_BF16, std::vector<uint64_t>(9, 8 * T), least, 0, s, e);
+        forms(ZIPCCL_BF16, std::vector<uint64_t>(128, 4 * T), least, 1, 0, 0);
+        forms(ZIPCCL_FP32, std::vector<uint64_t>(32, 4 * T), least, 1, 0, 0);
+        forms(ZIPCCL_FP32, std::vector<uint64_t>(33, 4 * T), least, 0, s, e);
+        std::vector<uint64_t> mixed(129, T);                          /* the second launch holds the one large chunk */
+        mixed[128] = 9 * T;
+        forms(ZIPCCL_BF16, mixed, least, 1, s, e);
+    }
     CHECK(zipccl_decompress(out, big, in, n, ZIPCCL_FP32, C, ce.data(), nullptr, nullptr) == ZIPCCL_OK);
     CHECK(zipccl_decompress_reduce(out, big, in, 5000, ZIPCCL_BF16, 1024, ZIPCCL_BF16, nullptr, nullptr) == ZIPCCL_OK);
     CHECK(zipccl_estimate_table(in, 100000, ZIPCCL_BF16, (zipccl_table_t*)out, nullptr, ws, big, nullptr) == ZIPCCL_OK);

@@ -71,10 +71,10 @@ def test_single_slot_is_widened_exactly_for_every_bf16_pattern():
 
 
 @pytest.mark.parametrize("dtype,n", [(z.BF16, 2048 * 8192 + 5000), (z.BF16, 700 * 8192 + 4 * 2048 + 1500),
-                                     (z.FP32, 2600 * 8192 + 2048 + 77)], ids=["bf16_four", "bf16_two", "fp32_two"])
+                                     (z.FP32, 2600 * 8192 + 2048 + 77)], ids=["bf16_2048_tiles", "bf16_700_tiles", "fp32_2600_tiles"])
 def test_reduce_large_shards_take_several_groups_per_wave(dtype, n):
-    """Past a size that depends on the dtype a workgroup takes two groups per wave, and four for bf16 shards of a
-    multiple of 2048 whole tiles; the rest behind the whole tiles runs in the same launch."""
+    """Past a size that depends on the dtype a wave takes two groups, bf16 as a pair of neighbours; the rest behind the
+    whole tiles runs in the same launch."""
     rng = np.random.default_rng(44)
     sig = [0.02, 0.03]
     _check(_peers(rng, 2, n, dtype, sig), dtype, sig, z.FP32, "large shard")
@@ -374,6 +374,47 @@ def test_reduce_on_either_side_of_the_size_from_which_more_peers_go_in_pairs(P, 
     rng = np.random.default_rng(P * n)
     peers = _peers(rng, P, n, z.BF16, [0.02, 0.5])
     _check(peers, z.BF16, [0.02, 0.5], z.FP32, f"P={P} n={n}")
+
+
+@pytest.mark.parametrize("n", [512 * 8192 - 1, 512 * 8192])
+def test_reduce_of_more_than_16_peers_on_either_side_of_the_pairs(n):
+    """17 peers: pairs from 512 tiles on.  Every sum against the oracle, and with one slot's header rejected, which moves
+    every later slot up by one in the pipeline."""
+    rng = np.random.default_rng(n)
+    P, victim = 17, 6
+    peers = _peers(rng, P, n, z.BF16, [0.02])
+    buf = _receive_buffer(peers, z.BF16, [0.02])
+    cap1 = z.zipccl_max_compressed_size(n, z.BF16, 1)
+    slots = buf.cpu().numpy()
+    for rejected in (False, True):
+        if rejected:
+            buf[victim * cap1 + 2] = 0x00                              # its magic
+            slots = np.concatenate([slots[:victim * cap1], slots[(victim + 1) * cap1:]])
+        d_out = torch.full((n,), 0x3C3C3C3C, dtype=torch.int32, device=DEV)
+        d_st = torch.zeros(1, dtype=torch.int32, device=DEV)
+        print(f"[reduce 17] n={n} rejected={rejected}", flush=True)
+        z.zipccl_decompress_reduce(buf, d_out, n, z.BF16, P, z.FP32, d_st)
+        torch.cuda.synchronize()
+        assert int(d_st.item()) == (4 if rejected else 0)
+        want = oracle.decompress_reduce(slots, n, z.BF16, P - rejected, z.FP32)
+        assert np.array_equal(d_out.cpu().numpy().view(np.uint32), want), rejected
+
+
+def test_reduce_of_a_large_shard_into_an_output_that_is_only_element_aligned():
+    """bf16 sums at an odd element: no whole tile may be stored 4-byte aligned, so the kernel built for pairs runs its
+    general form alone, two groups per wave."""
+    rng = np.random.default_rng(62)
+    P, n = 3, 384 * 8192 + 17
+    buf = _receive_buffer(_peers(rng, P, n, z.BF16, [0.02]), z.BF16, [0.02])
+    want = oracle.decompress_reduce(buf.cpu().numpy(), n, z.BF16, P, z.BF16)
+    backing = torch.full((n + 64,), 0x1234, dtype=torch.int16, device=DEV)
+    d_st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    z.zipccl_decompress_reduce(buf, backing[31:31 + n], n, z.BF16, P, z.BF16, d_st)
+    torch.cuda.synchronize()
+    got = backing.cpu().numpy().view(np.uint16)
+    assert int(d_st.item()) == 0
+    assert np.array_equal(got[31:31 + n], want)
+    assert (got[:31] == 0x1234).all() and (got[31 + n:] == 0x1234).all()
 
 
 def test_reduce_pairs_flag_damage_and_leave_rejected_slots_out():

@@ -88,9 +88,10 @@ def test_static_workspace_compress_rejects_what_does_not_fit_and_bad_arguments()
 def test_static_workspace_compress_replays_inside_a_hip_graph():
     """What the entry point is for: captured once (after a first call outside the capture, which looks up the
     array's address), replayed on fresh input contents with the program's own eager work in between; every replay
-    must equal zipccl_compress on the same input."""
+    must equal zipccl_compress on the same input.  The first chunk has more tiles than a compress without a workspace
+    takes, so the captured kernels use the array."""
     rng = np.random.default_rng(22)
-    ce = np.array([8192 * 5 + 3, 0, 20000, 8192 * 2], dtype=np.uint64)
+    ce = np.array([8192 * 9 + 3, 0, 20000, 8192 * 2], dtype=np.uint64)
     n, C = int(ce.sum()), len(ce)
     table = z.zipccl_build_table(0.3, z.BF16)
     cap = z.zipccl_max_compressed_size(n, z.BF16, C, ce)
