@@ -43,20 +43,35 @@ static __device__ __align__(256) uint8_t scratch[ZIPCCL_STATIC_SCRATCH_BYTES];
  * fewer than 8. */
 enum LoadForm { kWhole, kRest, kTiny };
 
+/* kRest: the 16 bytes that hold piece q of the lane's values. */
+template <int DT>
+__device__ __forceinline__ u32x4 request_rest(const uint8_t* __restrict__ cin, uint64_t gbase, uint32_t lane, uint64_t n, uint32_t q)
+{
+    constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u, PER16 = 16u / ES;
+    const uint32_t left = gbase >= n ? 0u : (uint32_t)min(n - gbase, (uint64_t)kGroup);
+    const int64_t base = left != 0u ? (int64_t)gbase : 0;                    /* a group past the end: the chunk's first */
+    const uint32_t e = lane * PER16 + q * (kGroup / 2);
+    const uint32_t here = e >= left ? 0u : min(left - e, PER16);
+    /* one with none loads from where the group has 16 bytes, or from the 16 bytes the chunk ends with */
+    const int32_t none = left != 0u && left < PER16 ? (int32_t)left - (int32_t)PER16 : 0;
+    const int32_t at = here != 0u ? (int32_t)e - (int32_t)(PER16 - here) : none;
+    return ld_stream_a2(cin + (base + at) * (int64_t)ES);
+}
+
 /*
  * Load the lane's 8 values of the group at chunk-relative element gbase: bf16: 8 consecutive ones; fp32: two quads,
  * [4 lane, 4 lane + 4) of the group's first half and of its second, so that each load is 16 contiguous bytes per
  * lane (32 contiguous bytes per lane cost ~7 % of the bandwidth, measured).
  * hp[k] packs the high 16-bit words of values 2k (low half) and 2k+1 (high half); lp[k] the low words (fp32 only).
- * vmask bit j = value j exists; values that do not exist read as 0.  kRest: no load is under a condition, so that all
- * groups' loads are in flight together: a lane (or quad) that the chunk's end cuts short loads the 16 bytes that end
- * there and moves them down, one without values loads 16 bytes that exist.  With eight loads under conditions per lane,
- * each waited for, the tile behind the last whole one was what a call ended with: 8191 bf16 values 9.4 -> 7.7 us, 8 chunks
- * of 2 097 147 22.8 -> 17.1 us, fp32 37.3 -> 27.6.
+ * vmask bit j = value j exists; values that do not exist read as 0.  kRest: no load is under a condition, and the caller
+ * requests every group's before it has the first moved into place (`rest`: request_rest): a lane (or quad) that the
+ * chunk's end cuts short loads the 16 bytes that end there and moves them down, one without values loads 16 bytes that exist.
+ * With eight loads under conditions per lane, each waited for, the tile behind the last whole one was what a call ended
+ * with: 8191 bf16 values in two kernels 9.4 -> 7.7 us, 8 chunks of 2 097 147 22.8 -> 17.1 us, fp32 37.3 -> 27.6.
  */
 template <int DT, int FORM>
 __device__ __forceinline__ void load_lane(const uint8_t* __restrict__ cin, uint64_t gbase, uint32_t lane, uint64_t n,
-                                          uint32_t hp[4], uint32_t lp[4], uint32_t& vmask)
+                                          uint32_t hp[4], uint32_t lp[4], uint32_t& vmask, const u32x4* rest = nullptr)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u, PER16 = 16u / ES, NQ = DT == ZIPCCL_BF16 ? 1u : 2u;
     u32x4 v[NQ];
@@ -68,7 +83,6 @@ __device__ __forceinline__ void load_lane(const uint8_t* __restrict__ cin, uint6
         for (uint32_t q = 0; q < NQ; ++q) v[q] = ld_stream_a2(p + q * 1024u + lane * 16u);
     } else {
         const uint32_t left = gbase >= n ? 0u : (uint32_t)min(n - gbase, (uint64_t)kGroup);      /* values of the group */
-        const int64_t base = left != 0u ? (int64_t)gbase : 0;                    /* a group past the end: the chunk's first */
         vmask = 0;
 #pragma unroll
         for (uint32_t q = 0; q < NQ; ++q) {
@@ -77,10 +91,7 @@ __device__ __forceinline__ void load_lane(const uint8_t* __restrict__ cin, uint6
             vmask |= ((1u << here) - 1u) << (4u * q);
             uint32_t w[4];
             if (FORM == kRest) {
-                /* one with none loads from where the group has 16 bytes, or from the 16 bytes the chunk ends with */
-                const int32_t none = left != 0u && left < PER16 ? (int32_t)left - (int32_t)PER16 : 0;
-                const int32_t at = here != 0u ? (int32_t)e - (int32_t)(PER16 - here) : none;
-                const u32x4 t = ld_stream_a2(cin + (base + at) * (int64_t)ES);
+                const u32x4 t = rest[q];
                 w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
                 const uint32_t down = here != 0u ? PER16 - here : 0u;            /* values that belong to the 16 bytes before */
                 const uint32_t dw = ES * down / 4u;                              /* whole words of them, 0 .. 3 */
@@ -376,9 +387,19 @@ __global__ __launch_bounds__(kThreads) void k_compress(const CompressArgs a)
             compress_group<DT, true, STORE>(slot, L, n, ts, group_of(wave, u), k7, lane, sh, hp[u], lp[u], vm[u]);
     } else {
         if (n >= 8u) {
+            /* every request before the first use of what one brings: left to itself the compiler waits for each of the
+               four loads (fp32: for each four of eight) before the next (5000 bf16 values 4.9 -> 4.45 us, 8195 in two reads
+               9.0 -> 8.2) */
+            constexpr uint32_t NQ = DT == ZIPCCL_BF16 ? 1u : 2u;
+            u32x4 rest[kGroupsPerWave][NQ];
 #pragma unroll
             for (uint32_t u = 0; u < kGroupsPerWave; ++u)
-                load_lane<DT, kRest>(cin, ts + (uint64_t)group_of(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u]);
+#pragma unroll
+                for (uint32_t q = 0; q < NQ; ++q) rest[u][q] = request_rest<DT>(cin, ts + (uint64_t)group_of(wave, u) * kGroup, lane, n, q);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (uint32_t u = 0; u < kGroupsPerWave; ++u)
+                load_lane<DT, kRest>(cin, ts + (uint64_t)group_of(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u], rest[u]);
         } else {
 #pragma unroll
             for (uint32_t u = 0; u < kGroupsPerWave; ++u)
