@@ -90,10 +90,11 @@ struct DecEsc {
     uint32_t bad;            /* nonzero: planes and IDX disagree about the group */
 };
 
-/* r.base and next bound the group's slice of the zero-point list: check them, set r.count. */
-__device__ __forceinline__ void check_index(DecIn& r, uint32_t next, uint32_t n_esc, bool ascend)
+/* r.base and next bound the group's slice of the zero-point list: check them, set r.count.  That the first two entries
+ * of a chunk ascend is checked elsewhere, once. */
+__device__ __forceinline__ void check_index(DecIn& r, uint32_t next, uint32_t n_esc)
 {
-    r.idx_bad = slice_bad(r.base, next, n_esc, ascend);
+    r.idx_bad = slice_bad(r.base, next, n_esc, false);
     r.count = r.idx_bad ? 0u : next - r.base;
 }
 
@@ -445,7 +446,7 @@ void k_decompress(const DecompressArgs a)
             if (FAST) in[u].vmask = 0xFFu;
             else if (g >= ng) in[u].base = n_esc;
             if (g + 1 >= ng) next[u] = n_esc;
-            check_index(in[u], next[u], n_esc, false);
+            check_index(in[u], next[u], n_esc);
         }
 #pragma unroll
         for (uint32_t u = 0; u < GPW; ++u) decode_fetch_list(slot, L, in[u], next[u], lane, lv[u]);
@@ -608,7 +609,7 @@ __device__ __forceinline__ void reduce_stages(const ReduceArgs& a, const SlotLay
         const uint8_t* __restrict__ slot = a.comp + r.pre_off;
         const uint32_t next = r.pre_g + 1u < ng ? r.pre_next : r.pre_nesc;
         r.in.base = r.pre_base;
-        check_index(r.in, next, r.pre_nesc, true);
+        check_index(r.in, next, r.pre_nesc);
         if (!FAST || r.pre_g != g_iss) {
             g_iss = r.pre_g;
             const uint64_t gs = (uint64_t)g_iss * kGroup, e = gs + lane * kLaneElems;
@@ -970,7 +971,8 @@ __device__ __forceinline__ void reduce_pair(const ReduceArgs& a, const SlotLayou
  * workgroups pay for the header checks and the table build; 1 for small shards, and for the rest behind whole
  * tiles, so that there are enough workgroups to fill the chip.  PAIR: whole tiles are taken by reduce_pair
  * (a.gpw = 2).  REST = false: the launch holds whole tiles only (the general form is compiled out: it costs the
- * whole-tile workgroups registers to share a kernel with it).  Dynamic LDS: one 32-bit word per peer.
+ * whole-tile workgroups registers to share a kernel with it).  Workgroup a.n_work, if there is one, only looks at the slots'
+ * first index entries.  Dynamic LDS: one 32-bit word per peer.
  */
 template <int DT, int ODT, bool REST, bool PAIR>
 __global__ __launch_bounds__(kThreads, DT == ZIPCCL_BF16 ? (REST ? 7 : 8) : 6) void k_decompress_reduce(const ReduceArgs a)
@@ -1022,6 +1024,19 @@ __global__ __launch_bounds__(kThreads, DT == ZIPCCL_BF16 ? (REST ? 7 : 8) : 6) v
     n_acc = __builtin_amdgcn_readfirstlane(n_acc);
     uint32_t bad = n_acc != a.n_peers;
 
+    if (!PAIR && blockIdx.x == a.n_work) {
+        /* a workgroup behind the others looks whether the first two index entries of every slot ascend, for shards whose
+           first group is not in a pair, which asks for itself.  (Asked at every stage, this costs 16 peers' slots of a few
+           tiles 3 %; by the waves of the first workgroup, in the header check or at their end, 1 to 2 %.) */
+        for (uint32_t j = threadIdx.x; j < n_acc; j += kThreads) {
+            const uint8_t* const slot = a.comp + (uint64_t)s_peer[j] * a.slot_cap;
+            const uint32_t* const idx = reinterpret_cast<const uint32_t*>(slot + L.idx);
+            const uint32_t n_esc = *reinterpret_cast<const uint32_t*>(slot + 24);
+            bad |= slice_bad(idx[0], n > kGroup ? idx[1] : n_esc, n_esc, true);
+        }
+        if (bad && a.status) atomicOr(a.status, (uint32_t)ZIPCCL_ERR_CORRUPT);
+        return;
+    }
     if (PAIR && whole) {                /* whole tiles of 8 groups: two neighbouring ones per wave */
         if (n_acc != 0u) {
             reduce_pair<ODT>(a, L, ts + (uint64_t)wave * (2 * kGroup), n_acc, lane, s_esc[wave], s_tab, s_peer, n_acc == a.n_peers, bad);
@@ -1141,13 +1156,14 @@ int launch_decompress_reduce(int dt, int out_dt, const ReduceArgs& a, void* stre
     const uint64_t per_rest = (uint64_t)kGroup * kWavesPerBlock * b.gpw_rest;
     uint64_t n_rest = (rest + per_rest - 1) / per_rest;
     if (a.n == 0) n_rest = 1;           /* one workgroup that only checks the headers */
-    const dim3 grid((uint32_t)(full + n_rest));
+    b.n_work = (uint32_t)(full + n_rest);
+    const bool pair = dt == ZIPCCL_BF16 && b.gpw == 2u && full != 0;
+    const dim3 grid(b.n_work + (pair || a.n == 0 ? 0u : 1u));      /* the last one: the slots' first index entries */
 #define ZIPCCL_REDUCE(DT, ODT, PAIR)                                                                                   \
     do {                                                                                                               \
         if (n_rest) hipLaunchKernelGGL((k_decompress_reduce<DT, ODT, true, PAIR>), grid, block, lds_bytes, s, b);      \
         else hipLaunchKernelGGL((k_decompress_reduce<DT, ODT, false, PAIR>), grid, block, lds_bytes, s, b);            \
     } while (0)
-    const bool pair = dt == ZIPCCL_BF16 && b.gpw == 2u;
     if (pair && out_dt == ZIPCCL_FP32) ZIPCCL_REDUCE(ZIPCCL_BF16, ZIPCCL_FP32, true);
     else if (pair) ZIPCCL_REDUCE(ZIPCCL_BF16, ZIPCCL_BF16, true);
     else if (dt == ZIPCCL_BF16 && out_dt == ZIPCCL_FP32) ZIPCCL_REDUCE(ZIPCCL_BF16, ZIPCCL_FP32, false);

@@ -169,6 +169,7 @@ struct ReduceArgs {
     /* set by the launcher: */
     uint32_t gpw;            /* groups per wave in the workgroups that take whole tiles */
     uint32_t n_full;         /* how many those are: workgroups 0 .. n_full - 1 */
+    uint32_t n_work;         /* workgroups that sum; one more may look at the slots' first index entries */
     uint32_t gpw_rest;       /* groups per wave in the workgroups after them, which take the rest of the shard */
 };
 

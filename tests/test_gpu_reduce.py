@@ -401,8 +401,8 @@ def test_reduce_of_more_than_16_peers_on_either_side_of_the_pairs(n):
 
 
 def test_reduce_of_a_large_shard_into_an_output_that_is_only_element_aligned():
-    """bf16 sums at an odd element: no whole tile may be stored 4-byte aligned, so the kernel built for pairs runs its
-    general form alone, two groups per wave."""
+    """bf16 sums at an odd element: no whole tile can be stored in dwords, so that a shard of a size for pairs is taken by
+    the general form alone, two groups per wave."""
     rng = np.random.default_rng(62)
     P, n = 3, 384 * 8192 + 17
     buf = _receive_buffer(_peers(rng, P, n, z.BF16, [0.02]), z.BF16, [0.02])
