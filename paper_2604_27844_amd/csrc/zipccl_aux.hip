@@ -129,10 +129,10 @@ __global__ __launch_bounds__(kThreads) void k_estimate_finish(const MomentArgs a
  * each for one or more chunks at once (one histogram and one table per chunk; the whole tensor is one chunk):
  *   large    k_clear_hist zeroes one histogram per chunk in the workspace, k_magnitude_hist (or its sampled form)
  *            adds to it what about one workgroup per compute unit has counted in its LDS, k_robust_finish looks
- *            for the rank.  2^24 bf16 values, one chunk: 2.0 + 11.6 + 3.7 us (2.4 of each is the launch; the
- *            histogram kernel reads for 3.3, counts for 2.4 beyond that and flushes for 4).  With 64-bit counts
- *            zeroed, flushed and read twice over by the finish, whose one thread then took four erf in a row, the
- *            same three kernels were 3.0 + 13.8 + 11.2 us.
+ *            for the rank.  2^24 bf16 values, one chunk: 2.0 + 11.6 + 3.7 us, launches included (the
+ *            histogram kernel without its flush: 4 us less).  With 64-bit counts zeroed, flushed and read twice over
+ *            by the finish, whose one thread then took four erf in a row, the same three kernels were 3.0 + 13.8 +
+ *            11.2 us.
  *   small    (at most kFusedGroups groups to count in every chunk) k_robust_partial: a few workgroups per chunk, each
  *            of which stores its own counts; k_robust_join adds them up and looks for the rank.  Nothing to clear, no
  *            atomics on memory.
