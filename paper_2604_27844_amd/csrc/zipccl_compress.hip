@@ -321,33 +321,58 @@ __device__ __forceinline__ void finish_chunk(uint8_t* __restrict__ slot, const S
     if (tid == 0 && chunk_bytes) *chunk_bytes = cbytes;
 }
 
-template <int DT, int MODE>
-__global__ __launch_bounds__(kThreads) void k_compress(const CompressArgs a)
+/* Kernel arguments: CompressArgs without its table, which follows in the form that the launch allows; small ones, see
+ * EqualSplit. */
+struct CompressIo {
+    const uint8_t* in;
+    uint8_t* out;
+    uint64_t* chunk_bytes;
+    const uint32_t* d_table;
+    uint32_t dec_lo, table_stride;
+};
+struct NoParking {};                                        /* kModeDirect */
+struct Parking {
+    uint32_t *tile_total, *tile_prefix;
+    uint8_t* stash;
+};
+
+/* dec[0..3] and dec[4..7]: from the kernel arguments (dec[1..7] are consecutive, the host has checked it) or, if the table
+ * was estimated on the device, two words in its memory. */
+__device__ __forceinline__ void table_words(const CompressIo& a, uint32_t c, uint32_t& dec_lo, uint32_t& dec_hi)
+{
+    if (a.d_table) {
+        const uint32_t* __restrict__ tab_c = a.d_table + c * a.table_stride;      /* one table for all chunks, or one each */
+        dec_lo = tab_c[0];
+        dec_hi = tab_c[1];
+    } else {
+        dec_lo = a.dec_lo;
+        dec_hi = ((a.dec_lo >> 8) & 0xFFu) * 0x01010101u + 0x06050403u;
+    }
+}
+
+template <int DT, int MODE, class PARK, class SPLIT>
+__global__ __launch_bounds__(kThreads) void k_compress(const CompressIo a, const PARK park, const SPLIT split)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
     constexpr bool STORE = MODE != kModeCount;
     __shared__ CompressShared sh;
 
-    /* grid = (tiles of the largest chunk, chunks): no search, the chunk's geometry is three scalar loads */
+    /* grid = (tiles of the largest chunk, chunks): no search, the chunk's geometry is three scalar loads at most */
     const uint32_t c = blockIdx.y;
-    const uint32_t first = a.tab.tile_start[c];
-    const uint32_t ntc = a.tab.tile_start[c + 1] - first;
-    if (blockIdx.x >= ntc) return;
-    const uint32_t t = first + blockIdx.x;
-    const bool last_tile = blockIdx.x + 1u == ntc;
-    const uint64_t n = a.tab.elem_off[c + 1] - a.tab.elem_off[c];
+    const ChunkPlace place = place_of(split, c, DT);
+    if (blockIdx.x >= place.tiles) return;
+    const bool last_tile = blockIdx.x + 1u == place.tiles;
+    const uint64_t n = place.n;
     const uint64_t ts = (uint64_t)blockIdx.x * kTile;
-    const uint8_t* __restrict__ cin = a.in + a.tab.elem_off[c] * ES;
-    uint8_t* __restrict__ slot = a.out + a.tab.slot_off[c];
+    const uint8_t* __restrict__ cin = a.in + place.elem_off * ES;
+    uint8_t* __restrict__ slot = a.out + place.slot_off;
     const SlotLayout L = slot_layout(n, DT);
     const bool fast = ts + kTile <= n;                      /* a whole tile */
     const uint32_t lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   /* keep wave-derived math scalar */
-    /* the table is a kernel argument, or (estimated on the device) two words in device memory */
-    const uint32_t* __restrict__ tab_c = a.d_table + c * a.table_stride;      /* one table for all chunks, or one each */
-    const uint32_t dec_lo = a.d_table ? tab_c[0] : a.dec_lo;
-    const uint32_t dec_hi = a.d_table ? tab_c[1] : a.dec_hi;
-    const uint32_t e0 = a.d_table ? (dec_lo >> 8) & 0xFFu : a.e0;
+    uint32_t dec_lo, dec_hi;
+    table_words(a, c, dec_lo, dec_hi);
+    const uint32_t e0 = (dec_lo >> 8) & 0xFFu;
     const uint32_t k7 = ((e0 - 1u) << 7) * 0x00010001u;
 
     /* all four groups' loads go out before the first is encoded: four times the bytes in flight per
@@ -417,19 +442,19 @@ __global__ __launch_bounds__(kThreads) void k_compress(const CompressArgs a)
     const uint32_t ginc = row_incl_scan(gc);
     const uint32_t gex = ginc - gc;
     const uint32_t tile_total = __builtin_amdgcn_readlane(ginc, kGroupsPerTile - 1);
-    if (MODE == kModeCount) {
-        if (threadIdx.x == 0) a.tile_total[t] = tile_total;
-        return;
+    if constexpr (MODE == kModeCount || MODE == kModeStash) {
+        if (threadIdx.x == 0) park.tile_total[place.tile + blockIdx.x] = tile_total;
+        if (MODE == kModeCount) return;
     }
-    if (MODE == kModeStash && threadIdx.x == 0) a.tile_total[t] = tile_total;
 
     /* kModeEmit and kModeDirect know the zero-points of the chunk before this tile; kModeStash works tile-local */
     uint32_t P = 0;
-    if (MODE == kModeEmit) P = a.tile_prefix[t];
+    if constexpr (MODE == kModeEmit) P = park.tile_prefix[place.tile + blockIdx.x];
     if (MODE == kModeDirect) P = (sh.before[0] + sh.before[1]) + (sh.before[2] + sh.before[3]);
     const uint64_t ng = (n + kGroup - 1) / kGroup;
     uint32_t* __restrict__ idx = reinterpret_cast<uint32_t*>(slot + L.idx);
-    uint8_t* __restrict__ esc = MODE != kModeStash ? slot + L.esc + P : a.stash + a.tab.elem_off[c] + ts;
+    uint8_t* __restrict__ esc = slot + L.esc + P;
+    if constexpr (MODE == kModeStash) esc = park.stash + place.elem_off + ts;
 
     if (wave == 0) {
         /* group index (section 4.2.3); k_place adds the tile's prefix in stash mode */
@@ -490,8 +515,8 @@ __device__ __forceinline__ void move_words(uint32_t* __restrict__ d32, const uin
  */
 /* SCAN: there was no k_tile_scan; the workgroup sums the chunk's tile counts before its own tiles itself
  * (chunks of at most kPlaceScanTiles tiles: the counts are few and cache-resident). */
-template <int DT, bool SCAN>
-__global__ __launch_bounds__(kThreads) void k_place(const CompressArgs a)
+template <int DT, bool SCAN, class SPLIT>
+__global__ __launch_bounds__(kThreads) void k_place(const CompressIo a, const Parking park, const SPLIT split)
 {
     constexpr uint32_t kSub = 16;                       /* lanes per tile */
     constexpr uint32_t kPlaceBig = 1024;                /* bytes a 16-lane group moves on its own */
@@ -505,8 +530,8 @@ __global__ __launch_bounds__(kThreads) void k_place(const CompressArgs a)
 
     /* grid = (16-tile groups of the largest chunk, chunks): the chunk's geometry is wave-uniform */
     const uint32_t c = blockIdx.y;
-    const uint32_t first = a.tab.tile_start[c];
-    const uint32_t ntc = a.tab.tile_start[c + 1] - first;
+    const ChunkPlace place = place_of(split, c, DT);
+    const uint32_t first = place.tile, ntc = place.tiles;
     if (blockIdx.x * (kThreads / kSub) >= ntc) return;  /* a shorter chunk than the largest of the launch */
     if (SCAN) {
         /* counts of the chunk's tiles before this workgroup's, and the exclusive prefix inside it */
@@ -515,30 +540,29 @@ __global__ __launch_bounds__(kThreads) void k_place(const CompressArgs a)
         uint32_t i = threadIdx.x;
         for (; i + 3u * kThreads < t0; i += 4u * kThreads) {
 #pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) part[k] += a.tile_total[first + i + k * kThreads];
+            for (uint32_t k = 0; k < 4; ++k) part[k] += park.tile_total[first + i + k * kThreads];
         }
-        for (; i < t0; i += kThreads) part[0] += a.tile_total[first + i];
+        for (; i < t0; i += kThreads) part[0] += park.tile_total[first + i];
         const uint32_t inc = wave_incl_scan((part[0] + part[1]) + (part[2] + part[3]));
         if ((threadIdx.x & 63u) == 63u) s_wave[threadIdx.x >> 6] = inc;
         if (threadIdx.x < kThreads / kSub) {            /* one row of 16 lanes */
-            const uint32_t mine = t0 + threadIdx.x < ntc ? a.tile_total[first + t0 + threadIdx.x] : 0u;
+            const uint32_t mine = t0 + threadIdx.x < ntc ? park.tile_total[first + t0 + threadIdx.x] : 0u;
             s_ex[threadIdx.x] = row_incl_scan(mine) - mine;
         }
     }
     __syncthreads();
-    const uint64_t n = a.tab.elem_off[c + 1] - a.tab.elem_off[c];
-    uint8_t* __restrict__ slot = a.out + a.tab.slot_off[c];
+    const uint64_t n = place.n;
+    uint8_t* __restrict__ slot = a.out + place.slot_off;
     const SlotLayout L = slot_layout(n, DT);
-    const uint32_t* __restrict__ tab_c = a.d_table + c * a.table_stride;
-    const uint32_t dec_lo = a.d_table ? tab_c[0] : a.dec_lo;
-    const uint32_t dec_hi = a.d_table ? tab_c[1] : a.dec_hi;
+    uint32_t dec_lo, dec_hi;
+    table_words(a, c, dec_lo, dec_hi);
 
     const uint32_t sub = threadIdx.x % kSub;
     const uint32_t tw = threadIdx.x / kSub;             /* tile inside the workgroup */
     const uint32_t ti = blockIdx.x * (kThreads / kSub) + tw;
     if (ti < ntc) {
         const uint32_t t = first + ti;
-        const uint8_t* __restrict__ src = a.stash + a.tab.elem_off[c] + (uint64_t)ti * kTile;
+        const uint8_t* __restrict__ src = park.stash + place.elem_off + (uint64_t)ti * kTile;
         /* everything that does not depend on the counts is loaded together with them:
            the tile's 16 index entries and the first 64 bytes of its stash */
         const uint64_t ng = (n + kGroup - 1) / kGroup;
@@ -548,8 +572,8 @@ __global__ __launch_bounds__(kThreads) void k_place(const CompressArgs a)
         if (g < ng) idx_local = idx[g];
         uint32_t P;
         if (SCAN) P = ((s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3])) + s_ex[tw];
-        else P = a.tile_prefix[t];
-        const uint32_t cnt = a.tile_total[t];
+        else P = park.tile_prefix[t];
+        const uint32_t cnt = park.tile_total[t];
         if (P != 0u && g < ng) idx[g] = idx_local + P;
 
         /* byte-exact move to an arbitrarily aligned destination: head bytes, aligned words, tail bytes */
@@ -668,23 +692,37 @@ int static_scratch(void** ptr, size_t* bytes)
     return 0;
 }
 
-int launch_compress(int dt, int mode, const CompressArgs& a, void* stream)
+static CompressIo io_of(const CompressArgs& a) { return CompressIo{a.in, a.out, a.chunk_bytes, a.d_table, a.dec_lo, a.table_stride}; }
+static Parking parking_of(const CompressArgs& a) { return Parking{a.tile_total, a.tile_prefix, a.stash}; }
+
+/* The smallest arguments that hold the split; the two-read kernels, whose calls are none of the small ones, take the table. */
+template <int DT>
+static void launch_compress_dt(int mode, const CompressArgs& a, hipStream_t s)
 {
     const dim3 grid(max_chunk_tiles(a.tab), a.tab.n_chunks), block(kThreads);
-    hipStream_t s = (hipStream_t)stream;
-#define ZIPCCL_LAUNCH(DT, MODE) hipLaunchKernelGGL((k_compress<DT, MODE>), grid, block, 0, s, a)
-    if (dt == ZIPCCL_BF16) {
-        if (mode == kModeCount) ZIPCCL_LAUNCH(ZIPCCL_BF16, kModeCount);
-        else if (mode == kModeEmit) ZIPCCL_LAUNCH(ZIPCCL_BF16, kModeEmit);
-        else if (mode == kModeDirect) ZIPCCL_LAUNCH(ZIPCCL_BF16, kModeDirect);
-        else ZIPCCL_LAUNCH(ZIPCCL_BF16, kModeStash);
+    const CompressIo io = io_of(a);
+    const Parking park = parking_of(a);
+    const bool equal = is_equal_split(a.tab);
+#define ZIPCCL_LAUNCH(MODE, PARK, P, SPLIT, S) hipLaunchKernelGGL((k_compress<DT, MODE, PARK, SPLIT>), grid, block, 0, s, io, P, S)
+    if (mode == kModeDirect) {
+        if (equal) ZIPCCL_LAUNCH(kModeDirect, NoParking, NoParking{}, EqualSplit, equal_split(a.tab));
+        else if (is_few_split(a.tab)) ZIPCCL_LAUNCH(kModeDirect, NoParking, NoParking{}, FewSplit, few_split(a.tab));
+        else ZIPCCL_LAUNCH(kModeDirect, NoParking, NoParking{}, ChunkTab, a.tab);
+    } else if (mode == kModeStash) {
+        if (equal) ZIPCCL_LAUNCH(kModeStash, Parking, park, EqualSplit, equal_split(a.tab));
+        else ZIPCCL_LAUNCH(kModeStash, Parking, park, ChunkTab, a.tab);
+    } else if (mode == kModeCount) {
+        ZIPCCL_LAUNCH(kModeCount, Parking, park, ChunkTab, a.tab);
     } else {
-        if (mode == kModeCount) ZIPCCL_LAUNCH(ZIPCCL_FP32, kModeCount);
-        else if (mode == kModeEmit) ZIPCCL_LAUNCH(ZIPCCL_FP32, kModeEmit);
-        else if (mode == kModeDirect) ZIPCCL_LAUNCH(ZIPCCL_FP32, kModeDirect);
-        else ZIPCCL_LAUNCH(ZIPCCL_FP32, kModeStash);
+        ZIPCCL_LAUNCH(kModeEmit, Parking, park, ChunkTab, a.tab);
     }
 #undef ZIPCCL_LAUNCH
+}
+
+int launch_compress(int dt, int mode, const CompressArgs& a, void* stream)
+{
+    if (dt == ZIPCCL_BF16) launch_compress_dt<ZIPCCL_BF16>(mode, a, (hipStream_t)stream);
+    else launch_compress_dt<ZIPCCL_FP32>(mode, a, (hipStream_t)stream);
     return (int)hipGetLastError();
 }
 
@@ -695,17 +733,21 @@ int launch_tile_scan(const CompressArgs& a, void* stream)
     return (int)hipGetLastError();
 }
 
-int launch_place(int dt, bool scan, const CompressArgs& a, void* stream)
+template <int DT>
+static void launch_place_dt(bool scan, const CompressArgs& a, hipStream_t s)
 {
     const dim3 grid((max_chunk_tiles(a.tab) + 15) / 16, a.tab.n_chunks), block(kThreads);   /* 16 tiles per workgroup */
-    hipStream_t s = (hipStream_t)stream;
-    if (dt == ZIPCCL_BF16) {
-        if (scan) hipLaunchKernelGGL((k_place<ZIPCCL_BF16, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_place<ZIPCCL_BF16, false>), grid, block, 0, s, a);
-    } else {
-        if (scan) hipLaunchKernelGGL((k_place<ZIPCCL_FP32, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_place<ZIPCCL_FP32, false>), grid, block, 0, s, a);
-    }
+    const CompressIo io = io_of(a);
+    const Parking park = parking_of(a);
+    if (!scan) hipLaunchKernelGGL((k_place<DT, false, ChunkTab>), grid, block, 0, s, io, park, a.tab);
+    else if (is_equal_split(a.tab)) hipLaunchKernelGGL((k_place<DT, true, EqualSplit>), grid, block, 0, s, io, park, equal_split(a.tab));
+    else hipLaunchKernelGGL((k_place<DT, true, ChunkTab>), grid, block, 0, s, io, park, a.tab);
+}
+
+int launch_place(int dt, bool scan, const CompressArgs& a, void* stream)
+{
+    if (dt == ZIPCCL_BF16) launch_place_dt<ZIPCCL_BF16>(scan, a, (hipStream_t)stream);
+    else launch_place_dt<ZIPCCL_FP32>(scan, a, (hipStream_t)stream);
     return (int)hipGetLastError();
 }
 

@@ -361,12 +361,20 @@ __device__ __forceinline__ bool check_header(const HeaderWords& hdr, const SlotL
     return ok;
 }
 
+/* Kernel arguments: DecompressArgs without its table, which follows in the form that the launch allows (see EqualSplit). */
+struct DecompressIo {
+    const uint8_t* comp;
+    uint64_t comp_capacity;
+    uint8_t* out;
+    uint32_t* status;
+};
+
 /* GPW (1, 2 or 4) groups per wave: a workgroup decodes a tile of 4 * GPW groups.  The compressed format does not know
  * tiles (groups are located through IDX alone), so this is free to differ from the compress side's tile. */
-template <int DT, uint32_t GPW>
+template <int DT, uint32_t GPW, class SPLIT>
 /* waves per SIMD: 8 (<= 64 VGPRs); launches with four fp32 groups per wave hold no more than 4 */
 __global__ __launch_bounds__(kThreads, DT == ZIPCCL_FP32 && GPW == 4u ? 4 : 8)
-void k_decompress(const DecompressArgs a)
+void k_decompress(const DecompressIo a, const SPLIT split)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
     constexpr uint32_t TILE = kGroup * kWavesPerBlock * GPW;
@@ -375,12 +383,13 @@ void k_decompress(const DecompressArgs a)
 
     /* grid = (tiles of the largest chunk, chunks) */
     const uint32_t c = blockIdx.y;
-    const uint64_t n = a.tab.elem_off[c + 1] - a.tab.elem_off[c];
+    const ChunkPlace place = place_of(split, c, DT);
+    const uint64_t n = place.n;
     const uint32_t tiles = n == 0 ? 1u : (uint32_t)((n + TILE - 1) / TILE);    /* an empty chunk still has its header checked */
     if (blockIdx.x >= tiles) return;
     const uint64_t ts = (uint64_t)blockIdx.x * TILE;
-    const uint8_t* __restrict__ slot = a.comp + a.tab.slot_off[c];
-    uint8_t* __restrict__ cout = a.out + a.tab.elem_off[c] * ES;
+    const uint8_t* __restrict__ slot = a.comp + place.slot_off;
+    uint8_t* __restrict__ cout = a.out + place.elem_off * ES;
     const SlotLayout L = slot_layout(n, DT);
     /* whole tiles need no masks */
     const bool fast = ts + TILE <= n;
@@ -423,7 +432,7 @@ void k_decompress(const DecompressArgs a)
     build_tables(s_tab);
 
     uint32_t e0, n_esc;
-    const bool ok = check_header<DT>(hdr, L, n, a.tab.slot_off[c], a.comp_capacity, e0, n_esc);
+    const bool ok = check_header<DT>(hdr, L, n, place.slot_off, a.comp_capacity, e0, n_esc);
     __syncthreads();
     if (!ok) {
         if (threadIdx.x == 0 && a.status) atomicOr(a.status, (uint32_t)ZIPCCL_ERR_CORRUPT);
@@ -1081,7 +1090,10 @@ static int launch_decompress_gpw(const DecompressArgs& a, hipStream_t s)
         tiles = t > tiles ? t : tiles;
     }
     const dim3 grid((uint32_t)tiles, a.tab.n_chunks), block(kThreads);
-    hipLaunchKernelGGL((k_decompress<DT, GPW>), grid, block, 0, s, a);
+    const DecompressIo io = {a.comp, a.comp_capacity, a.out, a.status};
+    if (is_equal_split(a.tab)) hipLaunchKernelGGL((k_decompress<DT, GPW, EqualSplit>), grid, block, 0, s, io, equal_split(a.tab));
+    else if (GPW < 4u && is_few_split(a.tab)) hipLaunchKernelGGL((k_decompress<DT, GPW, FewSplit>), grid, block, 0, s, io, few_split(a.tab));
+    else hipLaunchKernelGGL((k_decompress<DT, GPW, ChunkTab>), grid, block, 0, s, io, a.tab);
     return (int)hipGetLastError();
 }
 

@@ -31,6 +31,27 @@ static void check_tab(const ChunkTab& t)
     }
 }
 
+/* and the short forms of it that kernels are handed must say the same */
+static int g_equal = 0, g_few = 0;
+static void check_forms(const ChunkTab& t, int dt)
+{
+    const bool equal = is_equal_split(t), few = is_few_split(t);
+    for (uint32_t c = 0; c < t.n_chunks; ++c) {
+        const ChunkPlace want = place_of(t, c, dt);
+        CHECK(want.n == t.elem_off[c + 1] - t.elem_off[c] && want.tiles == tiles_of(want.n));
+        if (equal) {
+            const ChunkPlace p = place_of(equal_split(t), c, dt);
+            CHECK(p.elem_off == want.elem_off && p.n == want.n && p.slot_off == want.slot_off && p.tile == want.tile && p.tiles == want.tiles);
+        }
+        if (few) {
+            const ChunkPlace p = place_of(few_split(t), c, dt);
+            CHECK(p.elem_off == want.elem_off && p.n == want.n && p.slot_off == want.slot_off && p.tiles == want.tiles);
+        }
+    }
+    g_equal += equal;
+    g_few += few;
+}
+
 int launch_estimate(int, const MomentArgs& a, void*) { CHECK(a.n_blocks >= 1 && a.n_blocks <= kMomentBlocks); ++g_launches; return 0; }
 int launch_estimate_robust(int, const HistArgs& a, void*)
 {
@@ -51,6 +72,7 @@ static int g_by_mode[4];
 int launch_compress(int dt, int mode, const CompressArgs& a, void*)
 {
     check_tab(a.tab);
+    check_forms(a.tab, dt);
     if (mode == kModeDirect)
         for (uint32_t c = 0; c < a.tab.n_chunks; ++c)
             CHECK(a.tab.tile_start[c + 1] - a.tab.tile_start[c] <= (dt == ZIPCCL_BF16 ? 8u : 4u));
@@ -61,7 +83,7 @@ int launch_compress(int dt, int mode, const CompressArgs& a, void*)
 }
 int launch_tile_scan(const CompressArgs& a, void*) { check_tab(a.tab); ++g_launches; return 0; }
 int launch_place(int, bool, const CompressArgs& a, void*) { check_tab(a.tab); ++g_launches; return 0; }
-int launch_decompress(int, const DecompressArgs& a, void*) { check_tab(a.tab); ++g_launches; return 0; }
+int launch_decompress(int dt, const DecompressArgs& a, void*) { check_tab(a.tab); check_forms(a.tab, dt); ++g_launches; return 0; }
 int launch_decompress_reduce(int, int, const ReduceArgs& a, void*) { CHECK(a.n_peers >= 1 && a.n_peers <= kMaxPeers); ++g_launches; return 0; }
 int static_scratch(void** ptr, size_t* bytes)
 {
@@ -208,6 +230,20 @@ int main()
         mixed[128] = 9 * T;
         forms(ZIPCCL_BF16, mixed, least, 1, s, e);
     }
+    /* the short forms of the chunk table (check_forms): equal splits, given as such or chunk by chunk, and a few uneven chunks */
+    const int equal0 = g_equal, few0 = g_few;
+    for (zipccl_dtype_t dt : {ZIPCCL_BF16, ZIPCCL_FP32})
+        for (uint32_t k : {1u, 2u, 7u, 8u, 9u, 128u, 130u})
+            for (uint64_t each : {0ull, 1ull, 511ull, 512ull, 8191ull, 8192ull, 8193ull, 65537ull, 0x20000000ull, 0xFFFFFFFFull}) {
+                std::vector<uint64_t> split(k, each);
+                CHECK(zipccl_decompress(out, SIZE_MAX / 2, in, each * k, dt, k, nullptr, nullptr, nullptr) == ZIPCCL_OK);
+                CHECK(zipccl_decompress(out, SIZE_MAX / 2, in, each * k, dt, k, split.data(), nullptr, nullptr) == ZIPCCL_OK);
+                uint64_t total = 0;
+                for (uint32_t c = 0; c < k; ++c) total += split[c] = (each >> (c % 5)) + c % 3;
+                if (each < 0xFFFFFFFFull)
+                    CHECK(zipccl_decompress(out, SIZE_MAX / 2, in, total, dt, k, split.data(), nullptr, nullptr) == ZIPCCL_OK);
+            }
+    CHECK(g_equal - equal0 >= 2 * 2 * 7 * 10 && g_few - few0 >= 2 * 2 * 4 * 9);
     CHECK(zipccl_decompress(out, big, in, n, ZIPCCL_FP32, C, ce.data(), nullptr, nullptr) == ZIPCCL_OK);
     CHECK(zipccl_decompress_reduce(out, big, in, 5000, ZIPCCL_BF16, 1024, ZIPCCL_BF16, nullptr, nullptr) == ZIPCCL_OK);
     CHECK(zipccl_estimate_table(in, 100000, ZIPCCL_BF16, (zipccl_table_t*)out, nullptr, ws, big, nullptr) == ZIPCCL_OK);
