@@ -50,20 +50,27 @@ struct DecTables {
     uint2 expand4[16];   /* building block of expand[] */
 };
 
-/* Contains a workgroup barrier; the caller's next barrier makes the tables visible. */
+/* Contains a workgroup barrier; the caller's next barrier makes the tables visible.  The first 256 threads of the
+ * workgroup's build them. */
+template <uint32_t THREADS = kThreads>
 __device__ __forceinline__ void build_tables(DecTables& t)
 {
-    const uint32_t b = threadIdx.x;                                   /* kThreads == 256 */
+    const uint32_t b = threadIdx.x;
+    const bool mine = THREADS == 256u || b < 256u;
     if (b < 16) t.expand4[b] = expand_entry(b);
-    const uint32_t lo = spread4(b & 15u), hi = spread4(b >> 4);
-    t.spread[0][b] = make_uint2(lo, hi);
-    t.spread[1][b] = make_uint2(lo << 1, hi << 1);
-    t.spread[2][b] = make_uint2(lo << 2, hi << 2);
+    if (mine) {
+        const uint32_t lo = spread4(b & 15u), hi = spread4(b >> 4);
+        t.spread[0][b] = make_uint2(lo, hi);
+        t.spread[1][b] = make_uint2(lo << 1, hi << 1);
+        t.spread[2][b] = make_uint2(lo << 2, hi << 2);
+    }
     __syncthreads();
-    /* values 4..7 continue in the window where values 0..3 stopped */
-    const uint2 a = t.expand4[b & 15u], c = t.expand4[b >> 4];
-    const uint32_t skip = __popc(b & 15u) * 0x01010101u;
-    t.expand[b] = u32x4{a.x, c.x + (skip & c.y), a.y, c.y};
+    if (mine) {
+        /* values 4..7 continue in the window where values 0..3 stopped */
+        const uint2 a = t.expand4[b & 15u], c = t.expand4[b >> 4];
+        const uint32_t skip = __popc(b & 15u) * 0x01010101u;
+        t.expand[b] = u32x4{a.x, c.x + (skip & c.y), a.y, c.y};
+    }
 }
 
 /* Bytes of LDS per group for its zero-point exponents: 512 + up to 15 of misalignment, rounded up to
@@ -1078,6 +1085,207 @@ __global__ __launch_bounds__(kThreads, DT == ZIPCCL_BF16 ? (REST ? 7 : 8) : 6) v
     if (bad && a.status) atomicOr(a.status, (uint32_t)ZIPCCL_ERR_CORRUPT);
 }
 
+/* Arguments of k_reduce_split, with the slot's layout from the host: a shard that is small enough for it has offsets of 32 bits. */
+struct SplitArgs {
+    const uint8_t* comp;
+    uint64_t comp_capacity, slot_cap;
+    uint8_t* out;
+    uint32_t* status;
+    uint32_t n, n_peers;
+    uint32_t lo, p0, plane_bytes, idx, esc;       /* SlotLayout; sm is 128 */
+};
+
+/*
+ * The same sums for small shards, which have too few groups to fill the chip: S waves share a group's peers, Q consecutive
+ * ones each per round of S * Q, decode them into LDS, and every wave then adds an S-th of the group's values over all
+ * peers of the round, in slot order.  A wave per group walks its peers one after the other, and that chain of decodes is
+ * what a small call lasts; here it is Q long.  Nothing of a slot but its zero-point list depends on its header, so the
+ * rest is requested before the headers are checked, and a round's before the sums of the one before it.  G groups per
+ * workgroup share its tables (8 x 1 000 003 bf16 values: 8.2 us with a wave per group, 7.1 with G = 1, 6.9 with 2).  At
+ * that size vector and scalar issue are what bounds it, some 290 instructions of each per wave, half of them the two
+ * decodes; below 2^18 values it is latency: launch, headers, index, list (8 x 2^15: 6.3 -> 3.8 us, 2.1 of them the launch).
+ * Dynamic LDS: one 32-bit word per peer.
+ */
+template <int DT, int ODT, uint32_t S, uint32_t G, uint32_t Q>
+__global__ __launch_bounds__(64u * S * G) void k_reduce_split(const SplitArgs a)
+{
+    constexpr uint32_t OES = ODT == ZIPCCL_BF16 ? 2u : 4u, THREADS = 64u * S * G, R = S * Q;
+    constexpr uint32_t PIECES = DT == ZIPCCL_BF16 ? 1u : 2u;          /* 16-byte pieces of a lane's 8 decoded values */
+    constexpr uint32_t NV = kLaneElems / S;                           /* values per lane in the sums */
+    extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];
+    uint32_t* const s_ok = reinterpret_cast<uint32_t*>(s_dyn);        /* per slot: accepted? */
+    __shared__ DecTables s_tab;
+    __shared__ __attribute__((aligned(16))) uint8_t s_esc[S * G][1024];
+    __shared__ __attribute__((aligned(16))) uint8_t s_val[G][R][PIECES * 1024u];
+    __shared__ uint32_t s_rejected;
+
+    const uint32_t n = a.n, ng = (n + kGroup - 1u) / kGroup;
+    const uint32_t lane = lane_id();
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t sub = wave % S, gw = wave / S;
+    const bool here = blockIdx.x * G + gw < ng;                       /* the last workgroup may have fewer groups */
+    const uint32_t g = min(blockIdx.x * G + gw, ng - 1u), gs = g * kGroup;
+    const bool last_group = g + 1u == ng;
+    const uint32_t left = n - gs, e = lane * kLaneElems;              /* values from the group's first on; the lane's first */
+    /* lanes past the end of the shard read the group's first bytes instead */
+    const uint32_t lane8 = e < left ? e : 0u;
+    const uint32_t vmask = e >= left ? 0u : (1u << min(left - e, 8u)) - 1u;
+
+    struct Stage { DecIn in; uint32_t next, nesc, dec; const uint8_t* slot; } st[Q];
+    auto request = [&](uint32_t first) {
+        const uint32_t p = first + sub * Q, last = a.n_peers - 1u;
+        const uint8_t* slot = a.comp + min(p, last) * a.slot_cap;
+#pragma unroll
+        for (uint32_t q = 0; q < Q; ++q) {
+            Stage& r = st[q];
+            r.slot = slot;
+            r.nesc = load_const_u32(slot + 24);
+            r.dec = load_const_u32(slot + 40);
+            const uint8_t* const idx = slot + (a.idx + 4u * g);
+            r.in.base = load_const_u32(idx);
+            r.next = load_const_u32(idx + (last_group ? 0u : 4u));
+            const u32x2 sm = ld_stream<u32x2>((slot + (128u + gs)) + lane8);
+            r.in.sm0 = sm.x; r.in.sm1 = sm.y;
+            /* half a cache line each, whose other half another wave wants: not streamed */
+            const uint8_t* const pl = slot + (a.p0 + gs / 8u);
+            r.in.b0 = *(pl + lane);
+            r.in.b1 = *((pl + a.plane_bytes) + lane);
+            r.in.b2 = *((pl + 2u * a.plane_bytes) + lane);
+            if (DT == ZIPCCL_FP32) {
+                const u32x4 lo = ld_stream<u32x4>((slot + (a.lo + 2u * gs)) + 2u * lane8);
+                r.in.lo[0] = lo.x; r.in.lo[1] = lo.y; r.in.lo[2] = lo.z; r.in.lo[3] = lo.w;
+            }
+            if (p + q < last) slot += a.slot_cap;                     /* behind the last peer: the last once more */
+        }
+    };
+    request(0);
+
+    if (threadIdx.x == 0) s_rejected = 0;
+    build_tables<THREADS>(s_tab);                                     /* contains a barrier */
+    SlotLayout L;                                                     /* what check_header wants of it */
+    L.esc = a.esc;
+    for (uint32_t p = threadIdx.x; p < a.n_peers; p += THREADS) {
+        const uint64_t slot_off = (uint64_t)p * a.slot_cap;
+        uint32_t e0 = 0, n_esc = 0;
+        const bool ok = check_header<DT>(load_header(a.comp + slot_off), L, n, slot_off, a.comp_capacity, e0, n_esc);
+        s_ok[p] = ok;
+        if (!ok) atomicAdd(&s_rejected, 1u);
+    }
+    __syncthreads();
+    const uint32_t rejected = __builtin_amdgcn_readfirstlane(s_rejected);
+    uint32_t bad = rejected;
+
+    float acc[NV];
+#pragma unroll
+    for (uint32_t j = 0; j < NV; ++j) acc[j] = -0.0f;
+    const uint32_t i0 = (sub * 64u + lane) * NV;                      /* the lane's values of the group in the sums */
+    uint8_t* const lds = s_esc[wave];
+    for (uint32_t first = 0;;) {
+        const uint32_t p0 = first + sub * Q;
+        u32x4 lv[Q];
+        bool go[Q];
+#pragma unroll
+        for (uint32_t q = 0; q < Q; ++q) {
+            Stage& r = st[q];
+            go[q] = p0 + q < a.n_peers;
+            /* of a rejected slot nothing but the static part may be read */
+            if (rejected != 0u && go[q]) go[q] = __builtin_amdgcn_readfirstlane(s_ok[p0 + q]) != 0u;
+            if (last_group) r.next = r.nesc;
+            r.in.idx_bad = slice_bad(r.in.base, r.next, r.nesc, true);
+            r.in.count = r.in.idx_bad | (uint32_t)!go[q] ? 0u : r.next - r.in.base;
+            r.in.vmask = vmask;
+            /* the list as in decode_fetch_list, relative to 16 bytes before it */
+            const uint32_t end = r.in.count != 0u ? r.next : 0u, a16 = (r.in.base & ~15u) + 16u * lane;
+            lv[q] = *reinterpret_cast<const u32x4*>((r.slot + (a.esc - 16u)) + (a16 < end ? a16 + 16u : 0u));
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < Q; ++q) {
+            if (!go[q]) continue;                                     /* wave-uniform */
+            *reinterpret_cast<u32x4*>(lds + 16u * lane) = lv[q];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const DecEsc es = decode_locate(st[q].in, lds);
+            __builtin_amdgcn_wave_barrier();
+            bad |= es.bad;
+            uint32_t hp[4];
+            decode_values(st[q].in, es, (st[q].dec >> 8) & 0xFFu, s_tab, hp);
+            u32x4* const to = reinterpret_cast<u32x4*>(s_val[gw][sub * Q + q] + lane * (16u * PIECES));
+            if (DT == ZIPCCL_BF16) {
+                to[0] = u32x4{hp[0], hp[1], hp[2], hp[3]};
+            } else {
+                uint32_t x[8];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    x[2 * k] = perm(hp[k], st[q].in.lo[k], 0x05040100u);
+                    x[2 * k + 1] = perm(hp[k], st[q].in.lo[k], 0x07060302u);
+                }
+                to[0] = u32x4{x[0], x[1], x[2], x[3]};
+                to[PIECES - 1u] = u32x4{x[4], x[5], x[6], x[7]};
+            }
+        }
+        const uint32_t count = min(R, a.n_peers - first), done = first;
+        first += R;
+        const bool more = first < a.n_peers;
+        if (more) request(first);
+        __syncthreads();
+        auto add = [&](uint32_t j) {
+            typedef float values __attribute__((ext_vector_type(NV)));
+            typedef uint16_t halves __attribute__((ext_vector_type(NV)));
+            const uint8_t* const v = s_val[gw][j] + i0 * (DT == ZIPCCL_BF16 ? 2u : 4u);
+            if (DT == ZIPCCL_BF16) {
+                const halves x = *reinterpret_cast<const halves*>(v);
+#pragma unroll
+                for (uint32_t k = 0; k < NV; ++k) acc[k] += __uint_as_float((uint32_t)x[k] << 16);
+            } else {
+                const values x = *reinterpret_cast<const values*>(v);
+#pragma unroll
+                for (uint32_t k = 0; k < NV; ++k) acc[k] += x[k];
+            }
+        };
+        if (rejected == 0u && count == R) {
+#pragma unroll
+            for (uint32_t j = 0; j < R; ++j) add(j);
+        } else {
+            for (uint32_t j = 0; j < count; ++j)
+                if (s_ok[done + j] != 0u) add(j);
+        }
+        if (!more) break;
+        __syncthreads();
+    }
+    if (!here) return;
+    if (rejected == a.n_peers) {                                      /* the sum of nothing */
+#pragma unroll
+        for (uint32_t j = 0; j < NV; ++j) acc[j] = 0.0f;
+    }
+    uint32_t u[NV];
+#pragma unroll
+    for (uint32_t j = 0; j < NV; ++j) {
+        u[j] = sum_bits(acc[j]);
+        if (ODT == ZIPCCL_BF16) u[j] = f32_bits_to_bf16_bits(u[j]);
+    }
+    uint8_t* __restrict__ o = (a.out + (uint64_t)gs * OES) + i0 * OES;
+    if (left >= kGroup) {                                             /* a whole group, at any element */
+        typedef uint32_t words __attribute__((ext_vector_type(NV), aligned(4)));
+        typedef uint16_t halves __attribute__((ext_vector_type(NV), aligned(2)));
+        words w;
+        halves h;
+#pragma unroll
+        for (uint32_t j = 0; j < NV; ++j) { w[j] = u[j]; h[j] = (uint16_t)u[j]; }
+        if (ODT == ZIPCCL_FP32) *reinterpret_cast<words*>(o) = w;
+        else *reinterpret_cast<halves*>(o) = h;
+    } else {
+#pragma unroll
+        for (uint32_t j = 0; j < NV; ++j) {
+            if (i0 + j < left) {
+                if (ODT == ZIPCCL_FP32) *reinterpret_cast<uint32_t*>(o + j * 4u) = u[j];
+                else *reinterpret_cast<uint16_t*>(o + j * 2u) = (uint16_t)u[j];
+            }
+        }
+    }
+    if (bad && a.status) atomicOr(a.status, (uint32_t)ZIPCCL_ERR_CORRUPT);
+}
+
 } // namespace
 
 template <int DT, uint32_t GPW>
@@ -1150,9 +1358,52 @@ static uint32_t reduce_groups_per_wave(uint64_t n, int dt, int out_dt, uint32_t 
     return tiles < from ? 1u : 2u;
 }
 
+/*
+ * Which shards take k_reduce_split, with how many waves per group x peers per wave and round: those whose groups, one per
+ * wave, leave most of the chip's waves empty, while the split's own work per wave (tables, headers, handing over) still
+ * costs less than the chain it cuts.  us, wave per group / split, bf16, 2^18 values: 2 peers 3.8 / 3.3 (2 x 1), 4 4.7 / 3.3 (4 x 1),
+ * 8 6.6 / 4.0 (4 x 2), 16 10.6 / 5.2 (8 x 2; 5.9 with 4 x 2), 64 34.3 / 13.0.  They meet at about 1.6 * 10^6 values for 2 peers,
+ * 1.2 * 10^6 where the peers fill the rounds (8 peers 9.5 / 8.5 there, 9.3 / 9.4 at 1.35 * 10^6), 0.8 * 10^6 otherwise (5 peers
+ * 6.5 / 5.7 at 0.7, 6.5 / 6.5 at 1.05); fp32, which moves more per value, at 1.4 and 0.8 * 10^6 (8 peers 8.6 / 7.3 at 0.7, 8.9 / 8.8
+ * at 1.05), and 4 x 1 is no worse than 4 x 2 there.
+ */
+enum SplitForm { kNoSplit, kSplit2x1, kSplit4x1, kSplit4x2, kSplit8x2 };
+
+static SplitForm split_form(uint64_t n, int dt, uint32_t n_peers)
+{
+    const bool bf16 = dt == ZIPCCL_BF16;
+    if (n == 0 || n_peers < 2u) return kNoSplit;
+    if (n_peers == 2u) return n <= (bf16 ? 192u : 160u) * (uint64_t)kTile ? kSplit2x1 : kNoSplit;
+    if (n > (bf16 ? (n_peers % 4u == 0u ? 146u : 96u) : 86u) * (uint64_t)kTile) return kNoSplit;
+    if ((n_peers > 8u && n <= 16u * kTile) || (n_peers > 12u && n <= 32u * kTile)) return kSplit8x2;
+    return bf16 && (n_peers - 1u) % 8u >= 4u ? kSplit4x2 : kSplit4x1;      /* a last round of 8 that is at least 5 full */
+}
+
+template <uint32_t S, uint32_t G, uint32_t Q>
+static int launch_reduce_split(int dt, int out_dt, const ReduceArgs& a, hipStream_t s)
+{
+    const dim3 grid((uint32_t)((a.n + kGroup * G - 1) / (kGroup * G))), block(64u * S * G);
+    const size_t lds_bytes = sizeof(uint32_t) * a.n_peers;
+    const SlotLayout L = slot_layout(a.n, dt);
+    const SplitArgs b = {a.comp, a.comp_capacity, a.slot_cap, a.out, a.status, (uint32_t)a.n, a.n_peers,
+                         (uint32_t)L.lo, (uint32_t)L.p0, (uint32_t)L.plane_bytes, (uint32_t)L.idx, (uint32_t)L.esc};
+    if (dt == ZIPCCL_BF16 && out_dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_reduce_split<ZIPCCL_BF16, ZIPCCL_BF16, S, G, Q>), grid, block, lds_bytes, s, b);
+    else if (dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_reduce_split<ZIPCCL_BF16, ZIPCCL_FP32, S, G, Q>), grid, block, lds_bytes, s, b);
+    else if (out_dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_reduce_split<ZIPCCL_FP32, ZIPCCL_BF16, S, G, Q>), grid, block, lds_bytes, s, b);
+    else hipLaunchKernelGGL((k_reduce_split<ZIPCCL_FP32, ZIPCCL_FP32, S, G, Q>), grid, block, lds_bytes, s, b);
+    return (int)hipGetLastError();
+}
+
 int launch_decompress_reduce(int dt, int out_dt, const ReduceArgs& a, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
+    switch (split_form(a.n, dt, a.n_peers)) {
+        case kSplit2x1: return launch_reduce_split<2, 4, 1>(dt, out_dt, a, s);
+        case kSplit4x1: return launch_reduce_split<4, 2, 1>(dt, out_dt, a, s);
+        case kSplit4x2: return launch_reduce_split<4, 2, 2>(dt, out_dt, a, s);
+        case kSplit8x2: return launch_reduce_split<8, 1, 2>(dt, out_dt, a, s);
+        case kNoSplit: break;
+    }
     const dim3 block(kThreads);
     ReduceArgs b = a;
     b.gpw = reduce_groups_per_wave(a.n, dt, out_dt, a.n_peers);

@@ -483,3 +483,63 @@ def test_reduce_pairs_flag_whole_index_words_and_stay_inside_the_list():
     assert run(buf) == 0
     assert np.array_equal(d_out.cpu().numpy().view(np.uint32),
                           oracle.decompress_reduce(buf.cpu().numpy(), n, z.BF16, P, z.FP32))
+
+
+T = 8192
+
+
+@pytest.mark.parametrize("dtype,P,n", [(z.BF16, P, n) for P, n in (
+    (2, 1), (2, 192 * T), (2, 192 * T + 1), (3, 511), (3, 96 * T), (3, 96 * T + 1), (4, 146 * T - 1), (4, 146 * T + 1), (5, 513), (6, 4097),
+    (7, 96 * T - 511), (8, 146 * T), (8, 146 * T + 1), (9, 7), (9, 16 * T), (9, 16 * T + 1), (13, 32 * T), (13, 32 * T + 1), (17, 3000), (33, 1025))]
+    + [(z.FP32, P, n) for P, n in ((2, 1), (2, 160 * T), (2, 160 * T + 1), (3, 513), (4, 86 * T), (8, 86 * T + 1), (9, 16 * T), (12, 20001),
+                                   (13, 32 * T), (14, 32 * T + 1))])
+def test_reduce_of_small_shards_split_over_peers(dtype, P, n):
+    """Several waves share a group's peers: every split on either side of its sizes, rounds that end in the middle, groups
+    cut short, a last workgroup with fewer groups, slices of the list of any length; sums into an output of any element
+    alignment, and with a slot rejected in the first, a middle or the last place.  Bit-equal to the oracle."""
+    rng = np.random.default_rng(60 + P + n)
+    sig = [0.02, 0.5]
+    peers = [_uneven(rng, (n // 3072 + 1) * 3072, p)[:n].copy() if p % 2 else x for p, x in enumerate(_peers(rng, P, n, dtype, sig))] if dtype == z.BF16 else _peers(rng, P, n, dtype, sig)
+    for out_dt in (z.FP32, z.BF16):
+        _check(peers, dtype, sig, out_dt, f"P={P} n={n} out={out_dt}")
+    if n > 40 * T:
+        return
+    buf = _receive_buffer(peers, dtype, sig)
+    cap1 = z.zipccl_max_compressed_size(n, dtype, 1)
+    for victim in sorted({0, P // 2, P - 1}):
+        print(f"[reduce split] rejected slot {victim}", flush=True)
+        bad = buf.clone()
+        bad[victim * cap1 + 2] = 0x00                              # its magic
+        left = np.concatenate([buf.cpu().numpy()[:victim * cap1], buf.cpu().numpy()[(victim + 1) * cap1:]])
+        want = oracle.decompress_reduce(left, n, dtype, P - 1, z.BF16)
+        d_out = torch.full((n + 1,), 0x3C3C, dtype=torch.int16, device=DEV)
+        d_st = torch.zeros(1, dtype=torch.int32, device=DEV)
+        z.zipccl_decompress_reduce(bad, d_out[1:], n, dtype, P, z.BF16, d_st)
+        torch.cuda.synchronize()
+        assert int(d_st.item()) == 4
+        assert np.array_equal(d_out.cpu().numpy().view(np.uint16)[1:], want) and int(d_out[0]) == 0x3C3C
+
+
+@pytest.mark.parametrize("dtype,P,n", [(z.BF16, 1, 6 * 2048 + 100), (z.BF16, 1, 700), (z.BF16, 2, 9000), (z.BF16, 8, 9000), (z.BF16, 13, 2000), (z.FP32, 4, 5000)])
+def test_reduce_of_small_shards_flags_damage_inside_a_slot(dtype, P, n):
+    """Every kernel that small shards go to: index entries outside the list, too far apart or descending, and planes that say
+    something else than the index, in the last slot's last or first group."""
+    rng = np.random.default_rng(61)
+    buf = _receive_buffer(_peers(rng, P, n, dtype, [0.02]), dtype, [0.02])
+    cap1 = z.zipccl_max_compressed_size(n, dtype, 1)
+    pad = lambda x: (x + 127) // 128 * 128
+    p0 = 128 + pad(n) + (pad(2 * n) if dtype == z.FP32 else 0)
+    pb = pad((n + 7) // 8)
+    idx, ng = p0 + 3 * pb, (n + 511) // 512
+    zeros = [0, 0, 0, 0]
+    for label, edits in {"beyond": [(idx + 4 * (ng - 1), [0xFF, 0xFF, 0xFF, 0x7F])], "too far": [(idx + 4, [600 & 0xFF, 600 >> 8, 0, 0])],
+                         "wraps": [(idx, [0xF0, 0xFF, 0xFF, 0xFF])], "planes": [(p0 + 3, zeros), (p0 + pb + 3, zeros), (p0 + 2 * pb + 3, zeros)]}.items():
+        print(f"[reduce split] P={P} n={n} damage: {label}", flush=True)
+        bad = buf.clone()
+        for at, val in edits:
+            bad[(P - 1) * cap1 + at:(P - 1) * cap1 + at + 4] = torch.tensor(val, dtype=torch.uint8, device=DEV)
+        d_out = torch.zeros(n, dtype=torch.int32, device=DEV)
+        d_st = torch.zeros(1, dtype=torch.int32, device=DEV)
+        z.zipccl_decompress_reduce(bad, d_out, n, dtype, P, z.FP32, d_st)
+        torch.cuda.synchronize()
+        assert int(d_st.item()) == 4, label
