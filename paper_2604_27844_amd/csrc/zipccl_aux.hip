@@ -123,20 +123,16 @@ __global__ __launch_bounds__(kThreads) void k_estimate_finish(const MomentArgs a
 /*
  * Robust sigma (for Eq.5 / Eq.2 when the tensor is not the zero-mean Gaussian of section 4.1: outlier
  * channels, LayerNorm gains among matrix weights): the median of |w| over Phi^-1(3/4).  The median is taken
- * over the 15-bit magnitudes of the values' high 16-bit words, so it is a count: a histogram of all 32768
- * magnitudes, in which the bin of rank (K - 1) / 2 among the K magnitudes that are neither zero nor Inf/NaN is
- * looked for.  Integer work until the final division: the result does not depend on any order.  Three forms,
- * each for one or more chunks at once (one histogram and one table per chunk; the whole tensor is one chunk):
- *   large    k_clear_hist zeroes one histogram per chunk in the workspace, k_magnitude_hist (or its sampled form)
- *            adds to it what about one workgroup per compute unit has counted in its LDS, k_robust_finish looks
- *            for the rank.  2^24 bf16 values, one chunk: 2.0 + 11.6 + 3.7 us, launches included (the
- *            histogram kernel without its flush: 4 us less).  With 64-bit counts zeroed, flushed and read twice over
- *            by the finish, whose one thread then took four erf in a row, the same three kernels were 3.0 + 13.8 +
- *            11.2 us.
- *   small    (at most kFusedGroups groups to count in every chunk) k_robust_partial: a few workgroups per chunk, each
- *            of which stores its own counts; k_robust_join adds them up and looks for the rank.  Nothing to clear, no
- *            atomics on memory.
- *   smaller  (or as many chunks as compute units) k_robust_chunk_fused: one workgroup per chunk, one kernel.
+ * over the 15-bit magnitudes of the values' high 16-bit words, so it is a count: the magnitude of rank (K - 1) / 2
+ * among the K magnitudes that are neither zero nor Inf/NaN.  Integer work until the final division: the result does
+ * not depend on any order.  Three forms, the first two for one or more chunks at once (one table per chunk; the whole
+ * tensor is one chunk):
+ *   windowed k_window_count: a few workgroups per chunk; each looks for the median of the same small sample of the
+ *            chunk, counts only the kWindow magnitudes around that one by one, and how many there are below and in all,
+ *            and stores its own counts.  k_window_finish adds them up; if the rank lies in the window, as it does unless
+ *            the sample misled, that gives the median, and if not, its workgroups count all magnitudes after all.
+ *   small    k_robust_chunk_fused: one workgroup per chunk with a histogram of all 32768 magnitudes in its LDS.
+ *   huge     (2^32 values or more) that histogram, 64 bits wide, in memory: k_clear_hist, k_magnitude_hist, k_robust_finish.
  */
 constexpr uint32_t kMagBins = 32768;
 constexpr uint32_t kHistThreads = 1024;
@@ -163,16 +159,14 @@ __device__ __forceinline__ bool bin_counts(uint32_t b) { return b != 0u && b < k
 
 constexpr uint32_t kClearThreads = 1024;
 
-/* One workgroup per histogram, 8 or 16 16-byte stores per thread (spread over 16 or 32 times as many workgroups the
- * kernel took 5 us longer for 64 histograms: the launch, not the memory, is its limit). */
-template <typename CNT>
+/* One workgroup, 16 16-byte stores per thread. */
 __global__ __launch_bounds__(kClearThreads) void k_clear_hist(unsigned long long* hist)
 {
-    /* grid = chunks (the workspace is 8-byte aligned: the 16-byte stores are issued at that alignment) */
-    u32x4_a4* const p = reinterpret_cast<u32x4_a4*>(hist + (uint64_t)blockIdx.x * (kHistBytes / 8)) + threadIdx.x;
+    /* the workspace is 8-byte aligned: the 16-byte stores are issued at that alignment */
+    u32x4_a4* const p = reinterpret_cast<u32x4_a4*>(hist) + threadIdx.x;
     const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (uint32_t k = 0; k < kMagBins * sizeof(CNT) / (16u * kClearThreads); ++k) p[k * kClearThreads] = zero;
+    for (uint32_t k = 0; k < kHistBytes / (16u * kClearThreads); ++k) p[k * kClearThreads] = zero;
 }
 
 /* 16 bytes per thread and step: zeroes the workgroup's histogram (the caller's barrier follows) */
@@ -185,11 +179,10 @@ __device__ __forceinline__ void zero_lds_hist(uint32_t* s_hist)
 }
 
 /* Add what the workgroup counted to the chunk's histogram.  The workgroups start at different rows: their atomics
- * on one line come from eight XCDs and take their turns (the flush is 4 us of a call on 2^24 values). */
+ * on one line come from eight XCDs and take their turns (256 workgroups: 4 us). */
 template <typename CNT>
-__device__ __forceinline__ void flush_lds_hist(const uint32_t* s_hist, unsigned long long* hist_c, uint32_t wg)
+__device__ __forceinline__ void flush_lds_hist(const uint32_t* s_hist, CNT* hist, uint32_t wg)
 {
-    CNT* const hist = reinterpret_cast<CNT*>(hist_c);
     const uint32_t turn = wg * 128u;
     for (uint32_t i = threadIdx.x; i < kMagBins; i += kHistThreads) {
         const uint32_t b = (i + turn) & (kMagBins - 1u);
@@ -198,22 +191,18 @@ __device__ __forceinline__ void flush_lds_hist(const uint32_t* s_hist, unsigned 
     }
 }
 
-template <int DT, typename CNT>
-__global__ __launch_bounds__(kHistThreads) void k_magnitude_hist(const HistArgs a)
+/* Workgroup `part` of `parts` counts its part of a tensor's magnitudes; zeroes s_hist first.  A tensor starts at some
+ * element: the values in front of its first 16-byte boundary and behind its last one are taken one by one, the rest in 16-byte pieces. */
+template <int DT>
+__device__ __forceinline__ void tensor_into_lds(uint32_t* s_hist, const uint8_t* __restrict__ in, uint64_t n, uint32_t part, uint32_t parts)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
     constexpr uint32_t PER16 = 16u / ES;
     constexpr uint32_t NF = 4;                               /* loads in flight per thread */
-    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kMagBins];     /* 128 KiB */
-    /* grid = (workgroups per chunk, chunks); a chunk starts at some element of the tensor: the values in front of
-       its first 16-byte boundary and behind its last one are taken one by one, the rest in 16-byte pieces */
-    const uint32_t c = blockIdx.y;
-    const uint8_t* __restrict__ in = a.in + a.tab.elem_off[c] * ES;
-    const uint64_t n = a.tab.elem_off[c + 1] - a.tab.elem_off[c];
     const uint64_t head = min(n, (uint64_t)(((16u - (uint32_t)(reinterpret_cast<uintptr_t>(in) & 15u)) & 15u) / ES));
     const uint64_t n16 = (n - head) / PER16;
     const uint8_t* __restrict__ mid = in + head * ES;
-    const uint64_t stride = (uint64_t)gridDim.x * kHistThreads;
+    const uint64_t stride = (uint64_t)parts * kHistThreads;
     auto count = [&](const u32x4& v) {
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -227,7 +216,7 @@ __global__ __launch_bounds__(kHistThreads) void k_magnitude_hist(const HistArgs 
                                               : *reinterpret_cast<const uint32_t*>(in + e * 4) >> 16;
         atomicAdd(&s_hist[hi & 0x7FFFu], 1u);
     };
-    uint64_t i = (uint64_t)blockIdx.x * kHistThreads + threadIdx.x;
+    uint64_t i = (uint64_t)part * kHistThreads + threadIdx.x;
     u32x4 v[NF];
     auto load = [&](uint64_t at) {
 #pragma unroll
@@ -246,13 +235,30 @@ __global__ __launch_bounds__(kHistThreads) void k_magnitude_hist(const HistArgs 
         if (more) load(i);
     }
     for (; i < n16; i += stride) count(ld_stream<u32x4>(mid + i * 16));
-    if (blockIdx.x == 0) {                                    /* head and tail: fewer than 16 bytes each */
+    if (part == 0) {                                          /* head and tail: fewer than 16 bytes each */
         if (threadIdx.x < head) count_one(threadIdx.x);
         const uint64_t done = head + n16 * PER16;
         if (done + threadIdx.x < n) count_one(done + threadIdx.x);
     }
+}
+
+/* Arguments of the kernels below but for the split into chunks, which follows in the form that the launch allows. */
+struct RobustIo {
+    const uint8_t* in;
+    unsigned long long* hist;         /* kHistBytes per chunk */
+    uint8_t* table;                   /* 8 bytes per chunk */
+    double* sigma;                    /* one per chunk; may be null */
+    uint32_t stride;                  /* 1: every value counts; a power of two S: one group of 512 values per S groups */
+    uint32_t shared;                  /* windowed form: more than kFusedGroups groups to count in some chunk */
+};
+
+template <int DT>
+__global__ __launch_bounds__(kHistThreads) void k_magnitude_hist(const RobustIo a, uint64_t n)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kMagBins];     /* 128 KiB */
+    tensor_into_lds<DT>(s_hist, a.in, n, blockIdx.x, gridDim.x);
     __syncthreads();
-    flush_lds_hist<CNT>(s_hist, a.hist + (uint64_t)c * (kHistBytes / 8), blockIdx.x);
+    flush_lds_hist(s_hist, a.hist, blockIdx.x);
 }
 
 /*
@@ -346,21 +352,6 @@ __device__ __forceinline__ uint32_t sample_blocks(uint64_t n, uint32_t S)
     return (uint32_t)(((n + kGroup - 1) / kGroup + S - 1) / S);
 }
 
-template <int DT>
-__global__ __launch_bounds__(kHistThreads) void k_magnitude_hist_sampled(const HistArgs a)
-{
-    constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
-    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kMagBins];     /* 128 KiB */
-    /* grid = (workgroups per chunk, chunks) */
-    const uint32_t c = blockIdx.y;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t n = a.tab.elem_off[c + 1] - a.tab.elem_off[c];
-    sample_into_lds<DT, 4>(s_hist, a.in + a.tab.elem_off[c] * ES, n, a.sample_stride, blockIdx.x * kHistWaves + wave,
-                           sample_blocks(n, a.sample_stride), gridDim.x * kHistWaves);
-    __syncthreads();
-    flush_lds_hist<uint32_t>(s_hist, a.hist + (uint64_t)c * (kHistBytes / 8), blockIdx.x);
-}
-
 /*
  * Rank and table of one chunk by one workgroup of 1024 threads.  `bins` yields 16 bytes of counts at a time: in step k
  * thread t holds the PER bins from (k * 1024 + t) * PER on, so a wave's step is one row of 64 * PER consecutive
@@ -439,36 +430,33 @@ __device__ __forceinline__ void rank_and_table(LOAD bins, CNT* s_row, uint8_t* t
     table_from_sigma(med / 0.6744897501960817, table, sigma);     /* Phi^-1(3/4) */
 }
 
-/* One workgroup per chunk, after the histogram kernels: 8 (32-bit counts) or 16 loads per thread, all in flight together. */
-template <typename CNT>
-__global__ __launch_bounds__(kHistThreads) void k_robust_finish(const HistArgs a)
+/* One workgroup, after the histogram of a huge tensor: 16 loads per thread, all in flight together. */
+__global__ __launch_bounds__(kHistThreads) void k_robust_finish(const RobustIo a)
 {
-    constexpr uint32_t PER = 16u / sizeof(CNT);
-    __shared__ CNT s_row[kMagBins / (64u * PER)];
-    /* grid = chunks */
-    const u32x4_a4* const hist = reinterpret_cast<const u32x4_a4*>(a.hist + (uint64_t)blockIdx.x * (kHistBytes / 8)) + threadIdx.x;
+    typedef unsigned long long CNT;
+    __shared__ CNT s_row[kMagBins / 128u];
+    const u32x4_a4* const hist = reinterpret_cast<const u32x4_a4*>(a.hist) + threadIdx.x;
     rank_and_table<CNT>([&](uint32_t k, CNT* out) {
         const u32x4 q = hist[k * kHistThreads];
         __builtin_memcpy(out, &q, 16);
-    }, s_row, a.table + 8u * blockIdx.x, a.sigma ? a.sigma + blockIdx.x : nullptr);
+    }, s_row, a.table, a.sigma);
 }
 
 /*
  * A chunk whose sample is small enough for one workgroup: histogram, rank and table in one kernel, nothing outside LDS.
  * grid = chunks.
  */
-template <int DT>
-__global__ __launch_bounds__(kHistThreads) void k_robust_chunk_fused(const HistArgs a)
+template <int DT, class SPLIT>
+__global__ __launch_bounds__(kHistThreads) void k_robust_chunk_fused(const RobustIo a, const SPLIT split)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
     __shared__ __attribute__((aligned(16))) uint32_t s_hist[kMagBins];     /* 128 KiB */
     __shared__ uint32_t s_row[kMagBins / 256u];
     const uint32_t c = blockIdx.x;
+    const ChunkPlace place = place_of(split, c, DT);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t n = a.tab.elem_off[c + 1] - a.tab.elem_off[c];
     /* one workgroup per chunk has the chunk's whole latency to hide: eight groups in flight per wave */
-    sample_into_lds<DT, 8>(s_hist, a.in + a.tab.elem_off[c] * ES, n, a.sample_stride, wave,
-                           sample_blocks(n, a.sample_stride), kHistWaves);
+    sample_into_lds<DT, 8>(s_hist, a.in + place.elem_off * ES, place.n, a.stride, wave, sample_blocks(place.n, a.stride), kHistWaves);
     __syncthreads();
     rank_and_table<uint32_t>([&](uint32_t k, uint32_t* out) {
         const u32x4 q = reinterpret_cast<const u32x4*>(s_hist)[k * kHistThreads + threadIdx.x];
@@ -477,96 +465,322 @@ __global__ __launch_bounds__(kHistThreads) void k_robust_chunk_fused(const HistA
 }
 
 /*
- * Chunks that are too large for one workgroup to count quickly (a group of 512 values takes its compute unit's LDS
- * atomics 36 ns) and too few to fill the chip: G = gridDim.x <= 4 workgroups per chunk, each with at most 127 of
- * its blocks, i.e. fewer than 2^16 values, so that 16 bits hold every count.  A workgroup stores the rows of 256 bins in
- * which it counted anything, and the sum of every row, in its own 64 KiB of the chunk's workspace: the counts of the
- * bins that never count (Inf / NaN, 128 of them) leave room for the 128 row sums.
+ * What a workgroup of k_window_count leaves in its chunk's workspace, and behind the last of these, in the workspace's
+ * second half, a histogram of 32-bit counts, zeroed, for the case that the window does not hold the rank.
  */
-constexpr uint32_t kPartials = 4;
-constexpr uint32_t kPartialBytes = kMagBins * 2;
-constexpr uint32_t kPartialGroups = 127;
-static_assert(kPartials * kPartialBytes <= kHistBytes && kPartials * kPartialGroups == kFusedGroups &&
-              kPartialGroups * kGroup < 65536u && kMagBins - kFirstNonFinite == kMagBins / 256u, "layout of the partial counts");
+constexpr uint32_t kWindow = 112;            /* magnitudes: 7/8 of an octave */
+struct Partial {
+    uint32_t bins[kWindow];                  /* counts of the magnitudes lo, lo + 1, ... */
+    uint32_t below, valid, inside, lo;       /* neither zero nor Inf/NaN: those below lo, all, those in the window */
+    uint32_t arrived;                        /* first one: workgroups that have added to the histogram */
+    uint32_t unused[128 - kWindow - 5];
+};
+constexpr uint32_t kPartialsBytes = kHistBytes / 2;
+static_assert(sizeof(Partial) * kHistBlocks <= kPartialsBytes && kMagBins * 4u <= kHistBytes - kPartialsBytes, "layout of a chunk's workspace");
 
-template <int DT>
-__global__ __launch_bounds__(kHistThreads) void k_robust_partial(const HistArgs a)
+/* The median of a sample of up to 1024 values of the chunk, up to 8 magnitudes low: 64 strata of equal length, 16
+ * consecutive values at a hashed position of each (256 positions of four cost 64 chunks 1 to 2 us more: pages).  By 16 waves that
+ * hold all of it and look at one threshold each, four bits of the result per step.  request() issues the loads, the
+ * rest happens in find(). */
+struct SampleMedian {
+    uint32_t w[2];                           /* four magnitudes of threads 0 .. 255; those that do not count are 0x7FFF */
+
+    template <int DT>
+    __device__ __forceinline__ void request(const uint8_t* __restrict__ in, uint64_t n)
+    {
+        constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
+        const uint32_t t = threadIdx.x;
+        w[0] = w[1] = 0u;
+        if (t >= 256u) return;
+        if (n >= 1024u) {
+            const uint32_t stratum = t / 4u, len = (uint32_t)((n - 16u) / 64u);
+            const uint8_t* const p = in + ((uint64_t)stratum * len + (((uint64_t)(stratum * 2654435761u) * len) >> 32) + 4u * (t & 3u)) * ES;
+            if (DT == ZIPCCL_BF16) {
+                const u32x2 v = *reinterpret_cast<const u32x2_a2*>(p);
+                w[0] = v.x; w[1] = v.y;
+            } else {
+                const u32x4 v = *reinterpret_cast<const u32x4_a4*>(p);
+                w[0] = perm(v.y, v.x, 0x07060302u); w[1] = perm(v.w, v.z, 0x07060302u);
+            }
+        } else {
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                const uint32_t e = t * 4u + j;
+                if (e < n) {
+                    const uint32_t hi = DT == ZIPCCL_BF16 ? *reinterpret_cast<const uint16_t*>(in + e * 2u) : *reinterpret_cast<const uint32_t*>(in + e * 4u) >> 16;
+                    w[j >> 1] |= hi << (16u * (j & 1u));
+                }
+            }
+        }
+    }
+
+    /* s_sample: 512 words, s_cnt: 2 x 16 words.  Called by all threads of the workgroup. */
+    __device__ __forceinline__ uint32_t find(uint32_t* s_sample, uint32_t* s_cnt, uint32_t wave, uint32_t lane)
+    {
+        if (threadIdx.x < 256u) {
+            u32x2 m;
+#pragma unroll
+            for (uint32_t k = 0; k < 2; ++k) {
+                const uint32_t x = w[k] & 0x7FFF7FFFu;
+                const uint32_t lo = bin_counts(x & 0xFFFFu) ? x & 0xFFFFu : 0x7FFFu, hi = bin_counts(x >> 16) ? x >> 16 : 0x7FFFu;
+                m[k] = lo | (hi << 16);
+            }
+            *reinterpret_cast<u32x2*>(s_sample + 2u * threadIdx.x) = m;
+        }
+        __syncthreads();
+        uint32_t x[8];
+#pragma unroll
+        for (uint32_t q = 0; q < 2; ++q) {
+            const u32x4 v = *reinterpret_cast<const u32x4*>(s_sample + 4u * (lane + 64u * q));
+            x[4 * q] = v.x; x[4 * q + 1] = v.y; x[4 * q + 2] = v.z; x[4 * q + 3] = v.w;
+        }
+        uint32_t base = 0, rank = 0;
+#pragma unroll
+        for (uint32_t step = 0; step < 3; ++step) {
+            const uint32_t shift = 11u - 4u * step;
+            /* the last wave counts all that count, once */
+            const uint32_t limit = (wave == 15u ? 0x7F80u : base + ((wave + 1u) << shift)) * 0x00010001u;
+            uint32_t cnt = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) cnt += __popc(pk_sub_u16(x[k], limit) & 0x80008000u);
+            cnt = wave_incl_scan(cnt);
+            uint32_t* const s = s_cnt + 16u * (step & 1u);
+            if (lane == 63u) s[wave] = cnt;
+            __syncthreads();
+            const uint32_t below = s[lane & 15u];
+            if (step == 0) rank = (__builtin_amdgcn_readlane(below, 15) - 1u) / 2u;
+            base += (uint32_t)__popcll(__ballot(below <= rank) & 0x7FFFu) << shift;
+        }
+        return base;
+    }
+};
+
+/*
+ * Reading bounds it in large tensors (2^29 bf16 values: 172 us, 6.2 TB/s); 2^24 values take 10.7 us, of which the launch is 2, the
+ * sample 1.5, reading from HBM alone would be 5 and the additions in LDS alone 4 (with 4 us less to flush and nothing to zero,
+ * estimate and table 18.1 -> 15.5 us; 2^20: 14.2 -> 9.3).  Every value still costs an addition in LDS, but to 112 counters
+ * instead of 32768: nothing large is zeroed, and a workgroup's counts are 512 bytes that it stores, where a histogram in
+ * memory took a kernel that zeroes it and 4 us of atomic additions from 256 workgroups to the same lines.  Values
+ * outside the window are added to a counter of the lane's own, so that they neither branch nor collide.
+ * grid = (workgroups per chunk, chunks).  STREAM: the tensor is too large to stay in the caches for the compress
+ * that usually follows.
+ */
+template <int DT, bool STREAM, class SPLIT>
+__global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a, const SPLIT split)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
-    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kMagBins];     /* 128 KiB */
-    /* grid = (workgroups per chunk, chunks) */
+    constexpr uint32_t NV = DT == ZIPCCL_BF16 ? 1u : 2u;     /* 16-byte pieces per lane and group */
+    constexpr uint32_t NF = 2;                               /* groups in flight per wave: twice as many leave the memory idle between their batches */
+    __shared__ __attribute__((aligned(16))) uint32_t s_sample[512];
+    __shared__ uint32_t s_cnt[32];
+    /* below, window, above (or not counted): outside the window a counter per lane and side, both on the lane's own bank */
+    __shared__ uint32_t s_bins[64u + kWindow + 64u];
+    __shared__ uint32_t s_valid[kHistWaves];
     const uint32_t c = blockIdx.y;
-    const uint32_t lane = threadIdx.x & 63u;
+    const ChunkPlace place = place_of(split, c, DT);
+    const uint64_t n = place.n;
+    const uint8_t* __restrict__ in = a.in + place.elem_off * ES;
+    const uint32_t lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t n = a.tab.elem_off[c + 1] - a.tab.elem_off[c];
-    const uint32_t blocks = sample_blocks(n, a.sample_stride);               /* at most kFusedGroups */
-    sample_into_lds<DT, 8>(s_hist, a.in + a.tab.elem_off[c] * ES, n, a.sample_stride,
-                           blockIdx.x * blocks / gridDim.x + wave, (blockIdx.x + 1u) * blocks / gridDim.x, kHistWaves);
-    __syncthreads();
-    uint16_t* const mine = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(a.hist + (uint64_t)c * (kHistBytes / 8)) +
-                                                       blockIdx.x * kPartialBytes);
+    const uint32_t S = a.stride, blocks = sample_blocks(n, S), n_waves = gridDim.x * kHistWaves;
+    uint32_t k0 = blockIdx.x * kHistWaves + wave;
+
+    SampleMedian median;
+    median.request<DT>(in, n);
+    /* the last block's group may be cut short by the chunk's end, or missing; the blocks before it hold whole ones */
+    const uint32_t whole = blocks == 0u ? 0u : blocks - 1u;
+    auto group_of = [&](uint32_t k) { return k * S + (((k * 2654435761u) >> 16) & (S - 1u)); };
+    u32x4 v[NF][NV];
+    auto load = [&](uint32_t u, uint32_t k) {
 #pragma unroll
-    for (uint32_t k = 0; k < kMagBins / (256u * kHistWaves); ++k) {
-        const uint32_t row = k * kHistWaves + wave, b = row * 256u + lane * 4u;
-        u32x4 q = *reinterpret_cast<const u32x4*>(s_hist + b);
-        if (b == 0u) q.x = 0u;
-        if (b >= kFirstNonFinite) q = u32x4{0u, 0u, 0u, 0u};
-        const uint32_t sum = __builtin_amdgcn_readlane(wave_incl_scan((q.x + q.y) + (q.z + q.w)), 63);
-        if (sum != 0u && b < kFirstNonFinite)
-            *reinterpret_cast<u32x2*>(mine + b) = u32x2{q.x | (q.y << 16), q.z | (q.w << 16)};
-        if (lane == 0) mine[kFirstNonFinite + row] = (uint16_t)sum;
+        for (uint32_t q = 0; q < NV; ++q) {
+            const uint8_t* const p = (in + (uint64_t)group_of(k) * (kGroup * ES)) + q * 1024u + lane * 16u;
+            v[u][q] = STREAM ? ld_stream_a2(p) : (u32x4)*reinterpret_cast<const u32x4_a2*>(p);
+        }
+    };
+    bool more = k0 + (NF - 1u) * n_waves < whole;
+    if (more) {
+#pragma unroll
+        for (uint32_t u = 0; u < NF; ++u) load(u, k0 + u * n_waves);
+    }
+    if (threadIdx.x < kWindow + 128u) s_bins[threadIdx.x] = 0u;
+    const uint32_t at = median.find(s_sample, s_cnt, wave, lane) + 4u;
+    const uint32_t lo = min(max(at, kWindow / 2u + 65u) - kWindow / 2u, kFirstNonFinite - kWindow);
+
+    /* on magnitudes less one, so that zeros go to the top, behind Inf/NaN; d is signed, 64 for lo (which is 65 at least, so
+       that the top stays positive) */
+    const uint32_t from2 = (lo - 65u) * 0x00010001u, first2 = lane * 0x00010001u, last2 = (64u + kWindow + ((lane - kWindow) & 63u)) * 0x00010001u;
+    uint32_t invalid = 0, calls = 0;
+    auto count = [&](const uint32_t w[4]) {
+        ++calls;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t m = pk_sub_u16(w[k], 0x00010001u) & 0x7FFF7FFFu;
+            invalid += __popc((m + 0x00810081u) & 0x80008000u);               /* from 0x7F7F on */
+            const uint32_t b = pk_max_i16(pk_min_i16(pk_sub_u16(m, from2), last2), first2);
+            atomicAdd(&s_bins[b & 0xFFFFu], 1u);
+            atomicAdd(&s_bins[b >> 16], 1u);
+        }
+    };
+    auto count_loaded = [&](uint32_t u) {
+        const u32x4 x = v[u][0], y = v[u][NV - 1u];
+        if (DT == ZIPCCL_BF16) {
+            const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+            count(w);
+        } else {
+            const uint32_t w[4] = {perm(x.y, x.x, 0x07060302u), perm(x.w, x.z, 0x07060302u), perm(y.y, y.x, 0x07060302u), perm(y.w, y.z, 0x07060302u)};
+            count(w);
+        }
+    };
+    while (more) {
+#pragma unroll
+        for (uint32_t u = 0; u < NF; ++u) count_loaded(u);
+        k0 += NF * n_waves;
+        more = k0 + (NF - 1u) * n_waves < whole;
+        if (more) {
+#pragma unroll
+            for (uint32_t u = 0; u < NF; ++u) load(u, k0 + u * n_waves);
+        }
+    }
+    /* what is left, fewer than NF groups; one that is not there loads the chunk's first and is not counted */
+    if (k0 < whole) {
+#pragma unroll
+        for (uint32_t u = 0; u + 1u < NF; ++u) load(u, k0 + u * n_waves < whole ? k0 + u * n_waves : 0u);
+#pragma unroll
+        for (uint32_t u = 0; u + 1u < NF; ++u)
+            if (k0 + u * n_waves < whole) count_loaded(u);
+    }
+    if (blocks != 0u && whole % n_waves == blockIdx.x * kHistWaves + wave) {
+        const uint64_t first = (uint64_t)group_of(whole) * kGroup;
+        uint32_t w[4] = {0u, 0u, 0u, 0u};                    /* values that do not exist count as zeros */
+#pragma unroll
+        for (uint32_t j = 0; j < kLaneElems; ++j) {
+            const uint64_t e = first + j * 64u + lane;
+            if (e < n) w[j >> 1] |= (DT == ZIPCCL_BF16 ? *reinterpret_cast<const uint16_t*>(in + e * 2u)
+                                                       : *reinterpret_cast<const uint32_t*>(in + e * 4u) >> 16) << (16u * (j & 1u));
+        }
+        count(w);
+    }
+    Partial* const part = reinterpret_cast<Partial*>(a.hist + (uint64_t)c * (kHistBytes / 8u));
+    if (a.shared) {
+        /* what the histogram of all magnitudes would be added to, if it comes to that; not earlier, where the wave's later
+           loads would wait for these stores (64 chunks of 2^21 fp32 values 106 us at the start, 96 here) */
+        u32x4_a4* const hist = reinterpret_cast<u32x4_a4*>(reinterpret_cast<uint8_t*>(part) + kPartialsBytes);
+        for (uint32_t i = blockIdx.x * kHistThreads + threadIdx.x; i < kMagBins / 4u; i += gridDim.x * kHistThreads) hist[i] = u32x4{0u, 0u, 0u, 0u};
+    }
+    const uint32_t counted = wave_incl_scan(8u * calls - invalid);
+    if (lane == 63u) s_valid[wave] = counted;
+    __syncthreads();
+    if (wave >= 2u) return;
+    uint32_t* const mine = part[blockIdx.x].bins;
+    if (threadIdx.x < kWindow) mine[threadIdx.x] = s_bins[64u + threadIdx.x];
+    if (wave == 0u) return;
+    const uint32_t inside = wave_incl_scan(s_bins[64u + lane] + (lane + 64u < kWindow ? s_bins[128u + lane] : 0u));
+    const uint32_t below = wave_incl_scan(s_bins[lane]);
+    const uint32_t valid = __builtin_amdgcn_readlane(row_incl_scan(s_valid[lane & 15u]), 15);
+    if (lane == 63u) {
+        *reinterpret_cast<u32x4_a4*>(&part[blockIdx.x].below) = u32x4{below, valid, inside, lo};
+        part[blockIdx.x].arrived = 0u;
     }
 }
 
-/* One wave per chunk: the row of the rank from the row sums, then the bin from that row of every partial. */
-__global__ __launch_bounds__(64) void k_robust_join(const HistArgs a)
+/*
+ * One workgroup per chunk adds up the `parts` Partials of it and looks for the rank among them: 1024 threads, a sixteen-byte
+ * piece of a 32nd of the Partials each, all loads in flight together.  Where the sample misled, so that the rank
+ * is not in the window, every magnitude is counted: by that workgroup alone in its LDS (`shared` not set: a chunk of at most
+ * kFusedGroups groups to count), or by all of the grid's, which add to the histogram that k_window_count zeroed; the last
+ * to arrive looks for the rank there.  No workgroup waits for another.  grid = (workgroups per chunk for that, chunks).
+ */
+template <int DT, class SPLIT>
+__global__ __launch_bounds__(kHistThreads) void k_window_finish(const RobustIo a, uint32_t parts, const SPLIT split)
 {
-    /* grid = chunks; a.n_blocks partials each */
-    const uint32_t c = blockIdx.x, lane = lane_id();
-    const uint8_t* const part = reinterpret_cast<const uint8_t*>(a.hist + (uint64_t)c * (kHistBytes / 8));
+    constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u, ROWS = kHistThreads / 32u, Q = kWindow / 4u;
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kMagBins];     /* 128 KiB */
+    __shared__ uint32_t s_head[3][4];
+    __shared__ uint32_t s_row[kMagBins / 256u];
+    const uint32_t c = blockIdx.y, t = threadIdx.x, lane = lane_id();
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    Partial* const part = reinterpret_cast<Partial*>(a.hist + (uint64_t)c * (kHistBytes / 8u));
     uint8_t* const table = a.table + 8u * c;
     double* const sigma = a.sigma ? a.sigma + c : nullptr;
-    uint32_t sums[kPartials];                                  /* of rows 2 lane (low half) and 2 lane + 1 */
+
+    const u32x4 head = *reinterpret_cast<const u32x4_a4*>(&part[min(t, parts - 1u)].below);      /* below, valid, inside, lo */
+    const uint32_t row = t / 32u, q = min(t & 31u, Q - 1u);
+    if (blockIdx.x == 0u) {
+        u32x4 v[kHistBlocks / ROWS], sum = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (uint32_t g = 0; g < kPartials; ++g)
-        sums[g] = g < a.n_blocks ? *reinterpret_cast<const uint32_t*>(part + g * kPartialBytes + 2u * (kFirstNonFinite + 2u * lane)) : 0u;
-    uint32_t even = 0, odd = 0;
+        for (uint32_t k = 0; k < kHistBlocks / ROWS; ++k) v[k] = reinterpret_cast<const u32x4_a4*>(part[min(row + ROWS * k, parts - 1u)].bins)[q];
 #pragma unroll
-    for (uint32_t g = 0; g < kPartials; ++g) { even += sums[g] & 0xFFFFu; odd += sums[g] >> 16; }
-    const uint32_t upto = wave_incl_scan(even + odd);
-    const uint32_t total = __builtin_amdgcn_readlane(upto, 63);
-    if (total == 0u) {
-        table_from_sigma(__longlong_as_double(0x7FF8000000000000ll), table, sigma);
-        return;
+        for (uint32_t k = 0; k < kHistBlocks / ROWS; ++k)
+            if (row + ROWS * k < parts) sum += v[k];
+        reinterpret_cast<u32x4*>(s_hist)[row * 32u + (t & 31u)] = sum;
     }
-    const uint32_t rank = (total - 1u) / 2u;
-    uint32_t before = upto - even - odd;
-    const uint32_t at = (uint32_t)__builtin_ctzll(__ballot(rank >= before && rank < upto));
-    uint32_t row = 2u * lane;
-    if (rank >= before + even) { before += even; ++row; }
-    row = __builtin_amdgcn_readlane(row, at);
-    before = __builtin_amdgcn_readlane(before, at);
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    if (wave < 4u) {
 #pragma unroll
-    for (uint32_t g = 0; g < kPartials; ++g) {
-        const uint32_t of_row = __builtin_amdgcn_readlane(sums[g], at) >> (16u * (row & 1u)) & 0xFFFFu;
-        if (of_row != 0u && row * 256u + lane * 4u < kFirstNonFinite) {      /* rows without counts were not stored */
-            const u32x2 q = *reinterpret_cast<const u32x2*>(part + g * kPartialBytes + 2u * (row * 256u + lane * 4u));
-            w[0] += q.x & 0xFFFFu; w[1] += q.x >> 16; w[2] += q.y & 0xFFFFu; w[3] += q.y >> 16;
+        for (uint32_t k = 0; k < 3; ++k) {
+            const uint32_t inc = wave_incl_scan(t < parts ? head[k] : 0u);
+            if (lane == 63u) s_head[k][wave] = inc;
         }
     }
-    const uint32_t sum = (w[0] + w[1]) + (w[2] + w[3]);
-    uint32_t run = before + wave_incl_scan(sum) - sum;
-    const uint64_t owner = __ballot(rank >= run && rank < run + sum);
-    uint32_t bin = row * 256u + lane * 4u;
-#pragma unroll
-    for (uint32_t j = 0; j < 3; ++j) {
-        run += w[j];
-        if (rank >= run) bin = row * 256u + lane * 4u + j + 1u;
+    __syncthreads();
+    const uint32_t below = (s_head[0][0] + s_head[0][1]) + (s_head[0][2] + s_head[0][3]);
+    const uint32_t valid = (s_head[1][0] + s_head[1][1]) + (s_head[1][2] + s_head[1][3]);
+    const uint32_t inside = (s_head[2][0] + s_head[2][1]) + (s_head[2][2] + s_head[2][3]);
+    const uint32_t rank = (valid - 1u) / 2u;
+    if (valid == 0u) {
+        if (blockIdx.x == 0u && wave == 0u) table_from_sigma(__longlong_as_double(0x7FF8000000000000ll), table, sigma);
+        return;
     }
-    bin = __builtin_amdgcn_readlane(bin, (uint32_t)__builtin_ctzll(owner));
-    const double med = (double)__uint_as_float(bin << 16);
-    table_from_sigma(med / 0.6744897501960817, table, sigma);     /* Phi^-1(3/4) */
+    if (rank >= below && rank - below < inside) {
+        if (blockIdx.x != 0u || wave != 0u) return;
+        uint32_t even = 0, odd = 0;                          /* counts of magnitudes lo + 2 lane and lo + 2 lane + 1 */
+        if (lane < kWindow / 2u) {
+#pragma unroll
+            for (uint32_t r = 0; r < ROWS; ++r) {
+                const u32x2 w = *reinterpret_cast<const u32x2*>(s_hist + r * 128u + 2u * lane);
+                even += w.x;
+                odd += w.y;
+            }
+        }
+        const uint32_t inc = below + wave_incl_scan(even + odd);
+        const uint64_t owner = __ballot(rank >= inc - even - odd && rank < inc);
+        uint32_t bin = head.w + 2u * lane + (uint32_t)(rank >= inc - odd);
+        bin = __builtin_amdgcn_readlane(bin, (uint32_t)__builtin_ctzll(owner));
+        const double med = (double)__uint_as_float(bin << 16);
+        table_from_sigma(med / 0.6744897501960817, table, sigma);     /* Phi^-1(3/4) */
+        return;
+    }
+    const ChunkPlace place = place_of(split, c, DT);
+    const uint8_t* __restrict__ in = a.in + place.elem_off * ES;
+    __syncthreads();                                         /* s_hist is used anew */
+    if (a.stride == 1u) tensor_into_lds<DT>(s_hist, in, place.n, blockIdx.x, gridDim.x);
+    else sample_into_lds<DT, 4>(s_hist, in, place.n, a.stride, blockIdx.x * kHistWaves + wave, sample_blocks(place.n, a.stride), gridDim.x * kHistWaves);
+    __syncthreads();
+    if (!a.shared) {
+        rank_and_table<uint32_t>([&](uint32_t k, uint32_t* out) {
+            const u32x4 x = reinterpret_cast<const u32x4*>(s_hist)[k * kHistThreads + t];
+            __builtin_memcpy(out, &x, 16);
+        }, s_row, table, sigma);
+        return;
+    }
+    uint32_t* const hist = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(part) + kPartialsBytes);
+    flush_lds_hist(s_hist, hist, blockIdx.x);
+    /* every thread's additions have been made when the workgroup arrives.  One fence per workgroup: each walks its XCD's
+       L2, and one per wave took the fallback from 30 to 90 us */
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (t == 0u) {
+        __threadfence();
+        s_head[0][0] = atomicAdd(&part[0].arrived, 1u);
+        __threadfence();
+    }
+    __syncthreads();
+    if (s_head[0][0] + 1u != gridDim.x) return;
+    rank_and_table<uint32_t>([&](uint32_t k, uint32_t* out) {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)                     /* other workgroups' additions: past this XCD's caches */
+            out[j] = __hip_atomic_load(hist + (k * kHistThreads + t) * 4u + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }, s_row, table, sigma);
 }
 
 } // namespace
@@ -582,56 +796,77 @@ int launch_estimate(int dt, const MomentArgs& a, void* stream)
 }
 
 
-/* Several workgroups per chunk and a second kernel from this many groups in the largest chunk on, as long as there are
- * no more of them than compute units (a compute unit's LDS holds one at a time).  Measured, us, bf16, one workgroup
- * against several: 64 chunks of 128 groups 10.2 / 11.2, of 192 13.1 / 11.9, of 448 21.9 / 14.0; one chunk of 128
- * groups 9.4 / 9.7, of 500 20.9 / 12.4; 128 chunks of 192 (two workgroups each) 13.4 / 12.5, and of 256, where two
- * workgroups per chunk cannot hold them, 15.5 / 15.9.  fp32: 64 chunks of 448 38.1 / 20.5. */
-constexpr uint32_t kPartialFrom = 160;
-
-int launch_estimate_robust_fused(int dt, const HistArgs& a, void* stream)
+/* Groups to count in the launch's largest chunk. */
+static uint64_t groups_to_count(const HistArgs& a)
 {
-    hipStream_t s = (hipStream_t)stream;
     uint64_t largest = 0;
     for (uint32_t c = 0; c < a.tab.n_chunks; ++c) largest = std::max(largest, a.tab.elem_off[c + 1] - a.tab.elem_off[c]);
-    const uint64_t groups = ((largest + kGroup - 1) / kGroup + a.sample_stride - 1) / a.sample_stride;
+    return ((largest + kGroup - 1) / kGroup + a.sample_stride - 1) / a.sample_stride;
+}
+
+template <int DT, class SPLIT>
+static int launch_window(const HistArgs& a, const SPLIT& split, bool shared, hipStream_t s)
+{
+    const RobustIo io = {a.in, a.hist, a.table, a.sigma, a.sample_stride, shared};
     const uint32_t chunks = a.tab.n_chunks;
-    HistArgs b = a;
-    b.n_blocks = (uint32_t)std::max<uint64_t>(std::min(kHistBlocks / chunks, kPartials), (groups + kPartialGroups - 1) / kPartialGroups);
-    if (groups >= kPartialFrom && b.n_blocks * chunks <= kHistBlocks) {
-        const dim3 grid(b.n_blocks, chunks);
-        if (dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_robust_partial<ZIPCCL_BF16>), grid, dim3(kHistThreads), 0, s, b);
-        else hipLaunchKernelGGL((k_robust_partial<ZIPCCL_FP32>), grid, dim3(kHistThreads), 0, s, b);
-        if (hipGetLastError() != hipSuccess) return 1;
-        hipLaunchKernelGGL(k_robust_join, dim3(chunks), dim3(64), 0, s, b);
-        return (int)hipGetLastError();
-    }
-    if (dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_robust_chunk_fused<ZIPCCL_BF16>), dim3(chunks), dim3(kHistThreads), 0, s, a);
-    else hipLaunchKernelGGL((k_robust_chunk_fused<ZIPCCL_FP32>), dim3(chunks), dim3(kHistThreads), 0, s, a);
+    const uint64_t groups = groups_to_count(a);
+    /* two groups per wave at least (2^20 bf16 values 9.4 us, 10.4 with four), one workgroup per compute unit at most */
+    const uint32_t parts = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((groups + 31) / 32, kHistBlocks / chunks));
+    /* workgroups for the case that the window does not hold the rank: most of the time they only start and end, which is worth
+       a microsecond of a call on less than 2^25 values */
+    const uint32_t finish = !shared ? 1u : (groups <= 65536u ? (parts + 7u) / 8u : parts);
+    /* a tensor of up to 64 MiB stays in the caches for the compress that usually follows (2^24 bf16 values, estimate and
+       compress: 35.7 us with streamed loads, 31.9 without); larger ones do not, and are read faster streamed (2^26: 33 us, 36) */
+    const bool stream = a.tab.elem_off[chunks] * (DT == ZIPCCL_BF16 ? 2u : 4u) > (64ull << 20);
+    const dim3 grid(parts, chunks), block(kHistThreads);
+    if (stream) hipLaunchKernelGGL((k_window_count<DT, true, SPLIT>), grid, block, 0, s, io, split);
+    else hipLaunchKernelGGL((k_window_count<DT, false, SPLIT>), grid, block, 0, s, io, split);
+    if (hipGetLastError() != hipSuccess) return 1;
+    hipLaunchKernelGGL((k_window_finish<DT, SPLIT>), dim3(finish, chunks), block, 0, s, io, parts, split);
     return (int)hipGetLastError();
 }
 
-template <int DT, typename CNT>
-static int launch_large(const HistArgs& a, hipStream_t s)
+template <int DT>
+static int launch_huge(const HistArgs& a, hipStream_t s)
 {
-    const dim3 grid(a.n_blocks, a.tab.n_chunks), chunks(a.tab.n_chunks);
-    hipLaunchKernelGGL((k_clear_hist<CNT>), chunks, dim3(kClearThreads), 0, s, a.hist);
+    const RobustIo io = {a.in, a.hist, a.table, a.sigma, 1u, 1u};
+    hipLaunchKernelGGL(k_clear_hist, dim3(1), dim3(kClearThreads), 0, s, a.hist);
     if (hipGetLastError() != hipSuccess) return 1;
-    if (a.sample_stride > 1u) hipLaunchKernelGGL((k_magnitude_hist_sampled<DT>), grid, dim3(kHistThreads), 0, s, a);
-    else hipLaunchKernelGGL((k_magnitude_hist<DT, CNT>), grid, dim3(kHistThreads), 0, s, a);
+    hipLaunchKernelGGL((k_magnitude_hist<DT>), dim3(a.n_blocks), dim3(kHistThreads), 0, s, io, a.tab.elem_off[1]);
     if (hipGetLastError() != hipSuccess) return 1;
-    hipLaunchKernelGGL((k_robust_finish<CNT>), chunks, dim3(kHistThreads), 0, s, a);
+    hipLaunchKernelGGL(k_robust_finish, dim3(1), dim3(kHistThreads), 0, s, io);
     return (int)hipGetLastError();
+}
+
+/*
+ * One kernel or two for chunks of at most kFusedGroups groups to count (us, bf16, one / two): one chunk of 64 groups 7.6 / 8.4,
+ * of 128 9.3 / 8.3, of 512 14.1 / 8.8; 8 chunks of 64 8.1 / 9.2, of 256 11.5 / 9.3; 64 chunks of 128 10.6 / 12.5, of 192 13.1 /
+ * 13.3, of 448 22 / 14; 128 chunks of 256 16.2 / 16.8: the more chunks, the fewer workgroups are left for each of them.
+ */
+template <int DT>
+static int launch_robust(const HistArgs& a, bool small, hipStream_t s)
+{
+    const uint32_t chunks = a.tab.n_chunks;
+    if (small && groups_to_count(a) < (chunks <= 16u ? 100u : (chunks <= 64u ? 180u : 260u))) {
+        const RobustIo io = {a.in, a.hist, a.table, a.sigma, a.sample_stride, 0u};
+        if (is_equal_split(a.tab)) hipLaunchKernelGGL((k_robust_chunk_fused<DT, EqualSplit>), dim3(chunks), dim3(kHistThreads), 0, s, io, equal_split(a.tab));
+        else hipLaunchKernelGGL((k_robust_chunk_fused<DT, ChunkTab>), dim3(chunks), dim3(kHistThreads), 0, s, io, a.tab);
+        return (int)hipGetLastError();
+    }
+    /* 2^32 values or more: only a whole tensor, every value of which counts */
+    if (chunks == 1u && a.tab.elem_off[1] > ZIPCCL_MAX_CHUNK_ELEMS) return launch_huge<DT>(a, s);
+    if (is_equal_split(a.tab)) return launch_window<DT>(a, equal_split(a.tab), !small, s);
+    return launch_window<DT>(a, a.tab, !small, s);
+}
+
+int launch_estimate_robust_fused(int dt, const HistArgs& a, void* stream)
+{
+    return dt == ZIPCCL_BF16 ? launch_robust<ZIPCCL_BF16>(a, true, (hipStream_t)stream) : launch_robust<ZIPCCL_FP32>(a, true, (hipStream_t)stream);
 }
 
 int launch_estimate_robust(int dt, const HistArgs& a, void* stream)
 {
-    hipStream_t s = (hipStream_t)stream;
-    /* 32-bit counts unless some chunk could overflow them; a sample is only taken of chunks below 2^32 values */
-    bool wide = false;
-    for (uint32_t c = 0; c < a.tab.n_chunks; ++c) wide |= a.tab.elem_off[c + 1] - a.tab.elem_off[c] > ZIPCCL_MAX_CHUNK_ELEMS;
-    if (wide) return dt == ZIPCCL_BF16 ? launch_large<ZIPCCL_BF16, unsigned long long>(a, s) : launch_large<ZIPCCL_FP32, unsigned long long>(a, s);
-    return dt == ZIPCCL_BF16 ? launch_large<ZIPCCL_BF16, uint32_t>(a, s) : launch_large<ZIPCCL_FP32, uint32_t>(a, s);
+    return dt == ZIPCCL_BF16 ? launch_robust<ZIPCCL_BF16>(a, false, (hipStream_t)stream) : launch_robust<ZIPCCL_FP32>(a, false, (hipStream_t)stream);
 }
 
 } // namespace zipccl

@@ -386,3 +386,36 @@ def test_estimate_of_chunks_shared_by_a_few_workgroups(dtype):
     many = rng.standard_normal(100 * 200 * G, dtype=np.float32)      # 100 chunks: two workgroups each
     _sampled_case(W.f32_to_bf16_words(many) if dtype == z.BF16 else many.view(np.uint32).copy(), dtype,
                   np.full(100, 200 * G, dtype=np.uint64), 1, f"100 chunks dtype={dtype}")
+
+
+@pytest.mark.parametrize("dtype", [z.BF16, z.FP32])
+@pytest.mark.parametrize("ce,stride", [((200 * 512 - 3,), 1), ((508 * 512 + 1,), 1), ((1 << 21,), 1), ((1 << 21, 5, 0, 300_000), 4),
+                                       ((600 * 512, 70_001, 1 << 20), 1), ((90 * 512,) * 20 + (181 * 512,), 1)])
+def test_estimate_of_chunks_whose_small_sample_misleads(dtype, ce, stride):
+    """The windowed count looks at 16 values of each of 64 strata before it counts: chunks where those say nothing about
+    the median.  The sampled values alone at another scale, above or below the rest; everything zero but a short run; two
+    halves far apart, so that the median is the largest value of the one or the smallest of the other; chunks that do
+    not mislead beside them.  Bit-equal to the oracle."""
+    rng = np.random.default_rng(71)
+    base = rng.standard_normal(sum(ce), dtype=np.float32)
+    starts = np.concatenate([[0], np.cumsum(ce)])
+    def sampled(n):
+        length = (n - 16) // 64
+        k = np.arange(64, dtype=np.uint64)
+        at = k * np.uint64(length) + ((k * np.uint64(2654435761) % np.uint64(2 ** 32)) * np.uint64(length) >> np.uint64(32))
+        return (at.astype(np.int64)[:, None] + np.arange(16)).ravel()
+    for kind in ("high", "low", "run", "halves"):
+        x = base.copy()
+        for c, n in enumerate(ce):
+            if n < 1024 or c % 2:
+                continue
+            part = x[starts[c]:starts[c] + n]
+            if kind in ("high", "low"):
+                part[sampled(n)] *= np.float32(1e6 if kind == "high" else 1e-6)
+            elif kind == "run":
+                part[:n // 3] = 0.0
+                part[n // 3 + 700:] = 0.0
+            else:
+                part[::2] = np.abs(part[::2]) * np.float32(1e6) + 1
+        words = W.f32_to_bf16_words(x) if dtype == z.BF16 else x.view(np.uint32).copy()
+        _sampled_case(words, dtype, np.array(ce, dtype=np.uint64), stride, f"misled {kind} {ce[:3]} dtype={dtype}")
