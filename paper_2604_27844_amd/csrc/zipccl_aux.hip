@@ -598,10 +598,10 @@ __global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a,
             v[u][q] = STREAM ? ld_stream_a2(p) : (u32x4)*reinterpret_cast<const u32x4_a2*>(p);
         }
     };
-    bool more = k0 + (NF - 1u) * n_waves < whole;
-    if (more) {
+    /* a group that is not there loads the chunk's first and is not counted */
+    if (k0 < whole) {
 #pragma unroll
-        for (uint32_t u = 0; u < NF; ++u) load(u, k0 + u * n_waves);
+        for (uint32_t u = 0; u < NF; ++u) load(u, k0 + u * n_waves < whole ? k0 + u * n_waves : 0u);
     }
     if (threadIdx.x < kWindow + 128u) s_bins[threadIdx.x] = 0u;
     const uint32_t at = median.find(s_sample, s_cnt, wave, lane) + 4u;
@@ -632,23 +632,20 @@ __global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a,
             count(w);
         }
     };
-    while (more) {
+    while (k0 < whole) {
+        if (k0 + (NF - 1u) * n_waves < whole) {
 #pragma unroll
-        for (uint32_t u = 0; u < NF; ++u) count_loaded(u);
-        k0 += NF * n_waves;
-        more = k0 + (NF - 1u) * n_waves < whole;
-        if (more) {
+            for (uint32_t u = 0; u < NF; ++u) count_loaded(u);
+        } else {
 #pragma unroll
-            for (uint32_t u = 0; u < NF; ++u) load(u, k0 + u * n_waves);
+            for (uint32_t u = 0; u + 1u < NF; ++u)
+                if (k0 + u * n_waves < whole) count_loaded(u);
         }
-    }
-    /* what is left, fewer than NF groups; one that is not there loads the chunk's first and is not counted */
-    if (k0 < whole) {
+        k0 += NF * n_waves;
+        if (k0 < whole) {
 #pragma unroll
-        for (uint32_t u = 0; u + 1u < NF; ++u) load(u, k0 + u * n_waves < whole ? k0 + u * n_waves : 0u);
-#pragma unroll
-        for (uint32_t u = 0; u + 1u < NF; ++u)
-            if (k0 + u * n_waves < whole) count_loaded(u);
+            for (uint32_t u = 0; u < NF; ++u) load(u, k0 + u * n_waves < whole ? k0 + u * n_waves : 0u);
+        }
     }
     if (blocks != 0u && whole % n_waves == blockIdx.x * kHistWaves + wave) {
         const uint64_t first = (uint64_t)group_of(whole) * kGroup;
@@ -815,9 +812,10 @@ static int launch_window(const HistArgs& a, const SPLIT& split, bool shared, hip
     /* workgroups for the case that the window does not hold the rank: most of the time they only start and end, which is worth
        a microsecond of a call on less than 2^25 values */
     const uint32_t finish = !shared ? 1u : (groups <= 65536u ? (parts + 7u) / 8u : parts);
-    /* a tensor of up to 64 MiB stays in the caches for the compress that usually follows (2^24 bf16 values, estimate and
-       compress: 35.7 us with streamed loads, 31.9 without); larger ones do not, and are read faster streamed (2^26: 33 us, 36) */
-    const bool stream = a.tab.elem_off[chunks] * (DT == ZIPCCL_BF16 ? 2u : 4u) > (64ull << 20);
+    /* up to 64 MiB of counted values, 32 of sampled ones, stay in the caches for the compress that usually follows (us, estimate and compress, streamed
+       loads / plain: 2^24 bf16 values 35.7 / 31.9, 64 experts of 512 x 7168 from one group in 16 156.0 / 152.6); larger tensors do
+       not, and are read faster streamed (2^26: 33, 36; 64 MiB in scattered kilobytes, estimate alone, 25.9 / 28.8) */
+    const bool stream = a.tab.elem_off[chunks] / a.sample_stride * (DT == ZIPCCL_BF16 ? 2u : 4u) > (a.sample_stride == 1u ? 64ull << 20 : 32ull << 20);
     const dim3 grid(parts, chunks), block(kHistThreads);
     if (stream) hipLaunchKernelGGL((k_window_count<DT, true, SPLIT>), grid, block, 0, s, io, split);
     else hipLaunchKernelGGL((k_window_count<DT, false, SPLIT>), grid, block, 0, s, io, split);
