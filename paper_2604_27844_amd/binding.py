@@ -1,4 +1,5 @@
-"""ctypes binding of libzipccl.so: same names as include/zipccl.h, argument marshalling only.
+"""Binding of libzipccl.so: same names as include/zipccl.h, argument marshalling only.  The calls that work on device
+buffers go through zipccl_python.so (csrc/zipccl_python.cpp), the others through ctypes.
 
 Device buffers are torch tensors (PyTorch-ROCm owns memory and streams); every step of the
 path runs in the library's HIP kernels.  There is no fallback: a missing library is an error.
@@ -7,6 +8,7 @@ import ctypes
 import os
 
 import numpy as np
+import torch                    # zipccl_python.so looks into its tensors
 
 from . import build_lib
 
@@ -94,6 +96,14 @@ def _load():
     return lib
 
 
+def _load_native():
+    if not os.path.exists(build_lib.PYTHON):
+        build_lib.build(lib=build_lib.PYTHON)
+    from . import zipccl_python
+    zipccl_python.setup(zipccl_table_t, _host_array, _raw_stream_functions)
+    return zipccl_python
+
+
 _lib = _load()
 EXPORTS = ("zipccl_build_table", "zipccl_max_compressed_size", "zipccl_chunk_slot_offsets", "zipccl_chunk_static_bytes",
            "zipccl_compress_workspace_size", "zipccl_compress_min_workspace_size", "zipccl_compress", "zipccl_decompress", "zipccl_decompress_reduce", "zipccl_status_string",
@@ -104,10 +114,14 @@ EXPORTS = ("zipccl_build_table", "zipccl_max_compressed_size", "zipccl_chunk_slo
            "zipccl_compress_chunk_tables")
 
 
+def _host_array(chunk_elems):
+    return np.ascontiguousarray(np.asarray(chunk_elems, dtype=np.uint64))
+
+
 def _host_u64(chunk_elems):
     if chunk_elems is None:
         return None, None
-    a = np.ascontiguousarray(np.asarray(chunk_elems, dtype=np.uint64))
+    a = _host_array(chunk_elems)
     return a, a.__array_interface__["data"][0]
 
 
@@ -120,27 +134,25 @@ def _dptr(t):
     return t.data_ptr()
 
 
-_current_stream = None
-
-
-def _resolve_current_stream():
-    """How to ask for the handle of the calling thread's current stream on its current device.  torch.cuda.current_stream()
-    builds a Stream object for it, 2.8 us of a small call's ten; the two calls underneath take 0.2."""
-    import torch
+def _raw_stream_functions():
+    """Two functions: the handle of a device's current stream, given the other one's result, the current device.
+    torch.cuda.current_stream() builds a Stream object for the handle, 2.8 us of a small call's five; the two calls
+    underneath take 0.2."""
     raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
     if raw is None or device is None:
-        return lambda: torch.cuda.current_stream().cuda_stream
+        return (lambda _: torch.cuda.current_stream().cuda_stream), (lambda: None)
     torch.cuda.init()
-    return lambda: raw(device())
+    return raw, device
 
 
 def _stream(stream):
     if stream is None:
-        global _current_stream
-        if _current_stream is None:
-            _current_stream = _resolve_current_stream()
-        return _current_stream()
+        raw, device = _raw_stream_functions()
+        return raw(device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+_native = _load_native()
 
 
 def zipccl_status_string(code):
@@ -182,11 +194,8 @@ def zipccl_compress_min_workspace_size(n_elems, dt, n_chunks=1, chunk_elems=None
 def zipccl_compress(d_in, n_elems, dt, n_chunks, chunk_elems, table, d_out, d_chunk_bytes, d_workspace,
                     stream=None, out_capacity=None, workspace_bytes=None):
     """d_in / d_out / d_chunk_bytes / d_workspace are torch GPU tensors (any dtype; raw bytes)."""
-    _keep, p = _host_u64(chunk_elems)
-    cap = d_out.nbytes if out_capacity is None else int(out_capacity)
-    wsb = d_workspace.nbytes if workspace_bytes is None else int(workspace_bytes)
-    rc = _lib.zipccl_compress(_dptr(d_in), int(n_elems), dt, int(n_chunks), p, ctypes.byref(table),
-                              _dptr(d_out), cap, _dptr(d_chunk_bytes), _dptr(d_workspace), wsb, _stream(stream))
+    rc = _native.compress(d_in, n_elems, dt, n_chunks, chunk_elems, table, d_out, out_capacity, d_chunk_bytes,
+                          d_workspace, workspace_bytes, stream)
     if rc:
         raise ZipcclError(rc, "zipccl_compress")
 
@@ -194,29 +203,22 @@ def zipccl_compress(d_in, n_elems, dt, n_chunks, chunk_elems, table, d_out, d_ch
 def zipccl_compress_static(d_in, n_elems, dt, n_chunks, chunk_elems, table, d_out, d_chunk_bytes, stream=None,
                            out_capacity=None):
     """zipccl_compress with the library's own fixed workspace (no allocation, no workspace argument)."""
-    _keep, p = _host_u64(chunk_elems)
-    cap = d_out.nbytes if out_capacity is None else int(out_capacity)
-    rc = _lib.zipccl_compress_static(_dptr(d_in), int(n_elems), dt, int(n_chunks), p, ctypes.byref(table),
-                                     _dptr(d_out), cap, _dptr(d_chunk_bytes), _stream(stream))
+    rc = _native.compress_static(d_in, n_elems, dt, n_chunks, chunk_elems, table, d_out, out_capacity,
+                                 d_chunk_bytes, stream)
     if rc:
         raise ZipcclError(rc, "zipccl_compress_static")
 
 
 def zipccl_decompress(d_comp, d_out, n_elems, dt, n_chunks=1, chunk_elems=None, d_status=None, stream=None,
                       comp_capacity=None):
-    _keep, p = _host_u64(chunk_elems)
-    cap = d_comp.nbytes if comp_capacity is None else int(comp_capacity)
-    rc = _lib.zipccl_decompress(_dptr(d_comp), cap, _dptr(d_out), int(n_elems), dt, int(n_chunks), p,
-                                _dptr(d_status), _stream(stream))
+    rc = _native.decompress(d_comp, comp_capacity, d_out, n_elems, dt, n_chunks, chunk_elems, d_status, stream)
     if rc:
         raise ZipcclError(rc, "zipccl_decompress")
 
 
 def zipccl_decompress_reduce(d_comp, d_out, n_elems, dt, n_peers, out_dt=FP32, d_status=None, stream=None,
                              comp_capacity=None):
-    cap = d_comp.nbytes if comp_capacity is None else int(comp_capacity)
-    rc = _lib.zipccl_decompress_reduce(_dptr(d_comp), cap, _dptr(d_out), int(n_elems), dt, int(n_peers), out_dt,
-                                       _dptr(d_status), _stream(stream))
+    rc = _native.decompress_reduce(d_comp, comp_capacity, d_out, n_elems, dt, n_peers, out_dt, d_status, stream)
     if rc:
         raise ZipcclError(rc, "zipccl_decompress_reduce")
 
@@ -245,9 +247,7 @@ def zipccl_estimate_workspace_size():
 
 def zipccl_estimate_table(d_in, n_elems, dt, d_table, d_sigma, d_workspace, stream=None):
     """d_table: 8-byte GPU tensor; d_sigma: float64 GPU tensor of one element or None."""
-    wsb = d_workspace.nbytes
-    rc = _lib.zipccl_estimate_table(_dptr(d_in), int(n_elems), dt, _dptr(d_table), _dptr(d_sigma),
-                                    _dptr(d_workspace), wsb, _stream(stream))
+    rc = _native.estimate_table(d_in, n_elems, dt, d_table, d_sigma, d_workspace, stream)
     if rc:
         raise ZipcclError(rc, "zipccl_estimate_table")
 
@@ -258,9 +258,7 @@ def zipccl_estimate_robust_workspace_size():
 
 def zipccl_estimate_table_robust(d_in, n_elems, dt, d_table, d_sigma, d_workspace, stream=None):
     """As zipccl_estimate_table, with sigma = median of the magnitudes / Phi^-1(3/4)."""
-    wsb = d_workspace.nbytes
-    rc = _lib.zipccl_estimate_table_robust(_dptr(d_in), int(n_elems), dt, _dptr(d_table), _dptr(d_sigma),
-                                           _dptr(d_workspace), wsb, _stream(stream))
+    rc = _native.estimate_table_robust(d_in, n_elems, dt, d_table, d_sigma, d_workspace, stream)
     if rc:
         raise ZipcclError(rc, "zipccl_estimate_table_robust")
 
@@ -271,10 +269,8 @@ def zipccl_estimate_chunk_tables_workspace_size(n_chunks):
 
 def zipccl_estimate_chunk_tables(d_in, n_elems, dt, n_chunks, chunk_elems, d_tables, d_sigmas, d_workspace, stream=None):
     """d_tables: 8 * n_chunks bytes on the GPU; d_sigmas: n_chunks float64 on the GPU or None."""
-    _keep, p = _host_u64(chunk_elems)
-    wsb = d_workspace.nbytes
-    rc = _lib.zipccl_estimate_chunk_tables(_dptr(d_in), int(n_elems), dt, int(n_chunks), p, _dptr(d_tables),
-                                           _dptr(d_sigmas), _dptr(d_workspace), wsb, _stream(stream))
+    rc = _native.estimate_chunk_tables(d_in, n_elems, dt, n_chunks, chunk_elems, None, d_tables, d_sigmas,
+                                       d_workspace, stream)
     if rc:
         raise ZipcclError(rc, "zipccl_estimate_chunk_tables")
 
@@ -282,35 +278,24 @@ def zipccl_estimate_chunk_tables(d_in, n_elems, dt, n_chunks, chunk_elems, d_tab
 def zipccl_estimate_chunk_tables_sampled(d_in, n_elems, dt, n_chunks, chunk_elems, sample_stride, d_tables, d_sigmas,
                                          d_workspace, stream=None):
     """As zipccl_estimate_chunk_tables, from one group of 512 values per sample_stride groups of every chunk."""
-    _keep, p = _host_u64(chunk_elems)
-    wsb = d_workspace.nbytes
-    rc = _lib.zipccl_estimate_chunk_tables_sampled(_dptr(d_in), int(n_elems), dt, int(n_chunks), p, int(sample_stride),
-                                                   _dptr(d_tables), _dptr(d_sigmas), _dptr(d_workspace), wsb,
-                                                   _stream(stream))
+    rc = _native.estimate_chunk_tables(d_in, n_elems, dt, n_chunks, chunk_elems, int(sample_stride), d_tables, d_sigmas,
+                                       d_workspace, stream)
     if rc:
         raise ZipcclError(rc, "zipccl_estimate_chunk_tables_sampled")
 
 
 def zipccl_compress_chunk_tables(d_in, n_elems, dt, n_chunks, chunk_elems, d_tables, d_out, d_chunk_bytes,
                                  d_workspace, stream=None, workspace_bytes=None):
-    _keep, p = _host_u64(chunk_elems)
-    cap = d_out.nbytes
-    wsb = d_workspace.nbytes if workspace_bytes is None else int(workspace_bytes)
-    rc = _lib.zipccl_compress_chunk_tables(_dptr(d_in), int(n_elems), dt, int(n_chunks), p, _dptr(d_tables),
-                                           _dptr(d_out), cap, _dptr(d_chunk_bytes), _dptr(d_workspace), wsb,
-                                           _stream(stream))
+    rc = _native.compress_chunk_tables(d_in, n_elems, dt, n_chunks, chunk_elems, d_tables, d_out, None, d_chunk_bytes,
+                                       d_workspace, workspace_bytes, stream)
     if rc:
         raise ZipcclError(rc, "zipccl_compress_chunk_tables")
 
 
 def zipccl_compress_device_table(d_in, n_elems, dt, n_chunks, chunk_elems, d_table, d_out, d_chunk_bytes,
                                  d_workspace, stream=None, workspace_bytes=None):
-    _keep, p = _host_u64(chunk_elems)
-    cap = d_out.nbytes
-    wsb = d_workspace.nbytes if workspace_bytes is None else int(workspace_bytes)
-    rc = _lib.zipccl_compress_device_table(_dptr(d_in), int(n_elems), dt, int(n_chunks), p, _dptr(d_table),
-                                           _dptr(d_out), cap, _dptr(d_chunk_bytes), _dptr(d_workspace), wsb,
-                                           _stream(stream))
+    rc = _native.compress_device_table(d_in, n_elems, dt, n_chunks, chunk_elems, d_table, d_out, None, d_chunk_bytes,
+                                       d_workspace, workspace_bytes, stream)
     if rc:
         raise ZipcclError(rc, "zipccl_compress_device_table")
 

@@ -1,18 +1,21 @@
 """Build libzipccl.so (the codec) and libzipccl_yardstick.so (the benchmark's plain-copy kernel) in-tree with
-hipcc for gfx950 (cross-compiles without a GPU)."""
+hipcc for gfx950 (cross-compiles without a GPU), and zipccl_python.so (the binding's calls) with the host compiler."""
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libzipccl.so")
 YARDSTICK = os.path.join(HERE, "libzipccl_yardstick.so")
+PYTHON = os.path.join(HERE, "zipccl_python.so")
 SOURCES = ["zipccl_compress.hip", "zipccl_decompress.hip", "zipccl_aux.hip", "zipccl_host.cpp"]
 HEADERS = [os.path.join(CSRC, "zipccl_internal.h"), os.path.join(CSRC, "zipccl_device.h"),
            os.path.join(ROOT, "include", "zipccl.h")]
 TARGETS = {LIB: [os.path.join(CSRC, s) for s in SOURCES],
-           YARDSTICK: [os.path.join(CSRC, "zipccl_yardstick.hip")]}
+           YARDSTICK: [os.path.join(CSRC, "zipccl_yardstick.hip")],
+           PYTHON: [os.path.join(CSRC, "zipccl_python.cpp")]}
 
 
 def stale(lib=LIB):
@@ -21,6 +24,20 @@ def stale(lib=LIB):
     t = os.path.getmtime(lib)
     deps = TARGETS[lib] + HEADERS + [os.path.join(ROOT, "include", "zipccl_yardstick.h")]
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def _python_command(sources, out):
+    import torch
+    from torch.utils import cpp_extension
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-I", os.path.join(ROOT, "include")]
+    for path in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", path]
+    cmd += sources + ["-o", out, "-L", HERE, "-lzipccl", "-Wl,-rpath,$ORIGIN"]
+    for path in cpp_extension.library_paths():
+        cmd += ["-L", path]
+    return cmd + ["-lc10", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
 
 
 def build(force=True, verbose=False, lib=None):
@@ -35,6 +52,8 @@ def build(force=True, verbose=False, lib=None):
                "-Wall", "-Wno-unused-command-line-argument",
                "-I", os.path.join(ROOT, "include"), "-I", CSRC]
         cmd += sources + ["-o", tmp]
+        if target == PYTHON:
+            cmd = _python_command(sources, tmp)
         if verbose:
             print(" ".join(cmd))
         subprocess.check_call(cmd)

@@ -127,3 +127,36 @@ def test_argument_errors_return_before_any_launch():
     assert sampled(16, k=3) == 1                          # 2^20 values do not split into 3 equal chunks
     assert sampled(16, wsb=100) == 3
     assert z.zipccl_status_string(4) == "corrupt compressed data"
+
+
+def test_calls_on_device_buffers_check_their_arguments_before_the_library_is_called():
+    """What the binding itself refuses, without a GPU: tensors that are not on one or not contiguous, objects that are no
+    tensors, tables and types of the wrong kind, workspaces that are not there."""
+    import torch
+    t = z.zipccl_build_table(1.0)
+    cpu = torch.zeros(64, dtype=torch.uint8)
+    class Odd(torch.Tensor):
+        pass
+    for bad in (cpu, cpu[::2], cpu.as_subclass(Odd), torch.nn.Parameter(torch.zeros(4))):
+        with pytest.raises(ValueError):
+            z.zipccl_compress(bad, 8, z.BF16, 1, None, t, None, None, None, out_capacity=1, workspace_bytes=1)
+        with pytest.raises(ValueError):
+            z.zipccl_decompress(bad, bad, 8, z.BF16)
+        with pytest.raises(ValueError):
+            z.zipccl_estimate_table_robust(bad, 8, z.BF16, bad, None, bad)
+    for bad in (3, "buffer", np.zeros(8)):
+        with pytest.raises(AttributeError):
+            z.zipccl_decompress_reduce(bad, bad, 8, z.BF16, 2)
+    with pytest.raises(AttributeError):
+        z.zipccl_compress(None, 0, z.BF16, 1, None, t, None, None, None)           # no buffer to take a capacity from
+    with pytest.raises(TypeError):
+        z.zipccl_compress(None, 0, z.BF16, 1, None, 7, None, None, None, stream=0, out_capacity=0, workspace_bytes=0)
+    with pytest.raises(TypeError):
+        z.zipccl_compress(None, 0, 0.0, 1, None, t, None, None, None, stream=0, out_capacity=0, workspace_bytes=0)
+    for counts in (None, [0], (0,), np.zeros(1, dtype=np.int64), np.zeros(1, dtype=np.uint64), np.zeros(2, dtype=np.uint64)[::2]):
+        with pytest.raises(z.ZipcclError) as ei:                                   # read, handed on, and refused by the library
+            z.zipccl_compress(None, 0, z.BF16, 1, counts, t, None, None, None, stream=0, out_capacity=0, workspace_bytes=0)
+        assert ei.value.code == 1
+    with pytest.raises(z.ZipcclError) as ei:
+        z.zipccl_compress_static(None, 0, 7, np.uint32(1), None, t, None, None, stream=0, out_capacity=0)
+    assert ei.value.code == 2
