@@ -26,6 +26,7 @@
  * Everything here is integer work.
  */
 #include <mutex>
+#include <type_traits>
 
 #include "zipccl_device.h"
 
@@ -526,6 +527,7 @@ __global__ __launch_bounds__(kThreads) void k_place(const CompressIo a, const Pa
     __shared__ uint32_t s_big[kThreads / kSub];
     __shared__ uint64_t s_src[kThreads / kSub], s_dst[kThreads / kSub];
     __shared__ uint32_t s_nw[kThreads / kSub], s_sh[kThreads / kSub];
+    constexpr uint32_t kAhead = 4;                      /* words per lane moved with what is requested ahead of the counts */
     if (threadIdx.x == 0) s_nbig = 0;
 
     /* grid = (16-tile groups of the largest chunk, chunks): the chunk's geometry is wave-uniform */
@@ -533,6 +535,32 @@ __global__ __launch_bounds__(kThreads) void k_place(const CompressIo a, const Pa
     const ChunkPlace place = place_of(split, c, DT);
     const uint32_t first = place.tile, ntc = place.tiles;
     if (blockIdx.x * (kThreads / kSub) >= ntc) return;  /* a shorter chunk than the largest of the launch */
+    const uint64_t n = place.n;
+    uint8_t* __restrict__ slot = a.out + place.slot_off;
+    const SlotLayout L = slot_layout(n, DT);
+    const uint32_t sub = threadIdx.x % kSub;
+    const uint32_t tw = threadIdx.x / kSub;             /* tile inside the workgroup */
+    const uint32_t ti = blockIdx.x * (kThreads / kSub) + tw;
+    const uint32_t tl = min(ti, ntc - 1u);              /* past the last tile: the last one once more, not stored */
+
+    /* Requested before anything is known: the tile's count, its 16 index entries, and the first bytes of its stash, 8 where
+       a lane's 4 will be some of them, wherever the destination's words begin.  (The stash of a tile holds a byte for each of its
+       values, and 64 readable ones follow the last.) */
+    const uint8_t* __restrict__ src = park.stash + place.elem_off + (uint64_t)tl * kTile;
+    const uint32_t room = (uint32_t)min(n - (uint64_t)tl * kTile, (uint64_t)kTile);       /* values of the tile */
+    const uint64_t ng = (n + kGroup - 1) / kGroup;
+    uint32_t* __restrict__ idx = reinterpret_cast<uint32_t*>(slot + L.idx);
+    const uint64_t g = (uint64_t)tl * kGroupsPerTile + sub;
+    const uint32_t cnt = park.tile_total[first + tl];
+    const uint32_t idx_local = g < ng ? idx[g] : 0u;
+    uint32_t w0[kAhead], w1[kAhead];
+#pragma unroll
+    for (uint32_t k = 0; k < kAhead; ++k) {
+        const uint32_t at = 4u * (k * kSub + sub);
+        typedef u32x2 u32x2_a1 __attribute__((aligned(1)));
+        const u32x2 v = *reinterpret_cast<const u32x2_a1*>(src + (at < room ? at : 0u));
+        w0[k] = v.x; w1[k] = v.y;
+    }
     if (SCAN) {
         /* counts of the chunk's tiles before this workgroup's, and the exclusive prefix inside it */
         const uint32_t t0 = blockIdx.x * (kThreads / kSub);
@@ -551,67 +579,70 @@ __global__ __launch_bounds__(kThreads) void k_place(const CompressIo a, const Pa
         }
     }
     __syncthreads();
-    const uint64_t n = place.n;
-    uint8_t* __restrict__ slot = a.out + place.slot_off;
-    const SlotLayout L = slot_layout(n, DT);
     uint32_t dec_lo, dec_hi;
     table_words(a, c, dec_lo, dec_hi);
 
-    const uint32_t sub = threadIdx.x % kSub;
-    const uint32_t tw = threadIdx.x / kSub;             /* tile inside the workgroup */
-    const uint32_t ti = blockIdx.x * (kThreads / kSub) + tw;
     if (ti < ntc) {
-        const uint32_t t = first + ti;
-        const uint8_t* __restrict__ src = park.stash + place.elem_off + (uint64_t)ti * kTile;
-        /* everything that does not depend on the counts is loaded together with them:
-           the tile's 16 index entries and the first 64 bytes of its stash */
-        const uint64_t ng = (n + kGroup - 1) / kGroup;
-        uint32_t* __restrict__ idx = reinterpret_cast<uint32_t*>(slot + L.idx);
-        const uint64_t g = (uint64_t)ti * kGroupsPerTile + sub;
-        uint32_t idx_local = 0;
-        if (g < ng) idx_local = idx[g];
         uint32_t P;
         if (SCAN) P = ((s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3])) + s_ex[tw];
-        else P = park.tile_prefix[t];
-        const uint32_t cnt = park.tile_total[t];
+        else P = park.tile_prefix[first + ti];
         if (P != 0u && g < ng) idx[g] = idx_local + P;
 
         /* byte-exact move to an arbitrarily aligned destination: head bytes, aligned words, tail bytes */
         uint8_t* __restrict__ dst = slot + L.esc + P;
         const uint32_t head = min((uint32_t)(-(int64_t)reinterpret_cast<uintptr_t>(dst)) & 3u, cnt);
         const uint32_t nw = (cnt - head) >> 2;
-        const uint32_t done = head + 4u * nw;
-        const uint32_t sh8 = reinterpret_cast<uintptr_t>(src + head) & 3u;
-        const uint32_t* __restrict__ s32 = reinterpret_cast<const uint32_t*>(
-            reinterpret_cast<uintptr_t>(src + head) & ~(uintptr_t)3);
+        const uint32_t done = head + 4u * nw, tail = cnt - done;
         uint32_t* __restrict__ d32 = reinterpret_cast<uint32_t*>(dst + head);
-        uint8_t hb = 0, tb = 0;
-        if (sub < head) hb = src[sub];
-        if (sub < cnt - done) tb = src[done + sub];
-        if (cnt <= kPlaceBig) {
-            move_words<4>(d32, s32, nw, sh8, sub, kSub);
-        } else if (sub == 0) {
-            const uint32_t k = atomicAdd(&s_nbig, 1u);
-            s_big[k] = tw;
-            s_src[tw] = reinterpret_cast<uint64_t>(s32);
-            s_dst[tw] = reinterpret_cast<uint64_t>(d32);
-            s_nw[tw] = nw;
-            s_sh[tw] = sh8;
+        if (sub == 0u) {
+            for (uint32_t i = 0; i < head; ++i) dst[i] = (uint8_t)(w0[0] >> (8u * i));
         }
-        if (sub < head) dst[sub] = hb;
-        if (sub < cnt - done) dst[done + sub] = tb;
+#pragma unroll
+        for (uint32_t k = 0; k < kAhead; ++k) {
+            const uint32_t i = k * kSub + sub;
+            const uint32_t v = __builtin_amdgcn_alignbyte(w1[k], w0[k], head);
+            if (i < nw) d32[i] = v;
+            if (i == nw)
+                for (uint32_t j = 0; j < tail; ++j) dst[done + j] = (uint8_t)(v >> (8u * j));
+        }
+        if (nw >= kAhead * kSub) {                      /* more than that */
+            uint8_t tb = 0;
+            if (sub < tail) tb = src[done + sub];
+            const uint8_t* const from = src + head + 4u * kAhead * kSub;
+            const uint32_t sh8 = reinterpret_cast<uintptr_t>(from) & 3u;
+            const uint32_t* __restrict__ s32 = reinterpret_cast<const uint32_t*>(reinterpret_cast<uintptr_t>(from) & ~(uintptr_t)3);
+            if (cnt <= kPlaceBig) {
+                move_words<4>(d32 + kAhead * kSub, s32, nw - kAhead * kSub, sh8, sub, kSub);
+            } else if (sub == 0) {
+                const uint32_t k = atomicAdd(&s_nbig, 1u);
+                s_big[k] = tw;
+                s_src[tw] = reinterpret_cast<uint64_t>(s32);
+                s_dst[tw] = reinterpret_cast<uint64_t>(d32 + kAhead * kSub);
+                s_nw[tw] = nw - kAhead * kSub;
+                s_sh[tw] = sh8;
+            }
+            if (sub < tail) dst[done + sub] = tb;
+        }
         if (ti + 1u == ntc)
             finish_chunk<DT, kSub>(slot, L, n, (uint64_t)P + cnt, dec_lo, dec_hi,
                                    a.chunk_bytes ? a.chunk_bytes + c : nullptr, sub);
     }
     __syncthreads();
     const uint32_t nbig = s_nbig;
-    for (uint32_t b = 0; b < nbig; ++b) {
-        const uint32_t k = s_big[b];
-        /* 8 words per lane: a whole tile (at most 2048 words) in one step */
-        move_words<8>(reinterpret_cast<uint32_t*>(s_dst[k]), reinterpret_cast<const uint32_t*>(s_src[k]), s_nw[k],
-                      s_sh[k], threadIdx.x, kThreads);
-    }
+    /* all four waves on a single tile, two on each of two or three, one on each of more; 8 words per lane and step (16 tiles
+       of nothing but zero-points one after the other: 2^20 values 49.8 us, 36.4 a wave each) */
+    const uint32_t wave = threadIdx.x >> 6;
+    auto move = [&](auto waves) {
+        constexpr uint32_t per = decltype(waves)::value;
+        for (uint32_t b = wave / per; b < nbig; b += kWavesPerBlock / per) {
+            const uint32_t k = s_big[b];
+            move_words<8>(reinterpret_cast<uint32_t*>(s_dst[k]), reinterpret_cast<const uint32_t*>(s_src[k]), s_nw[k],
+                          s_sh[k], (wave % per) * 64u + lane_id(), per * 64u);
+        }
+    };
+    if (nbig == 1u) move(std::integral_constant<uint32_t, 4>{});
+    else if (nbig <= 3u) move(std::integral_constant<uint32_t, 2>{});
+    else move(std::integral_constant<uint32_t, 1>{});
 }
 
 /*
