@@ -5,7 +5,7 @@
  *              section 4.2 re-designed for wave64: one wave handles a group of 512 values,
  *              8 values per lane (consecutive: one 16-byte load for bf16; whole fp32 groups: two
  *              quads, one from each half of the group, one 16-byte load each), a workgroup of
- *              4 waves handles a tile of 16 groups.  Per lane the work is SWAR on packed
+ *              8 or 16 waves handles a tile of 16 groups.  Per lane the work is SWAR on packed
  *              words: v_perm_b32 gathers the sign/mantissa and exponent bytes, packed 16-bit
  *              sub/min produce the codes, v_dot4_u32_u8 transposes code bits into plane bytes.
  *              Plane bytes and zero-point exponents are staged in LDS and leave as wide
@@ -189,15 +189,16 @@ __device__ __forceinline__ uint32_t count8(const uint32_t w[4], uint32_t first, 
     return cnt;
 }
 
-/* The groups of a wave are four apart in the tile, which shares a short tile evenly among the waves (neighbours instead:
+/* The groups of a wave are WAVES apart in the tile, which shares a short tile evenly among the waves (neighbours instead:
  * 64 chunks of 65 531 bf16 values 12.0 against 10.6 us, whole tiles 1 % slower). */
-__device__ __forceinline__ uint32_t group_of(uint32_t wave, uint32_t u) { return u * kWavesPerBlock + wave; }
+template <uint32_t WAVES>
+__device__ __forceinline__ uint32_t group_of(uint32_t wave, uint32_t u) { return u * WAVES + wave; }
 
 struct CompressShared {
     uint8_t planes[3][kTile / 8];          /* plane bytes of the tile, natural order */
     uint8_t esc[kGroupsPerTile][kGroup];   /* zero-point exponents, one region per group */
     uint32_t gcnt[kGroupsPerTile];         /* zero-points per group */
-    uint32_t before[kWavesPerBlock];       /* kModeDirect: zero-points a wave counted in the tiles before */
+    uint32_t before[kGroupsPerTile];       /* kModeDirect: zero-points a wave counted in the tiles before */
 };
 
 /* One group of one wave, its values already loaded (load_lane): encode, store SM/LO, stage planes and
@@ -351,11 +352,14 @@ __device__ __forceinline__ void table_words(const CompressIo& a, uint32_t c, uin
     }
 }
 
-template <int DT, int MODE, class PARK, class SPLIT>
-__global__ __launch_bounds__(kThreads) void k_compress(const CompressIo a, const PARK park, const SPLIT split)
+/* WAVES (8 or 16, see kWideTiles) share a tile: with four, of four groups each, 2^29 bf16 values took 4 % longer, and in launches
+ * that leave most of the chip empty a wave's encodes came one after the other (32 x 4096 values 4.5 us, 3.8 with 16). */
+template <int DT, int MODE, uint32_t WAVES, class PARK, class SPLIT>
+__global__ __launch_bounds__(64u * WAVES) void k_compress(const CompressIo a, const PARK park, const SPLIT split)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
     constexpr bool STORE = MODE != kModeCount;
+    constexpr uint32_t GPW = kGroupsPerTile / WAVES;
     __shared__ CompressShared sh;
 
     /* grid = (tiles of the largest chunk, chunks): no search, the chunk's geometry is three scalar loads at most */
@@ -376,9 +380,9 @@ __global__ __launch_bounds__(kThreads) void k_compress(const CompressIo a, const
     const uint32_t e0 = (dec_lo >> 8) & 0xFFu;
     const uint32_t k7 = ((e0 - 1u) << 7) * 0x00010001u;
 
-    /* all four groups' loads go out before the first is encoded: four times the bytes in flight per
-       wave, and no wait for a load ever includes the stores of the group before */
-    uint32_t hp[kGroupsPerWave][4], lp[kGroupsPerWave][4], vm[kGroupsPerWave];
+    /* all of the wave's loads go out before its first group is encoded: more bytes in flight, and no wait for a load ever
+       includes the stores of the group before */
+    uint32_t hp[GPW][4], lp[GPW][4], vm[GPW];
     /* kModeDirect: the zero-points of the chunk's tiles before this one, which are few, whole, and read by other
        workgroups too; two tiles' loads in flight together, while the tile's own travel */
     auto count_before = [&] {
@@ -386,15 +390,15 @@ __global__ __launch_bounds__(kThreads) void k_compress(const CompressIo a, const
         const uint32_t first = e0 * 0x00800080u;
         uint32_t cnt = 0;
         for (uint32_t b = 0; b < blockIdx.x; b += 2) {
-            uint32_t h[2][kGroupsPerWave][4], l[4], m;
+            uint32_t h[2][GPW][4], l[4], m;
 #pragma unroll
             for (uint32_t k = 0; k < 2; ++k)
 #pragma unroll
-                for (uint32_t u = 0; u < kGroupsPerWave; ++u)
-                    load_lane<DT, kWhole>(cin, (uint64_t)min(b + k, blockIdx.x - 1u) * kTile + group_of(wave, u) * kGroup, lane, n, h[k][u], l, m);
+                for (uint32_t u = 0; u < GPW; ++u)
+                    load_lane<DT, kWhole>(cin, (uint64_t)min(b + k, blockIdx.x - 1u) * kTile + group_of<WAVES>(wave, u) * kGroup, lane, n, h[k][u], l, m);
             uint32_t second = 0;
 #pragma unroll
-            for (uint32_t u = 0; u < kGroupsPerWave; ++u) {
+            for (uint32_t u = 0; u < GPW; ++u) {
                 cnt = count8(h[0][u], first, cnt);
                 second = count8(h[1][u], first, second);
             }
@@ -405,36 +409,36 @@ __global__ __launch_bounds__(kThreads) void k_compress(const CompressIo a, const
     };
     if (fast) {
 #pragma unroll
-        for (uint32_t u = 0; u < kGroupsPerWave; ++u)
-            load_lane<DT, kWhole>(cin, ts + (uint64_t)group_of(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u]);
+        for (uint32_t u = 0; u < GPW; ++u)
+            load_lane<DT, kWhole>(cin, ts + (uint64_t)group_of<WAVES>(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u]);
         count_before();
 #pragma unroll
-        for (uint32_t u = 0; u < kGroupsPerWave; ++u)
-            compress_group<DT, true, STORE>(slot, L, n, ts, group_of(wave, u), k7, lane, sh, hp[u], lp[u], vm[u]);
+        for (uint32_t u = 0; u < GPW; ++u)
+            compress_group<DT, true, STORE>(slot, L, n, ts, group_of<WAVES>(wave, u), k7, lane, sh, hp[u], lp[u], vm[u]);
     } else {
         if (n >= 8u) {
             /* every request before the first use of what one brings: left to itself the compiler waits for each of the
                four loads (fp32: for each four of eight) before the next (5000 bf16 values 4.9 -> 4.45 us, 8195 in two reads
                9.0 -> 8.2) */
             constexpr uint32_t NQ = DT == ZIPCCL_BF16 ? 1u : 2u;
-            u32x4 rest[kGroupsPerWave][NQ];
+            u32x4 rest[GPW][NQ];
 #pragma unroll
-            for (uint32_t u = 0; u < kGroupsPerWave; ++u)
+            for (uint32_t u = 0; u < GPW; ++u)
 #pragma unroll
-                for (uint32_t q = 0; q < NQ; ++q) rest[u][q] = request_rest<DT>(cin, ts + (uint64_t)group_of(wave, u) * kGroup, lane, n, q);
+                for (uint32_t q = 0; q < NQ; ++q) rest[u][q] = request_rest<DT>(cin, ts + (uint64_t)group_of<WAVES>(wave, u) * kGroup, lane, n, q);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (uint32_t u = 0; u < kGroupsPerWave; ++u)
-                load_lane<DT, kRest>(cin, ts + (uint64_t)group_of(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u], rest[u]);
+            for (uint32_t u = 0; u < GPW; ++u)
+                load_lane<DT, kRest>(cin, ts + (uint64_t)group_of<WAVES>(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u], rest[u]);
         } else {
 #pragma unroll
-            for (uint32_t u = 0; u < kGroupsPerWave; ++u)
-                load_lane<DT, kTiny>(cin, ts + (uint64_t)group_of(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u]);
+            for (uint32_t u = 0; u < GPW; ++u)
+                load_lane<DT, kTiny>(cin, ts + (uint64_t)group_of<WAVES>(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u]);
         }
         count_before();
 #pragma unroll
-        for (uint32_t u = 0; u < kGroupsPerWave; ++u)
-            compress_group<DT, false, STORE>(slot, L, n, ts, group_of(wave, u), k7, lane, sh, hp[u], lp[u], vm[u]);
+        for (uint32_t u = 0; u < GPW; ++u)
+            compress_group<DT, false, STORE>(slot, L, n, ts, group_of<WAVES>(wave, u), k7, lane, sh, hp[u], lp[u], vm[u]);
     }
     __syncthreads();
 
@@ -451,7 +455,7 @@ __global__ __launch_bounds__(kThreads) void k_compress(const CompressIo a, const
     /* kModeEmit and kModeDirect know the zero-points of the chunk before this tile; kModeStash works tile-local */
     uint32_t P = 0;
     if constexpr (MODE == kModeEmit) P = park.tile_prefix[place.tile + blockIdx.x];
-    if (MODE == kModeDirect) P = (sh.before[0] + sh.before[1]) + (sh.before[2] + sh.before[3]);
+    if (MODE == kModeDirect) P = __builtin_amdgcn_readlane(row_incl_scan(lane < WAVES ? sh.before[lane] : 0u), WAVES - 1u);
     const uint64_t ng = (n + kGroup - 1) / kGroup;
     uint32_t* __restrict__ idx = reinterpret_cast<uint32_t*>(slot + L.idx);
     uint8_t* __restrict__ esc = slot + L.esc + P;
@@ -461,7 +465,7 @@ __global__ __launch_bounds__(kThreads) void k_compress(const CompressIo a, const
         /* group index (section 4.2.3); k_place adds the tile's prefix in stash mode */
         const uint64_t g = ts / kGroup + lane;
         if (lane < kGroupsPerTile && g < ng) idx[g] = P + gex;
-    } else {
+    } else if (WAVES == 4u || wave < 4u) {
         /* waves 1..3: one plane each, 16 bytes per lane */
         const uint32_t k = wave - 1u;
         const uint64_t pb = ts / 8 + lane * 16u;
@@ -469,18 +473,23 @@ __global__ __launch_bounds__(kThreads) void k_compress(const CompressIo a, const
             st_stream<u32x4>((slot + L.p0 + k * L.plane_bytes + ts / 8) + lane * 16u,
                              *reinterpret_cast<const u32x4*>(&sh.planes[k][lane * 16u]));
     }
-    /* zero-point exponents: every wave copies the segments of its own groups, in element order */
+    /* zero-point exponents: every wave copies the segments of its own groups, in element order; of most groups there are no
+       more than 64, whose LDS reads go out together */
+    uint8_t first64[GPW];
 #pragma unroll
-    for (uint32_t u = 0; u < kGroupsPerWave; ++u) {
-        const uint32_t gi = group_of(wave, u);
+    for (uint32_t u = 0; u < GPW; ++u) first64[u] = sh.esc[group_of<WAVES>(wave, u)][lane];
+#pragma unroll
+    for (uint32_t u = 0; u < GPW; ++u) {
+        const uint32_t gi = group_of<WAVES>(wave, u);
         const uint32_t cnt = __builtin_amdgcn_readlane(gc, gi);
         uint8_t* dst = esc + __builtin_amdgcn_readlane(gex, gi);
+        if (lane < cnt) dst[lane] = first64[u];
 #pragma unroll 1
-        for (uint32_t i = lane; i < cnt; i += 64u) dst[i] = sh.esc[gi][i];
+        for (uint32_t i = lane + 64u; i < cnt; i += 64u) dst[i] = sh.esc[gi][i];
     }
 
     if ((MODE == kModeEmit || MODE == kModeDirect) && last_tile)
-        finish_chunk<DT, kThreads>(slot, L, n, (uint64_t)P + tile_total, dec_lo, dec_hi,
+        finish_chunk<DT, 64u * WAVES>(slot, L, n, (uint64_t)P + tile_total, dec_lo, dec_hi,
                                    a.chunk_bytes ? a.chunk_bytes + c : nullptr, threadIdx.x);
 }
 
@@ -726,15 +735,30 @@ int static_scratch(void** ptr, size_t* bytes)
 static CompressIo io_of(const CompressArgs& a) { return CompressIo{a.in, a.out, a.chunk_bytes, a.d_table, a.dec_lo, a.table_stride}; }
 static Parking parking_of(const CompressArgs& a) { return Parking{a.tile_total, a.tile_prefix, a.stash}; }
 
+/*
+ * Waves per tile: 16, one group each, for fp32, whose groups are two loads each, and in bf16 launches of up to this many
+ * tiles, where every wave beyond the first few has a SIMD of its own; 8 in larger bf16 launches, where 16 hold too
+ * few bytes in flight and 4 are slower from start to end.  us, 4 / 8 / 16 waves, bf16: 2^17 values in 8 chunks 4.5 / 4.0 / 3.8, 2^21
+ * 7.9 / 7.55 / 7.5, 9 * 2^18 8.2 / 7.9 / 8.1, 2^23 11.5 / 11.3 / 12.6, 2^29 in 64 315 / 303 / 382; fp32: 2^17 5.5 / 4.65 / 4.2, 2^23 17.1 /
+ * 16.5 / 16.4, 2^27 in 64 175 / 171 / 168.
+ */
+constexpr uint32_t kWideTiles = 256;
+template <int DT> constexpr uint32_t kManyWaves = DT == ZIPCCL_BF16 ? 8u : 16u;
+
 /* The smallest arguments that hold the split; the two-read kernels, whose calls are none of the small ones, take the table. */
 template <int DT>
 static void launch_compress_dt(int mode, const CompressArgs& a, hipStream_t s)
 {
-    const dim3 grid(max_chunk_tiles(a.tab), a.tab.n_chunks), block(kThreads);
+    const dim3 grid(max_chunk_tiles(a.tab), a.tab.n_chunks);
     const CompressIo io = io_of(a);
     const Parking park = parking_of(a);
     const bool equal = is_equal_split(a.tab);
-#define ZIPCCL_LAUNCH(MODE, PARK, P, SPLIT, S) hipLaunchKernelGGL((k_compress<DT, MODE, PARK, SPLIT>), grid, block, 0, s, io, P, S)
+    const bool many = DT == ZIPCCL_BF16 && a.tab.tile_start[a.tab.n_chunks] > kWideTiles;
+#define ZIPCCL_LAUNCH(MODE, PARK, P, SPLIT, S)                                                                         \
+    do {                                                                                                               \
+        if (many) hipLaunchKernelGGL((k_compress<DT, MODE, kManyWaves<DT>, PARK, SPLIT>), grid, dim3(64u * kManyWaves<DT>), 0, s, io, P, S); \
+        else hipLaunchKernelGGL((k_compress<DT, MODE, 16u, PARK, SPLIT>), grid, dim3(1024u), 0, s, io, P, S);          \
+    } while (0)
     if (mode == kModeDirect) {
         if (equal) ZIPCCL_LAUNCH(kModeDirect, NoParking, NoParking{}, EqualSplit, equal_split(a.tab));
         else if (is_few_split(a.tab)) ZIPCCL_LAUNCH(kModeDirect, NoParking, NoParking{}, FewSplit, few_split(a.tab));

@@ -14,7 +14,7 @@
 
 namespace zipccl {
 
-/* Work decomposition: a workgroup of 4 wave64 handles one TILE of 16 groups; a wave handles
+/* Work decomposition: a workgroup handles one TILE of 16 groups (of 4 waves, unless a kernel says otherwise); a wave handles
  * a group of 512 elements at a time, 8 consecutive elements per lane (one 16-byte bf16 load). */
 constexpr uint32_t kLaneElems = 8;
 constexpr uint32_t kGroup = ZIPCCL_GROUP;
