@@ -139,7 +139,7 @@ __device__ __forceinline__ uint32_t value_mask(uint64_t n, uint64_t gs, uint32_t
  * empty): no load is under a condition, so all groups' loads are in flight together.  The planes of a group that has
  * any value are there as a whole.
  */
-template <int DT, bool FAST>
+template <int DT, bool FAST, bool STREAM = true>
 __device__ __forceinline__ void decode_load(const uint8_t* __restrict__ slot, const SlotLayout& L, uint64_t n,
                                             uint64_t gstart, uint32_t lane, DecIn& r)
 {
@@ -153,21 +153,21 @@ __device__ __forceinline__ void decode_load(const uint8_t* __restrict__ slot, co
     const uint32_t pi = DT == ZIPCCL_BF16 ? lane : (lane >> 1) + 32u * (lane & 1u);
     const uint32_t ia = FAST || (r.vmask & 15u) ? lane * 4u : 0u, ib = FAST || (r.vmask >> 4) ? kGroup / 2 + lane * 4u : 0u;
     if (DT == ZIPCCL_BF16) {
-        const u32x2 v = ld_stream<u32x2>(sm + (FAST || r.vmask ? lane * 8u : 0u));
+        const u32x2 v = ld_as<STREAM, u32x2>(sm + (FAST || r.vmask ? lane * 8u : 0u));
         r.sm0 = v.x; r.sm1 = v.y;
     } else {
-        r.sm0 = ld_stream<uint32_t>(sm + ia);
-        r.sm1 = ld_stream<uint32_t>(sm + ib);
+        r.sm0 = ld_as<STREAM, uint32_t>(sm + ia);
+        r.sm1 = ld_as<STREAM, uint32_t>(sm + ib);
     }
     /* the planes before the low words: they are wanted first, and loads are waited for in order */
-    r.b0 = ld_stream<uint8_t>(pl + pi);
-    r.b1 = ld_stream<uint8_t>((pl + L.plane_bytes) + pi);
-    r.b2 = ld_stream<uint8_t>((pl + 2 * L.plane_bytes) + pi);
+    r.b0 = ld_as<STREAM, uint8_t>(pl + pi);
+    r.b1 = ld_as<STREAM, uint8_t>((pl + L.plane_bytes) + pi);
+    r.b2 = ld_as<STREAM, uint8_t>((pl + 2 * L.plane_bytes) + pi);
     r.lo[0] = r.lo[1] = r.lo[2] = r.lo[3] = 0;
     if (DT == ZIPCCL_FP32) {
         const uint8_t* __restrict__ lo = slot + L.lo + 2 * gs;
-        const u32x2 la = ld_stream<u32x2>(lo + 2u * ia);
-        const u32x2 lb = ld_stream<u32x2>(lo + 2u * ib);
+        const u32x2 la = ld_as<STREAM, u32x2>(lo + 2u * ia);
+        const u32x2 lb = ld_as<STREAM, u32x2>(lo + 2u * ib);
         r.lo[0] = la.x; r.lo[1] = la.y; r.lo[2] = lb.x; r.lo[3] = lb.y;
     }
 }
@@ -378,7 +378,7 @@ struct DecompressIo {
 
 /* GPW (1, 2 or 4) groups per wave: a workgroup decodes a tile of 4 * GPW groups.  The compressed format does not know
  * tiles (groups are located through IDX alone), so this is free to differ from the compress side's tile. */
-template <int DT, uint32_t GPW, class SPLIT>
+template <int DT, uint32_t GPW, bool STREAM, class SPLIT>
 /* waves per SIMD: 8 (<= 64 VGPRs); launches with four fp32 groups per wave hold no more than 4 */
 __global__ __launch_bounds__(kThreads, DT == ZIPCCL_FP32 && GPW == 4u ? 4 : 8)
 void k_decompress(const DecompressIo a, const SPLIT split)
@@ -424,10 +424,10 @@ void k_decompress(const DecompressIo a, const SPLIT split)
         const uint32_t* __restrict__ idx = reinterpret_cast<const uint32_t*>(slot + L.idx);
         if (fast) {
 #pragma unroll
-            for (uint32_t u = 0; u < GPW; ++u) decode_load<DT, true>(slot, L, n, gs0 + (uint64_t)(u * step) * kGroup, lane, in[u]);
+            for (uint32_t u = 0; u < GPW; ++u) decode_load<DT, true, STREAM>(slot, L, n, gs0 + (uint64_t)(u * step) * kGroup, lane, in[u]);
         } else {
 #pragma unroll
-            for (uint32_t u = 0; u < GPW; ++u) decode_load<DT, false>(slot, L, n, gs0 + (uint64_t)(u * step) * kGroup, lane, in[u]);
+            for (uint32_t u = 0; u < GPW; ++u) decode_load<DT, false, STREAM>(slot, L, n, gs0 + (uint64_t)(u * step) * kGroup, lane, in[u]);
         }
 #pragma unroll
         for (uint32_t u = 0; u < GPW; ++u) {
@@ -1288,7 +1288,7 @@ __global__ __launch_bounds__(64u * S * G) void k_reduce_split(const SplitArgs a)
 
 } // namespace
 
-template <int DT, uint32_t GPW>
+template <int DT, uint32_t GPW, bool STREAM = true>
 static int launch_decompress_gpw(const DecompressArgs& a, hipStream_t s)
 {
     constexpr uint64_t TILE = (uint64_t)kGroup * kWavesPerBlock * GPW;
@@ -1299,9 +1299,9 @@ static int launch_decompress_gpw(const DecompressArgs& a, hipStream_t s)
     }
     const dim3 grid((uint32_t)tiles, a.tab.n_chunks), block(kThreads);
     const DecompressIo io = {a.comp, a.comp_capacity, a.out, a.status};
-    if (is_equal_split(a.tab)) hipLaunchKernelGGL((k_decompress<DT, GPW, EqualSplit>), grid, block, 0, s, io, equal_split(a.tab));
-    else if (GPW < 4u && is_few_split(a.tab)) hipLaunchKernelGGL((k_decompress<DT, GPW, FewSplit>), grid, block, 0, s, io, few_split(a.tab));
-    else hipLaunchKernelGGL((k_decompress<DT, GPW, ChunkTab>), grid, block, 0, s, io, a.tab);
+    if (is_equal_split(a.tab)) hipLaunchKernelGGL((k_decompress<DT, GPW, STREAM, EqualSplit>), grid, block, 0, s, io, equal_split(a.tab));
+    else if (GPW < 4u && is_few_split(a.tab)) hipLaunchKernelGGL((k_decompress<DT, GPW, STREAM, FewSplit>), grid, block, 0, s, io, few_split(a.tab));
+    else hipLaunchKernelGGL((k_decompress<DT, GPW, STREAM, ChunkTab>), grid, block, 0, s, io, a.tab);
     return (int)hipGetLastError();
 }
 
@@ -1317,7 +1317,13 @@ static int launch_decompress_gpw(const DecompressArgs& a, hipStream_t s)
  * fp32 these are the ones that end at 6 and at 8 * 2^20.  Four only where the chunks start on line boundaries (64 chunks of
  * 131 073 bf16 values 7.9 us with two neighbouring groups, 8.3 with four), and below 5 * 2^20 bf16 values not for many
  * chunks with rests (128 chunks of 37 824 values 6 % slower with four).
+ *
+ * Launches of four groups on 21 to 40 MiB of values do not stream their loads: what is read of several such buffers
+ * then stays in the last-level cache.  us, streamed / plain, with 1, 3, 5 and 12 sets of buffers in turn: 2^24 bf16 values 11.0 / 11.1, 12.7 /
+ * 11.4, 12.9 / 11.1, 13.0 / 12.9; 11 * 2^19 fp32 8.2 / 8.1, 9.6 / 8.4, 9.9 / 8.3, 10.2 / 8.8.  Smaller launches lose up to a tenth (2^23
+ * bf16, 5 sets, 6.2 / 6.9), larger ones 2 to 5 %.
  */
+constexpr uint64_t kPlainFrom = 21ull << 19;
 int launch_decompress(int dt, const DecompressArgs& a, void* stream)
 {
     const uint64_t n = a.tab.elem_off[a.tab.n_chunks] - a.tab.elem_off[0];
@@ -1331,12 +1337,13 @@ int launch_decompress(int dt, const DecompressArgs& a, void* stream)
     if (dt == ZIPCCL_FP32) {
         if (n < (2ull << 20)) return launch_decompress_gpw<ZIPCCL_FP32, 1>(a, s);
         const bool four = (n > (5ull << 20) && n <= (6ull << 20)) || (n > (29ull << 18) && n <= (8ull << 20));
-        return lines && four ? launch_decompress_gpw<ZIPCCL_FP32, 4>(a, s) : launch_decompress_gpw<ZIPCCL_FP32, 2>(a, s);
+        return lines && four ? launch_decompress_gpw<ZIPCCL_FP32, 4, false>(a, s) : launch_decompress_gpw<ZIPCCL_FP32, 2>(a, s);
     }
     if (n < (1ull << 20)) return launch_decompress_gpw<ZIPCCL_BF16, 1>(a, s);
     const bool few_rests = a.tab.n_chunks <= 64u || ends % kTile == 0;
     const bool four = n < (20ull << 20) && (n > (5ull << 20) || (n > (4ull << 20) && few_rests));
-    return lines && four ? launch_decompress_gpw<ZIPCCL_BF16, 4>(a, s) : launch_decompress_gpw<ZIPCCL_BF16, 2>(a, s);
+    if (!lines || !four) return launch_decompress_gpw<ZIPCCL_BF16, 2>(a, s);
+    return n > kPlainFrom ? launch_decompress_gpw<ZIPCCL_BF16, 4, false>(a, s) : launch_decompress_gpw<ZIPCCL_BF16, 4>(a, s);
 }
 
 

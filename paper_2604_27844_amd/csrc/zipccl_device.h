@@ -25,6 +25,8 @@ typedef uint32_t u32_a2 __attribute__((aligned(2)));
 /* streaming accesses: every tensor byte is touched once, so keep it out of the way of the caches */
 template <typename T>
 __device__ __forceinline__ T ld_stream(const void* p) { return __builtin_nontemporal_load(static_cast<const T*>(p)); }
+template <bool STREAM, typename T>
+__device__ __forceinline__ T ld_as(const void* p) { return STREAM ? ld_stream<T>(p) : *static_cast<const T*>(p); }
 template <typename T>
 __device__ __forceinline__ void st_stream(void* p, T v) { __builtin_nontemporal_store(v, static_cast<T*>(p)); }
 __device__ __forceinline__ void st_stream_a4(void* p, u32x4 v) { __builtin_nontemporal_store(v, static_cast<u32x4_a4*>(p)); }
