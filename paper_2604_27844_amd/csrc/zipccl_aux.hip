@@ -49,20 +49,27 @@ __device__ __forceinline__ double value_at(const uint8_t* in, uint64_t i)
  * is not finite): sum d^2 - (sum d)^2 / N then cancels only as far as the pivot is from the mean, not as far
  * as the mean is from zero.  Every workgroup writes its partial sums; k_estimate_finish adds the partials in a
  * fixed order, forms sigma, and picks the window (table_from_sigma).
+ *
+ * Large tensors are bound by reading (2^29 bf16 values 166 us, 6.5 TB/s), with one streamed load in flight per thread: with four the call takes
+ * 5 % longer.  Up to 64 MiB, where ramps and latencies count, a thread has four loads in flight and does not stream, so that
+ * the compress that usually follows finds the tensor in the caches, and workgroups take 4096 values instead of 16384 until
+ * there are 2048.  us, before / after, the call: bf16 2^17 6.7 / 5.8, 2^20 6.8 / 5.9, 2^24 12.5 / 11.5, with the compress 28.7 / 26.5; fp32 2^20
+ * 7.6 / 5.8, 2^22 10.7 / 8.5, with the compress 24.3 / 19.2.  The 16-byte loads are issued at the tensor's own alignment, which the
+ * hardware takes (value by value off a 16-byte boundary: 2^24 bf16 values 25 us, 10.6 now; 2^26 51, 31).
  */
-template <int DT>
+template <int DT, bool STREAM>
 __global__ __launch_bounds__(kThreads) void k_moments(const MomentArgs a)
 {
+    constexpr uint32_t NF = STREAM ? 1u : 4u;          /* pieces in flight per thread */
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
     constexpr uint32_t PER16 = 16u / ES;               /* values per 16-byte load */
     __shared__ double s_sum[kWavesPerBlock], s_sq[kWavesPerBlock];
     double sum = 0.0, sq = 0.0;
     double pivot = a.n ? value_at<DT>(a.in, 0) : 0.0;
     if (!(fabs(pivot) < __longlong_as_double(0x7FF0000000000000ll))) pivot = 0.0;
-    const bool aligned = (reinterpret_cast<uintptr_t>(a.in) & 15u) == 0;
-    const uint64_t n16 = aligned ? a.n / PER16 : 0;    /* 16-byte pieces handled with vector loads */
-    for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < n16; i += (uint64_t)gridDim.x * kThreads) {
-        const u32x4 v = ld_stream<u32x4>(a.in + i * 16);
+    const uint64_t n16 = a.n / PER16, stride = (uint64_t)gridDim.x * kThreads;        /* 16-byte pieces */
+    auto load = [&](uint64_t i) { return STREAM ? ld_stream_a2(a.in + i * 16) : (u32x4)*reinterpret_cast<const u32x4_a2*>(a.in + i * 16); };
+    auto add = [&](const u32x4& v) {
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -75,10 +82,19 @@ __global__ __launch_bounds__(kThreads) void k_moments(const MomentArgs a)
                 sum += x; sq += x * x;
             }
         }
+    };
+    for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < n16; i += NF * stride) {
+        u32x4 v[NF];                                   /* past the end the first of them once more, not added */
+#pragma unroll
+        for (uint32_t u = 0; u < NF; ++u) v[u] = load(i + u * stride < n16 ? i + u * stride : i);
+#pragma unroll
+        for (uint32_t u = 0; u < NF; ++u)
+            if (i + u * stride < n16) add(v[u]);
     }
-    /* the tail (and everything, for a misaligned tensor) element by element */
-    for (uint64_t i = n16 * PER16 + (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < a.n; i += (uint64_t)gridDim.x * kThreads) {
-        const double x = value_at<DT>(a.in, i) - pivot;
+    /* fewer than 16 bytes are left */
+    const uint64_t tail = n16 * PER16 + (uint64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (tail < a.n) {
+        const double x = value_at<DT>(a.in, tail) - pivot;
         sum += x; sq += x * x;
     }
     /* fixed-order reduction: lanes by butterfly, waves in order */
@@ -100,21 +116,32 @@ __global__ __launch_bounds__(kThreads) void k_moments(const MomentArgs a)
 
 __global__ __launch_bounds__(kThreads) void k_estimate_finish(const MomentArgs a)
 {
-    __shared__ double s_sum[kThreads], s_sq[kThreads];
-    double sum = 0.0, sq = 0.0;
-    for (uint32_t i = threadIdx.x; i < a.n_blocks; i += kThreads) { sum += a.partial[2 * i]; sq += a.partial[2 * i + 1]; }
-    s_sum[threadIdx.x] = sum;
-    s_sq[threadIdx.x] = sq;
-    __syncthreads();
-    for (uint32_t d = kThreads / 2; d >= 1; d >>= 1) {
-        if (threadIdx.x < d) { s_sum[threadIdx.x] += s_sum[threadIdx.x + d]; s_sq[threadIdx.x] += s_sq[threadIdx.x + d]; }
-        __syncthreads();
+    /* all of a thread's partial sums are requested together */
+    constexpr uint32_t PER = kMomentBlocks / kThreads;
+    __shared__ double s_sum[kWavesPerBlock], s_sq[kWavesPerBlock];
+    double p[PER][2], sum = 0.0, sq = 0.0;
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+        const uint32_t i = min(threadIdx.x + k * kThreads, a.n_blocks - 1u);
+        p[k][0] = a.partial[2 * i];
+        p[k][1] = a.partial[2 * i + 1];
     }
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k)
+        if (threadIdx.x + k * kThreads < a.n_blocks) { sum += p[k][0]; sq += p[k][1]; }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        sum += __shfl_xor(sum, d, 64);
+        sq += __shfl_xor(sq, d, 64);
+    }
+    if ((threadIdx.x & 63u) == 0) { s_sum[threadIdx.x >> 6] = sum; s_sq[threadIdx.x >> 6] = sq; }
+    __syncthreads();
     if (threadIdx.x >= 64) return;
     const double N = (double)a.n;
     double sigma = __longlong_as_double(0x7FF8000000000000ll);          /* NaN for fewer than two values */
     if (a.n >= 2) {
-        const double var = (s_sq[0] - s_sum[0] * s_sum[0] / N) / (N - 1.0);      /* sums of x - pivot */
+        const double ts = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]), tq = (s_sq[0] + s_sq[1]) + (s_sq[2] + s_sq[3]);
+        const double var = (tq - ts * ts / N) / (N - 1.0);                       /* sums of x - pivot */
         sigma = sqrt(var > 0.0 ? var : (var == var ? 0.0 : var));
     }
     table_from_sigma(sigma, a.table, a.sigma);
@@ -785,8 +812,11 @@ __global__ __launch_bounds__(kHistThreads) void k_window_finish(const RobustIo a
 int launch_estimate(int dt, const MomentArgs& a, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
-    if (dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_moments<ZIPCCL_BF16>), dim3(a.n_blocks), dim3(kThreads), 0, s, a);
-    else hipLaunchKernelGGL((k_moments<ZIPCCL_FP32>), dim3(a.n_blocks), dim3(kThreads), 0, s, a);
+    const bool stream_loads = a.n * (dt == ZIPCCL_BF16 ? 2u : 4u) > (64ull << 20);         /* see launch_window */
+    if (dt == ZIPCCL_BF16 && stream_loads) hipLaunchKernelGGL((k_moments<ZIPCCL_BF16, true>), dim3(a.n_blocks), dim3(kThreads), 0, s, a);
+    else if (dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_moments<ZIPCCL_BF16, false>), dim3(a.n_blocks), dim3(kThreads), 0, s, a);
+    else if (stream_loads) hipLaunchKernelGGL((k_moments<ZIPCCL_FP32, true>), dim3(a.n_blocks), dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL((k_moments<ZIPCCL_FP32, false>), dim3(a.n_blocks), dim3(kThreads), 0, s, a);
     if (hipGetLastError() != hipSuccess) return 1;
     hipLaunchKernelGGL(k_estimate_finish, dim3(1), dim3(kThreads), 0, s, a);
     return (int)hipGetLastError();

@@ -334,7 +334,7 @@ zipccl_status_t zipccl_estimate_table(const void* d_in, size_t n_elems, zipccl_d
     a.in = static_cast<const uint8_t*>(d_in);
     a.n = n_elems;
     a.partial = static_cast<double*>(d_workspace);
-    const uint64_t want = (n_elems + 16383) / 16384;             /* about 64 values per thread at least */
+    const uint64_t want = (n_elems + 4095) / 4096;               /* about 16 values per thread at least */
     a.n_blocks = (uint32_t)(want < 1 ? 1 : (want > kMomentBlocks ? kMomentBlocks : want));
     a.table = reinterpret_cast<uint8_t*>(d_table);
     a.sigma = d_sigma;

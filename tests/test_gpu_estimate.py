@@ -92,7 +92,7 @@ def test_estimate_edge_cases():
     for label, x in cases.items():
         dec, s = osg.estimate_table(x, z.BF16)
         d_in = to_device_words(x)
-        # a view that starts 2 bytes into an allocation: the element-wise path
+        # a view that starts 2 bytes into an allocation
         d_off = torch.zeros(x.size + 1, dtype=torch.int16, device=DEV)
         d_off[1:] = d_in
         for d in (d_in, d_off[1:]):
@@ -102,6 +102,23 @@ def test_estimate_edge_cases():
                 assert math.isnan(got_s), label
             else:
                 assert got_s == pytest.approx(s, rel=1e-10, abs=1e-300), label
+
+
+@pytest.mark.parametrize("dtype", [z.BF16, z.FP32])
+@pytest.mark.parametrize("n", [3, 7, 8, 9, 4095, 4096, 4097, 4 * 4096 + 13, 2048 * 4096 - 1, 2048 * 4096 + 5, 3 * 2048 * 4096 + 7, (1 << 25) + 3])
+def test_estimate_at_the_edges_of_pieces_and_workgroups(dtype, n):
+    """Remainders of a 16-byte piece, of a thread's pieces in flight and of the grid, at every alignment of the start."""
+    rng = np.random.default_rng(n)
+    x = (rng.standard_normal(n, dtype=np.float32) * np.float32(0.3) + np.float32(0.7)).astype(np.float32)
+    words = W.f32_to_bf16_words(x) if dtype == z.BF16 else x.view(np.uint32)
+    dec, s = osg.estimate_table(words, dtype)
+    d_in = to_device_words(words)
+    for off in (0, 1, 2, 3):
+        d = torch.full((n + 8,), -1, dtype=d_in.dtype, device=DEV)                # NaNs around it
+        d[off:off + n] = d_in
+        _, got_dec, got_s = _estimate(d[off:off + n], n, dtype)
+        assert got_s == pytest.approx(s, rel=1e-10), off
+        assert got_dec == list(dec) or not _away_from_boundary(s)
 
 
 def test_plain_estimate_far_from_zero_mean_does_not_cancel():
