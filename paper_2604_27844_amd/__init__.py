@@ -1,7 +1,7 @@
 """MI355X-native ZipCCL exponent-coding codec (compress / decompress hot path).
 
 The product is ``libzipccl.so`` (HIP kernels for gfx950 behind a C ABI, see
-``include/zipccl.h``).  ``binding`` is a thin ctypes layer with the same names.
+``include/zipccl.h``).  ``binding`` has the same names: argument marshalling only.
 ``workloads`` holds only seeded input generators.
 """
 
