@@ -118,10 +118,12 @@ def _host_array(chunk_elems):
     return np.ascontiguousarray(np.asarray(chunk_elems, dtype=np.uint64))
 
 
-def _host_u64(chunk_elems):
+def _host_u64(chunk_elems, n_chunks):
     if chunk_elems is None:
         return None, None
     a = _host_array(chunk_elems)
+    if a.size < int(n_chunks):
+        raise ValueError(f"{a.size} element counts for {int(n_chunks)} chunks")
     return a, a.__array_interface__["data"][0]
 
 
@@ -168,12 +170,12 @@ def zipccl_build_table(sigma, dt=BF16):
 
 
 def zipccl_max_compressed_size(n_elems, dt, n_chunks=1, chunk_elems=None):
-    _keep, p = _host_u64(chunk_elems)
+    _keep, p = _host_u64(chunk_elems, n_chunks)
     return int(_lib.zipccl_max_compressed_size(int(n_elems), dt, int(n_chunks), p))
 
 
 def zipccl_chunk_slot_offsets(n_elems, dt, n_chunks=1, chunk_elems=None):
-    _keep, p = _host_u64(chunk_elems)
+    _keep, p = _host_u64(chunk_elems, n_chunks)
     off = np.zeros(int(n_chunks) + 1, dtype=np.uint64)
     rc = _lib.zipccl_chunk_slot_offsets(int(n_elems), dt, int(n_chunks), p, off.ctypes.data_as(ctypes.c_void_p))
     if rc:
@@ -182,12 +184,12 @@ def zipccl_chunk_slot_offsets(n_elems, dt, n_chunks=1, chunk_elems=None):
 
 
 def zipccl_compress_workspace_size(n_elems, dt, n_chunks=1, chunk_elems=None):
-    _keep, p = _host_u64(chunk_elems)
+    _keep, p = _host_u64(chunk_elems, n_chunks)
     return int(_lib.zipccl_compress_workspace_size(int(n_elems), dt, int(n_chunks), p))
 
 
 def zipccl_compress_min_workspace_size(n_elems, dt, n_chunks=1, chunk_elems=None):
-    _keep, p = _host_u64(chunk_elems)
+    _keep, p = _host_u64(chunk_elems, n_chunks)
     return int(_lib.zipccl_compress_min_workspace_size(int(n_elems), dt, int(n_chunks), p))
 
 
@@ -301,7 +303,7 @@ def zipccl_compress_device_table(d_in, n_elems, dt, n_chunks, chunk_elems, d_tab
 
 
 def zipccl_chunk_static_bytes(n_elems, dt, n_chunks=1, chunk_elems=None):
-    _keep, p = _host_u64(chunk_elems)
+    _keep, p = _host_u64(chunk_elems, n_chunks)
     out = np.zeros(int(n_chunks), dtype=np.uint64)
     rc = _lib.zipccl_chunk_static_bytes(int(n_elems), dt, int(n_chunks), p, out.ctypes.data_as(ctypes.c_void_p))
     if rc:

@@ -140,17 +140,22 @@ bool as_table(PyObject* o, View& view, const zipccl_table_t** p)
     return true;
 }
 
-/* element counts: None, or a C-contiguous array of uint64; anything else is made one first */
-bool as_counts(PyObject* o, View& view, const uint64_t** p)
+/* element counts, one per chunk at least: None, or a C-contiguous array of uint64; anything else is made one first */
+bool as_counts(PyObject* o, uint32_t chunks, View& view, const uint64_t** p)
 {
     *p = nullptr;
     if (o == Py_None) return true;
-    if (PyObject_CheckBuffer(o) && PyObject_GetBuffer(o, &view.b, PyBUF_C_CONTIGUOUS | PyBUF_FORMAT) == 0) {
-        const char* f = view.b.format;
-        if (view.b.itemsize == 8 && f && (f[0] == 'L' || f[0] == 'Q') && f[1] == 0) {
+    auto all_there = [&] {
+        if ((uint64_t)view.b.len / 8u >= chunks) {
             *p = static_cast<const uint64_t*>(view.b.buf);
             return true;
         }
+        PyErr_Format(PyExc_ValueError, "%zd element counts for %u chunks", view.b.len / 8, (unsigned)chunks);
+        return false;
+    };
+    if (PyObject_CheckBuffer(o) && PyObject_GetBuffer(o, &view.b, PyBUF_C_CONTIGUOUS | PyBUF_FORMAT) == 0) {
+        const char* f = view.b.format;
+        if (view.b.itemsize == 8 && f && (f[0] == 'L' || f[0] == 'Q') && f[1] == 0) return all_there();
         PyBuffer_Release(&view.b);
     }
     PyErr_Clear();
@@ -158,9 +163,7 @@ bool as_counts(PyObject* o, View& view, const uint64_t** p)
     if (!a) return false;
     const int rc = PyObject_GetBuffer(a, &view.b, PyBUF_C_CONTIGUOUS);        /* keeps the array */
     Py_DECREF(a);
-    if (rc != 0) return false;
-    *p = static_cast<const uint64_t*>(view.b.buf);
-    return true;
+    return rc == 0 && all_there();
 }
 
 bool as_bytes(PyObject* o, uint64_t* bytes)          /* None: leave what the buffer holds */
@@ -183,7 +186,7 @@ struct Shape {
 
     bool read(PyObject* n_, PyObject* dt_, PyObject* chunks_, PyObject* counts_)
     {
-        return as_u64(n_, &n) && as_int(dt_, &dt) && as_u64(chunks_, &chunks) && as_counts(counts_, counts_view, &counts);
+        return as_u64(n_, &n) && as_int(dt_, &dt) && as_u64(chunks_, &chunks) && as_counts(counts_, (uint32_t)chunks, counts_view, &counts);
     }
 };
 

@@ -160,3 +160,18 @@ def test_calls_on_device_buffers_check_their_arguments_before_the_library_is_cal
     with pytest.raises(z.ZipcclError) as ei:
         z.zipccl_compress_static(None, 0, 7, np.uint32(1), None, t, None, None, stream=0, out_capacity=0)
     assert ei.value.code == 2
+
+
+def test_fewer_element_counts_than_chunks_are_refused():
+    """The library reads one count per chunk; every call that takes counts says so before it reads past their end."""
+    t = z.zipccl_build_table(1.0)
+    for counts in (np.array([16], dtype=np.uint64), np.zeros(0, dtype=np.uint64), [16], np.arange(8, dtype=np.uint64)[::4]):
+        for call in (lambda: z.zipccl_max_compressed_size(16, z.BF16, 3, counts), lambda: z.zipccl_chunk_slot_offsets(16, z.BF16, 3, counts),
+                     lambda: z.zipccl_chunk_static_bytes(16, z.BF16, 3, counts),
+                     lambda: z.zipccl_compress_workspace_size(16, z.BF16, 3, counts), lambda: z.zipccl_compress_min_workspace_size(16, z.BF16, 3, counts),
+                     lambda: z.zipccl_compress(None, 16, z.BF16, 3, counts, t, None, None, None, stream=0, out_capacity=0, workspace_bytes=0),
+                     lambda: z.zipccl_compress_static(None, 16, z.BF16, 3, counts, t, None, None, stream=0, out_capacity=0),
+                     lambda: z.zipccl_decompress(None, None, 16, z.BF16, 3, counts, stream=0, comp_capacity=0)):
+            with pytest.raises(ValueError, match="element counts for 3 chunks"):
+                call()
+    assert z.zipccl_max_compressed_size(16, z.BF16, 1, [16, 5]) == z.zipccl_max_compressed_size(16, z.BF16, 1)     # more than that are not looked at
