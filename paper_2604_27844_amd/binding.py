@@ -1,14 +1,15 @@
 """Binding of libzipccl.so: same names as include/zipccl.h, argument marshalling only.  The calls that work on device
-buffers go through zipccl_python.so (csrc/zipccl_python.cpp), the others through ctypes.
+buffers go through the module zipccl_python (csrc/zipccl_python.cpp), the others through ctypes.
 
 Device buffers are torch tensors (PyTorch-ROCm owns memory and streams); every step of the
 path runs in the library's HIP kernels.  There is no fallback: a missing library is an error.
 """
 import ctypes
+import importlib.util
 import os
 
 import numpy as np
-import torch                    # zipccl_python.so looks into its tensors
+import torch                    # zipccl_python looks into its tensors
 
 from . import build_lib
 
@@ -97,9 +98,12 @@ def _load():
 
 
 def _load_native():
-    if not os.path.exists(build_lib.PYTHON):
-        build_lib.build(lib=build_lib.PYTHON)
-    from . import zipccl_python
+    path = build_lib.python_module()
+    if not os.path.exists(path):
+        build_lib.build(lib=path)
+    spec = importlib.util.spec_from_file_location(__package__ + ".zipccl_python", path)
+    zipccl_python = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(zipccl_python)
     zipccl_python.setup(zipccl_table_t, _host_array, _raw_stream_functions)
     return zipccl_python
 

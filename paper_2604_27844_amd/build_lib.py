@@ -1,5 +1,5 @@
 """Build libzipccl.so (the codec) and libzipccl_yardstick.so (the benchmark's plain-copy kernel) in-tree with
-hipcc for gfx950 (cross-compiles without a GPU), and zipccl_python.so (the binding's calls) with the host compiler."""
+hipcc for gfx950 (cross-compiles without a GPU), and the module zipccl_python (the binding's calls) with the host compiler."""
 import os
 import subprocess
 import sysconfig
@@ -9,20 +9,29 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libzipccl.so")
 YARDSTICK = os.path.join(HERE, "libzipccl_yardstick.so")
-PYTHON = os.path.join(HERE, "zipccl_python.so")
 SOURCES = ["zipccl_compress.hip", "zipccl_decompress.hip", "zipccl_aux.hip", "zipccl_host.cpp"]
 HEADERS = [os.path.join(CSRC, "zipccl_internal.h"), os.path.join(CSRC, "zipccl_device.h"),
            os.path.join(ROOT, "include", "zipccl.h")]
 TARGETS = {LIB: [os.path.join(CSRC, s) for s in SOURCES],
-           YARDSTICK: [os.path.join(CSRC, "zipccl_yardstick.hip")],
-           PYTHON: [os.path.join(CSRC, "zipccl_python.cpp")]}
+           YARDSTICK: [os.path.join(CSRC, "zipccl_yardstick.hip")]}
+
+
+def python_module():
+    """The module's file.  Compiled in are this interpreter's object layouts and this torch's tensor layout, so both are in its
+    name: what was built for others is not found."""
+    import torch
+    return os.path.join(HERE, f"zipccl_python-torch{torch.__version__}{sysconfig.get_config_var('EXT_SUFFIX')}")
+
+
+def _sources(target):
+    return TARGETS.get(target) or [os.path.join(CSRC, "zipccl_python.cpp")]
 
 
 def stale(lib=LIB):
     if not os.path.exists(lib):
         return True
     t = os.path.getmtime(lib)
-    deps = TARGETS[lib] + HEADERS + [os.path.join(ROOT, "include", "zipccl_yardstick.h")]
+    deps = _sources(lib) + HEADERS + [os.path.join(ROOT, "include", "zipccl_yardstick.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 
@@ -43,16 +52,17 @@ def _python_command(sources, out):
 def build(force=True, verbose=False, lib=None):
     """Compile every target (or the one named); returns the codec library's path."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    for target, sources in TARGETS.items():
-        if (lib is not None and target != lib) or (not force and not stale(target)):
+    for target in [*TARGETS, python_module()] if lib is None else [lib]:
+        if not force and not stale(target):
             continue
+        sources = _sources(target)
         tmp = target + f".{os.getpid()}.tmp"
         cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                "-Wall", "-Wno-unused-command-line-argument",
                "-I", os.path.join(ROOT, "include"), "-I", CSRC]
         cmd += sources + ["-o", tmp]
-        if target == PYTHON:
+        if target not in TARGETS:
             cmd = _python_command(sources, tmp)
         if verbose:
             print(" ".join(cmd))

@@ -4,6 +4,8 @@ import ctypes
 import math
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -175,3 +177,26 @@ def test_fewer_element_counts_than_chunks_are_refused():
             with pytest.raises(ValueError, match="element counts for 3 chunks"):
                 call()
     assert z.zipccl_max_compressed_size(16, z.BF16, 1, [16, 5]) == z.zipccl_max_compressed_size(16, z.BF16, 1)     # more than that are not looked at
+
+
+def _run_python(code):
+    return subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+
+
+def test_a_module_built_for_another_torch_or_python_is_not_loaded():
+    """zipccl_python has torch's and the interpreter's layouts compiled in: what was built for others is neither found nor
+    loaded, a new one is built instead."""
+    for change in ("import torch; torch.__version__ = '0.0.0+other'",
+                   "import sysconfig; get = sysconfig.get_config_var; "
+                   "sysconfig.get_config_var = lambda name: '.cpython-39-x86_64-linux-gnu.so' if name == 'EXT_SUFFIX' else get(name)"):
+        r = _run_python(f"""
+{change}
+import paper_2604_27844_amd.build_lib as b
+def build(*a, **k):
+    print('built anew')
+    raise SystemExit(0)
+b.build = build
+import paper_2604_27844_amd.binding as z
+z.zipccl_decompress(None, None, 0, z.BF16, stream=0, comp_capacity=0)
+""")
+        assert r.returncode == 0 and r.stdout.split() == ["built", "anew"], r.stderr
