@@ -9,7 +9,11 @@ import importlib.util
 import os
 
 import numpy as np
-import torch                    # zipccl_python looks into its tensors
+
+try:
+    import torch                # zipccl_python looks into its tensors
+except ImportError:             # the calls that need no device need numpy alone
+    torch = None
 
 from . import build_lib
 
@@ -158,7 +162,16 @@ def _stream(stream):
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
-_native = _load_native()
+class _NotLoaded:
+    """Stands for zipccl_python where torch or the built module is not there: the first call on device buffers asks for both."""
+
+    def __getattr__(self, name):
+        global _native
+        _native = _load_native()
+        return getattr(_native, name)
+
+
+_native = _load_native() if torch is not None and os.path.exists(build_lib.python_module()) else _NotLoaded()
 
 
 def zipccl_status_string(code):

@@ -50,9 +50,16 @@ def _python_command(sources, out):
 
 
 def build(force=True, verbose=False, lib=None):
-    """Compile every target (or the one named); returns the codec library's path."""
+    """Compile every target (or the one named); returns the codec library's path.  Without torch the module, which only
+    takes its tensors, is left out."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    for target in [*TARGETS, python_module()] if lib is None else [lib]:
+    targets = [*TARGETS] if lib is None else [lib]
+    if lib is None:
+        try:
+            targets.append(python_module())
+        except ImportError:
+            pass
+    for target in targets:
         if not force and not stale(target):
             continue
         sources = _sources(target)

@@ -200,3 +200,23 @@ import paper_2604_27844_amd.binding as z
 z.zipccl_decompress(None, None, 0, z.BF16, stream=0, comp_capacity=0)
 """)
         assert r.returncode == 0 and r.stdout.split() == ["built", "anew"], r.stderr
+
+
+def test_calls_that_need_no_device_need_neither_torch_nor_the_module():
+    """Tables, sizes and the switcher with numpy alone, and where the module for device buffers cannot be built; a call on
+    device buffers then says what is missing."""
+    for missing, error in (("import sys; sys.modules['torch'] = None", "ImportError"),
+                           ("import paper_2604_27844_amd.build_lib as b; b.python_module = lambda: '/nonexistent/zipccl_python.so'; "
+                            "b.stop = lambda **k: (_ for _ in ()).throw(RuntimeError(k['lib'])); b.build = b.stop", "RuntimeError")):
+        r = _run_python(f"""
+{missing}
+import paper_2604_27844_amd.binding as z
+assert list(bytes(z.zipccl_build_table(1.0).dec)) == {[int(e) for e in oracle.build_table(1.0)]}
+assert z.zipccl_max_compressed_size(100, z.BF16, 2, [40, 60]) == z.zipccl_chunk_slot_offsets(100, z.BF16, 2, [40, 60])[-1]
+assert z.zipccl_switch_prefers_zipped(1.0, 1.0, 0.0, 1.0, 1.0, 1.0, 0.5)[0] == 1
+try:
+    z.zipccl_decompress(None, None, 0, z.BF16, stream=0, comp_capacity=0)
+except {error}:
+    print("refused")
+""")
+        assert r.returncode == 0 and r.stdout.split() == ["refused"], r.stderr
