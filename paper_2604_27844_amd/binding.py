@@ -251,6 +251,8 @@ def zipccl_switch_prefers_zipped(alpha_rs, beta_rs, alpha_a2a, beta_a2a, d_bytes
 
 
 def zipccl_fit_link_model(d_bytes, t_seconds):
+    if len(t_seconds) < len(d_bytes):
+        raise ValueError(f"{len(t_seconds)} times for {len(d_bytes)} sizes")
     d = (ctypes.c_double * len(d_bytes))(*d_bytes)
     t = (ctypes.c_double * len(t_seconds))(*t_seconds)
     a, b = ctypes.c_double(), ctypes.c_double()

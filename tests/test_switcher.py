@@ -59,3 +59,5 @@ def test_library_rejects_bad_arguments():
         z.zipccl_fit_link_model([1e6, 1e6], [1e-3, 2e-3])           # a single size: no slope
     with pytest.raises(z.ZipcclError):
         z.zipccl_fit_link_model([1e6], [1e-3])
+    with pytest.raises(ValueError):
+        z.zipccl_fit_link_model([1e6, 2e6, 3e6], [1e-3])            # the library reads a time for every size
