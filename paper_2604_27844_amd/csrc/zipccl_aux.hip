@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kThreads) void k_estimate_finish(const MomentArgs a
  * not depend on any order.  Three forms, the first two for one or more chunks at once (one table per chunk; the whole
  * tensor is one chunk):
  *   windowed k_window_count: a few workgroups per chunk; each looks for the median of the same small sample of the
- *            chunk, counts only the kWindow magnitudes around that one by one, and how many there are below and in all,
+ *            chunk, counts only a window of magnitudes around that one by one, and how many there are below and in all,
  *            and stores its own counts.  k_window_finish adds them up; if the rank lies in the window, as it does unless
  *            the sample misled, that gives the median, and if not, its workgroups count all magnitudes after all.
  *   small    k_robust_chunk_fused: one workgroup per chunk with a histogram of all 32768 magnitudes in its LDS.
@@ -276,7 +276,7 @@ struct RobustIo {
     uint8_t* table;                   /* 8 bytes per chunk */
     double* sigma;                    /* one per chunk; may be null */
     uint32_t stride;                  /* 1: every value counts; a power of two S: one group of 512 values per S groups */
-    uint32_t shared;                  /* windowed form: more than kFusedGroups groups to count in some chunk */
+    uint32_t shared;                  /* windowed form: see WindowPlan */
 };
 
 template <int DT>
@@ -495,22 +495,33 @@ __global__ __launch_bounds__(kHistThreads) void k_robust_chunk_fused(const Robus
  * What a workgroup of k_window_count leaves in its chunk's workspace, and behind the last of these, in the workspace's
  * second half, a histogram of 32-bit counts, zeroed, for the case that the window does not hold the rank.
  */
-constexpr uint32_t kWindow = 112;            /* magnitudes: 7/8 of an octave */
+constexpr uint32_t kNarrow = 112, kWide = 496;        /* magnitudes in the window: 7/8 of an octave, or nearly 4 octaves */
+template <uint32_t W>
 struct Partial {
-    uint32_t bins[kWindow];                  /* counts of the magnitudes lo, lo + 1, ... */
+    uint32_t bins[W];                        /* counts of the magnitudes lo, lo + 1, ... */
     uint32_t below, valid, inside, lo;       /* neither zero nor Inf/NaN: those below lo, all, those in the window */
     uint32_t arrived;                        /* first one: workgroups that have added to the histogram */
-    uint32_t unused[128 - kWindow - 5];
+    uint32_t unused[11];
 };
 constexpr uint32_t kPartialsBytes = kHistBytes / 2;
-static_assert(sizeof(Partial) * kHistBlocks <= kPartialsBytes && kMagBins * 4u <= kHistBytes - kPartialsBytes, "layout of a chunk's workspace");
+static_assert(sizeof(Partial<kNarrow>) * kHistBlocks <= kPartialsBytes && sizeof(Partial<kWide>) * kWideParts <= kPartialsBytes &&
+              kMagBins * 4u <= kHistBytes - kPartialsBytes, "layout of a chunk's workspace");
 
-/* The median of a sample of up to 1024 values of the chunk, up to 8 magnitudes low: 64 strata of equal length, 16
+/*
+ * The median of a sample of the chunk, up to 8 magnitudes low: up to 1024 values, 64 strata of equal length, 16
  * consecutive values at a hashed position of each (256 positions of four cost 64 chunks 1 to 2 us more: pages).  By 16 waves that
- * hold all of it and look at one threshold each, four bits of the result per step.  request() issues the loads, the
- * rest happens in find(). */
+ * hold all of it and look at one threshold each, four bits of the result per step.  request() issues the loads.
+ *
+ * Neighbours are often alike, and then such a sample weighs little more than its 64 positions, too little for the narrow window
+ * where rows differ much: with rows of 4096 normal values whose scales are log-normal, spread by e^1 / e^1.5 / e^2 / e^3, the rank was outside for
+ * 1 / 7 / 11 / 24 of 60 tensors of 512 rows, and everything was counted twice.  The sample shows it: the octave of its median and
+ * the two beside it hold 0.74 of its values if they are normal, 0.54 / 0.43 / 0.36 / 0.26 with such rows.  Below a half, request_one()
+ * takes 1024 values at 1024 places, after which none of these tensors misses.  That costs 2 to 3 us, as much as the
+ * second counts that it saves come to at 0.5 (us per call, tensors in turn, without / with: 2^20 bf16 values, e^2, 16.6 / 13.2; 2^24 31.5 / 20.1; 2^26
+ * 53.7 / 32.2; normal values 10.7 / 10.8, 16.9 / 17.0, 29.5 / 29.7).
+ */
 struct SampleMedian {
-    uint32_t w[2];                           /* four magnitudes of threads 0 .. 255; those that do not count are 0x7FFF */
+    uint32_t w[2];                           /* four magnitudes of a thread; those that do not count are 0x7FFF */
 
     template <int DT>
     __device__ __forceinline__ void request(const uint8_t* __restrict__ in, uint64_t n)
@@ -541,8 +552,18 @@ struct SampleMedian {
         }
     }
 
-    /* s_sample: 512 words, s_cnt: 2 x 16 words.  Called by all threads of the workgroup. */
-    __device__ __forceinline__ uint32_t find(uint32_t* s_sample, uint32_t* s_cnt, uint32_t wave, uint32_t lane)
+    /* One value of each thread, from the groups of 512 that will be counted, `whole` (not 0) of them, group_of(k) whole in the
+       chunk for every k < whole: a hashed one of each 1024th part of them, at a hashed place in it. */
+    template <int DT, class GROUP_OF>
+    __device__ __forceinline__ static uint32_t request_one(const uint8_t* __restrict__ in, uint32_t whole, GROUP_OF group_of)
+    {
+        const uint32_t t = threadIdx.x, hash = t * 2654435761u;
+        const uint32_t k = (uint32_t)(((uint64_t)((t << 16) | (hash >> 16)) * whole) >> 26);
+        const uint64_t e = (uint64_t)group_of(k) * kGroup + (hash & (kGroup - 1u));
+        return DT == ZIPCCL_BF16 ? *reinterpret_cast<const uint16_t*>(in + e * 2u) : *reinterpret_cast<const uint32_t*>(in + e * 4u) >> 16;
+    }
+
+    __device__ __forceinline__ void put(uint32_t* s_sample)
     {
         if (threadIdx.x < 256u) {
             u32x2 m;
@@ -554,6 +575,18 @@ struct SampleMedian {
             }
             *reinterpret_cast<u32x2*>(s_sample + 2u * threadIdx.x) = m;
         }
+    }
+
+    __device__ __forceinline__ static void put_one(uint32_t* s_sample, uint32_t value)
+    {
+        const uint32_t x = value & 0x7FFFu;
+        reinterpret_cast<uint16_t*>(s_sample)[threadIdx.x] = (uint16_t)(bin_counts(x) ? x : 0x7FFFu);
+    }
+
+    /* The median of what was put into s_sample (512 words); s_cnt: 2 x 16 words.  Called by all threads of the workgroup;
+       doubtful is the same in all of them. */
+    __device__ __forceinline__ static uint32_t find(const uint32_t* s_sample, uint32_t* s_cnt, uint32_t wave, uint32_t lane, bool& doubtful)
+    {
         __syncthreads();
         uint32_t x[8];
 #pragma unroll
@@ -561,21 +594,29 @@ struct SampleMedian {
             const u32x4 v = *reinterpret_cast<const u32x4*>(s_sample + 4u * (lane + 64u * q));
             x[4 * q] = v.x; x[4 * q + 1] = v.y; x[4 * q + 2] = v.z; x[4 * q + 3] = v.w;
         }
-        uint32_t base = 0, rank = 0;
+        auto below_limit = [&](uint32_t limit) {
+            uint32_t cnt = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) cnt += __popc(pk_sub_u16(x[k], limit * 0x00010001u) & 0x80008000u);
+            return cnt;
+        };
+        uint32_t base = 0, rank = 0, valid = 0;
 #pragma unroll
         for (uint32_t step = 0; step < 3; ++step) {
             const uint32_t shift = 11u - 4u * step;
-            /* the last wave counts all that count, once */
-            const uint32_t limit = (wave == 15u ? 0x7F80u : base + ((wave + 1u) << shift)) * 0x00010001u;
-            uint32_t cnt = 0;
-#pragma unroll
-            for (uint32_t k = 0; k < 8; ++k) cnt += __popc(pk_sub_u16(x[k], limit) & 0x80008000u);
+            /* the last wave counts all that count, once, and in the last step, which starts at the median's octave, those of the
+               three octaves around it */
+            const bool last = wave == 15u;
+            uint32_t cnt = below_limit(!last ? base + ((wave + 1u) << shift) : (step < 2u ? kFirstNonFinite : min(base + 256u, kFirstNonFinite)));
+            if (last && step == 2u) cnt -= below_limit(max(base, 128u) - 128u);
             cnt = wave_incl_scan(cnt);
             uint32_t* const s = s_cnt + 16u * (step & 1u);
             if (lane == 63u) s[wave] = cnt;
             __syncthreads();
             const uint32_t below = s[lane & 15u];
-            if (step == 0) rank = (__builtin_amdgcn_readlane(below, 15) - 1u) / 2u;
+            const uint32_t lasts = __builtin_amdgcn_readlane(below, 15);
+            if (step == 0) { valid = lasts; rank = (valid - 1u) / 2u; }
+            if (step == 2) doubtful = lasts * 2u < valid;
             base += (uint32_t)__popcll(__ballot(below <= rank) & 0x7FFFu) << shift;
         }
         return base;
@@ -585,14 +626,14 @@ struct SampleMedian {
 /*
  * Reading bounds it in large tensors (2^29 bf16 values: 172 us, 6.2 TB/s); 2^24 values take 10.7 us, of which the launch is 2, the
  * sample 1.5, reading from HBM alone would be 5 and the additions in LDS alone 4 (with 4 us less to flush and nothing to zero,
- * estimate and table 18.1 -> 15.5 us; 2^20: 14.2 -> 9.3).  Every value still costs an addition in LDS, but to 112 counters
- * instead of 32768: nothing large is zeroed, and a workgroup's counts are 512 bytes that it stores, where a histogram in
+ * estimate and table 18.1 -> 15.5 us; 2^20: 14.2 -> 9.3).  Every value still costs an addition in LDS, but to 112 or 496 counters
+ * instead of 32768: nothing large is zeroed, and a workgroup's counts are 512 bytes (or 2 KiB) that it stores, where a histogram in
  * memory took a kernel that zeroes it and 4 us of atomic additions from 256 workgroups to the same lines.  Values
  * outside the window are added to a counter of the lane's own, so that they neither branch nor collide.
  * grid = (workgroups per chunk, chunks).  STREAM: the tensor is too large to stay in the caches for the compress
  * that usually follows.
  */
-template <int DT, bool STREAM, class SPLIT>
+template <int DT, uint32_t W, bool STREAM, class SPLIT>
 __global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a, const SPLIT split)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
@@ -601,7 +642,7 @@ __global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a,
     __shared__ __attribute__((aligned(16))) uint32_t s_sample[512];
     __shared__ uint32_t s_cnt[32];
     /* below, window, above (or not counted): outside the window a counter per lane and side, both on the lane's own bank */
-    __shared__ uint32_t s_bins[64u + kWindow + 64u];
+    __shared__ uint32_t s_bins[64u + W + 64u];
     __shared__ uint32_t s_valid[kHistWaves];
     const uint32_t c = blockIdx.y;
     const ChunkPlace place = place_of(split, c, DT);
@@ -630,13 +671,19 @@ __global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a,
 #pragma unroll
         for (uint32_t u = 0; u < NF; ++u) load(u, k0 + u * n_waves < whole ? k0 + u * n_waves : 0u);
     }
-    if (threadIdx.x < kWindow + 128u) s_bins[threadIdx.x] = 0u;
-    const uint32_t at = median.find(s_sample, s_cnt, wave, lane) + 4u;
-    const uint32_t lo = min(max(at, kWindow / 2u + 65u) - kWindow / 2u, kFirstNonFinite - kWindow);
+    for (uint32_t i = threadIdx.x; i < W + 128u; i += kHistThreads) s_bins[i] = 0u;
+    bool doubtful;                                           /* the wide window holds what such a sample can be off */
+    median.put(s_sample);
+    uint32_t at = SampleMedian::find(s_sample, s_cnt, wave, lane, doubtful) + 4u;
+    if (W == kNarrow && doubtful && whole >= 16u) {                          /* fewer groups are soon counted once more */
+        SampleMedian::put_one(s_sample, SampleMedian::request_one<DT>(in, whole, group_of));
+        at = SampleMedian::find(s_sample, s_cnt, wave, lane, doubtful) + 4u;
+    }
+    const uint32_t lo = min(max(at, W / 2u + 65u) - W / 2u, kFirstNonFinite - W);
 
     /* on magnitudes less one, so that zeros go to the top, behind Inf/NaN; d is signed, 64 for lo (which is 65 at least, so
        that the top stays positive) */
-    const uint32_t from2 = (lo - 65u) * 0x00010001u, first2 = lane * 0x00010001u, last2 = (64u + kWindow + ((lane - kWindow) & 63u)) * 0x00010001u;
+    const uint32_t from2 = (lo - 65u) * 0x00010001u, first2 = lane * 0x00010001u, last2 = (64u + W + ((lane - W) & 63u)) * 0x00010001u;
     uint32_t invalid = 0, calls = 0;
     auto count = [&](const uint32_t w[4]) {
         ++calls;
@@ -685,7 +732,7 @@ __global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a,
         }
         count(w);
     }
-    Partial* const part = reinterpret_cast<Partial*>(a.hist + (uint64_t)c * (kHistBytes / 8u));
+    Partial<W>* const part = reinterpret_cast<Partial<W>*>(a.hist + (uint64_t)c * (kHistBytes / 8u));
     if (a.shared) {
         /* what the histogram of all magnitudes would be added to, if it comes to that; not earlier, where the wave's later
            loads would wait for these stores (64 chunks of 2^21 fp32 values 106 us at the start, 96 here) */
@@ -695,11 +742,14 @@ __global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a,
     const uint32_t counted = wave_incl_scan(8u * calls - invalid);
     if (lane == 63u) s_valid[wave] = counted;
     __syncthreads();
-    if (wave >= 2u) return;
     uint32_t* const mine = part[blockIdx.x].bins;
-    if (threadIdx.x < kWindow) mine[threadIdx.x] = s_bins[64u + threadIdx.x];
-    if (wave == 0u) return;
-    const uint32_t inside = wave_incl_scan(s_bins[64u + lane] + (lane + 64u < kWindow ? s_bins[128u + lane] : 0u));
+    if (threadIdx.x < W) mine[threadIdx.x] = s_bins[64u + threadIdx.x];
+    if (wave != 1u) return;
+    uint32_t inside = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < W; k += 64u)
+        if (k + lane < W) inside += s_bins[64u + k + lane];
+    inside = wave_incl_scan(inside);
     const uint32_t below = wave_incl_scan(s_bins[lane]);
     const uint32_t valid = __builtin_amdgcn_readlane(row_incl_scan(s_valid[lane & 15u]), 15);
     if (lane == 63u) {
@@ -710,34 +760,36 @@ __global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a,
 
 /*
  * One workgroup per chunk adds up the `parts` Partials of it and looks for the rank among them: 1024 threads, a sixteen-byte
- * piece of a 32nd of the Partials each, all loads in flight together.  Where the sample misled, so that the rank
- * is not in the window, every magnitude is counted: by that workgroup alone in its LDS (`shared` not set: a chunk of at most
- * kFusedGroups groups to count), or by all of the grid's, which add to the histogram that k_window_count zeroed; the last
+ * piece of a 32nd (wide window: an eighth) of the Partials each, all loads in flight together.  Where the sample misled, so that the rank
+ * is not in the window, every magnitude is counted: by that workgroup alone in its LDS (`shared` not set),
+ * or by all of the grid's, which add to the histogram that k_window_count zeroed; the last
  * to arrive looks for the rank there.  No workgroup waits for another.  grid = (workgroups per chunk for that, chunks).
  */
-template <int DT, class SPLIT>
+template <int DT, uint32_t W, class SPLIT>
 __global__ __launch_bounds__(kHistThreads) void k_window_finish(const RobustIo a, uint32_t parts, const SPLIT split)
 {
-    constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u, ROWS = kHistThreads / 32u, Q = kWindow / 4u;
+    constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u, PIECES = W == kNarrow ? 32u : 128u, ROWS = kHistThreads / PIECES;
+    constexpr uint32_t MOST = W == kNarrow ? kHistBlocks : kWideParts;
     __shared__ __attribute__((aligned(16))) uint32_t s_hist[kMagBins];     /* 128 KiB */
     __shared__ uint32_t s_head[3][4];
     __shared__ uint32_t s_row[kMagBins / 256u];
     const uint32_t c = blockIdx.y, t = threadIdx.x, lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    Partial* const part = reinterpret_cast<Partial*>(a.hist + (uint64_t)c * (kHistBytes / 8u));
+    Partial<W>* const part = reinterpret_cast<Partial<W>*>(a.hist + (uint64_t)c * (kHistBytes / 8u));
     uint8_t* const table = a.table + 8u * c;
     double* const sigma = a.sigma ? a.sigma + c : nullptr;
 
     const u32x4 head = *reinterpret_cast<const u32x4_a4*>(&part[min(t, parts - 1u)].below);      /* below, valid, inside, lo */
-    const uint32_t row = t / 32u, q = min(t & 31u, Q - 1u);
+    const uint32_t row = t / PIECES, q = min(t % PIECES, W / 4u - 1u);
     if (blockIdx.x == 0u) {
-        u32x4 v[kHistBlocks / ROWS], sum = {0u, 0u, 0u, 0u};
+        u32x4 v[MOST / ROWS], sum = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (uint32_t k = 0; k < kHistBlocks / ROWS; ++k) v[k] = reinterpret_cast<const u32x4_a4*>(part[min(row + ROWS * k, parts - 1u)].bins)[q];
+        for (uint32_t k = 0; k < MOST / ROWS; ++k)
+            if (W == kNarrow || ROWS * k < parts) v[k] = reinterpret_cast<const u32x4_a4*>(part[min(row + ROWS * k, parts - 1u)].bins)[q];
 #pragma unroll
-        for (uint32_t k = 0; k < kHistBlocks / ROWS; ++k)
+        for (uint32_t k = 0; k < MOST / ROWS; ++k)
             if (row + ROWS * k < parts) sum += v[k];
-        reinterpret_cast<u32x4*>(s_hist)[row * 32u + (t & 31u)] = sum;
+        reinterpret_cast<u32x4*>(s_hist)[t] = sum;
     }
     if (wave < 4u) {
 #pragma unroll
@@ -756,19 +808,27 @@ __global__ __launch_bounds__(kHistThreads) void k_window_finish(const RobustIo a
         return;
     }
     if (rank >= below && rank - below < inside) {
-        if (blockIdx.x != 0u || wave != 0u) return;
-        uint32_t even = 0, odd = 0;                          /* counts of magnitudes lo + 2 lane and lo + 2 lane + 1 */
-        if (lane < kWindow / 2u) {
+        if (blockIdx.x != 0u) return;
+        if (W <= 128u && wave != 0u) return;
+        uint32_t even = 0, odd = 0;                          /* counts of magnitudes lo + 2 t and lo + 2 t + 1 */
+        if (t < W / 2u) {
 #pragma unroll
             for (uint32_t r = 0; r < ROWS; ++r) {
-                const u32x2 w = *reinterpret_cast<const u32x2*>(s_hist + r * 128u + 2u * lane);
+                const u32x2 w = *reinterpret_cast<const u32x2*>(s_hist + r * (4u * PIECES) + 2u * t);
                 even += w.x;
                 odd += w.y;
             }
         }
-        const uint32_t inc = below + wave_incl_scan(even + odd);
+        uint32_t inc = wave_incl_scan(even + odd);
+        if (W > 128u) {
+            if (lane == 63u) s_row[wave] = inc;
+            __syncthreads();
+            for (uint32_t w = 0; w < wave; ++w) inc += s_row[w];
+        }
+        inc += below;
         const uint64_t owner = __ballot(rank >= inc - even - odd && rank < inc);
-        uint32_t bin = head.w + 2u * lane + (uint32_t)(rank >= inc - odd);
+        if (W > 128u && owner == 0u) return;                 /* another wave's */
+        uint32_t bin = head.w + 2u * t + (uint32_t)(rank >= inc - odd);
         bin = __builtin_amdgcn_readlane(bin, (uint32_t)__builtin_ctzll(owner));
         const double med = (double)__uint_as_float(bin << 16);
         table_from_sigma(med / 0.6744897501960817, table, sigma);     /* Phi^-1(3/4) */
@@ -781,6 +841,7 @@ __global__ __launch_bounds__(kHistThreads) void k_window_finish(const RobustIo a
     else sample_into_lds<DT, 4>(s_hist, in, place.n, a.stride, blockIdx.x * kHistWaves + wave, sample_blocks(place.n, a.stride), gridDim.x * kHistWaves);
     __syncthreads();
     if (!a.shared) {
+        if (t == 0u) part[0].arrived = 1u;
         rank_and_table<uint32_t>([&](uint32_t k, uint32_t* out) {
             const u32x4 x = reinterpret_cast<const u32x4*>(s_hist)[k * kHistThreads + t];
             __builtin_memcpy(out, &x, 16);
@@ -823,34 +884,16 @@ int launch_estimate(int dt, const MomentArgs& a, void* stream)
 }
 
 
-/* Groups to count in the launch's largest chunk. */
-static uint64_t groups_to_count(const HistArgs& a)
+template <int DT, uint32_t W, class SPLIT>
+static int launch_window(const HistArgs& a, const WindowPlan& plan, const SPLIT& split, hipStream_t s)
 {
-    uint64_t largest = 0;
-    for (uint32_t c = 0; c < a.tab.n_chunks; ++c) largest = std::max(largest, a.tab.elem_off[c + 1] - a.tab.elem_off[c]);
-    return ((largest + kGroup - 1) / kGroup + a.sample_stride - 1) / a.sample_stride;
-}
-
-template <int DT, class SPLIT>
-static int launch_window(const HistArgs& a, const SPLIT& split, bool shared, hipStream_t s)
-{
-    const RobustIo io = {a.in, a.hist, a.table, a.sigma, a.sample_stride, shared};
+    const RobustIo io = {a.in, a.hist, a.table, a.sigma, a.sample_stride, plan.shared};
     const uint32_t chunks = a.tab.n_chunks;
-    const uint64_t groups = groups_to_count(a);
-    /* two groups per wave at least (2^20 bf16 values 9.4 us, 10.4 with four), one workgroup per compute unit at most */
-    const uint32_t parts = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((groups + 31) / 32, kHistBlocks / chunks));
-    /* workgroups for the case that the window does not hold the rank: most of the time they only start and end, which is worth
-       a microsecond of a call on less than 2^25 values */
-    const uint32_t finish = !shared ? 1u : (groups <= 65536u ? (parts + 7u) / 8u : parts);
-    /* up to 64 MiB of counted values, 32 of sampled ones, stay in the caches for the compress that usually follows (us, estimate and compress, streamed
-       loads / plain: 2^24 bf16 values 35.7 / 31.9, 64 experts of 512 x 7168 from one group in 16 156.0 / 152.6); larger tensors do
-       not, and are read faster streamed (2^26: 33, 36; 64 MiB in scattered kilobytes, estimate alone, 25.9 / 28.8) */
-    const bool stream = a.tab.elem_off[chunks] / a.sample_stride * (DT == ZIPCCL_BF16 ? 2u : 4u) > (a.sample_stride == 1u ? 64ull << 20 : 32ull << 20);
-    const dim3 grid(parts, chunks), block(kHistThreads);
-    if (stream) hipLaunchKernelGGL((k_window_count<DT, true, SPLIT>), grid, block, 0, s, io, split);
-    else hipLaunchKernelGGL((k_window_count<DT, false, SPLIT>), grid, block, 0, s, io, split);
+    const dim3 grid(plan.parts, chunks), block(kHistThreads);
+    if (plan.stream) hipLaunchKernelGGL((k_window_count<DT, W, true, SPLIT>), grid, block, 0, s, io, split);
+    else hipLaunchKernelGGL((k_window_count<DT, W, false, SPLIT>), grid, block, 0, s, io, split);
     if (hipGetLastError() != hipSuccess) return 1;
-    hipLaunchKernelGGL((k_window_finish<DT, SPLIT>), dim3(finish, chunks), block, 0, s, io, parts, split);
+    hipLaunchKernelGGL((k_window_finish<DT, W, SPLIT>), dim3(plan.finish, chunks), block, 0, s, io, plan.parts, split);
     return (int)hipGetLastError();
 }
 
@@ -875,7 +918,7 @@ template <int DT>
 static int launch_robust(const HistArgs& a, bool small, hipStream_t s)
 {
     const uint32_t chunks = a.tab.n_chunks;
-    if (small && groups_to_count(a) < (chunks <= 16u ? 100u : (chunks <= 64u ? 180u : 260u))) {
+    if (small && groups_to_count(a.tab, a.sample_stride) < (chunks <= 16u ? 100u : (chunks <= 64u ? 180u : 260u))) {
         const RobustIo io = {a.in, a.hist, a.table, a.sigma, a.sample_stride, 0u};
         if (is_equal_split(a.tab)) hipLaunchKernelGGL((k_robust_chunk_fused<DT, EqualSplit>), dim3(chunks), dim3(kHistThreads), 0, s, io, equal_split(a.tab));
         else hipLaunchKernelGGL((k_robust_chunk_fused<DT, ChunkTab>), dim3(chunks), dim3(kHistThreads), 0, s, io, a.tab);
@@ -883,8 +926,9 @@ static int launch_robust(const HistArgs& a, bool small, hipStream_t s)
     }
     /* 2^32 values or more: only a whole tensor, every value of which counts */
     if (chunks == 1u && a.tab.elem_off[1] > ZIPCCL_MAX_CHUNK_ELEMS) return launch_huge<DT>(a, s);
-    if (is_equal_split(a.tab)) return launch_window<DT>(a, equal_split(a.tab), !small, s);
-    return launch_window<DT>(a, a.tab, !small, s);
+    const WindowPlan plan = window_plan(a.tab, DT, a.sample_stride);
+    if (is_equal_split(a.tab)) return plan.wide ? launch_window<DT, kWide>(a, plan, equal_split(a.tab), s) : launch_window<DT, kNarrow>(a, plan, equal_split(a.tab), s);
+    return plan.wide ? launch_window<DT, kWide>(a, plan, a.tab, s) : launch_window<DT, kNarrow>(a, plan, a.tab, s);
 }
 
 int launch_estimate_robust_fused(int dt, const HistArgs& a, void* stream)

@@ -211,6 +211,51 @@ struct HistArgs {
     ChunkTab tab;            /* the launch's chunks (elem_off; the other fields are not used) */
 };
 
+/* Groups to count in the launch's largest chunk. */
+ZIPCCL_HD uint64_t groups_to_count(const ChunkTab& t, uint32_t sample_stride)
+{
+    uint64_t largest = 0;
+    for (uint32_t c = 0; c < t.n_chunks; ++c)
+        if (t.elem_off[c + 1] - t.elem_off[c] > largest) largest = t.elem_off[c + 1] - t.elem_off[c];
+    return ((largest + kGroup - 1) / kGroup + sample_stride - 1) / sample_stride;
+}
+
+/* How the windowed count of a launch runs (k_window_count, k_window_finish). */
+struct WindowPlan {
+    uint32_t parts;          /* workgroups per chunk that count */
+    uint32_t finish;         /* workgroups per chunk of the finish, and of a second count */
+    bool wide;               /* the wide window */
+    bool shared;             /* a second count goes to a histogram that the first kernel zeroes */
+    bool stream;             /* loads past the caches */
+};
+constexpr uint32_t kWideParts = 32;                  /* workgroups per chunk that a chunk's workspace has room for with the wide window */
+constexpr uint32_t kManyChunks = 32, kManyChunksAlone = 2048;
+
+ZIPCCL_HD WindowPlan window_plan(const ChunkTab& t, int dt, uint32_t sample_stride)
+{
+    WindowPlan p;
+    const uint64_t groups = groups_to_count(t, sample_stride);
+    /* two groups per wave at least (2^20 bf16 values 9.4 us, 10.4 with four), one workgroup per compute unit at most */
+    const uint64_t want = (groups + 31) / 32, most = kHistBlocks / t.n_chunks;
+    p.parts = (uint32_t)(want < 1 ? 1 : (want < most ? want : most));
+    /* The wide window is never left by values that the narrow one loses 1 in 5 times (rows of scales spread by e^2), and where few
+       workgroups share a chunk its counts are no more to read than the narrow one's elsewhere (us, bf16, tensors in turn, narrow / wide, normal
+       values: 64 chunks of 2^19 24.7 / 24.4, 64 of 3 670 016 from one group in 16 15.5 / 15.3; rows spread by e^2: 28.6 / 24.1; 8 of 2^21 from
+       one group in 16 13.8 / 10.6) */
+    p.wide = p.parts <= kWideParts;
+    /* 128 KiB zeroed per chunk are time in a launch of many small chunks (64 of 2^19 bf16 values 26.6 us with, 24.7 without), which fill the
+       chip with one workgroup each should all of them be counted twice (64 of 2^20 110 us with, 95 without; 8 of 2^20 38 and 76) */
+    p.shared = groups > (t.n_chunks >= kManyChunks ? kManyChunksAlone : kFusedGroups);
+    /* workgroups for the case that the window does not hold the rank: most of the time they only start and end, which is worth
+       a microsecond of a call on less than 2^25 values */
+    p.finish = !p.shared ? 1u : (groups <= 65536u ? (p.parts + 7u) / 8u : p.parts);
+    /* up to 64 MiB of counted values, 32 of sampled ones, stay in the caches for the compress that usually follows (us, estimate and compress, streamed
+       loads / plain: 2^24 bf16 values 35.7 / 31.9, 64 experts of 512 x 7168 from one group in 16 156.0 / 152.6); larger tensors do
+       not, and are read faster streamed (2^26: 33, 36; 64 MiB in scattered kilobytes, estimate alone, 25.9 / 28.8) */
+    p.stream = t.elem_off[t.n_chunks] / sample_stride * elem_size(dt) > (sample_stride == 1u ? 64ull << 20 : 32ull << 20);
+    return p;
+}
+
 struct DecompressArgs {
     const uint8_t* comp;
     uint64_t comp_capacity;  /* readable bytes from comp */

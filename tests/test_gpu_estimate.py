@@ -407,7 +407,8 @@ def test_estimate_of_chunks_shared_by_a_few_workgroups(dtype):
 
 @pytest.mark.parametrize("dtype", [z.BF16, z.FP32])
 @pytest.mark.parametrize("ce,stride", [((200 * 512 - 3,), 1), ((508 * 512 + 1,), 1), ((1 << 21,), 1), ((1 << 21, 5, 0, 300_000), 4),
-                                       ((600 * 512, 70_001, 1 << 20), 1), ((90 * 512,) * 20 + (181 * 512,), 1)])
+                                       ((600 * 512, 70_001, 1 << 20), 1), ((90 * 512,) * 20 + (181 * 512,), 1),
+                                       ((2048 * 512,) + (70_001,) * 8, 1), ((2048 * 512,) + (20_001,) * 31, 1), ((2049 * 512,) + (20_001,) * 31, 1)])
 def test_estimate_of_chunks_whose_small_sample_misleads(dtype, ce, stride):
     """The windowed count looks at 16 values of each of 64 strata before it counts: chunks where those say nothing about
     the median.  The sampled values alone at another scale, above or below the rest; everything zero but a short run; two
@@ -436,3 +437,32 @@ def test_estimate_of_chunks_whose_small_sample_misleads(dtype, ce, stride):
                 part[::2] = np.abs(part[::2]) * np.float32(1e6) + 1
         words = W.f32_to_bf16_words(x) if dtype == z.BF16 else x.view(np.uint32).copy()
         _sampled_case(words, dtype, np.array(ce, dtype=np.uint64), stride, f"misled {kind} {ce[:3]} dtype={dtype}")
+
+
+@pytest.mark.parametrize("dtype", [z.BF16, z.FP32])
+def test_estimate_of_rows_of_different_scales_is_counted_once(dtype):
+    """Rows of 4096 values whose scales are log-normal, spread by e^1 to e^3, sparse ones, and tokens of 7168 sampled per chunk: the
+    windowed count looks again where its sample's values lie far apart, so that the window holds the rank and nothing
+    is counted a second time.  A second count leaves its workgroups' number behind the chunk's first window of counts."""
+    rng = np.random.default_rng(73)
+    def scaled(n, row, s):
+        return rng.standard_normal(n, dtype=np.float32) * np.repeat(np.exp(s * rng.standard_normal(n // row)), row).astype(np.float32)
+    recounted = lambda ws, wide: int((ws.view(torch.int32).view(-1, 65536)[:, 500 if wide else 116] != 0).sum())       # 256 KiB per chunk
+    words = lambda x: W.f32_to_bf16_words(x) if dtype == z.BF16 else x.view(np.uint32).copy()
+    cases = [(scaled(1 << 21, 4096, s), 1, 1) for s in (1, 1, 1.5, 1.5, 2, 2, 2, 2, 3, 3, 3, 3)]
+    cases += [(scaled(1 << 18, 4096, 2), 1, 1), (scaled(8 * 192 * 7168, 7168, 2), 8, 4), (scaled(16 * 640 * 1024, 1024, 2), 16, 2)]
+    sparse = rng.standard_normal(1 << 21, dtype=np.float32)
+    sparse[rng.random(1 << 21) < 0.93] = 0.0
+    cases.append((sparse, 1, 1))
+    again = 0
+    for x, chunks, stride in cases:
+        x = words(x)
+        d_tabs = torch.zeros(8 * chunks, dtype=torch.uint8, device=DEV)
+        d_sig = torch.zeros(chunks, dtype=torch.float64, device=DEV)
+        d_ews = torch.full((z.zipccl_estimate_chunk_tables_workspace_size(chunks),), 0x77, dtype=torch.uint8, device=DEV)
+        z.zipccl_estimate_chunk_tables_sampled(to_device_words(x), x.size, dtype, chunks, None, stride, d_tabs, d_sig, d_ews)
+        torch.cuda.synchronize()
+        again += recounted(d_ews, chunks >= 8 or x.size <= 1 << 19)
+        decs, sig = osg.robust_chunk_tables_sampled(x, dtype, chunks, [x.size // chunks] * chunks, stride=stride)
+        assert np.array_equal(d_sig.cpu().numpy(), sig) and np.array_equal(d_tabs.cpu().numpy().reshape(chunks, 8), decs)
+    assert again == 0
