@@ -466,3 +466,32 @@ def test_estimate_of_rows_of_different_scales_is_counted_once(dtype):
         decs, sig = osg.robust_chunk_tables_sampled(x, dtype, chunks, [x.size // chunks] * chunks, stride=stride)
         assert np.array_equal(d_sig.cpu().numpy(), sig) and np.array_equal(d_tabs.cpu().numpy().reshape(chunks, 8), decs)
     assert again == 0
+
+
+def test_estimate_of_a_tensor_of_zero_rows_mostly_takes_a_few_times_the_usual():
+    """One group in a thousand of 2^24 values holds any: the sample misses them and everything is counted a second time.  What
+    that takes must not grow with the zeros, which do not count but would all be added to one word: 3 times the same call on normal
+    values, 34 times when they were.  (10: the device's own events, an average of 20 calls.)"""
+    n = 1 << 24
+    g = torch.Generator(device=DEV)
+    g.manual_seed(79)
+    x = torch.empty(n, dtype=torch.float32, device=DEV).normal_(generator=g)
+    sparse = x.clone()
+    sparse.view(-1, 512)[torch.rand(n // 512, device=DEV, generator=g) < 0.999] = 0.0
+    tab, ws = torch.zeros(8, dtype=torch.uint8, device=DEV), torch.empty(z.zipccl_estimate_robust_workspace_size(), dtype=torch.uint8, device=DEV)
+    def time_of(d):
+        d = d.to(torch.bfloat16)
+        call = lambda: z.zipccl_estimate_table_robust(d, n, z.BF16, tab, None, ws)
+        call()
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        for _ in range(20):
+            call()
+        end.record()
+        end.synchronize()
+        return start.elapsed_time(end)
+    assert time_of(sparse) < 10 * time_of(x)
+    words = sparse.to(torch.bfloat16).view(torch.int16).cpu().numpy().view(np.uint16)
+    dec, s = osg.robust_table(words, z.BF16)
+    _, got_dec, got_s = _estimate_robust(to_device_words(words), n, z.BF16)
+    assert got_s == s and got_dec == list(dec)
