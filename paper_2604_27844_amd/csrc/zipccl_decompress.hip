@@ -1318,10 +1318,14 @@ static int launch_decompress_gpw(const DecompressArgs& a, hipStream_t s)
  * 131 073 bf16 values 7.9 us with two neighbouring groups, 8.3 with four), and below 5 * 2^20 bf16 values not for many
  * chunks with rests (128 chunks of 37 824 values 6 % slower with four).
  *
- * Launches of four groups on 21 to 40 MiB of values do not stream their loads: what is read of several such buffers
- * then stays in the last-level cache.  us, streamed / plain, with 1, 3, 5 and 12 sets of buffers in turn: 2^24 bf16 values 11.0 / 11.1, 12.7 /
- * 11.4, 12.9 / 11.1, 13.0 / 12.9; 11 * 2^19 fp32 8.2 / 8.1, 9.6 / 8.4, 9.9 / 8.3, 10.2 / 8.8.  Smaller launches lose up to a tenth (2^23
- * bf16, 5 sets, 6.2 / 6.9), larger ones 2 to 5 %.
+ * Launches of four groups on more than kPlainFrom bf16 values (21 to 40 MiB of them), and all of fp32 values (20 to 24 and 29 to 32 MiB), do not
+ * stream their loads: of the compressed buffer, which something has written shortly before, a part is then still read from the last-level
+ * cache.  us, streamed / plain, with 1, 3, 5 and 12 sets of buffers in turn, 2^24 bf16 values: every buffer copied into before its call
+ * 13.7 / 10.8, 12.9 / 10.0, 10.2 / 9.2, 11.2 / 9.7; all copied into, then all decompressed 13.6 / 10.7, 13.9 / 10.1, 12.1 / 11.2, 13.1 / 13.5; not
+ * written between the calls 11.5 / 8.9, 11.6 / 10.1, 12.6 / 10.2, 12.9 / 12.9; compressed into before its call 12.0 / 10.4, 13.2 / 13.4, 12.8 /
+ * 12.8, 12.8 / 12.9.  6 * 2^20 fp32, copied into before the call: 11.8 / 9.7, 9.8 / 8.5, 8.3 / 8.2, 8.3 / 8.1.  With more sets than the cache holds
+ * between write and read it loses up to 6 %.  On either side of these sizes, buffers copied into before the call: 2^23 bf16 8.4 / 8.5, 7.1 / 6.9,
+ * 7.0 / 6.7, 5.6 / 6.6; 24 * 2^20, two groups per wave, 15.2 / 14.8, 11.1 / 12.1, 11.9 / 13.4, 11.9 / 13.3.
  */
 constexpr uint64_t kPlainFrom = 21ull << 19;
 int launch_decompress(int dt, const DecompressArgs& a, void* stream)
