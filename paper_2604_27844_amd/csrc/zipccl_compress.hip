@@ -465,7 +465,7 @@ __global__ __launch_bounds__(64u * WAVES) void k_compress(const CompressIo a, co
         /* group index (section 4.2.3); k_place adds the tile's prefix in stash mode */
         const uint64_t g = ts / kGroup + lane;
         if (lane < kGroupsPerTile && g < ng) idx[g] = P + gex;
-    } else if (WAVES == 4u || wave < 4u) {
+    } else if (wave < 4u) {
         /* waves 1..3: one plane each, 16 bytes per lane */
         const uint32_t k = wave - 1u;
         const uint64_t pb = ts / 8 + lane * 16u;
@@ -743,7 +743,6 @@ static Parking parking_of(const CompressArgs& a) { return Parking{a.tile_total, 
  * 16.5 / 16.4, 2^27 in 64 175 / 171 / 168.
  */
 constexpr uint32_t kWideTiles = 256;
-template <int DT> constexpr uint32_t kManyWaves = DT == ZIPCCL_BF16 ? 8u : 16u;
 
 /* The smallest arguments that hold the split; the two-read kernels, whose calls are none of the small ones, take the table. */
 template <int DT>
@@ -753,11 +752,15 @@ static void launch_compress_dt(int mode, const CompressArgs& a, hipStream_t s)
     const CompressIo io = io_of(a);
     const Parking park = parking_of(a);
     const bool equal = is_equal_split(a.tab);
-    const bool many = DT == ZIPCCL_BF16 && a.tab.tile_start[a.tab.n_chunks] > kWideTiles;
 #define ZIPCCL_LAUNCH(MODE, PARK, P, SPLIT, S)                                                                         \
     do {                                                                                                               \
-        if (many) hipLaunchKernelGGL((k_compress<DT, MODE, kManyWaves<DT>, PARK, SPLIT>), grid, dim3(64u * kManyWaves<DT>), 0, s, io, P, S); \
-        else hipLaunchKernelGGL((k_compress<DT, MODE, 16u, PARK, SPLIT>), grid, dim3(1024u), 0, s, io, P, S);          \
+        if constexpr (DT == ZIPCCL_BF16) {                                                                             \
+            if (a.tab.tile_start[a.tab.n_chunks] > kWideTiles) {                                                       \
+                hipLaunchKernelGGL((k_compress<DT, MODE, 8u, PARK, SPLIT>), grid, dim3(512u), 0, s, io, P, S);         \
+                break;                                                                                                 \
+            }                                                                                                          \
+        }                                                                                                              \
+        hipLaunchKernelGGL((k_compress<DT, MODE, 16u, PARK, SPLIT>), grid, dim3(1024u), 0, s, io, P, S);               \
     } while (0)
     if (mode == kModeDirect) {
         if (equal) ZIPCCL_LAUNCH(kModeDirect, NoParking, NoParking{}, EqualSplit, equal_split(a.tab));

@@ -1400,6 +1400,7 @@ static int launch_reduce_split(int dt, int out_dt, const ReduceArgs& a, hipStrea
                          (uint32_t)L.lo, (uint32_t)L.p0, (uint32_t)L.plane_bytes, (uint32_t)L.idx, (uint32_t)L.esc};
     if (dt == ZIPCCL_BF16 && out_dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_reduce_split<ZIPCCL_BF16, ZIPCCL_BF16, S, G, Q>), grid, block, lds_bytes, s, b);
     else if (dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_reduce_split<ZIPCCL_BF16, ZIPCCL_FP32, S, G, Q>), grid, block, lds_bytes, s, b);
+    else if constexpr (S == 4u && Q == 2u) return 1;      /* kSplit4x2 is a form for bf16 */
     else if (out_dt == ZIPCCL_BF16) hipLaunchKernelGGL((k_reduce_split<ZIPCCL_FP32, ZIPCCL_BF16, S, G, Q>), grid, block, lds_bytes, s, b);
     else hipLaunchKernelGGL((k_reduce_split<ZIPCCL_FP32, ZIPCCL_FP32, S, G, Q>), grid, block, lds_bytes, s, b);
     return (int)hipGetLastError();
