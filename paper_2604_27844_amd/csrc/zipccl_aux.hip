@@ -915,22 +915,17 @@ static int launch_huge(const HistArgs& a, hipStream_t s)
     const RobustIo io = {a.in, a.hist, a.table, a.sigma, 1u, 1u};
     hipLaunchKernelGGL(k_clear_hist, dim3(1), dim3(kClearThreads), 0, s, a.hist);
     if (hipGetLastError() != hipSuccess) return 1;
-    hipLaunchKernelGGL((k_magnitude_hist<DT>), dim3(a.n_blocks), dim3(kHistThreads), 0, s, io, a.tab.elem_off[1]);
+    hipLaunchKernelGGL((k_magnitude_hist<DT>), dim3(kHistBlocks), dim3(kHistThreads), 0, s, io, a.tab.elem_off[1]);
     if (hipGetLastError() != hipSuccess) return 1;
     hipLaunchKernelGGL(k_robust_finish, dim3(1), dim3(kHistThreads), 0, s, io);
     return (int)hipGetLastError();
 }
 
-/*
- * One kernel or two for chunks of at most kFusedGroups groups to count (us, bf16, one / two): one chunk of 64 groups 7.6 / 8.4,
- * of 128 9.3 / 8.3, of 512 14.1 / 8.8; 8 chunks of 64 8.1 / 9.2, of 256 11.5 / 9.3; 64 chunks of 128 10.6 / 12.5, of 192 13.1 /
- * 13.3, of 448 22 / 14; 128 chunks of 256 16.2 / 16.8: the more chunks, the fewer workgroups are left for each of them.
- */
 template <int DT>
-static int launch_robust(const HistArgs& a, bool small, hipStream_t s)
+static int launch_robust(const HistArgs& a, hipStream_t s)
 {
     const uint32_t chunks = a.tab.n_chunks;
-    if (small && groups_to_count(a.tab, a.sample_stride) < (chunks <= 16u ? 100u : (chunks <= 64u ? 180u : 260u))) {
+    if (robust_in_one_kernel(a.tab, a.sample_stride)) {
         const RobustIo io = {a.in, a.hist, a.table, a.sigma, a.sample_stride, 0u};
         if (is_equal_split(a.tab)) hipLaunchKernelGGL((k_robust_chunk_fused<DT, EqualSplit>), dim3(chunks), dim3(kHistThreads), 0, s, io, equal_split(a.tab));
         else hipLaunchKernelGGL((k_robust_chunk_fused<DT, ChunkTab>), dim3(chunks), dim3(kHistThreads), 0, s, io, a.tab);
@@ -943,14 +938,9 @@ static int launch_robust(const HistArgs& a, bool small, hipStream_t s)
     return plan.wide ? launch_window<DT, kWide>(a, plan, a.tab, s) : launch_window<DT, kNarrow>(a, plan, a.tab, s);
 }
 
-int launch_estimate_robust_fused(int dt, const HistArgs& a, void* stream)
-{
-    return dt == ZIPCCL_BF16 ? launch_robust<ZIPCCL_BF16>(a, true, (hipStream_t)stream) : launch_robust<ZIPCCL_FP32>(a, true, (hipStream_t)stream);
-}
-
 int launch_estimate_robust(int dt, const HistArgs& a, void* stream)
 {
-    return dt == ZIPCCL_BF16 ? launch_robust<ZIPCCL_BF16>(a, false, (hipStream_t)stream) : launch_robust<ZIPCCL_FP32>(a, false, (hipStream_t)stream);
+    return dt == ZIPCCL_BF16 ? launch_robust<ZIPCCL_BF16>(a, (hipStream_t)stream) : launch_robust<ZIPCCL_FP32>(a, (hipStream_t)stream);
 }
 
 } // namespace zipccl

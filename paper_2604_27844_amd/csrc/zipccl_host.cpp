@@ -229,9 +229,7 @@ zipccl_status_t compress_impl(const void* d_in, size_t n_elems, zipccl_dtype_t d
         a.d_table = reinterpret_cast<const uint32_t*>(d_table);
         a.table_stride = table_per_chunk ? 2u : 0u;
     } else {
-        a.e0 = table->dec[1];
         std::memcpy(&a.dec_lo, table->dec, 4);
-        std::memcpy(&a.dec_hi, table->dec + 4, 4);
     }
     uint64_t elem_base = 0, tile_base = 0;
     uint8_t* const ws = static_cast<uint8_t*>(d_workspace);
@@ -362,38 +360,13 @@ static zipccl_status_t estimate_chunk_tables_impl(const void* d_in, size_t n_ele
     if (workspace_bytes < zipccl_estimate_chunk_tables_workspace_size(n_chunks)) return ZIPCCL_ERR_BUFFER_TOO_SMALL;
     if ((uint64_t)n_chunks * (32768 / 1024) > 0x7FFFFFFFull) return ZIPCCL_ERR_INVALID_ARG;
     unsigned long long* const hist = static_cast<unsigned long long*>(d_workspace);
-    /* when every chunk's sample is small enough for one workgroup, one kernel does it all inside LDS: no histogram
-       in the workspace */
-    uint64_t largest_of_all = 0;
-    for (uint32_t c = 0; c < n_chunks; ++c) largest_of_all = std::max(largest_of_all, ce[c]);
-    const bool fused = ((largest_of_all + kGroup - 1) / kGroup + sample_stride - 1) / sample_stride <= kFusedGroups;
     const std::vector<uint64_t> no_slots(n_chunks + 1, 0);            /* slot offsets play no part here */
     HistArgs a;
     uint64_t elem_base = 0;
     for (uint32_t c0 = 0; c0 < n_chunks; c0 += kMaxBatch) {
         const uint32_t nb = (n_chunks - c0) < kMaxBatch ? (n_chunks - c0) : kMaxBatch;
         fill_tab(a.tab, ce, no_slots, c0, nb);
-        uint64_t largest = 0;
-        for (uint32_t c = 0; c < nb; ++c) largest = std::max(largest, ce[c0 + c]);
-        if (fused) {
-            a.n_blocks = 1;
-            a.sample_stride = sample_stride;
-            a.in = static_cast<const uint8_t*>(d_in) + elem_base * elem_size(dt);
-            a.hist = hist + (uint64_t)c0 * (kHistBytes / 8);
-            a.table = reinterpret_cast<uint8_t*>(d_tables + c0);
-            a.sigma = d_sigmas ? d_sigmas + c0 : nullptr;
-            if (launch_estimate_robust_fused(dt, a, stream) != 0) return ZIPCCL_ERR_DEVICE;
-            elem_base += a.tab.elem_off[nb];
-            continue;
-        }
-        /* a workgroup counts in 32 bits, and wants about 64 values per thread at least (of a sample: four groups
-           per wave); about one workgroup per compute unit in all */
-        const uint64_t sampled = (largest + sample_stride - 1) / sample_stride;
-        const uint64_t want = sample_stride > 1 ? (sampled + 32767) / 32768 : (largest + 65535) / 65536;
-        const uint64_t cap = std::max<uint64_t>(1, kHistBlocks / nb);
-        a.n_blocks = (uint32_t)std::min(std::max<uint64_t>(want, 1), cap);
         a.sample_stride = sample_stride;
-        if (largest / a.n_blocks >= 0xFFFFFFFFull) return ZIPCCL_ERR_INVALID_ARG;
         a.in = static_cast<const uint8_t*>(d_in) + elem_base * elem_size(dt);
         a.hist = hist + (uint64_t)c0 * (kHistBytes / 8);
         a.table = reinterpret_cast<uint8_t*>(d_tables + c0);
@@ -440,16 +413,11 @@ zipccl_status_t zipccl_estimate_table_robust(const void* d_in, size_t n_elems, z
     std::memset(&a.tab, 0, sizeof a.tab);
     a.tab.n_chunks = 1;
     for (uint32_t i = 1; i <= kMaxBatch; ++i) a.tab.elem_off[i] = whole;
-    const uint64_t want = (whole + 65535) / 65536;                    /* about 64 values per thread at least */
-    a.n_blocks = (uint32_t)(want < 1 ? 1 : (want > kHistBlocks ? kHistBlocks : want));
     a.sample_stride = 1;
     a.in = static_cast<const uint8_t*>(d_in);
     a.hist = hist;
     a.table = reinterpret_cast<uint8_t*>(d_table);
     a.sigma = d_sigma;
-    /* a tensor one workgroup can take on its own: one kernel */
-    if ((whole + kGroup - 1) / kGroup <= kFusedGroups)
-        return launch_estimate_robust_fused(dt, a, stream) == 0 ? ZIPCCL_OK : ZIPCCL_ERR_DEVICE;
     return launch_estimate_robust(dt, a, stream) == 0 ? ZIPCCL_OK : ZIPCCL_ERR_DEVICE;
 }
 

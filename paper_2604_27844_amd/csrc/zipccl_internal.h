@@ -28,7 +28,7 @@ constexpr uint32_t kVersion = 1;
 constexpr uint32_t kMagic = 0x4C43505Au;            /* "ZPCL" little-endian */
 constexpr uint32_t kWorkspaceHeader = 256;          /* reserved bytes before the per-tile arrays */
 constexpr uint32_t kMaxPeers = 1024;                /* slots one zipccl_decompress_reduce call can sum */
-constexpr uint32_t kFusedGroups = 508;              /* groups to count in a chunk up to which no histogram is shared by many workgroups */
+constexpr uint32_t kFusedGroups = 508;              /* groups to count in a chunk up to which a second count of it is one workgroup's */
 constexpr uint32_t kStashSlack = 64;                /* readable bytes past the last stash byte */
 
 /* header words (u32 index): 0 magic, 1 version, 2 dtype, 3 G, 4-5 n, 6-7 n_esc, 8-9 chunk_bytes, 10-11 dec[8] */
@@ -179,9 +179,8 @@ struct CompressArgs {
     uint32_t* tile_total;    /* one u32 per tile of this launch: its zero-point count */
     uint32_t* tile_prefix;   /* one u32 per tile: zero-points of its chunk before it */
     uint8_t* stash;          /* stash mode: one byte per input element of this launch (+ slack) */
-    uint32_t e0;             /* dec[1] */
-    uint32_t dec_lo, dec_hi; /* dec[0..3], dec[4..7] packed little-endian */
-    const uint32_t* d_table; /* when not null: the table lives in device memory (two words), e0/dec_* unused */
+    uint32_t dec_lo;         /* dec[0..3] packed little-endian: dec[1..7] are consecutive */
+    const uint32_t* d_table; /* when not null: the table lives in device memory (two words), dec_lo unused */
     uint32_t table_stride;   /* words from one chunk's table to the next: 0 = one table for all chunks, 2 = one each */
     ChunkTab tab;
 };
@@ -198,13 +197,12 @@ struct MomentArgs {
     double* sigma;           /* may be null */
 };
 
-constexpr uint32_t kHistBlocks = 256;                /* workgroups of the magnitude histogram: one per compute unit */
+constexpr uint32_t kHistBlocks = 256;                /* workgroups of the robust estimate: one per compute unit */
 constexpr uint32_t kHistBytes = 32768 * 8;           /* its workspace: one count per 15-bit magnitude, at most 64 bits each */
 
 struct HistArgs {
     const uint8_t* in;       /* first element of the launch's first chunk */
     unsigned long long* hist;   /* the launch's first chunk's workspace, kHistBytes per chunk */
-    uint32_t n_blocks;       /* workgroups per chunk */
     uint32_t sample_stride;  /* 1: every value counts; a power of two S: one group of 512 values per S groups */
     uint8_t* table;          /* device zipccl_table_t (8 bytes) per chunk of the launch */
     double* sigma;           /* one per chunk of the launch; may be null */
@@ -218,6 +216,16 @@ ZIPCCL_HD uint64_t groups_to_count(const ChunkTab& t, uint32_t sample_stride)
     for (uint32_t c = 0; c < t.n_chunks; ++c)
         if (t.elem_off[c + 1] - t.elem_off[c] > largest) largest = t.elem_off[c + 1] - t.elem_off[c];
     return ((largest + kGroup - 1) / kGroup + sample_stride - 1) / sample_stride;
+}
+
+/*
+ * Whether one workgroup per chunk does it all in one kernel (k_robust_chunk_fused), or a windowed count in two (us, bf16, one / two): one chunk of 64 groups
+ * to count 7.4 / 8.5, of 100 8.4 / 7.9, of 256 13 / 8.5; 8 chunks of 64 8.5 / 9.1, of 100 9.5 / 8.7, of 256 14 / 10.5; 64 chunks of 128 10.3 / 11.7, of 180
+ * 13.0 / 12.7, of 448 22 / 17; 128 chunks of 180 13.7 / 15.3, of 448 22.9 / 22.1: the more chunks, the fewer workgroups are left for each of them.
+ */
+ZIPCCL_HD bool robust_in_one_kernel(const ChunkTab& t, uint32_t sample_stride)
+{
+    return groups_to_count(t, sample_stride) < (t.n_chunks <= 16u ? 100u : (t.n_chunks <= 64u ? 180u : 260u));
 }
 
 /* How the windowed count of a launch runs (k_window_count, k_window_finish). */
@@ -289,7 +297,6 @@ enum CompressMode { kModeCount = 0, kModeEmit = 1, kModeStash = 2, kModeDirect =
  * they return a hipError_t as int */
 int launch_estimate(int dt, const MomentArgs& a, void* stream);
 int launch_estimate_robust(int dt, const HistArgs& a, void* stream);
-int launch_estimate_robust_fused(int dt, const HistArgs& a, void* stream);   /* chunks of at most kFusedGroups groups to count */
 int launch_compress(int dt, int mode, const CompressArgs& a, void* stream);
 /* device address and size of the library's own workspace on the current GPU (zipccl_compress_static) */
 int static_scratch(void** ptr, size_t* bytes);

@@ -53,19 +53,32 @@ static void check_forms(const ChunkTab& t, int dt)
 }
 
 int launch_estimate(int, const MomentArgs& a, void*) { CHECK(a.n_blocks >= 1 && a.n_blocks <= kMomentBlocks); ++g_launches; return 0; }
-int launch_estimate_robust(int, const HistArgs& a, void*)
+/* one kernel, a workgroup per chunk; or two, whose workgroups and windows must fit the device and a chunk's workspace */
+static int g_one_kernel = 0, g_wide = 0, g_narrow = 0, g_shared = 0, g_alone = 0;
+int launch_estimate_robust(int dt, const HistArgs& a, void*)
 {
-    CHECK(a.n_blocks >= 1 && a.n_blocks <= kHistBlocks && a.tab.n_chunks >= 1 && a.tab.n_chunks <= kMaxBatch);
+    CHECK(a.tab.n_chunks >= 1 && a.tab.n_chunks <= kMaxBatch);
     CHECK(a.sample_stride >= 1 && a.sample_stride <= ZIPCCL_MAX_SAMPLE_STRIDE && (a.sample_stride & (a.sample_stride - 1)) == 0);
     for (uint32_t c = 0; c < kMaxBatch; ++c) CHECK(a.tab.elem_off[c] <= a.tab.elem_off[c + 1]);
     ++g_launches;
+    uint64_t groups = 0;
+    for (uint32_t c = 0; c < a.tab.n_chunks; ++c) {
+        const uint64_t of = ((a.tab.elem_off[c + 1] - a.tab.elem_off[c] + kGroup - 1) / kGroup + a.sample_stride - 1) / a.sample_stride;
+        groups = of > groups ? of : groups;
+    }
+    CHECK(groups_to_count(a.tab, a.sample_stride) == groups);
+    if (robust_in_one_kernel(a.tab, a.sample_stride)) {
+        CHECK(groups <= kFusedGroups);
+        ++g_one_kernel;
+        return 0;
+    }
+    const WindowPlan p = window_plan(a.tab, dt, a.sample_stride);
+    CHECK(p.parts >= 1 && p.parts * a.tab.n_chunks <= kHistBlocks && p.finish >= 1 && p.finish <= p.parts);
+    CHECK(p.wide == (p.parts <= kWideParts) && p.parts * (p.wide ? 2048u : 512u) <= kHistBytes / 2);
+    CHECK(p.shared ? groups > kFusedGroups : (p.finish == 1 && groups <= kManyChunksAlone));
+    ++(p.wide ? g_wide : g_narrow);
+    ++(p.shared ? g_shared : g_alone);
     return 0;
-}
-int launch_estimate_robust_fused(int dt, const HistArgs& a, void* s)
-{
-    for (uint32_t c = 0; c < a.tab.n_chunks; ++c)           /* one workgroup per chunk: its sample must be small */
-        CHECK(((a.tab.elem_off[c + 1] - a.tab.elem_off[c] + kGroup - 1) / kGroup + a.sample_stride - 1) / a.sample_stride <= kFusedGroups);
-    return launch_estimate_robust(dt, a, s);
 }
 /* kModeDirect has no workgroup wait for another: every one counts the tiles before its own, so they have to be few */
 static int g_by_mode[4];
@@ -249,6 +262,17 @@ int main()
     CHECK(zipccl_estimate_table(in, 100000, ZIPCCL_BF16, (zipccl_table_t*)out, nullptr, ws, big, nullptr) == ZIPCCL_OK);
     CHECK(zipccl_estimate_table_robust(in, 100000, ZIPCCL_BF16, (zipccl_table_t*)out, nullptr, ws, big, nullptr) == ZIPCCL_OK);
     CHECK(zipccl_estimate_chunk_tables(in, n, ZIPCCL_FP32, C, ce.data(), (zipccl_table_t*)out, nullptr, ws, big, nullptr) == ZIPCCL_OK);
+    for (zipccl_dtype_t dt : {ZIPCCL_BF16, ZIPCCL_FP32})
+        for (uint32_t k : {1u, 2u, 7u, 8u, 9u, 16u, 17u, 31u, 32u, 64u, 65u, 127u, 128u, 130u})
+            for (uint64_t groups : {0ull, 1ull, 99ull, 100ull, 179ull, 180ull, 259ull, 260ull, 508ull, 509ull, 1024ull, 1025ull, 2048ull, 2049ull, 65536ull, 65537ull, 0x7FFFFFull})
+                for (uint32_t stride : {1u, 16u, 4096u}) {
+                    std::vector<uint64_t> split(k, groups * kGroup / 2);
+                    split[k / 2] = groups * kGroup;
+                    uint64_t total = 0;
+                    for (uint64_t v : split) total += v;
+                    CHECK(zipccl_estimate_chunk_tables_sampled(in, total, dt, k, split.data(), stride, (zipccl_table_t*)out, nullptr, ws, SIZE_MAX / 2, nullptr) == ZIPCCL_OK);
+                }
+    CHECK(g_one_kernel && g_wide && g_narrow && g_shared && g_alone);
     CHECK(zipccl_estimate_chunk_tables(in, n, ZIPCCL_FP32, C, ce.data(), (zipccl_table_t*)out, nullptr, ws, 1000, nullptr) == ZIPCCL_ERR_BUFFER_TOO_SMALL);
     CHECK(zipccl_estimate_chunk_tables(in, n + 1, ZIPCCL_FP32, C, ce.data(), (zipccl_table_t*)out, nullptr, ws, big, nullptr) == ZIPCCL_ERR_INVALID_ARG);
     for (uint32_t stride : {1u, 2u, 16u, 4096u})
