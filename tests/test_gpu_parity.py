@@ -398,7 +398,7 @@ def test_compress_and_decompress_replay_inside_a_hip_graph():
 @pytest.mark.parametrize("dtype", [z.BF16, z.FP32], ids=["bf16", "fp32"])
 @pytest.mark.parametrize("n", [(1 << 20) - 1, 1 << 20, (1 << 21) - 1, 1 << 21, 1 << 22, (1 << 22) + 1, 5 << 20, (5 << 20) + 1,
                                (11 << 19) - 1, 11 << 19, 6 << 20, (6 << 20) + 1, 29 << 18, (29 << 18) + 1, 1 << 23, (1 << 23) + 1,
-                               (20 << 20) - 1, 20 << 20])
+                               21 << 19, (21 << 19) + 1, (20 << 20) - 1, 20 << 20])
 def test_decode_on_either_side_of_every_tile_size(dtype, n):
     """Launches on either side of the sizes at which the decoder's groups per wave change: one chunk; ragged chunks that
     start at every alignment and end in every kind of rest; outputs that start 0 to 7 elements into an allocation.
@@ -427,7 +427,8 @@ def test_decode_on_either_side_of_every_tile_size(dtype, n):
         assert bool((back[:off] == 0x5B5B).all()) and bool((back[off + n:] == 0x5B5B).all())
 
 
-@pytest.mark.parametrize("dtype,n", [(z.BF16, (9 << 19) + 64), (z.BF16, (21 << 18) + 192), (z.FP32, (11 << 19) + 64), (z.FP32, 15 << 19)])
+@pytest.mark.parametrize("dtype,n", [(z.BF16, (9 << 19) + 64), (z.BF16, (21 << 18) + 192), (z.BF16, (23 << 19) + 192), (z.BF16, 21 << 19),
+                                     (z.BF16, (21 << 19) + 64), (z.FP32, (11 << 19) + 64), (z.FP32, 15 << 19)])
 def test_decode_of_chunks_on_line_boundaries_with_rests(dtype, n):
     """Launches in which a wave takes four groups, several chunks that start on cache lines and end in every kind of
     rest (whole groups, part of one, a single line, a tile less or more a line): exact words back, nothing written in
@@ -500,3 +501,18 @@ def test_small_chunks_on_either_side_of_the_one_launch_form(dtype, compress_path
         data = W.f32_to_bf16_words(f) if dtype == z.BF16 else f.view(np.uint32).copy()
         _say(f"[one launch] dtype={dtype} chunks={len(ce)} n={n} path={compress_path}")
         check_parity(data, dtype, 0.02, len(ce), ce, label=f"chunks={len(ce)} n={n}", form=compress_path)
+
+
+def test_launches_on_either_side_of_the_tiles_that_take_sixteen_waves(compress_path):
+    """bf16 launches of 255 to 257 tiles, up to 256 of which are compressed by 16 waves each and more by 8: one chunk, ragged
+    ones, a last tile of one value, zero-points dense in the first, absent or few in the others: bytes equal to the oracle's."""
+    rng = np.random.default_rng(90)
+    T = 8192
+    for ce in ([255 * T], [256 * T - 3], [256 * T], [256 * T + 1], [100 * T, 156 * T], [100 * T + 5, 156 * T], [255 * T, 1], [255 * T, 1, 0]):
+        ce = np.array(ce, dtype=np.uint64)
+        n = int(ce.sum())
+        f = rng.standard_normal(n, dtype=np.float32) * np.float32(0.02)
+        f[:T // 2] = 1e9
+        f[T:2 * T] = 0.02
+        _say(f"[sixteen waves] chunks={[int(v) for v in ce]} path={compress_path}")
+        check_parity(W.f32_to_bf16_words(f), z.BF16, 0.02, len(ce), ce, label=f"{len(ce)} chunks of {n}", form=compress_path)
