@@ -51,9 +51,10 @@ __device__ __forceinline__ double value_at(const uint8_t* in, uint64_t i)
  * fixed order, forms sigma, and picks the window (table_from_sigma).
  *
  * Large tensors are bound by reading (2^29 bf16 values 166 us, 6.5 TB/s), with one streamed load in flight per thread: with four the call takes
- * 5 % longer.  Up to 64 MiB, where ramps and latencies count, a thread has four loads in flight and does not stream, so that
+ * 5 % longer.  Up to 64 MiB, where ramps and latencies count, a thread requests four pieces at a time and does not stream, so that
  * the compress that usually follows finds the tensor in the caches, and workgroups take 4096 values instead of 16384 until
- * there are 2048.  us, before / after, the call: bf16 2^17 6.7 / 5.8, 2^20 6.8 / 5.9, 2^24 12.5 / 11.5, with the compress 28.7 / 26.5; fp32 2^20
+ * there are 2048.  (Of a bf16 tensor of up to 2^23 values a thread has two pieces; it requests the first of them twice more.)  us,
+ * before / after, the call: bf16 2^17 6.7 / 5.8, 2^20 6.8 / 5.9, 2^24 12.5 / 11.5, with the compress 28.7 / 26.5; fp32 2^20
  * 7.6 / 5.8, 2^22 10.7 / 8.5, with the compress 24.3 / 19.2.  The 16-byte loads are issued at the tensor's own alignment, which the
  * hardware takes (value by value off a 16-byte boundary: 2^24 bf16 values 25 us, 10.6 now; 2^26 51, 31).
  */
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(kThreads) void k_moments(const MomentArgs a)
         }
     };
     for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < n16; i += NF * stride) {
-        u32x4 v[NF];                                   /* past the end the first of them once more, not added */
+        u32x4 v[NF];                                   /* past the end the first of them again, not added */
 #pragma unroll
         for (uint32_t u = 0; u < NF; ++u) v[u] = load(i + u * stride < n16 ? i + u * stride : i);
 #pragma unroll
@@ -528,8 +529,8 @@ static_assert(sizeof(Partial<kNarrow>) * kHistBlocks <= kPartialsBytes && sizeof
  * where rows differ much: with rows of 4096 normal values whose scales are log-normal, spread by e^1 / e^1.5 / e^2 / e^3, the rank was outside for
  * 1 / 7 / 11 / 24 of 60 tensors of 512 rows, and everything was counted twice.  The sample shows it: the octave of its median and
  * the two beside it hold 0.74 of its values if they are normal, 0.54 / 0.43 / 0.36 / 0.26 with such rows.  Below a half, request_one()
- * takes 1024 values at 1024 places, after which none of these tensors misses.  That costs 2 to 3 us, as much as the
- * second counts that it saves come to at 0.5 (us per call, tensors in turn, without / with: 2^20 bf16 values, e^2, 16.6 / 13.2; 2^24 31.5 / 20.1; 2^26
+ * takes 1024 values at 1024 places, after which none of the tensors at e^1.5 and more misses.  That costs 2 to 3 us, as much as the
+ * second counts that it saves come to at about 0.45 (us per call, tensors in turn, without / with: 2^20 bf16 values, e^2, 16.6 / 13.2; 2^24 31.5 / 20.1; 2^26
  * 53.7 / 32.2; normal values 10.7 / 10.8, 16.9 / 17.0, 29.5 / 29.7).
  */
 struct SampleMedian {

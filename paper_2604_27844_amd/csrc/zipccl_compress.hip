@@ -20,7 +20,7 @@
  *              to their final place and finishes index and header.
  *              Calls on small chunks are one launch: in k_compress<kModeDirect> a workgroup counts the
  *              zero-points of its chunk's few tiles before its own itself and writes everything in place
- *              (32 x 4096 bf16 values in 8 chunks: 8.2 -> 4.8 us).
+ *              (32 x 4096 bf16 values in 8 chunks: 3.8 us, 8.2 when they were two).
  *              (Waiting in-kernel for the predecessors' counts costs a tile ~10 us of lateness
  *              of the slowest of them, measured; the stash costs ~5 % extra traffic.)
  * Everything here is integer work.
@@ -352,8 +352,9 @@ __device__ __forceinline__ void table_words(const CompressIo& a, uint32_t c, uin
     }
 }
 
-/* WAVES (8 or 16, see kWideTiles) share a tile: with four, of four groups each, 2^29 bf16 values took 4 % longer, and in launches
- * that leave most of the chip empty a wave's encodes came one after the other (32 x 4096 values 4.5 us, 3.8 with 16). */
+/* WAVES (8 or 16, see kWideTiles) share a tile: with four, of four groups each, 2^22 to 2^24 bf16 values took 3 to 6 % longer (from
+ * 2^27 on the same), and in launches that leave most of the chip empty a wave's encodes came one after the other (32 x 4096
+ * values 4.5 us, 3.8 with 16). */
 template <int DT, int MODE, uint32_t WAVES, class PARK, class SPLIT>
 __global__ __launch_bounds__(64u * WAVES) void k_compress(const CompressIo a, const PARK park, const SPLIT split)
 {
@@ -521,7 +522,7 @@ __device__ __forceinline__ void move_words(uint32_t* __restrict__ d32, const uin
  * dependent loads are in flight per wave) move the tile's zero-point exponents from the stash
  * to ESC[P, P + count), add P to the tile's 16 index entries, and the last tile of a chunk
  * writes header, padding and chunk_bytes.  Tiles dense in zero-points (more than kPlaceBig
- * bytes) are moved by the whole workgroup afterwards.
+ * bytes) are moved afterwards, by one, two or four of the workgroup's waves each.
  */
 /* SCAN: there was no k_tile_scan; the workgroup sums the chunk's tile counts before its own tiles itself
  * (chunks of at most kPlaceScanTiles tiles: the counts are few and cache-resident). */
@@ -738,9 +739,9 @@ static Parking parking_of(const CompressArgs& a) { return Parking{a.tile_total, 
 /*
  * Waves per tile: 16, one group each, for fp32, whose groups are two loads each, and in bf16 launches of up to this many
  * tiles, where every wave beyond the first few has a SIMD of its own; 8 in larger bf16 launches, where 16 hold too
- * few bytes in flight and 4 are slower from start to end.  us, 4 / 8 / 16 waves, bf16: 2^17 values in 8 chunks 4.5 / 4.0 / 3.8, 2^21
- * 7.9 / 7.55 / 7.5, 9 * 2^18 8.2 / 7.9 / 8.1, 2^23 11.5 / 11.3 / 12.6, 2^29 in 64 315 / 303 / 382; fp32: 2^17 5.5 / 4.65 / 4.2, 2^23 17.1 /
- * 16.5 / 16.4, 2^27 in 64 175 / 171 / 168.
+ * few bytes in flight.  us, 4 / 8 / 16 waves, bf16: 2^17 values in 8 chunks 4.5 / 4.0 / 3.8, 2^21 7.9 / 7.55 / 7.5, 9 * 2^18 7.9 / 7.7 / 7.8, 2^22
+ * in 8 8.4 / 8.1 / 8.9, 2^23 11.3 / 10.6 / 12.4, 2^24 15.8 / 15.4 / 18.5, 2^27 in 64 82.0 / 81.7 / 100.6, 2^29 302.4 / 302.4 / 390, with rows of gains
+ * 327.6 / 323.4 / 413; fp32: 2^17 5.5 / 4.65 / 4.2, 2^23 17.1 / 16.5 / 16.4, 2^27 in 64 175 / 171 / 168.
  */
 constexpr uint32_t kWideTiles = 256;
 
