@@ -245,8 +245,7 @@ def test_chunk_tables_match_oracle_and_follow_each_chunks_scale():
     _chunk_tables_case(many, z.BF16, np.full(300, 700, dtype=np.uint64), "300 chunks")
     tiny = np.array([0x3F80, 0x0000, 0x7F80, 0x4000, 0xC000, 0x0001, 0x4040], dtype=np.uint16)
     _chunk_tables_case(tiny, z.BF16, np.array([1, 2, 0, 4], dtype=np.uint64), "tiny chunks")
-    # chunks of more than 512 groups: histograms in the workspace, several workgroups per chunk, a finish kernel
-    # (smaller chunks are taken by one workgroup each, in one kernel)
+    # chunks of more than 508 groups: several workgroups per chunk, a finish kernel, a zeroed histogram in the workspace
     ce_big = np.array([700_001, 0, 1024 * 512 + 1, 1024 * 512, 40_000], dtype=np.uint64)
     sig_big = [0.02, 1.0, 3.0, 1e-3, 0.5]
     big = np.concatenate([W.f32_to_bf16_words(rng.standard_normal(int(n), dtype=np.float32) * np.float32(s)) for n, s in zip(ce_big, sig_big)])
@@ -353,7 +352,7 @@ def test_sampled_estimate_seeded_fuzz():
         assert np.array_equal(d_tabs.cpu().numpy().reshape(C, 8), decs), case
 
 
-@pytest.mark.parametrize("n", [5000, 300_007])                # one kernel; histogram in the workspace
+@pytest.mark.parametrize("n", [5000, 300_007, 600_007])       # one kernel; the wide window; the narrow one
 def test_robust_rank_at_the_edges_of_the_bins(n):
     """The rank's bin at the ends of what counts and of every unit the search works in (4 bins of a thread, 256 of a
     wave, 4096 of a step), alone and between neighbours: sigma bit-equal to the oracle's (a count)."""
@@ -385,9 +384,8 @@ def test_robust_counts_past_32_bits():
 
 @pytest.mark.parametrize("dtype", [z.BF16, z.FP32])
 def test_estimate_of_chunks_shared_by_a_few_workgroups(dtype):
-    """Chunks on either side of the sizes at which the number of workgroups per chunk changes (one below 160 groups to
-    count, up to four below 509, then a histogram in the workspace), a workgroup's counts all in one bin (127 groups of
-    equal values: the largest 16-bit count), ragged and element-aligned chunks beside empty ones: bit-equal to the oracle."""
+    """Chunks of one workgroup to a few (32 groups to count each, up to 508 in all without a shared histogram for a second
+    count), counts all in one bin, ragged and element-aligned chunks beside empty ones: bit-equal to the oracle."""
     rng = np.random.default_rng(31)
     G = 512
     for stride, groups in ((1, (159, 160, 161, 254, 255)), (1, (381, 382, 507, 508)), (1, (509, 3)), (4, (4 * 160, 4 * 508 - 1, 4 * 508))):
