@@ -685,7 +685,7 @@ __global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a,
         for (uint32_t u = 0; u < NF; ++u) load(u, k0 + u * n_waves < whole ? k0 + u * n_waves : 0u);
     }
     for (uint32_t i = threadIdx.x; i < W + 128u; i += kHistThreads) s_bins[i] = 0u;
-    bool doubtful;                                           /* the wide window holds what such a sample can be off */
+    bool doubtful;                                           /* (the wide window holds what such a sample can be off) */
     median.put(s_sample);
     uint32_t at = SampleMedian::find(s_sample, s_cnt, wave, lane, doubtful) + 4u;
     if (W == kNarrow && doubtful && whole >= 16u) {                          /* fewer groups are soon counted once more */

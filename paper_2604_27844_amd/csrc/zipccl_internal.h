@@ -236,7 +236,7 @@ struct WindowPlan {
     bool shared;             /* a second count goes to a histogram that the first kernel zeroes */
     bool stream;             /* loads past the caches */
 };
-constexpr uint32_t kWideParts = 32;                  /* workgroups per chunk that a chunk's workspace has room for with the wide window */
+constexpr uint32_t kWideParts = 16;                  /* workgroups per chunk up to which the window is the wide one */
 constexpr uint32_t kManyChunks = 32, kManyChunksAlone = 2048;
 
 ZIPCCL_HD WindowPlan window_plan(const ChunkTab& t, int dt, uint32_t sample_stride)
@@ -247,9 +247,9 @@ ZIPCCL_HD WindowPlan window_plan(const ChunkTab& t, int dt, uint32_t sample_stri
     const uint64_t want = (groups + 31) / 32, most = kHistBlocks / t.n_chunks;
     p.parts = (uint32_t)(want < 1 ? 1 : (want < most ? want : most));
     /* The wide window is never left by values that the narrow one loses 1 in 5 times (rows of scales spread by e^2), and where few
-       workgroups share a chunk its counts are no more to read than the narrow one's elsewhere (us, bf16, tensors in turn, narrow / wide, normal
-       values: 64 chunks of 2^19 24.7 / 24.4, 64 of 3 670 016 from one group in 16 15.5 / 15.3; rows spread by e^2: 28.6 / 24.1; 8 of 2^21 from
-       one group in 16 13.8 / 10.6) */
+       workgroups share a chunk its counts are as quick to read.  us, bf16, tensors in turn, narrow / wide, normal values | rows spread by
+       e^2: 64 chunks of 2^19 24.7 / 24.4 | 28.6 / 24.1, 8 of 2^21 from one group in 16 (8 workgroups each) 11.3 / 10.8 | 13.8 / 10.7; with 32 workgroups
+       each normal values lose by it: 8 of 2^20 15.2 / 15.5 | 17.9 / 15.3, one of 2^19 10.8 / 11.1 | 13.1 / 10.8 */
     p.wide = p.parts <= kWideParts;
     /* 128 KiB zeroed per chunk are time in a launch of many small chunks (64 of 2^19 bf16 values 26.6 us with, 24.7 without), which fill the
        chip with one workgroup each should all of them be counted twice (64 of 2^20 110 us with, 95 without; 8 of 2^20 38 and 76) */
