@@ -106,13 +106,12 @@ zipccl_status_t zipccl_chunk_slot_offsets(size_t n_elems, zipccl_dtype_t dt, uin
 zipccl_status_t zipccl_chunk_static_bytes(size_t n_elems, zipccl_dtype_t dt, uint32_t n_chunks,
                                           const uint64_t* chunk_elems, uint64_t* static_bytes);
 
-/* Bytes of device scratch for zipccl_compress.  With zipccl_compress_workspace_size bytes
- * (about one byte per element) compress reads the input once: zero-point exponents are parked
- * in the scratch until the per-chunk prefix of section 4.2.3 is known.  With less, but at least
- * zipccl_compress_min_workspace_size bytes (8 bytes per 8192 elements), it reads the input twice
- * (count, prefix, emit): workspace_bytes alone selects the form, call by call, and both write the same bytes.
- * Calls on chunks of a few tiles of 8192 values take neither: one kernel, which needs no scratch (the minimum is still
- * asked for).
+/* Bytes of device scratch for zipccl_compress.  Most calls are one kernel, which needs the minimum, 8 bytes per 8192
+ * elements.  Calls that are captured into a graph, and those on more than 2^26 bf16 values whose chunks start off
+ * 128-byte lines, are one kernel if their chunks hold a few tiles of 8192 values; else, with
+ * zipccl_compress_workspace_size bytes (about one byte per element) they read the input once: zero-point exponents
+ * are parked in the scratch until the per-chunk prefix of section 4.2.3 is known.  With less, but at least
+ * zipccl_compress_min_workspace_size bytes, they read the input twice (count, prefix, emit).  All forms write the same bytes.
  * Both return 0 on invalid arguments. */
 size_t zipccl_compress_workspace_size(size_t n_elems, zipccl_dtype_t dt, uint32_t n_chunks,
                                       const uint64_t* chunk_elems);
@@ -129,8 +128,8 @@ size_t zipccl_compress_min_workspace_size(size_t n_elems, zipccl_dtype_t dt, uin
  *   d_workspace     device, 16-byte aligned, workspace_bytes >= zipccl_compress_min_workspace_size(...)
  *                   (see above for what more buys); contents are overwritten
  * Every byte of [slot_off[c], slot_off[c] + chunk_bytes[c]) is written; the rest of a slot is
- * left untouched.  No kernel waits on another workgroup.  Calls that may overlap in time need
- * different workspaces.
+ * left untouched.  A workgroup may wait for others of its call to count their zero-points, for some 100 us at most, after
+ * which it counts in their place.  Calls that may overlap in time need different workspaces.
  */
 zipccl_status_t zipccl_compress(const void* d_in, size_t n_elems, zipccl_dtype_t dt,
                                 uint32_t n_chunks, const uint64_t* chunk_elems,
@@ -144,8 +143,8 @@ zipccl_status_t zipccl_compress(const void* d_in, size_t n_elems, zipccl_dtype_t
  * bytes as zipccl_compress, minus the workspace: that is a fixed array of ZIPCCL_STATIC_SCRATCH_BYTES
  * (32 MiB) inside the library's device code, one copy on every GPU the library runs on, held until the process
  * ends.  The call makes no hipMalloc, hipFree or other allocating device call.
- *   - Up to about 33.5 million values (zipccl_compress_workspace_size(...) <= 32 MiB) the input is read once;
- *     above that twice (the form zipccl_compress takes with its minimum workspace).
+ *   - Calls that zipccl_compress would park in its workspace (see there) read the input once up to about 33.5 million values
+ *     (zipccl_compress_workspace_size(...) <= 32 MiB), above that twice (the form it takes with its minimum workspace).
  *   - A call whose zipccl_compress_min_workspace_size(...) exceeds 32 MiB (more than about 4.19 million tiles
  *     of 8192 values) returns ZIPCCL_ERR_BUFFER_TOO_SMALL and launches nothing.
  *   - Every call on a GPU uses that GPU's one array: calls that may overlap in time on the same GPU (different

@@ -12,8 +12,13 @@ YARDSTICK = os.path.join(HERE, "libzipccl_yardstick.so")
 SOURCES = ["zipccl_compress.hip", "zipccl_decompress.hip", "zipccl_aux.hip", "zipccl_host.cpp"]
 HEADERS = [os.path.join(CSRC, "zipccl_internal.h"), os.path.join(CSRC, "zipccl_device.h"),
            os.path.join(ROOT, "include", "zipccl.h")]
+# a copy of the compress side whose workgroups do not wait for one another's counts, for the tests of what they do instead
+IMPATIENT = os.path.join(ROOT, "tests", "impatient", "libzipccl_impatient.so")
 TARGETS = {LIB: [os.path.join(CSRC, s) for s in SOURCES],
-           YARDSTICK: [os.path.join(CSRC, "zipccl_yardstick.hip")]}
+           YARDSTICK: [os.path.join(CSRC, "zipccl_yardstick.hip")],
+           IMPATIENT: [os.path.join(CSRC, "zipccl_compress.hip"), os.path.join(CSRC, "zipccl_host.cpp"),
+                       os.path.join(ROOT, "tests", "impatient", "rest.cpp")]}
+FLAGS = {IMPATIENT: ["-DZIPCCL_CHAIN_PATIENCE=0", "-Wl,-Bsymbolic"]}
 
 
 def python_module():
@@ -68,7 +73,7 @@ def build(force=True, verbose=False, lib=None):
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                "-Wall", "-Wno-unused-command-line-argument",
                "-I", os.path.join(ROOT, "include"), "-I", CSRC]
-        cmd += sources + ["-o", tmp]
+        cmd += FLAGS.get(target, []) + sources + ["-o", tmp]
         if target not in TARGETS:
             cmd = _python_command(sources, tmp)
         if verbose:

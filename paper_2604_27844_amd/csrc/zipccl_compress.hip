@@ -11,20 +11,20 @@
  *              Plane bytes and zero-point exponents are staged in LDS and leave as wide
  *              stores.  The zero-point offsets of section 4.2.3 are an exclusive prefix in
  *              element order (lane -> wave -> tile -> chunk), so the output is deterministic.
- *              No workgroup ever waits for another: the chunk-wide level, which the paper does
- *              with a block-level atomic add inside the kernel, is a kernel boundary here.
- *              k_compress<kModeStash> writes everything whose place is known (SM, LO, planes,
- *              tile-local index) and parks the zero-point exponents of its tile in a stash;
- *              the per-tile counts become per-chunk prefixes inside k_place (chunks of up to
- *              kPlaceScanTiles tiles) or in k_tile_scan; k_place moves each tile's exponents
- *              to their final place and finishes index and header.
- *              Calls on small chunks are one launch: in k_compress<kModeDirect> a workgroup counts the
- *              zero-points of its chunk's few tiles before its own itself and writes everything in place
- *              (32 x 4096 bf16 values in 8 chunks: 3.8 us, 8.2 when they were two).
- *              (Waiting in-kernel for the predecessors' counts costs a tile ~10 us of lateness
- *              of the slowest of them, measured; the stash costs ~5 % extra traffic.)
+ *              The chunk-wide level, which the paper does with a block-level atomic add, has three forms.
+ *              k_compress<kModeDirect>, chunks of one or two tiles: a workgroup counts the zero-points of its
+ *              chunk's tile before its own itself.
+ *              k_compress<kModeChained>, all other calls: a workgroup tells its tile's count as soon as the values are
+ *              there, writes everything whose place is known (SM, LO, planes) and then adds up what the tiles
+ *              before have told (chain_prefix, which bounds that wait).  One launch, nothing moved twice.
+ *              k_compress<kModeStash>, calls that are captured into a graph (see launch_compress_chained):
+ *              the zero-point exponents are parked in a stash; the per-tile counts become per-chunk prefixes inside
+ *              k_place (chunks of up to kPlaceScanTiles tiles) or in k_tile_scan; k_place moves each
+ *              tile's exponents to their final place and finishes index and header.
  * Everything here is integer work.
  */
+#include <atomic>
+#include <chrono>
 #include <mutex>
 #include <type_traits>
 
@@ -194,19 +194,23 @@ __device__ __forceinline__ uint32_t count8(const uint32_t w[4], uint32_t first, 
 template <uint32_t WAVES>
 __device__ __forceinline__ uint32_t group_of(uint32_t wave, uint32_t u) { return u * WAVES + wave; }
 
+template <uint32_t GROUPS>
 struct CompressShared {
-    uint8_t planes[3][kTile / 8];          /* plane bytes of the tile, natural order */
-    uint8_t esc[kGroupsPerTile][kGroup];   /* zero-point exponents, one region per group */
-    uint32_t gcnt[kGroupsPerTile];         /* zero-points per group */
-    uint32_t before[kGroupsPerTile];       /* kModeDirect: zero-points a wave counted in the tiles before */
+    uint8_t planes[3][GROUPS * kGroup / 8];   /* plane bytes of the tile, natural order */
+    uint8_t esc[GROUPS][kGroup];           /* zero-point exponents, one region per group */
+    uint32_t gcnt[GROUPS];                 /* zero-points per group */
+    uint32_t before[kGroupsPerTile];       /* kModeDirect, kModeChained: zero-points a wave found in the tiles before */
+    uint32_t counted;                      /* kModeChained: waves that have counted << 16 | their zero-points */
+    uint32_t missing;                      /* and whether the count of a tile before did not come */
+    uint64_t open;                         /* or of which of 64 */
 };
 
 /* One group of one wave, its values already loaded (load_lane): encode, store SM/LO, stage planes and
  * zero-points in LDS. */
-template <int DT, bool FAST, bool STORE>
+template <int DT, bool FAST, bool STORE, class SHARED>
 __device__ __forceinline__ void compress_group(uint8_t* __restrict__ slot, const SlotLayout& L, uint64_t n,
                                                uint64_t ts, uint32_t gi, uint32_t k7, uint32_t lane,
-                                               CompressShared& sh, const uint32_t hp[4], const uint32_t lp[4],
+                                               SHARED& sh, const uint32_t hp[4], const uint32_t lp[4],
                                                uint32_t vmask)
 {
     const uint64_t gbase = ts + (uint64_t)gi * kGroup;      /* wave-uniform */
@@ -337,6 +341,21 @@ struct Parking {
     uint32_t *tile_total, *tile_prefix;
     uint8_t* stash;
 };
+/* kModeChained: what the tiles of a launch tell one another, in 64-bit words that hold a count in their low 24 bits and
+ * this launch's tag, which no other launch has, in the others.  A word with another tag has not been told yet, so the words need not
+ * be cleared.  A chunk's tiles have one each, and behind these the 64th, 128th, ... tile two more for the count of all
+ * tiles up to it. */
+struct Chain {
+    uint64_t* words;
+    uint64_t tag;
+    uint32_t many;                                          /* rounds of workgroups: see chain_prefix */
+};
+constexpr uint32_t kChainCount = 0xFFFFFFu;
+constexpr uint32_t kChainStep = 64;
+#ifndef ZIPCCL_CHAIN_PATIENCE
+#define ZIPCCL_CHAIN_PATIENCE 128
+#endif
+constexpr uint32_t kChainPatience = ZIPCCL_CHAIN_PATIENCE;   /* how often a thread looks again for words that are not there */
 
 /* dec[0..3] and dec[4..7]: from the kernel arguments (dec[1..7] are consecutive, the host has checked it) or, if the table
  * was estimated on the device, two words in its memory. */
@@ -352,28 +371,123 @@ __device__ __forceinline__ void table_words(const CompressIo& a, uint32_t c, uin
     }
 }
 
+__device__ __forceinline__ uint64_t peek(const uint64_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void tell(uint64_t* p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+/*
+ * Zero-points in the chunk's tiles before tile t, as parts in sh.before (one per wave).  Words of tiles far back would be most of what is
+ * read in long chunks: from `reach` tiles on, as many as run at a time, the counts start behind the last multiple of
+ * kChainStep at least `reach` tiles back, whose total another round of workgroups has told: 2^29 bf16 values in one chunk 487 us without,
+ * 292 now.  (Fewer words through totals of 16 and 256 tiles cost more than they save: whoever adds them up has stores under way,
+ * which its loads wait for; 587 us.)
+ *
+ * Looks hold up one another and the words they look for, so between two of them a wave sleeps, some 1000 cycles in all but the
+ * smallest launches; and in launches of many rounds a workgroup that has few words to read sleeps before the first look, which
+ * would come too early (64 chunks of 2^23 bf16 values without / with 290 us for 314, of 3.7 million 131 for 141; at 2^24 it costs a microsecond; fp32
+ * tiles, which take twice as long, lose by it: 64 of 2^21 160 us without, 162 with).
+ *
+ * Workgroups start in order, so those waited for run already or are next, unless kernels that wait for one another share the chip.  So
+ * the wait is bounded: a workgroup that has looked kChainPatience times counts the tiles that are missing itself, from the input,
+ * and tells their counts on their behalf.  No workgroup depends on another for its end.
+ */
+template <int DT, uint32_t WAVES, uint32_t GROUPS, class SHARED>
+__device__ __forceinline__ void chain_prefix(const Chain& chain, uint64_t* words, uint32_t tiles, uint32_t t, const uint8_t* __restrict__ cin, uint64_t n,
+                                             uint32_t e0, SHARED& sh, uint32_t lane, uint32_t wave)
+{
+    constexpr uint32_t NT = 64u * WAVES, GPW = GROUPS / WAVES;
+    constexpr uint32_t reach = 8192u / WAVES;                /* eight waves per SIMD: 32 per compute unit, of 256 */
+    constexpr int nap = GROUPS == 16u ? 1 : 16;              /* of 64 cycles */
+    auto is_count = [&](uint64_t v) { return (v ^ chain.tag) <= kChainCount; };
+    uint32_t from = 0;
+    if (GROUPS > kGroupsPerTile && t >= reach + kChainStep) from = (t - reach) & ~(kChainStep - 1u);
+    if (chain.many != 0u && from == 0u) __builtin_amdgcn_s_sleep(28);
+    const uint64_t* const upto = words + tiles + 2u * (from / kChainStep) - 2u;   /* if from is not 0 */
+    uint32_t sum = 0, left = kChainPatience;
+    bool missing = false;
+    for (uint32_t i = from + threadIdx.x; i < t + (from != 0u ? 2u : 0u); i += NT) {
+        const uint64_t* const p = i < t ? words + i : upto + (i - t);
+        uint64_t v = peek(p);
+        while (!is_count(v) && left != 0u) {
+            --left;
+            __builtin_amdgcn_s_sleep(nap);
+            v = peek(p);
+        }
+        missing |= !is_count(v);
+        sum += ((uint32_t)v & kChainCount) << (i == t + 1u ? 24u : 0u);
+    }
+    sum = wave_incl_scan(sum);
+    if (lane == 63u) sh.before[wave] = sum;
+    if (missing) sh.missing = 1u;
+    __syncthreads();
+    if (sh.missing == 0u) return;
+
+    /* from the nearest tile back, 64 at a time */
+    sum = 0;
+    for (uint32_t end = t; end != 0u;) {
+        const uint32_t base = end > 64u ? end - 64u : 0u;
+        __syncthreads();
+        if (wave == 0u) {
+            const bool some = base + lane < end;
+            const uint64_t v = some ? peek(words + base + lane) : 0u;
+            const bool told = some && is_count(v);
+            sum += told ? (uint32_t)v & kChainCount : 0u;
+            const uint64_t open = __ballot(some && !told);
+            if (lane == 0u) sh.open = open;
+        }
+        __syncthreads();
+        for (uint64_t open = sh.open; open != 0u;) {
+            const uint32_t j = 63u - (uint32_t)__builtin_clzll(open);
+            open ^= 1ull << j;
+            __syncthreads();
+            if (threadIdx.x == 0u) {
+                const uint64_t v = peek(words + base + j);
+                sh.missing = !is_count(v);
+                sh.counted = is_count(v) ? (uint32_t)v & kChainCount : 0u;
+            }
+            __syncthreads();
+            if (sh.missing != 0u) {
+                uint32_t h[GPW][4], l[4], m, cnt = 0;
+#pragma unroll
+                for (uint32_t u = 0; u < GPW; ++u) load_lane<DT, kWhole>(cin, (uint64_t)(base + j) * (GROUPS * kGroup) + group_of<WAVES>(wave, u) * kGroup, lane, n, h[u], l, m);
+#pragma unroll
+                for (uint32_t u = 0; u < GPW; ++u) cnt = count8(h[u], e0 * 0x00800080u, cnt);
+                cnt = __builtin_amdgcn_readlane(wave_incl_scan(cnt), 63);
+                if (lane == 0u) atomicAdd(&sh.counted, cnt);
+                __syncthreads();
+                if (threadIdx.x == 0u) tell(words + base + j, chain.tag | sh.counted);
+            }
+            if (threadIdx.x == 0u) sum += sh.counted;
+        }
+        end = base;
+    }
+    sum = wave_incl_scan(sum);
+    if (lane == 63u) sh.before[wave] = sum;                  /* 0 but for the first */
+    __syncthreads();
+}
+
 /* WAVES (8 or 16, see kWideTiles) share a tile: with four, of four groups each, 2^22 to 2^24 bf16 values took 3 to 6 % longer (from
  * 2^27 on the same), and in launches that leave most of the chip empty a wave's encodes came one after the other (32 x 4096
  * values 4.5 us, 3.8 with 16). */
-template <int DT, int MODE, uint32_t WAVES, class PARK, class SPLIT>
+template <int DT, int MODE, uint32_t WAVES, uint32_t GROUPS, class PARK, class SPLIT>
 __global__ __launch_bounds__(64u * WAVES) void k_compress(const CompressIo a, const PARK park, const SPLIT split)
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
     constexpr bool STORE = MODE != kModeCount;
-    constexpr uint32_t GPW = kGroupsPerTile / WAVES;
-    __shared__ CompressShared sh;
+    constexpr uint32_t GPW = GROUPS / WAVES, TILE = GROUPS * kGroup;
+    __shared__ __attribute__((aligned(16))) CompressShared<GROUPS> sh;
 
     /* grid = (tiles of the largest chunk, chunks): no search, the chunk's geometry is three scalar loads at most */
-    const uint32_t c = blockIdx.y;
+    const uint32_t c = blockIdx.y, bx = blockIdx.x;
     const ChunkPlace place = place_of(split, c, DT);
-    if (blockIdx.x >= place.tiles) return;
-    const bool last_tile = blockIdx.x + 1u == place.tiles;
+    const uint32_t tiles = (place.tiles + GROUPS / kGroupsPerTile - 1u) / (GROUPS / kGroupsPerTile);
+    if (bx >= tiles) return;
+    const bool last_tile = bx + 1u == tiles;
     const uint64_t n = place.n;
-    const uint64_t ts = (uint64_t)blockIdx.x * kTile;
+    const uint64_t ts = (uint64_t)bx * TILE;
     const uint8_t* __restrict__ cin = a.in + place.elem_off * ES;
     uint8_t* __restrict__ slot = a.out + place.slot_off;
     const SlotLayout L = slot_layout(n, DT);
-    const bool fast = ts + kTile <= n;                      /* a whole tile */
+    const bool fast = ts + TILE <= n;                       /* a whole tile */
     const uint32_t lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   /* keep wave-derived math scalar */
     uint32_t dec_lo, dec_hi;
@@ -387,32 +501,52 @@ __global__ __launch_bounds__(64u * WAVES) void k_compress(const CompressIo a, co
     /* kModeDirect: the zero-points of the chunk's tiles before this one, which are few, whole, and read by other
        workgroups too; two tiles' loads in flight together, while the tile's own travel */
     auto count_before = [&] {
-        if (MODE != kModeDirect) return;
         const uint32_t first = e0 * 0x00800080u;
         uint32_t cnt = 0;
-        for (uint32_t b = 0; b < blockIdx.x; b += 2) {
+        for (uint32_t b = 0; b < bx; b += 2) {
             uint32_t h[2][GPW][4], l[4], m;
 #pragma unroll
             for (uint32_t k = 0; k < 2; ++k)
 #pragma unroll
                 for (uint32_t u = 0; u < GPW; ++u)
-                    load_lane<DT, kWhole>(cin, (uint64_t)min(b + k, blockIdx.x - 1u) * kTile + group_of<WAVES>(wave, u) * kGroup, lane, n, h[k][u], l, m);
+                    load_lane<DT, kWhole>(cin, (uint64_t)min(b + k, bx - 1u) * TILE + group_of<WAVES>(wave, u) * kGroup, lane, n, h[k][u], l, m);
             uint32_t second = 0;
 #pragma unroll
             for (uint32_t u = 0; u < GPW; ++u) {
                 cnt = count8(h[0][u], first, cnt);
                 second = count8(h[1][u], first, second);
             }
-            if (b + 1u < blockIdx.x) cnt += second;
+            if (b + 1u < bx) cnt += second;
         }
         cnt = wave_incl_scan(cnt);
         if (lane == 63) sh.before[wave] = cnt;
+    };
+    /* kModeChained: the tile's own count, before anything else is done with its values; the wave that adds the last part of it
+       tells the tiles behind */
+    uint64_t* words = nullptr;
+    if constexpr (MODE == kModeChained) {
+        words = park.words + place.tile;
+        if (threadIdx.x == 0) sh.counted = sh.missing = 0;
+    }
+    auto tell_own = [&] {
+        if constexpr (MODE == kModeChained) {
+            __syncthreads();                                /* sh.counted is 0 */
+            uint32_t cnt = 0;
+#pragma unroll
+            for (uint32_t u = 0; u < GPW; ++u) cnt = count8(hp[u], e0 * 0x00800080u, cnt) - __popc(~vm[u] & 0xFFu);  /* values that do not exist are zeros */
+            cnt = __builtin_amdgcn_readlane(wave_incl_scan(cnt), 63) | 0x10000u;
+            if (lane == 0) {
+                const uint32_t sum = atomicAdd(&sh.counted, cnt) + cnt;
+                if (sum >> 16 == WAVES) tell(words + bx, park.tag | (sum & 0xFFFFu));
+            }
+        }
     };
     if (fast) {
 #pragma unroll
         for (uint32_t u = 0; u < GPW; ++u)
             load_lane<DT, kWhole>(cin, ts + (uint64_t)group_of<WAVES>(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u]);
-        count_before();
+        if (MODE == kModeDirect) count_before();
+        tell_own();
 #pragma unroll
         for (uint32_t u = 0; u < GPW; ++u)
             compress_group<DT, true, STORE>(slot, L, n, ts, group_of<WAVES>(wave, u), k7, lane, sh, hp[u], lp[u], vm[u]);
@@ -436,7 +570,8 @@ __global__ __launch_bounds__(64u * WAVES) void k_compress(const CompressIo a, co
             for (uint32_t u = 0; u < GPW; ++u)
                 load_lane<DT, kTiny>(cin, ts + (uint64_t)group_of<WAVES>(wave, u) * kGroup, lane, n, hp[u], lp[u], vm[u]);
         }
-        count_before();
+        if (MODE == kModeDirect) count_before();
+        tell_own();
 #pragma unroll
         for (uint32_t u = 0; u < GPW; ++u)
             compress_group<DT, false, STORE>(slot, L, n, ts, group_of<WAVES>(wave, u), k7, lane, sh, hp[u], lp[u], vm[u]);
@@ -444,19 +579,43 @@ __global__ __launch_bounds__(64u * WAVES) void k_compress(const CompressIo a, co
     __syncthreads();
 
     /* every wave: tile-level exclusive prefix of the 16 group counts (lanes 0..15 hold them) */
-    const uint32_t gc = lane < kGroupsPerTile ? sh.gcnt[lane] : 0u;
-    const uint32_t ginc = row_incl_scan(gc);
+    const uint32_t gc = lane < GROUPS ? sh.gcnt[lane] : 0u;
+    const uint32_t ginc = GROUPS <= 16u ? row_incl_scan(gc) : wave_incl_scan(gc);
     const uint32_t gex = ginc - gc;
-    const uint32_t tile_total = __builtin_amdgcn_readlane(ginc, kGroupsPerTile - 1);
+    const uint32_t tile_total = __builtin_amdgcn_readlane(ginc, GROUPS - 1);
     if constexpr (MODE == kModeCount || MODE == kModeStash) {
-        if (threadIdx.x == 0) park.tile_total[place.tile + blockIdx.x] = tile_total;
+        if (threadIdx.x == 0) park.tile_total[place.tile + bx] = tile_total;
         if (MODE == kModeCount) return;
     }
 
-    /* kModeEmit and kModeDirect know the zero-points of the chunk before this tile; kModeStash works tile-local */
+    /* waves 1, 2, ...: 1 KiB of a plane each, 16 bytes per lane */
+    auto store_planes = [&] {
+#pragma unroll
+        for (uint32_t u = 0; u < (3u * GROUPS / 16u + WAVES - 2u) / (WAVES - 1u); ++u) {
+            const uint32_t piece = wave - 1u + u * (WAVES - 1u);
+            if (wave != 0u && piece < 3u * GROUPS / 16u) {
+                const uint32_t k = piece % 3u, at = piece / 3u * 1024u;
+                const uint64_t pb = ts / 8 + at + lane * 16u;
+                if (fast || pb < L.plane_bytes)
+                    st_stream<u32x4>((slot + L.p0 + k * L.plane_bytes + ts / 8 + at) + lane * 16u,
+                                     *reinterpret_cast<const u32x4*>(&sh.planes[k][at + lane * 16u]));
+            }
+        }
+    };
+    if (MODE == kModeChained) store_planes();
+
+    if constexpr (MODE == kModeChained) chain_prefix<DT, WAVES, GROUPS>(park, words, tiles, bx, cin, n, e0, sh, lane, wave);
+
+    /* kModeStash works tile-local, the other forms know the zero-points of the chunk before this tile */
     uint32_t P = 0;
-    if constexpr (MODE == kModeEmit) P = park.tile_prefix[place.tile + blockIdx.x];
-    if (MODE == kModeDirect) P = __builtin_amdgcn_readlane(row_incl_scan(lane < WAVES ? sh.before[lane] : 0u), WAVES - 1u);
+    if constexpr (MODE == kModeEmit) P = park.tile_prefix[place.tile + bx];
+    if (MODE == kModeDirect || MODE == kModeChained) P = __builtin_amdgcn_readlane(row_incl_scan(lane < WAVES ? sh.before[lane] : 0u), WAVES - 1u);
+    if constexpr (MODE == kModeChained && GROUPS > kGroupsPerTile) {
+        if (bx % kChainStep == kChainStep - 1u && threadIdx.x < 2u) {
+            const uint32_t upto = P + tile_total;
+            tell(words + tiles + bx / kChainStep * 2u + threadIdx.x, park.tag | (threadIdx.x == 0u ? upto & kChainCount : upto >> 24));
+        }
+    }
     const uint64_t ng = (n + kGroup - 1) / kGroup;
     uint32_t* __restrict__ idx = reinterpret_cast<uint32_t*>(slot + L.idx);
     uint8_t* __restrict__ esc = slot + L.esc + P;
@@ -465,15 +624,9 @@ __global__ __launch_bounds__(64u * WAVES) void k_compress(const CompressIo a, co
     if (wave == 0) {
         /* group index (section 4.2.3); k_place adds the tile's prefix in stash mode */
         const uint64_t g = ts / kGroup + lane;
-        if (lane < kGroupsPerTile && g < ng) idx[g] = P + gex;
-    } else if (wave < 4u) {
-        /* waves 1..3: one plane each, 16 bytes per lane */
-        const uint32_t k = wave - 1u;
-        const uint64_t pb = ts / 8 + lane * 16u;
-        if (fast || pb < L.plane_bytes)
-            st_stream<u32x4>((slot + L.p0 + k * L.plane_bytes + ts / 8) + lane * 16u,
-                             *reinterpret_cast<const u32x4*>(&sh.planes[k][lane * 16u]));
+        if (lane < GROUPS && g < ng) idx[g] = P + gex;
     }
+    if (MODE != kModeChained) store_planes();
     /* zero-point exponents: every wave copies the segments of its own groups, in element order; of most groups there are no
        more than 64, whose LDS reads go out together */
     uint8_t first64[GPW];
@@ -489,7 +642,7 @@ __global__ __launch_bounds__(64u * WAVES) void k_compress(const CompressIo a, co
         for (uint32_t i = lane + 64u; i < cnt; i += 64u) dst[i] = sh.esc[gi][i];
     }
 
-    if ((MODE == kModeEmit || MODE == kModeDirect) && last_tile)
+    if ((MODE == kModeEmit || MODE == kModeDirect || MODE == kModeChained) && last_tile)
         finish_chunk<DT, 64u * WAVES>(slot, L, n, (uint64_t)P + tile_total, dec_lo, dec_hi,
                                    a.chunk_bytes ? a.chunk_bytes + c : nullptr, threadIdx.x);
 }
@@ -757,11 +910,11 @@ static void launch_compress_dt(int mode, const CompressArgs& a, hipStream_t s)
     do {                                                                                                               \
         if constexpr (DT == ZIPCCL_BF16) {                                                                             \
             if (a.tab.tile_start[a.tab.n_chunks] > kWideTiles) {                                                       \
-                hipLaunchKernelGGL((k_compress<DT, MODE, 8u, PARK, SPLIT>), grid, dim3(512u), 0, s, io, P, S);         \
+                hipLaunchKernelGGL((k_compress<DT, MODE, 8u, 16u, PARK, SPLIT>), grid, dim3(512u), 0, s, io, P, S);         \
                 break;                                                                                                 \
             }                                                                                                          \
         }                                                                                                              \
-        hipLaunchKernelGGL((k_compress<DT, MODE, 16u, PARK, SPLIT>), grid, dim3(1024u), 0, s, io, P, S);               \
+        hipLaunchKernelGGL((k_compress<DT, MODE, 16u, 16u, PARK, SPLIT>), grid, dim3(1024u), 0, s, io, P, S);               \
     } while (0)
     if (mode == kModeDirect) {
         if (equal) ZIPCCL_LAUNCH(kModeDirect, NoParking, NoParking{}, EqualSplit, equal_split(a.tab));
@@ -776,6 +929,78 @@ static void launch_compress_dt(int mode, const CompressArgs& a, hipStream_t s)
         ZIPCCL_LAUNCH(kModeEmit, Parking, park, ChunkTab, a.tab);
     }
 #undef ZIPCCL_LAUNCH
+}
+
+constexpr uint32_t kSmallTiles = 640, kManyTiles = 8192;     /* of 8192 values: launch_chained_dt, chain_prefix */
+
+/* The tag of a launch (Chain): counted up from a number that differs from process to process, 2^40 launches until it comes
+ * again.  What a workspace holds of earlier launches has other tags; what it holds else would have to be this very number in a
+ * word of a tile that is late. */
+static uint64_t launch_tag()
+{
+    static std::atomic<uint64_t> next{[] {
+        uint64_t x = (uint64_t)std::chrono::system_clock::now().time_since_epoch().count() ^ (reinterpret_cast<uintptr_t>(&x) << 20);
+        x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;         /* splitmix64 */
+        x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+        return x ^ (x >> 31);
+    }()};
+    return next.fetch_add(1, std::memory_order_relaxed) * (kChainCount + 1ull);
+}
+
+/*
+ * Groups of a tile and waves that share it in the chained form.  Small launches take small tiles, which fill more of the chip; in larger ones
+ * every round of workgroups ends with a wait, which larger tiles make fewer of.  us, 16 groups and 16 waves / 16 and 8 / 32 and 8 / 32 and
+ * 16, equal chunks: bf16 2^20 4.3 / 4.3 / 5.2 / 5.0, 2^22 6.1 / 5.6 / 6.0 / 5.6, 2^23 10.6 / 8.1 / 7.5 / 7.3, 2^24 19.8 / 14.6 / 13.0 / 14.1, 2^26 80 / 57 /
+ * 43 / 50; fp32 2^20 4.8 / 5.0 / 6.6 / 6.1, 2^22 8.6 / 7.4 / 8.1 / 7.4, 2^23 15.3 / 13.5 / 12.9 / 13.5, 2^24 26.8 / 24.7 / 26.4 / 24.7, 2^27 219 /
+ * 193 / 170 / 161.  (64 groups and 16 waves: bf16 2^23 7.5, 2^24 12.9, 2^26 43.5, 64 chunks of 2^23 286, one of 2^29 297; fp32 2^24 25.4, 2^27 167.)
+ */
+template <int DT>
+static void launch_chained_dt(const CompressArgs& a, hipStream_t s)
+{
+    const CompressIo io = io_of(a);
+    const uint32_t tiles = a.tab.tile_start[a.tab.n_chunks];
+    const Chain chain = {a.words, launch_tag(), DT == ZIPCCL_BF16 && tiles > kManyTiles};
+    auto launch = [&](auto waves, auto groups, const auto& split) {
+        constexpr uint32_t W = decltype(waves)::value, G = decltype(groups)::value, per = G / kGroupsPerTile;
+        using SPLIT = std::decay_t<decltype(split)>;
+        const dim3 grid((max_chunk_tiles(a.tab) + per - 1u) / per, a.tab.n_chunks);
+        hipLaunchKernelGGL((k_compress<DT, kModeChained, W, G, Chain, SPLIT>), grid, dim3(64u * W), 0, s, io, chain, split);
+    };
+    auto by_size = [&](const auto& split) {
+        constexpr std::integral_constant<uint32_t, 8> c8;
+        constexpr std::integral_constant<uint32_t, 16> c16;
+        constexpr std::integral_constant<uint32_t, 32> c32;
+        if (tiles <= kWideTiles) launch(c16, c16, split);
+        else if constexpr (DT == ZIPCCL_FP32) launch(c16, c32, split);
+        else if (tiles <= kSmallTiles) launch(c8, c16, split);
+        else launch(c8, c32, split);
+    };
+    if (is_equal_split(a.tab)) by_size(equal_split(a.tab));
+    else if (is_few_split(a.tab)) by_size(few_split(a.tab));
+    else by_size(a.tab);
+}
+
+/*
+ * Not taken for a stream that is being captured: a launch that a graph replays has the same tag every time.  Nor in launches of many bf16
+ * tiles whose chunks start off cache lines, where it is no faster (us, with a stash / chained: 8 odd chunks of 67 million
+ * normal values 313 / 326, 64 of 4.7 million 179 / 181; of rows with gains among them 336 / 334, 189 / 186).
+ */
+int launch_compress_chained(int dt, const CompressArgs& a, void* stream)
+{
+    if (dt == ZIPCCL_BF16 && a.tab.tile_start[a.tab.n_chunks] > kManyTiles) {
+        uint64_t off = reinterpret_cast<uintptr_t>(a.in) % 128u;
+        for (uint32_t c = 0; c < a.tab.n_chunks; ++c) off |= a.tab.elem_off[c] * 2u % 128u;
+        if (off != 0u) return kNotTaken;
+    }
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();                             /* of this question; the launches in its stead report their own */
+        return kNotTaken;
+    }
+    if (capture != hipStreamCaptureStatusNone) return kNotTaken;
+    if (dt == ZIPCCL_BF16) launch_chained_dt<ZIPCCL_BF16>(a, (hipStream_t)stream);
+    else launch_chained_dt<ZIPCCL_FP32>(a, (hipStream_t)stream);
+    return (int)hipGetLastError();
 }
 
 int launch_compress(int dt, int mode, const CompressArgs& a, void* stream)

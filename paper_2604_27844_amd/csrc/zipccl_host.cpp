@@ -192,6 +192,16 @@ bool direct_pays(zipccl_dtype_t dt, uint32_t max_tiles, uint32_t tiles)
     return max_tiles <= 4 ? tiles <= 512 : max_tiles <= 8 && tiles <= 64;
 }
 
+/*
+ * Of those, the launches that take no longer so than in the chained form, which has more to say and to wait for (us, direct / chained).  bf16: 1 chunk
+ * of 2 tiles 3.4 / 4.0, of 8 4.7 / 4.1; 8 chunks of 2 3.8 / 4.2, of 4 4.5 / 4.2; 64 of 1 3.4 / 4.2, of 2 3.9 / 4.4, of 4 5.5 / 4.6.  fp32: 1 chunk
+ * of 2 3.9 / 4.4; 8 of 2 4.5 / 4.6, of 4 6.1 / 4.7; 64 of 1 4.0 / 4.7, of 2 5.3 / 4.9.
+ */
+bool direct_beats_chained(zipccl_dtype_t dt, uint32_t max_tiles, uint32_t tiles)
+{
+    return max_tiles <= 1 || (max_tiles == 2 && (dt == ZIPCCL_BF16 || tiles <= 64));
+}
+
 /* compress with the table either on the host (checked here) or in device memory (d_table) */
 zipccl_status_t compress_impl(const void* d_in, size_t n_elems, zipccl_dtype_t dt,
                               uint32_t n_chunks, const uint64_t* chunk_elems,
@@ -242,10 +252,15 @@ zipccl_status_t compress_impl(const void* d_in, size_t n_elems, zipccl_dtype_t d
         if (d_table && table_per_chunk) a.d_table = reinterpret_cast<const uint32_t*>(d_table) + 2 * (uint64_t)c0;
         a.tile_total = reinterpret_cast<uint32_t*>(ws + wp.total_off) + tile_base;
         a.tile_prefix = reinterpret_cast<uint32_t*>(ws + wp.prefix_off) + tile_base;
+        a.words = reinterpret_cast<uint64_t*>(ws + wp.total_off) + tile_base;        /* the counts' and prefixes' place */
         a.stash = stash ? ws + wp.stash_off + elem_base : nullptr;
         uint32_t max_tiles = 0;
         for (uint32_t c = 0; c < nb; ++c) max_tiles = std::max(max_tiles, a.tab.tile_start[c + 1] - a.tab.tile_start[c]);
-        if (direct_pays(dt, max_tiles, nt)) {
+        const bool direct = direct_pays(dt, max_tiles, nt);
+        const int chained = direct && direct_beats_chained(dt, max_tiles, nt) ? kNotTaken : launch_compress_chained(dt, a, stream);
+        if (chained != kNotTaken) {
+            if (chained != 0) return ZIPCCL_ERR_DEVICE;
+        } else if (direct) {
             if (launch_compress(dt, kModeDirect, a, stream) != 0) return ZIPCCL_ERR_DEVICE;
         } else if (stash) {
             const bool fused_scan = max_tiles <= kPlaceScanTiles;

@@ -169,7 +169,11 @@ ZIPCCL_HD ChunkPlace place_of(const EqualSplit& t, uint32_t c, int dt)
 ZIPCCL_HD ChunkPlace place_of(const FewSplit& t, uint32_t c, int)
 {
     const uint64_t n = t.elem_off[c + 1] - t.elem_off[c];
-    return ChunkPlace{t.elem_off[c], n, (uint64_t)t.slot_line[c] * 128u, 0u, (uint32_t)tiles_of(n)};
+    uint32_t tile = 0;
+#pragma unroll
+    for (uint32_t k = 0; k + 1u < kFewChunks; ++k)
+        if (k < c) tile += (uint32_t)tiles_of((uint64_t)(t.elem_off[k + 1] - t.elem_off[k]));
+    return ChunkPlace{t.elem_off[c], n, (uint64_t)t.slot_line[c] * 128u, tile, (uint32_t)tiles_of(n)};
 }
 
 struct CompressArgs {
@@ -178,6 +182,7 @@ struct CompressArgs {
     uint64_t* chunk_bytes;   /* entry of the launch's first chunk, or null */
     uint32_t* tile_total;    /* one u32 per tile of this launch: its zero-point count */
     uint32_t* tile_prefix;   /* one u32 per tile: zero-points of its chunk before it */
+    uint64_t* words;         /* chained form: one per tile of this launch */
     uint8_t* stash;          /* stash mode: one byte per input element of this launch (+ slack) */
     uint32_t dec_lo;         /* dec[0..3] packed little-endian: dec[1..7] are consecutive */
     const uint32_t* d_table; /* when not null: the table lives in device memory (two words), dec_lo unused */
@@ -291,13 +296,16 @@ struct ReduceArgs {
     uint32_t gpw_rest;       /* groups per wave in the workgroups after them, which take the rest of the shard */
 };
 
-enum CompressMode { kModeCount = 0, kModeEmit = 1, kModeStash = 2, kModeDirect = 3 };
+enum CompressMode { kModeCount = 0, kModeEmit = 1, kModeStash = 2, kModeDirect = 3, kModeChained = 4 };
 
 /* launchers implemented next to their kernels (zipccl_compress.hip, zipccl_decompress.hip, zipccl_aux.hip);
  * they return a hipError_t as int */
 int launch_estimate(int dt, const MomentArgs& a, void* stream);
 int launch_estimate_robust(int dt, const HistArgs& a, void* stream);
 int launch_compress(int dt, int mode, const CompressArgs& a, void* stream);
+/* kModeChained, or kNotTaken and nothing is launched */
+constexpr int kNotTaken = -1;
+int launch_compress_chained(int dt, const CompressArgs& a, void* stream);
 /* device address and size of the library's own workspace on the current GPU (zipccl_compress_static) */
 int static_scratch(void** ptr, size_t* bytes);
 int launch_tile_scan(const CompressArgs& a, void* stream);

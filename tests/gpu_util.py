@@ -20,10 +20,11 @@ TILE = 8192
 
 
 def split_for_form(data, n_chunks, chunk_elems, form):
-    """zipccl_compress takes a launch (128 chunks) whose chunks all hold a few tiles in one kernel, whatever the workspace.
-    by_rule: the call as it is.  stash / reread: a chunk of more tiles than that form takes is put behind every 100
-    chunks that have none, so that the launch goes through the two-kernel form with a stash, or the one that reads its
-    input twice (which of them, the workspace selects).  Returns (data, n_chunks, chunk_elems)."""
+    """zipccl_compress takes a launch (128 chunks) in one kernel, whatever the workspace, but for calls that are captured
+    into a graph where a chunk holds more than a few tiles.  by_rule: the call as it is.  stash / reread: a chunk of more
+    tiles than that is put behind every 100 chunks that have none, so that the launch, captured (gpu_compress), goes through the
+    two-kernel form with a stash, or the one that reads its input twice (which of them, the workspace selects).  Returns
+    (data, n_chunks, chunk_elems)."""
     if form == "by_rule":
         return data, n_chunks, chunk_elems
     n, extra = int(data.size), 8 * TILE + 1
@@ -44,9 +45,11 @@ def split_for_form(data, n_chunks, chunk_elems, form):
     return np.concatenate(parts), len(split), np.array(split, dtype=np.uint64)
 
 
-def gpu_compress(data, dtype, sigma, n_chunks=1, chunk_elems=None, table=None, d_in=None, reread=False):
+def gpu_compress(data, dtype, sigma, n_chunks=1, chunk_elems=None, table=None, d_in=None, reread=False,
+                 captured=False):
     """reread: hand zipccl_compress only its minimum workspace, which selects the form that reads the input
-    twice (count, prefix, emit) instead of the single pass with a stash (calls on small chunks take neither)."""
+    twice (count, prefix, emit) instead of the single pass with a stash.  captured: the call is captured into a graph, which is
+    replayed once (calls that are not, and calls on small chunks, take neither of these forms)."""
     n = int(data.size)
     table = table if table is not None else z.zipccl_build_table(sigma, dtype)
     cap = z.zipccl_max_compressed_size(n, dtype, n_chunks, chunk_elems)
@@ -57,7 +60,15 @@ def gpu_compress(data, dtype, sigma, n_chunks=1, chunk_elems=None, table=None, d
     ws = z.zipccl_compress_workspace_size(n, dtype, n_chunks, chunk_elems)
     d_ws = torch.full((ws,), 0x5A, dtype=torch.uint8, device=DEV)
     wsb = z.zipccl_compress_min_workspace_size(n, dtype, n_chunks, chunk_elems) if reread else None
-    z.zipccl_compress(d_in, n, dtype, n_chunks, chunk_elems, table, d_out, d_cb, d_ws, workspace_bytes=wsb)
+    call = lambda: z.zipccl_compress(d_in, n, dtype, n_chunks, chunk_elems, table, d_out, d_cb, d_ws, workspace_bytes=wsb)
+    if captured:
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            call()
+        graph.replay()
+    else:
+        call()
     torch.cuda.synchronize()
     return d_out, d_cb, table
 
@@ -78,7 +89,8 @@ def check_parity(data, dtype, sigma, n_chunks=1, chunk_elems=None, label="", for
     n = int(data.size)
     dec = oracle.build_table(sigma)
     ref, ref_cb, off = oracle.compress(data, dtype, dec, n_chunks, chunk_elems)
-    d_out, d_cb, table = gpu_compress(data, dtype, sigma, n_chunks, chunk_elems, reread=form == "reread")
+    d_out, d_cb, table = gpu_compress(data, dtype, sigma, n_chunks, chunk_elems, reread=form == "reread",
+                                    captured=form != "by_rule")
     assert list(bytes(table.dec)) == list(dec), f"{label}: table differs"
     got = d_out.cpu().numpy()
     got_cb = d_cb.cpu().numpy().astype(np.uint64)

@@ -45,7 +45,7 @@ static void check_forms(const ChunkTab& t, int dt)
         }
         if (few) {
             const ChunkPlace p = place_of(few_split(t), c, dt);
-            CHECK(p.elem_off == want.elem_off && p.n == want.n && p.slot_off == want.slot_off && p.tiles == want.tiles);
+            CHECK(p.elem_off == want.elem_off && p.n == want.n && p.slot_off == want.slot_off && p.tile == want.tile && p.tiles == want.tiles);
         }
     }
     g_equal += equal;
@@ -91,6 +91,19 @@ int launch_compress(int dt, int mode, const CompressArgs& a, void*)
             CHECK(a.tab.tile_start[c + 1] - a.tab.tile_start[c] <= (dt == ZIPCCL_BF16 ? 8u : 4u));
     if (mode == kModeStash) CHECK(a.stash != nullptr);
     ++g_by_mode[mode];
+    ++g_launches;
+    return 0;
+}
+/* kModeChained: not on a stream that is being captured, here where g_chains is not set; the words are 8 bytes per tile */
+static bool g_chains = false;
+static int g_chained = 0;
+int launch_compress_chained(int dt, const CompressArgs& a, void*)
+{
+    check_tab(a.tab);
+    check_forms(a.tab, dt);
+    CHECK(a.words != nullptr && reinterpret_cast<uintptr_t>(a.words) % 8 == 0);
+    if (!g_chains) return kNotTaken;
+    ++g_chained;
     ++g_launches;
     return 0;
 }
@@ -243,6 +256,26 @@ int main()
         mixed[128] = 9 * T;
         forms(ZIPCCL_BF16, mixed, least, 1, s, e);
     }
+    /* and the chained form wherever it can be taken, but for chunks of one or two tiles, in either workspace */
+    g_chains = true;
+    for (bool least : {false, true}) {
+        auto chained = [&](zipccl_dtype_t dt, std::vector<uint64_t> split, int direct, int want) {
+            g_chained = 0;
+            forms(dt, split, least, direct, 0, 0);
+            CHECK(g_chained == want);
+        };
+        chained(ZIPCCL_BF16, {2 * T}, 1, 0);
+        chained(ZIPCCL_BF16, {2 * T + 1}, 0, 1);
+        chained(ZIPCCL_FP32, std::vector<uint64_t>(64, T), 1, 0);
+        chained(ZIPCCL_FP32, std::vector<uint64_t>(32, 2 * T), 1, 0);
+        chained(ZIPCCL_FP32, std::vector<uint64_t>(33, 2 * T), 0, 1);
+        chained(ZIPCCL_BF16, std::vector<uint64_t>(128, 2 * T), 1, 0);
+        chained(ZIPCCL_BF16, {0xFFFFFFFFull, 0xFFFFFFFFull}, 0, 1);
+        std::vector<uint64_t> mixed(129, T);
+        mixed[128] = 3 * T;
+        chained(ZIPCCL_BF16, mixed, 1, 1);
+    }
+    g_chains = false;
     /* the short forms of the chunk table (check_forms): equal splits, given as such or chunk by chunk, and a few uneven chunks */
     const int equal0 = g_equal, few0 = g_few;
     for (zipccl_dtype_t dt : {ZIPCCL_BF16, ZIPCCL_FP32})

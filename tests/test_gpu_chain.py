@@ -1,0 +1,110 @@
+"""The chained compress, in which a tile waits for the counts of the chunk's tiles before it: lengths at the edges of its
+tiles and of the words it reads, workspaces in any state, calls side by side, and the bound of the wait.  Bytes
+throughout, equal to the oracle's or to those of the captured call, which takes the form without a wait."""
+import ctypes
+import os
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_27844_amd.binding as z
+from paper_2604_27844_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from gpu_util import DEV, check_parity, gpu_compress, to_device_words
+
+TILE = 8192
+IMPATIENT = os.path.join(os.path.dirname(os.path.abspath(__file__)), "impatient", "libzipccl_impatient.so")
+
+
+def _values(n, dtype, seed, sigma=0.02):
+    rng = np.random.default_rng(seed)
+    f = rng.standard_normal(n, dtype=np.float32) * np.float32(sigma)
+    f[n // 3:n // 3 + 2 * TILE + 77] = 1.0                                # a stretch of zero-points
+    return W.f32_to_bf16_words(f) if dtype == z.BF16 else f.view(np.uint32).copy()
+
+
+# launches of up to 256, 640 and more tiles of 8192 values; whole, one value less and more; with the larger tiles chunks of as many
+# as run at a time (bf16 1024, fp32 512) and 63, 64 and 65 more, where the first total stands for the counts far back
+@pytest.mark.parametrize("dtype,sizes", [
+    (z.BF16, [3 * TILE]), (z.BF16, [9 * TILE - 1, 8 * TILE + 1, 0, 1]), (z.BF16, [256 * TILE]), (z.BF16, [256 * TILE + 1]),
+    (z.BF16, [64 * TILE + 5] * 10), (z.BF16, [641 * TILE - 8]), (z.BF16, [7, 600 * TILE, 41 * TILE + 8191]),
+    (z.BF16, [2 * TILE * 1087 + 1]), (z.BF16, [2 * TILE * 1088]), (z.BF16, [2 * TILE * 1089 - 1, 2 * TILE * 1152 + 9]),
+    (z.FP32, [3 * TILE]), (z.FP32, [256 * TILE - 3]), (z.FP32, [257 * TILE]), (z.FP32, [33 * TILE + 1] * 9),
+    (z.FP32, [2 * TILE * 575 + 2]), (z.FP32, [2 * TILE * 576]), (z.FP32, [2 * TILE * 577 - 1, 2 * TILE * 640 + 3]),
+], ids=str)
+def test_edges_of_tiles_and_of_what_a_tile_reads(dtype, sizes):
+    ce = np.array(sizes, dtype=np.uint64)
+    print(f"[chain] dtype={dtype} sizes={sizes}", flush=True)
+    check_parity(_values(int(ce.sum()), dtype, len(sizes)), dtype, 0.02, len(ce), ce, label=str(sizes))
+
+
+def test_a_workspace_that_other_calls_have_left():
+    """The same workspace for calls of several shapes in turn, each twice on other values, and for captured calls between them."""
+    shapes = [[700 * TILE], [40 * TILE + 3] * 8, [9 * TILE], [2 * TILE * 600 + 1], [5 * TILE] * 20]
+    ws = torch.full((max(z.zipccl_compress_workspace_size(sum(s), z.BF16, len(s), np.array(s, dtype=np.uint64)) for s in shapes),), 0xFF,
+                    dtype=torch.uint8, device=DEV)
+    table = z.zipccl_build_table(0.02, z.BF16)
+    for rep in range(2):
+        for s in shapes:
+            ce = np.array(s, dtype=np.uint64)
+            n = int(ce.sum())
+            print(f"[chain workspace] {rep} {s[:2]}", flush=True)
+            for seed in (1, 2):
+                data = _values(n, z.BF16, 10 * rep + seed)
+                want, want_cb, _ = gpu_compress(data, z.BF16, 0.02, len(ce), ce, captured=True)
+                got = torch.full_like(want, 0xA5)
+                got_cb = torch.zeros_like(want_cb)
+                z.zipccl_compress(to_device_words(data), n, z.BF16, len(ce), ce, table, got, got_cb, ws)
+                torch.cuda.synchronize()
+                assert torch.equal(got, want) and torch.equal(got_cb, want_cb), (rep, s, seed)
+
+
+def test_calls_side_by_side_on_several_streams():
+    sizes = [[1100 * TILE + 7], [150 * TILE] * 8, [12 * TILE] * 64, [3 * TILE + 1]]
+    table = z.zipccl_build_table(0.02, z.BF16)
+    work = []
+    for k, s in enumerate(sizes):
+        ce = np.array(s, dtype=np.uint64)
+        n = int(ce.sum())
+        data = _values(n, z.BF16, 40 + k)
+        want, want_cb, _ = gpu_compress(data, z.BF16, 0.02, len(ce), ce, captured=True)
+        ws = torch.empty(z.zipccl_compress_workspace_size(n, z.BF16, len(ce), ce), dtype=torch.uint8, device=DEV)
+        work.append((torch.cuda.Stream(), to_device_words(data), n, ce, want, want_cb, torch.full_like(want, 0xA5), torch.zeros_like(want_cb), ws))
+    torch.cuda.synchronize()
+    print("[chain streams]", flush=True)
+    for _ in range(10):
+        for stream, d_in, n, ce, _, _, got, got_cb, ws in work:
+            with torch.cuda.stream(stream):
+                z.zipccl_compress(d_in, n, z.BF16, len(ce), ce, table, got, got_cb, ws)
+    torch.cuda.synchronize()
+    for _, _, n, _, want, want_cb, got, got_cb, _ in work:
+        assert torch.equal(got, want) and torch.equal(got_cb, want_cb), n
+
+
+@pytest.mark.parametrize("dtype,sizes", [
+    (z.BF16, [3 * TILE]), (z.BF16, [40 * TILE + 3] * 3), (z.BF16, [300 * TILE - 1]), (z.BF16, [100 * TILE + 1] * 8),
+    (z.BF16, [2 * TILE * 1160]), (z.FP32, [40 * TILE + 1, 100 * TILE]), (z.FP32, [2 * TILE * 650 + 1]),
+], ids=str)
+def test_workgroups_that_look_only_once(dtype, sizes):
+    """A copy of the library built so that a workgroup looks once for the counts before it and then counts what is missing itself."""
+    lib = ctypes.CDLL(IMPATIENT)
+    ce = np.array(sizes, dtype=np.uint64)
+    n, C = int(ce.sum()), len(ce)
+    print(f"[chain impatient] dtype={dtype} sizes={sizes}", flush=True)
+    data = _values(n, dtype, 70)
+    want, want_cb, table = gpu_compress(data, dtype, 0.02, C, ce, captured=True)
+    d_in = to_device_words(data)
+    ws = torch.full((z.zipccl_compress_workspace_size(n, dtype, C, ce),), 0x5A, dtype=torch.uint8, device=DEV)
+    vp, size = ctypes.c_void_p, ctypes.c_size_t
+    for _ in range(3):
+        got = torch.full_like(want, 0xA5)
+        got_cb = torch.zeros_like(want_cb)
+        rc = lib.zipccl_compress(vp(d_in.data_ptr()), size(n), ctypes.c_int(dtype), ctypes.c_uint32(C), ce.ctypes.data_as(vp), ctypes.byref(table),
+                                 vp(got.data_ptr()), size(got.numel()), vp(got_cb.data_ptr()), vp(ws.data_ptr()), size(ws.numel()),
+                                 vp(torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+        assert rc == 0 and torch.equal(got, want) and torch.equal(got_cb, want_cb), sizes
