@@ -1288,6 +1288,18 @@ __global__ __launch_bounds__(64u * S * G) void k_reduce_split(const SplitArgs a)
 
 } // namespace
 
+/*
+ * Large fp32 launches ask for LDS that they do not use, so that five workgroups share a compute unit and not eight, which get in one
+ * another's way at the memory.  us with 8 / 6 / 5 / 4: 64 chunks of 2^21 values with rows of gains 163.4 / 164.0 / 161.2 / 163.9, normal
+ * ones 160.2 / 160.6 / 158.8 / -, one chunk of 2^27 162.5 / 162.8 / 159.5 / -, 2^26 82.4 / 82.5 / 81.5 / -; 64 odd chunks of 120 million values in
+ * all 149.5 / 151.2 / 149.5 / -, 2^25 43.0 / 42.9 / 42.9 / 43.8.  bf16 launches, with half the bytes in flight, lose by it (2^29 294 /
+ * 299 with 6).
+ */
+constexpr uint64_t kFiveFrom = 1ull << 25;
+constexpr uint32_t kFiveLds = 14u << 10;                     /* on top of 14.4 KiB; a compute unit has 160 */
+static_assert(5u * (sizeof(DecTables) + kWavesPerBlock * 2u * kEscRegion + kFiveLds) <= (160u << 10) &&
+              6u * (sizeof(DecTables) + kWavesPerBlock * 2u * kEscRegion + kFiveLds) > (160u << 10), "five, not six");
+
 template <int DT, uint32_t GPW, bool STREAM = true>
 static int launch_decompress_gpw(const DecompressArgs& a, hipStream_t s)
 {
@@ -1299,9 +1311,10 @@ static int launch_decompress_gpw(const DecompressArgs& a, hipStream_t s)
     }
     const dim3 grid((uint32_t)tiles, a.tab.n_chunks), block(kThreads);
     const DecompressIo io = {a.comp, a.comp_capacity, a.out, a.status};
-    if (is_equal_split(a.tab)) hipLaunchKernelGGL((k_decompress<DT, GPW, STREAM, EqualSplit>), grid, block, 0, s, io, equal_split(a.tab));
-    else if (GPW < 4u && is_few_split(a.tab)) hipLaunchKernelGGL((k_decompress<DT, GPW, STREAM, FewSplit>), grid, block, 0, s, io, few_split(a.tab));
-    else hipLaunchKernelGGL((k_decompress<DT, GPW, STREAM, ChunkTab>), grid, block, 0, s, io, a.tab);
+    const uint32_t lds = DT == ZIPCCL_FP32 && GPW == 2u && a.tab.elem_off[a.tab.n_chunks] > kFiveFrom ? kFiveLds : 0u;
+    if (is_equal_split(a.tab)) hipLaunchKernelGGL((k_decompress<DT, GPW, STREAM, EqualSplit>), grid, block, lds, s, io, equal_split(a.tab));
+    else if (GPW < 4u && is_few_split(a.tab)) hipLaunchKernelGGL((k_decompress<DT, GPW, STREAM, FewSplit>), grid, block, lds, s, io, few_split(a.tab));
+    else hipLaunchKernelGGL((k_decompress<DT, GPW, STREAM, ChunkTab>), grid, block, lds, s, io, a.tab);
     return (int)hipGetLastError();
 }
 
