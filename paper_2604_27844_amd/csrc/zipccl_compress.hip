@@ -931,7 +931,7 @@ static void launch_compress_dt(int mode, const CompressArgs& a, hipStream_t s)
 #undef ZIPCCL_LAUNCH
 }
 
-constexpr uint32_t kSmallTiles = 640, kManyTiles = 8192;     /* of 8192 values: launch_chained_dt, chain_prefix */
+constexpr uint32_t kSmallTiles = 640, kSmallTilesEstimated = 2048, kManyTiles = 8192;     /* of 8192 values: launch_chained_dt, chain_prefix */
 
 /* The tag of a launch (Chain): counted up from a number that differs from process to process, 2^40 launches until it comes
  * again.  What a workspace holds of earlier launches has other tags; what it holds else would have to be this very number in a
@@ -953,6 +953,11 @@ static uint64_t launch_tag()
  * 16, equal chunks: bf16 2^20 4.3 / 4.3 / 5.2 / 5.0, 2^22 6.1 / 5.6 / 6.0 / 5.6, 2^23 10.6 / 8.1 / 7.5 / 7.3, 2^24 19.8 / 14.6 / 13.0 / 14.1, 2^26 80 / 57 /
  * 43 / 50; fp32 2^20 4.8 / 5.0 / 6.6 / 6.1, 2^22 8.6 / 7.4 / 8.1 / 7.4, 2^23 15.3 / 13.5 / 12.9 / 13.5, 2^24 26.8 / 24.7 / 26.4 / 24.7, 2^27 219 /
  * 193 / 170 / 161.  (64 groups and 16 waves: bf16 2^23 7.5, 2^24 12.9, 2^26 43.5, 64 chunks of 2^23 286, one of 2^29 297; fp32 2^24 25.4, 2^27 167.)
+ *
+ * A table for the whole tensor in device memory says that an estimate has read the tensor just now, and what the caches hold of it
+ * comes so quickly that small tiles last longer.  Robust estimate and compress, 32 groups / 16 and 8 waves / with a stash: bf16 2^23
+ * 21.0 / 20.4 / 22.6, 2^24 26.8 / 26.0 / 26.7, 3 * 2^23 33.8 / 37.9 / 34.0; fp32 2^23 26.0 / 22.4 / 25.8, 2^24 39.6 / 38.5 / 39.7.  (Standard deviation and
+ * compress: bf16 2^24 24.1 / 25.2 / 26.9, fp32 2^23 23.3 / 23.8 / 26.5.)
  */
 template <int DT>
 static void launch_chained_dt(const CompressArgs& a, hipStream_t s)
@@ -960,6 +965,7 @@ static void launch_chained_dt(const CompressArgs& a, hipStream_t s)
     const CompressIo io = io_of(a);
     const uint32_t tiles = a.tab.tile_start[a.tab.n_chunks];
     const Chain chain = {a.words, launch_tag(), DT == ZIPCCL_BF16 && tiles > kManyTiles};
+    const bool estimated = a.d_table != nullptr && a.table_stride == 0u;
     auto launch = [&](auto waves, auto groups, const auto& split) {
         constexpr uint32_t W = decltype(waves)::value, G = decltype(groups)::value, per = G / kGroupsPerTile;
         using SPLIT = std::decay_t<decltype(split)>;
@@ -971,8 +977,8 @@ static void launch_chained_dt(const CompressArgs& a, hipStream_t s)
         constexpr std::integral_constant<uint32_t, 16> c16;
         constexpr std::integral_constant<uint32_t, 32> c32;
         if (tiles <= kWideTiles) launch(c16, c16, split);
+        else if (tiles <= (estimated ? kSmallTilesEstimated : kSmallTiles)) launch(c8, c16, split);
         else if constexpr (DT == ZIPCCL_FP32) launch(c16, c32, split);
-        else if (tiles <= kSmallTiles) launch(c8, c16, split);
         else launch(c8, c32, split);
     };
     if (is_equal_split(a.tab)) by_size(equal_split(a.tab));
