@@ -107,8 +107,9 @@ zipccl_status_t zipccl_chunk_static_bytes(size_t n_elems, zipccl_dtype_t dt, uin
                                           const uint64_t* chunk_elems, uint64_t* static_bytes);
 
 /* Bytes of device scratch for zipccl_compress.  Most calls are one kernel, which needs the minimum, 8 bytes per 8192
- * elements.  Calls that are captured into a graph, and those on more than 2^26 bf16 values whose chunks start off
- * 128-byte lines, are one kernel if their chunks hold a few tiles of 8192 values; else, with
+ * elements.  Calls that are captured into a graph, those on more than 2^26 bf16 values whose chunks start off 128-byte
+ * lines, and those of zipccl_compress_device_table on 2^24 to 2^26 bf16 values are one kernel if their chunks hold a few tiles of
+ * 8192 values; else, with
  * zipccl_compress_workspace_size bytes (about one byte per element) they read the input once: zero-point exponents
  * are parked in the scratch until the per-chunk prefix of section 4.2.3 is known.  With less, but at least
  * zipccl_compress_min_workspace_size bytes, they read the input twice (count, prefix, emit).  All forms write the same bytes.

@@ -947,6 +947,8 @@ static uint64_t launch_tag()
     return next.fetch_add(1, std::memory_order_relaxed) * (kChainCount + 1ull);
 }
 
+static bool is_estimated(const CompressArgs& a) { return a.d_table != nullptr && a.table_stride == 0u; }
+
 /*
  * Groups of a tile and waves that share it in the chained form.  Small launches take small tiles, which fill more of the chip; in larger ones
  * every round of workgroups ends with a wait, which larger tiles make fewer of.  us, 16 groups and 16 waves / 16 and 8 / 32 and 8 / 32 and
@@ -965,7 +967,6 @@ static void launch_chained_dt(const CompressArgs& a, hipStream_t s)
     const CompressIo io = io_of(a);
     const uint32_t tiles = a.tab.tile_start[a.tab.n_chunks];
     const Chain chain = {a.words, launch_tag(), DT == ZIPCCL_BF16 && tiles > kManyTiles};
-    const bool estimated = a.d_table != nullptr && a.table_stride == 0u;
     auto launch = [&](auto waves, auto groups, const auto& split) {
         constexpr uint32_t W = decltype(waves)::value, G = decltype(groups)::value, per = G / kGroupsPerTile;
         using SPLIT = std::decay_t<decltype(split)>;
@@ -977,7 +978,7 @@ static void launch_chained_dt(const CompressArgs& a, hipStream_t s)
         constexpr std::integral_constant<uint32_t, 16> c16;
         constexpr std::integral_constant<uint32_t, 32> c32;
         if (tiles <= kWideTiles) launch(c16, c16, split);
-        else if (tiles <= (estimated ? kSmallTilesEstimated : kSmallTiles)) launch(c8, c16, split);
+        else if (tiles <= (is_estimated(a) ? kSmallTilesEstimated : kSmallTiles)) launch(c8, c16, split);
         else if constexpr (DT == ZIPCCL_FP32) launch(c16, c32, split);
         else launch(c8, c32, split);
     };
@@ -989,11 +990,15 @@ static void launch_chained_dt(const CompressArgs& a, hipStream_t s)
 /*
  * Not taken for a stream that is being captured: a launch that a graph replays has the same tag every time.  Nor in launches of many bf16
  * tiles whose chunks start off cache lines, where it is no faster (us, with a stash / chained: 8 odd chunks of 67 million
- * normal values 313 / 326, 64 of 4.7 million 179 / 181; of rows with gains among them 336 / 334, 189 / 186).
+ * normal values 313 / 326, 64 of 4.7 million 179 / 181; of rows with gains among them 336 / 334, 189 / 186).  Nor for bf16 between the sizes
+ * where a table for the whole tensor is in device memory: the caches hold part of what the estimate has read, and one launch
+ * makes less of that (robust estimate and compress, with a stash / chained, 21 million values 30.8 / 32.7, 60 million 66.2 / 68.0).
  */
 int launch_compress_chained(int dt, const CompressArgs& a, void* stream)
 {
-    if (dt == ZIPCCL_BF16 && a.tab.tile_start[a.tab.n_chunks] > kManyTiles) {
+    const uint32_t tiles = a.tab.tile_start[a.tab.n_chunks];
+    if (dt == ZIPCCL_BF16 && is_estimated(a) && tiles > kSmallTilesEstimated && tiles <= kManyTiles) return kNotTaken;
+    if (dt == ZIPCCL_BF16 && tiles > kManyTiles) {
         uint64_t off = reinterpret_cast<uintptr_t>(a.in) % 128u;
         for (uint32_t c = 0; c < a.tab.n_chunks; ++c) off |= a.tab.elem_off[c] * 2u % 128u;
         if (off != 0u) return kNotTaken;
