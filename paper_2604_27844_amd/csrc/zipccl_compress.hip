@@ -341,16 +341,14 @@ struct Parking {
     uint32_t *tile_total, *tile_prefix;
     uint8_t* stash;
 };
-/* kModeChained: what the tiles of a launch tell one another, in 64-bit words that hold a count in their low 24 bits and
- * this launch's tag, which no other launch has, in the others.  A word with another tag has not been told yet, so the words need not
- * be cleared.  A chunk's tiles have one each, and behind these the 64th, 128th, ... tile two more for the count of all
+/* kModeChained: what the tiles of a launch tell one another, in words that hold a count and this launch's tag (chain_tag).  A word
+ * with another tag has not been told yet, so the words need not be cleared.  A chunk's tiles have one each, and behind these the 64th, 128th, ... tile two more for the count of all
  * tiles up to it. */
 struct Chain {
     uint64_t* words;
     uint64_t tag;
     uint32_t many;                                          /* rounds of workgroups: see chain_prefix */
 };
-constexpr uint32_t kChainCount = 0xFFFFFFu;
 constexpr uint32_t kChainStep = 64;
 #ifndef ZIPCCL_CHAIN_PATIENCE
 #define ZIPCCL_CHAIN_PATIENCE 128
@@ -397,7 +395,7 @@ __device__ __forceinline__ void chain_prefix(const Chain& chain, uint64_t* words
     constexpr uint32_t NT = 64u * WAVES, GPW = GROUPS / WAVES;
     constexpr uint32_t reach = 8192u / WAVES;                /* eight waves per SIMD: 32 per compute unit, of 256 */
     constexpr int nap = GROUPS == 16u ? 1 : 16;              /* of 64 cycles */
-    auto is_count = [&](uint64_t v) { return (v ^ chain.tag) <= kChainCount; };
+    auto is_count = [&](uint64_t v) { return chain_told(v, chain.tag); };
     uint32_t from = 0;
     if (GROUPS > kGroupsPerTile && t >= reach + kChainStep) from = (t - reach) & ~(kChainStep - 1u);
     if (chain.many != 0u && from == 0u) __builtin_amdgcn_s_sleep(28);
@@ -413,7 +411,7 @@ __device__ __forceinline__ void chain_prefix(const Chain& chain, uint64_t* words
             v = peek(p);
         }
         missing |= !is_count(v);
-        sum += ((uint32_t)v & kChainCount) << (i == t + 1u ? 24u : 0u);
+        sum += (uint32_t)(v & kChainCount) << (i == t + 1u ? 24u : 0u);
     }
     sum = wave_incl_scan(sum);
     if (lane == 63u) sh.before[wave] = sum;
@@ -430,7 +428,7 @@ __device__ __forceinline__ void chain_prefix(const Chain& chain, uint64_t* words
             const bool some = base + lane < end;
             const uint64_t v = some ? peek(words + base + lane) : 0u;
             const bool told = some && is_count(v);
-            sum += told ? (uint32_t)v & kChainCount : 0u;
+            sum += told ? (uint32_t)(v & kChainCount) : 0u;
             const uint64_t open = __ballot(some && !told);
             if (lane == 0u) sh.open = open;
         }
@@ -442,7 +440,7 @@ __device__ __forceinline__ void chain_prefix(const Chain& chain, uint64_t* words
             if (threadIdx.x == 0u) {
                 const uint64_t v = peek(words + base + j);
                 sh.missing = !is_count(v);
-                sh.counted = is_count(v) ? (uint32_t)v & kChainCount : 0u;
+                sh.counted = is_count(v) ? (uint32_t)(v & kChainCount) : 0u;
             }
             __syncthreads();
             if (sh.missing != 0u) {
@@ -933,18 +931,18 @@ static void launch_compress_dt(int mode, const CompressArgs& a, hipStream_t s)
 
 constexpr uint32_t kSmallTiles = 640, kSmallTilesEstimated = 2048, kManyTiles = 8192;     /* of 8192 values: launch_chained_dt, chain_prefix */
 
-/* The tag of a launch (Chain): counted up from a number that differs from process to process, 2^40 launches until it comes
- * again.  What a workspace holds of earlier launches has other tags; what it holds else would have to be this very number in a
- * word of a tile that is late. */
+/* The tag of a launch (Chain), whose number is counted up from one that differs from process to process.  What a workspace holds of
+ * earlier launches of this process has other tags; what else it holds would have to be this very one of 2^40 in a word of a tile
+ * that is late. */
 static uint64_t launch_tag()
 {
     static std::atomic<uint64_t> next{[] {
         uint64_t x = (uint64_t)std::chrono::system_clock::now().time_since_epoch().count() ^ (reinterpret_cast<uintptr_t>(&x) << 20);
         x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;         /* splitmix64 */
         x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
-        return x ^ (x >> 31);
+        return (x ^ (x >> 31)) % kChainTags;
     }()};
-    return next.fetch_add(1, std::memory_order_relaxed) * (kChainCount + 1ull);
+    return chain_tag(next.fetch_add(1, std::memory_order_relaxed));
 }
 
 static bool is_estimated(const CompressArgs& a) { return a.d_table != nullptr && a.table_stride == 0u; }

@@ -176,6 +176,16 @@ ZIPCCL_HD ChunkPlace place_of(const FewSplit& t, uint32_t c, int)
     return ChunkPlace{t.elem_off[c], n, (uint64_t)t.slot_line[c] * 128u, tile, (uint32_t)tiles_of(n)};
 }
 
+/*
+ * Chained compress: tiles tell one another their counts in 64-bit words, a count in the low 24 bits, the launch's tag in the others.
+ * The tag of the launch of this number: 2^40 - 2 launches until one comes again, and neither 0 nor all ones, which the words of a
+ * workspace that was cleared or filled hold.
+ */
+constexpr uint64_t kChainCount = 0xFFFFFFull;
+constexpr uint64_t kChainTags = (1ull << 40) - 2u;
+ZIPCCL_HD uint64_t chain_tag(uint64_t launch) { return (launch % kChainTags + 1u) * (kChainCount + 1u); }
+ZIPCCL_HD bool chain_told(uint64_t word, uint64_t tag) { return (word ^ tag) <= kChainCount; }
+
 struct CompressArgs {
     const uint8_t* in;       /* first element of the launch's first chunk */
     uint8_t* out;            /* compressed buffer base for this launch */

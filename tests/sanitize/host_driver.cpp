@@ -276,6 +276,13 @@ int main()
         chained(ZIPCCL_BF16, mixed, 1, 1);
     }
     g_chains = false;
+    /* a launch's tag: one of 2^40 - 2, from which what cleared and filled words hold differs as well as its neighbours' */
+    for (uint64_t base : {0ull, 1ull << 24, (1ull << 40) - 4u, 1ull << 40, 0xFFFFFFFFFFFFFFF0ull})
+        for (uint64_t k = base; k < base + 8u; ++k) {
+            const uint64_t tag = chain_tag(k);
+            CHECK((tag & kChainCount) == 0 && chain_told(tag, tag) && chain_told(tag | kChainCount, tag));
+            for (uint64_t other : {(uint64_t)0, ~(uint64_t)0, chain_tag(k + 1u), chain_tag(k + 1u) | kChainCount}) CHECK(!chain_told(other, tag));
+        }
     /* the short forms of the chunk table (check_forms): equal splits, given as such or chunk by chunk, and a few uneven chunks */
     const int equal0 = g_equal, few0 = g_few;
     for (zipccl_dtype_t dt : {ZIPCCL_BF16, ZIPCCL_FP32})
