@@ -129,8 +129,8 @@ size_t zipccl_compress_min_workspace_size(size_t n_elems, zipccl_dtype_t dt, uin
  *   d_workspace     device, 16-byte aligned, workspace_bytes >= zipccl_compress_min_workspace_size(...)
  *                   (see above for what more buys); contents are overwritten
  * Every byte of [slot_off[c], slot_off[c] + chunk_bytes[c]) is written; the rest of a slot is
- * left untouched.  A workgroup may wait for others of its call to count their zero-points, for some 100 us at most, after
- * which it counts in their place.  Calls that may overlap in time need different workspaces.
+ * left untouched.  A workgroup may wait for others of its call to count their zero-points: for some 0.2 ms at most, after which it counts
+ * in the place of those that have not, so that none needs another's to end.  Calls that may overlap in time need different workspaces.
  */
 zipccl_status_t zipccl_compress(const void* d_in, size_t n_elems, zipccl_dtype_t dt,
                                 uint32_t n_chunks, const uint64_t* chunk_elems,

@@ -202,7 +202,8 @@ struct CompressShared {
     uint32_t before[kGroupsPerTile];       /* kModeDirect, kModeChained: zero-points a wave found in the tiles before */
     uint32_t counted;                      /* kModeChained: waves that have counted << 16 | their zero-points */
     uint32_t missing;                      /* and whether the count of a tile before did not come */
-    uint64_t open;                         /* or of which of 64 */
+    uint64_t open;                         /* or of which of 64, */
+    uint32_t total;                        /* and whether the count of all tiles before these is known */
 };
 
 /* One group of one wave, its values already loaded (load_lane): encode, store SM/LO, stage planes and
@@ -353,7 +354,7 @@ constexpr uint32_t kChainStep = 64;
 #ifndef ZIPCCL_CHAIN_PATIENCE
 #define ZIPCCL_CHAIN_PATIENCE 128
 #endif
-constexpr uint32_t kChainPatience = ZIPCCL_CHAIN_PATIENCE;   /* how often a thread looks again for words that are not there */
+constexpr uint32_t kChainPatience = ZIPCCL_CHAIN_PATIENCE;   /* how often a wave looks again for words that are not there */
 
 /* dec[0..3] and dec[4..7]: from the kernel arguments (dec[1..7] are consecutive, the host has checked it) or, if the table
  * was estimated on the device, two words in its memory. */
@@ -384,9 +385,10 @@ __device__ __forceinline__ void tell(uint64_t* p, uint64_t v) { __hip_atomic_sto
  * would come too early (64 chunks of 2^23 bf16 values without / with 290 us for 314, of 3.7 million 131 for 141; at 2^24 it costs a microsecond; fp32
  * tiles, which take twice as long, lose by it: 64 of 2^21 160 us without, 162 with).
  *
- * Workgroups start in order, so those waited for run already or are next, unless kernels that wait for one another share the chip.  So
- * the wait is bounded: a workgroup that has looked kChainPatience times counts the tiles that are missing itself, from the input,
- * and tells their counts on their behalf.  No workgroup depends on another for its end.
+ * Workgroups start in order, so those waited for run already or are next, unless other kernels hold part of the chip.  So the wait is bounded: a
+ * workgroup one of whose waves has looked kChainPatience times, some 0.2 ms, goes back from its tile to the nearest total that has been told, and counts the
+ * tiles that are missing on the way itself, from the input, and tells their counts on their behalf.  No workgroup depends on
+ * another for its end.
  */
 template <int DT, uint32_t WAVES, uint32_t GROUPS, class SHARED>
 __device__ __forceinline__ void chain_prefix(const Chain& chain, uint64_t* words, uint32_t tiles, uint32_t t, const uint8_t* __restrict__ cin, uint64_t n,
@@ -405,10 +407,10 @@ __device__ __forceinline__ void chain_prefix(const Chain& chain, uint64_t* words
     for (uint32_t i = from + threadIdx.x; i < t + (from != 0u ? 2u : 0u); i += NT) {
         const uint64_t* const p = i < t ? words + i : upto + (i - t);
         uint64_t v = peek(p);
-        while (!is_count(v) && left != 0u) {
+        while (left != 0u && __ballot(!is_count(v)) != 0u) {    /* the same in all lanes that have a word */
             --left;
             __builtin_amdgcn_s_sleep(nap);
-            v = peek(p);
+            if (!is_count(v)) v = peek(p);
         }
         missing |= !is_count(v);
         sum += (uint32_t)(v & kChainCount) << (i == t + 1u ? 24u : 0u);
@@ -419,10 +421,11 @@ __device__ __forceinline__ void chain_prefix(const Chain& chain, uint64_t* words
     __syncthreads();
     if (sh.missing == 0u) return;
 
-    /* from the nearest tile back, 64 at a time */
+    /* from the nearest tile back, 64 at a time, each with the total before them */
     sum = 0;
-    for (uint32_t end = t; end != 0u;) {
-        const uint32_t base = end > 64u ? end - 64u : 0u;
+    bool total = false;
+    for (uint32_t end = t; end != 0u && !total;) {
+        const uint32_t base = (end - 1u) & ~(kChainStep - 1u);
         __syncthreads();
         if (wave == 0u) {
             const bool some = base + lane < end;
@@ -431,8 +434,17 @@ __device__ __forceinline__ void chain_prefix(const Chain& chain, uint64_t* words
             sum += told ? (uint32_t)(v & kChainCount) : 0u;
             const uint64_t open = __ballot(some && !told);
             if (lane == 0u) sh.open = open;
+        } else if (wave == 1u) {
+            bool known = false;
+            if (GROUPS > kGroupsPerTile && base != 0u) {
+                const uint64_t v = peek(words + tiles + 2u * (base / kChainStep) - 2u + (lane & 1u));
+                known = __ballot(is_count(v)) == ~0ull;
+                if (known && lane < 2u) sum += (uint32_t)(v & kChainCount) << (24u * lane);
+            }
+            if (lane == 0u) sh.total = known;
         }
         __syncthreads();
+        total = sh.total != 0u;
         for (uint64_t open = sh.open; open != 0u;) {
             const uint32_t j = 63u - (uint32_t)__builtin_clzll(open);
             open ^= 1ull << j;
@@ -459,7 +471,7 @@ __device__ __forceinline__ void chain_prefix(const Chain& chain, uint64_t* words
         end = base;
     }
     sum = wave_incl_scan(sum);
-    if (lane == 63u) sh.before[wave] = sum;                  /* 0 but for the first */
+    if (lane == 63u) sh.before[wave] = sum;                  /* 0 but for the first two */
     __syncthreads();
 }
 
