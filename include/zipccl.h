@@ -107,12 +107,11 @@ zipccl_status_t zipccl_chunk_static_bytes(size_t n_elems, zipccl_dtype_t dt, uin
                                           const uint64_t* chunk_elems, uint64_t* static_bytes);
 
 /* Bytes of device scratch for zipccl_compress.  Most calls are one kernel, which needs the minimum, 8 bytes per 8192
- * elements.  Calls that are captured into a graph, those on more than 2^26 bf16 values whose chunks start off 128-byte
- * lines, and those of zipccl_compress_device_table on 2^24 to 2^26 bf16 values are one kernel if their chunks hold a few tiles of
- * 8192 values; else, with
- * zipccl_compress_workspace_size bytes (about one byte per element) they read the input once: zero-point exponents
- * are parked in the scratch until the per-chunk prefix of section 4.2.3 is known.  With less, but at least
- * zipccl_compress_min_workspace_size bytes, they read the input twice (count, prefix, emit).  All forms write the same bytes.
+ * elements.  With zipccl_compress_workspace_size bytes (about one byte per element) calls on more than 2^26 bf16 values
+ * whose chunks start off 128-byte lines, those of zipccl_compress_device_table on 2^24 to 2^26 bf16 values, and those that are
+ * captured into a graph on chunks of more than a few tiles of 8192 values are two: zero-point exponents are parked in the scratch until the
+ * per-chunk prefix of section 4.2.3 is known.  With less, but at least zipccl_compress_min_workspace_size bytes, the captured ones read
+ * the input twice (count, prefix, emit).  All forms write the same bytes.
  * Both return 0 on invalid arguments. */
 size_t zipccl_compress_workspace_size(size_t n_elems, zipccl_dtype_t dt, uint32_t n_chunks,
                                       const uint64_t* chunk_elems);
@@ -144,8 +143,8 @@ zipccl_status_t zipccl_compress(const void* d_in, size_t n_elems, zipccl_dtype_t
  * bytes as zipccl_compress, minus the workspace: that is a fixed array of ZIPCCL_STATIC_SCRATCH_BYTES
  * (32 MiB) inside the library's device code, one copy on every GPU the library runs on, held until the process
  * ends.  The call makes no hipMalloc, hipFree or other allocating device call.
- *   - Calls that zipccl_compress would park in its workspace (see there) read the input once up to about 33.5 million values
- *     (zipccl_compress_workspace_size(...) <= 32 MiB), above that twice (the form it takes with its minimum workspace).
+ *   - Its forms are those of zipccl_compress, with zipccl_compress_workspace_size bytes up to about 33.5 million values
+ *     (zipccl_compress_workspace_size(...) <= 32 MiB), above that with the minimum.
  *   - A call whose zipccl_compress_min_workspace_size(...) exceeds 32 MiB (more than about 4.19 million tiles
  *     of 8192 values) returns ZIPCCL_ERR_BUFFER_TOO_SMALL and launches nothing.
  *   - Every call on a GPU uses that GPU's one array: calls that may overlap in time on the same GPU (different

@@ -941,7 +941,7 @@ static void launch_compress_dt(int mode, const CompressArgs& a, hipStream_t s)
 #undef ZIPCCL_LAUNCH
 }
 
-constexpr uint32_t kSmallTiles = 640, kSmallTilesEstimated = 2048, kManyTiles = 8192;     /* of 8192 values: launch_chained_dt, chain_prefix */
+constexpr uint32_t kSmallTiles = 640;                        /* of 8192 values: launch_chained_dt */
 
 /* The tag of a launch (Chain), whose number is counted up from one that differs from process to process.  What a workspace holds of
  * earlier launches of this process has other tags; what else it holds would have to be this very one of 2^40 in a word of a tile
@@ -956,8 +956,6 @@ static uint64_t launch_tag()
     }()};
     return chain_tag(next.fetch_add(1, std::memory_order_relaxed));
 }
-
-static bool is_estimated(const CompressArgs& a) { return a.d_table != nullptr && a.table_stride == 0u; }
 
 /*
  * Groups of a tile and waves that share it in the chained form.  Small launches take small tiles, which fill more of the chip; in larger ones
@@ -997,22 +995,10 @@ static void launch_chained_dt(const CompressArgs& a, hipStream_t s)
     else by_size(a.tab);
 }
 
-/*
- * Not taken for a stream that is being captured: a launch that a graph replays has the same tag every time.  Nor in launches of many bf16
- * tiles whose chunks start off cache lines, where it is no faster (us, with a stash / chained: 8 odd chunks of 67 million
- * normal values 313 / 326, 64 of 4.7 million 179 / 181; of rows with gains among them 336 / 334, 189 / 186).  Nor for bf16 between the sizes
- * where a table for the whole tensor is in device memory: the caches hold part of what the estimate has read, and one launch
- * makes less of that (robust estimate and compress, with a stash / chained, 21 million values 30.8 / 32.7, 60 million 66.2 / 68.0).
- */
+/* Not taken where it does not pay, nor for a stream that is being captured: a launch that a graph replays has the same tag every time. */
 int launch_compress_chained(int dt, const CompressArgs& a, void* stream)
 {
-    const uint32_t tiles = a.tab.tile_start[a.tab.n_chunks];
-    if (dt == ZIPCCL_BF16 && is_estimated(a) && tiles > kSmallTilesEstimated && tiles <= kManyTiles) return kNotTaken;
-    if (dt == ZIPCCL_BF16 && tiles > kManyTiles) {
-        uint64_t off = reinterpret_cast<uintptr_t>(a.in) % 128u;
-        for (uint32_t c = 0; c < a.tab.n_chunks; ++c) off |= a.tab.elem_off[c] * 2u % 128u;
-        if (off != 0u) return kNotTaken;
-    }
+    if (!chained_pays(a, dt)) return kNotTaken;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing((hipStream_t)stream, &capture) != hipSuccess) {
         (void)hipGetLastError();                             /* of this question; the launches in its stead report their own */

@@ -95,13 +95,14 @@ int launch_compress(int dt, int mode, const CompressArgs& a, void*)
     return 0;
 }
 /* kModeChained: not on a stream that is being captured, here where g_chains is not set; the words are 8 bytes per tile */
-static bool g_chains = false;
+static bool g_chains = false, g_pays = false;
 static int g_chained = 0;
 int launch_compress_chained(int dt, const CompressArgs& a, void*)
 {
     check_tab(a.tab);
     check_forms(a.tab, dt);
     CHECK(a.words != nullptr && reinterpret_cast<uintptr_t>(a.words) % 8 == 0);
+    g_pays = chained_pays(a, dt);
     if (!g_chains) return kNotTaken;
     ++g_chained;
     ++g_launches;
@@ -274,6 +275,17 @@ int main()
         std::vector<uint64_t> mixed(129, T);
         mixed[128] = 3 * T;
         chained(ZIPCCL_BF16, mixed, 1, 1);
+    }
+    /* where it pays: not for many bf16 tiles of chunks that start off cache lines, if there is room for a stash */
+    for (bool least : {false, true}) {
+        auto pays = [&](zipccl_dtype_t dt, std::vector<uint64_t> split, bool want) {
+            forms(dt, split, least, 0, 0, 0);
+            CHECK(g_pays == (want || least));
+        };
+        pays(ZIPCCL_BF16, {(kManyTiles - 1) * T - 1, T}, true);
+        pays(ZIPCCL_BF16, {kManyTiles * T / 2 + 1, kManyTiles * T / 2 + 63}, false);
+        pays(ZIPCCL_BF16, {kManyTiles * T / 2 + 64, kManyTiles * T / 2 + 64, 1}, true);
+        pays(ZIPCCL_FP32, {kManyTiles * T / 2 + 1, kManyTiles * T / 2 + 63}, true);
     }
     g_chains = false;
     /* a launch's tag: one of 2^40 - 2, from which what cleared and filled words hold differs as well as its neighbours' */

@@ -137,3 +137,57 @@ def test_the_way_back_to_a_total_is_as_short_in_a_long_chunk():
             took[C].append(start.elapsed_time(end))
         assert torch.equal(got, want) and torch.equal(got_cb, want_cb)
     assert sorted(took[1])[3] < 2 * sorted(took[16])[3], took
+
+
+def _all_forms(n, dtype, ce, call, label):
+    """call(out, sizes, workspace, its bytes), as it is and captured, with room for a stash and without, all in one workspace and twice over:
+    the same bytes from all.  Returns them."""
+    C = len(ce)
+    ws = torch.full((z.zipccl_compress_workspace_size(n, dtype, C, ce),), 0x5A, dtype=torch.uint8, device=DEV)
+    want = None
+    for captured, some in ((True, ws.numel()), (False, ws.numel()), (True, None), (False, None), (False, ws.numel())):
+        print(f"[chain forms] {label} captured={captured} workspace={'full' if some else 'least'}", flush=True)
+        out = torch.full((z.zipccl_max_compressed_size(n, dtype, C, ce),), 0xA5, dtype=torch.uint8, device=DEV)
+        sizes = torch.zeros(C, dtype=torch.int64, device=DEV)
+        some = some or z.zipccl_compress_min_workspace_size(n, dtype, C, ce)
+        if captured:
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                call(out, sizes, ws, some)
+            graph.replay()
+        else:
+            call(out, sizes, ws, some)
+        torch.cuda.synchronize()
+        if want is None:
+            want = out, sizes
+        assert torch.equal(out, want[0]) and torch.equal(sizes, want[1]), (label, captured, some)
+    return want
+
+
+def _device_values(n, dtype, seed):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    x = torch.randn(n, generator=gen, device=DEV).mul_(0.02)
+    x[n // 3:n // 3 + 2 * TILE + 77] = 1.0                                # a stretch of zero-points
+    return x.bfloat16() if dtype == z.BF16 else x
+
+
+# more than 8192 tiles of bf16 values in chunks that start off cache lines: with a stash, if there is room for one; and on lines
+@pytest.mark.parametrize("dtype,sizes", [
+    (z.BF16, [4096 * TILE + 1, 4096 * TILE + 63]), (z.BF16, [4096 * TILE + 64, 4096 * TILE + 64, 1]), (z.BF16, [8191 * TILE - 1, TILE]),
+    (z.FP32, [4096 * TILE + 1, 4096 * TILE + 63]),
+], ids=str)
+def test_many_tiles_on_and_off_cache_lines(dtype, sizes):
+    ce = np.array(sizes, dtype=np.uint64)
+    n, C = int(ce.sum()), len(ce)
+    x = _device_values(n, dtype, 5)
+    table = z.zipccl_build_table(0.02, dtype)
+    out, sizes_got = _all_forms(n, dtype, ce, lambda out, cb, ws, some: z.zipccl_compress(x, n, dtype, C, ce, table, out, cb, ws, workspace_bytes=some), str(sizes))
+    once = torch.full_like(out, 0xA5), torch.zeros_like(sizes_got)
+    z.zipccl_compress_static(x, n, dtype, C, ce, table, *once)
+    assert torch.equal(once[0], out) and torch.equal(once[1], sizes_got)
+    back, status = torch.zeros_like(x), torch.zeros(1, dtype=torch.int32, device=DEV)
+    z.zipccl_decompress(out, back, n, dtype, C, ce, status)
+    as_words = torch.int16 if dtype == z.BF16 else torch.int32
+    assert int(status.item()) == 0 and torch.equal(back.view(as_words), x.view(as_words))
