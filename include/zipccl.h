@@ -108,9 +108,8 @@ zipccl_status_t zipccl_chunk_static_bytes(size_t n_elems, zipccl_dtype_t dt, uin
 
 /* Bytes of device scratch for zipccl_compress.  Most calls are one kernel, which needs the minimum, 8 bytes per 8192
  * elements.  With zipccl_compress_workspace_size bytes (about one byte per element) calls on more than 2^26 bf16 values
- * whose chunks start off 128-byte lines, those of zipccl_compress_device_table on 2^24 to 2^26 bf16 values, and those that are
- * captured into a graph on chunks of more than a few tiles of 8192 values are two: zero-point exponents are parked in the scratch until the
- * per-chunk prefix of section 4.2.3 is known.  With less, but at least zipccl_compress_min_workspace_size bytes, the captured ones read
+ * whose chunks start off 128-byte lines, and those that are captured into a graph on chunks of more than a few tiles of 8192 values are
+ * two: zero-point exponents are parked in the scratch until the per-chunk prefix of section 4.2.3 is known.  With less, but at least zipccl_compress_min_workspace_size bytes, the captured ones read
  * the input twice (count, prefix, emit).  All forms write the same bytes.
  * Both return 0 on invalid arguments. */
 size_t zipccl_compress_workspace_size(size_t n_elems, zipccl_dtype_t dt, uint32_t n_chunks,

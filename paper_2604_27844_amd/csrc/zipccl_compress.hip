@@ -941,7 +941,10 @@ static void launch_compress_dt(int mode, const CompressArgs& a, hipStream_t s)
 #undef ZIPCCL_LAUNCH
 }
 
-constexpr uint32_t kSmallTiles = 640;                        /* of 8192 values: launch_chained_dt */
+/* of 8192 values: launch_chained_dt */
+constexpr uint32_t kSmallTiles = 640;
+template <int DT>
+constexpr uint32_t kSmallTilesEstimated = DT == ZIPCCL_BF16 ? 2304u : 2048u;
 
 /* The tag of a launch (Chain), whose number is counted up from one that differs from process to process.  What a workspace holds of
  * earlier launches of this process has other tags; what else it holds would have to be this very one of 2^40 in a word of a tile
@@ -957,6 +960,9 @@ static uint64_t launch_tag()
     return chain_tag(next.fetch_add(1, std::memory_order_relaxed));
 }
 
+/* Whether the table is one for the whole tensor in device memory. */
+static bool is_estimated(const CompressArgs& a) { return a.d_table != nullptr && a.table_stride == 0u; }
+
 /*
  * Groups of a tile and waves that share it in the chained form.  Small launches take small tiles, which fill more of the chip; in larger ones
  * every round of workgroups ends with a wait, which larger tiles make fewer of.  us, 16 groups and 16 waves / 16 and 8 / 32 and 8 / 32 and
@@ -964,10 +970,15 @@ static uint64_t launch_tag()
  * 43 / 50; fp32 2^20 4.8 / 5.0 / 6.6 / 6.1, 2^22 8.6 / 7.4 / 8.1 / 7.4, 2^23 15.3 / 13.5 / 12.9 / 13.5, 2^24 26.8 / 24.7 / 26.4 / 24.7, 2^27 219 /
  * 193 / 170 / 161.  (64 groups and 16 waves: bf16 2^23 7.5, 2^24 12.9, 2^26 43.5, 64 chunks of 2^23 286, one of 2^29 297; fp32 2^24 25.4, 2^27 167.)
  *
- * A table for the whole tensor in device memory says that an estimate has read the tensor just now, and what the caches hold of it
- * comes so quickly that small tiles last longer.  Robust estimate and compress, 32 groups / 16 and 8 waves / with a stash: bf16 2^23
- * 21.0 / 20.4 / 22.6, 2^24 26.8 / 26.0 / 26.7, 3 * 2^23 33.8 / 37.9 / 34.0; fp32 2^23 26.0 / 22.4 / 25.8, 2^24 39.6 / 38.5 / 39.7.  (Standard deviation and
- * compress: bf16 2^24 24.1 / 25.2 / 26.9, fp32 2^23 23.3 / 23.8 / 26.5.)
+ * A table for the whole tensor in device memory is most often the robust estimate's, which has read the tensor just now, and what the
+ * caches hold of it comes so quickly that small tiles last longer: up to the sizes at which they stop doing so.  us, 8 equal chunks (one and
+ * 64 much the same), estimate and compress, with a stash / 16 groups and 8 waves / 32 groups.  Behind the robust one, three tensors in turn: bf16 2^23 22.1 /
+ * 19.9 / 20.8, 2^24 27.0 / 26.1 / 26.8, 18 * 2^20 28.5 / 27.2 / 28.8, 18.5 * 2^20 30.2 / 30.7 / 30.1, 20 * 2^20 30.3 / 34.0 / 30.0, 2^25 40.1 / 47.3 / 41.0,
+ * 2^26 71.6 / 79.8 / 72.5 (one chunk 75.8 / 87.4 / 71.9); fp32 2^23 24.8 / 21.8 / 25.4, 2^24 39.9 / 38.5 / 39.7, 17 * 2^20 46.0 / 45.9 / 45.2.  The same with more
+ * tensors than the caches hold: bf16 2^23 24.3 / 21.7 / 20.6, 2^24 29.7 / 28.4 / 27.0, 2^25 40.3 / 47.6 / 40.7; fp32 2^23 26.3 / 23.4 / 25.7.  Others pay for the
+ * rule between 10 * 2^20 and its limit.  Standard deviation and compress: bf16 10 * 2^20 22.2 / 20.4 / 19.8, 2^24 27.0 / 26.1 / 24.1; fp32 2^24 41.5 / 39.5 /
+ * 38.4.  A table kept from earlier, and the tensor in the caches: bf16 10 * 2^20 13.0 / 9.9 / 9.9, 2^24 16.4 / 14.6 / 13.4; not there, 14.2 / 12.1 / 10.5 and
+ * 17.5 / 16.9 / 14.0; fp32 2^24 27.3 / 26.2 / 24.8.
  */
 template <int DT>
 static void launch_chained_dt(const CompressArgs& a, hipStream_t s)
@@ -986,7 +997,7 @@ static void launch_chained_dt(const CompressArgs& a, hipStream_t s)
         constexpr std::integral_constant<uint32_t, 16> c16;
         constexpr std::integral_constant<uint32_t, 32> c32;
         if (tiles <= kWideTiles) launch(c16, c16, split);
-        else if (tiles <= (is_estimated(a) ? kSmallTilesEstimated : kSmallTiles)) launch(c8, c16, split);
+        else if (tiles <= (is_estimated(a) ? kSmallTilesEstimated<DT> : kSmallTiles)) launch(c8, c16, split);
         else if constexpr (DT == ZIPCCL_FP32) launch(c16, c32, split);
         else launch(c8, c32, split);
     };

@@ -200,25 +200,19 @@ struct CompressArgs {
     ChunkTab tab;
 };
 
-constexpr uint32_t kSmallTilesEstimated = 2048, kManyTiles = 8192;     /* of 8192 values: chained_pays, launch_chained_dt */
-
-/* Whether the table is one for the whole tensor in device memory. */
-inline bool is_estimated(const CompressArgs& a) { return a.d_table != nullptr && a.table_stride == 0u; }
+constexpr uint32_t kManyTiles = 8192;                /* of 8192 values: chained_pays, launch_chained_dt */
 
 /*
  * Whether a call that is not captured compresses in the chained form rather than with a stash.  Always where the workspace has no room for
  * a stash, as the form without reads its input twice (us, twice / chained: 8 chunks of 21 * 2^20 values in all 26.4 / 17.6, 64 odd ones of
  * 120 million 117 / 77, 8 odd ones of 537 million 494 / 333).  Not in launches of many bf16
  * tiles whose chunks start off cache lines, where it is no faster (us, with a stash / chained: 8 odd chunks of 67 million
- * normal values 313 / 326, 64 of 4.7 million 179 / 181; of rows with gains among them 336 / 334, 189 / 186).  Nor for bf16 between the sizes
- * where a table for the whole tensor is in device memory: the caches hold part of what the estimate has read, and one launch
- * makes less of that (robust estimate and compress, with a stash / chained, 21 million values 30.8 / 32.7, 60 million 66.2 / 68.0).
+ * normal values 313 / 326, 64 of 4.7 million 179 / 181; of rows with gains among them 336 / 334, 189 / 186).
  */
 inline bool chained_pays(const CompressArgs& a, int dt)
 {
     const uint32_t tiles = a.tab.tile_start[a.tab.n_chunks];
     if (a.stash == nullptr || dt != ZIPCCL_BF16) return true;
-    if (is_estimated(a) && tiles > kSmallTilesEstimated && tiles <= kManyTiles) return false;
     uint64_t off = 0;
     if (tiles > kManyTiles) {
         off = reinterpret_cast<uintptr_t>(a.in) % 128u;

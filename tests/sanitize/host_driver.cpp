@@ -286,6 +286,12 @@ int main()
         pays(ZIPCCL_BF16, {kManyTiles * T / 2 + 1, kManyTiles * T / 2 + 63}, false);
         pays(ZIPCCL_BF16, {kManyTiles * T / 2 + 64, kManyTiles * T / 2 + 64, 1}, true);
         pays(ZIPCCL_FP32, {kManyTiles * T / 2 + 1, kManyTiles * T / 2 + 63}, true);
+        for (uint64_t tiles : {2048u, 2049u, 2304u, 2305u, 8191u}) {
+            const uint64_t split[2] = {tiles * T - 77, 77};
+            CHECK(zipccl_compress_device_table(in, tiles * T, ZIPCCL_BF16, 2, split, (const zipccl_table_t*)out, out, big, nullptr, ws,
+                                               least ? zipccl_compress_min_workspace_size(tiles * T, ZIPCCL_BF16, 2, split) : big, nullptr) == ZIPCCL_OK);
+            CHECK(g_pays);
+        }
     }
     g_chains = false;
     /* a launch's tag: one of 2^40 - 2, from which what cleared and filled words hold differs as well as its neighbours' */

@@ -191,3 +191,32 @@ def test_many_tiles_on_and_off_cache_lines(dtype, sizes):
     z.zipccl_decompress(out, back, n, dtype, C, ce, status)
     as_words = torch.int16 if dtype == z.BF16 else torch.int32
     assert int(status.item()) == 0 and torch.equal(back.view(as_words), x.view(as_words))
+
+
+# a table in device memory, one for all chunks (which has the smaller tiles up to 2304 tiles of bf16 and 2048 of fp32 values) or one for each
+@pytest.mark.parametrize("dtype,sizes", [
+    (z.BF16, [9 * TILE + 3] * 3), (z.BF16, [1152 * TILE] * 2), (z.BF16, [1152 * TILE, 1151 * TILE + 1, 1]), (z.BF16, [77, 4097 * TILE + 9, 4000 * TILE]),
+    (z.FP32, [5 * TILE + 1, 9 * TILE]), (z.FP32, [2048 * TILE - 2]), (z.FP32, [700 * TILE + 5, 1349 * TILE]),
+], ids=str)
+def test_tables_in_device_memory(dtype, sizes):
+    ce = np.array(sizes, dtype=np.uint64)
+    n, C = int(ce.sum()), len(ce)
+    x = _device_values(n, dtype, 6)
+    off = z.zipccl_chunk_slot_offsets(n, dtype, C, ce)
+    sigmas = [0.02 * 3.0 ** c for c in range(C)]
+    tables = [z.zipccl_build_table(s, dtype) for s in sigmas]
+    d_tables = torch.tensor([list(bytes(t.dec)) for t in tables], dtype=torch.uint8, device=DEV)
+    cases = {"one": lambda out, cb, ws, some: z.zipccl_compress_device_table(x, n, dtype, C, ce, d_tables, out, cb, ws, workspace_bytes=some),
+             "each": lambda out, cb, ws, some: z.zipccl_compress_chunk_tables(x, n, dtype, C, ce, d_tables, out, cb, ws, workspace_bytes=some)}
+    for name, call in cases.items():
+        out, cb = _all_forms(n, dtype, ce, call, f"{name} {sizes}")
+        start = 0
+        for c in range(C):                                                # as a call of its own, with the table on the host, makes it
+            m = int(ce[c])
+            alone = torch.full((z.zipccl_max_compressed_size(m, dtype),), 0xA5, dtype=torch.uint8, device=DEV)
+            alone_cb = torch.zeros(1, dtype=torch.int64, device=DEV)
+            ws = torch.empty(z.zipccl_compress_workspace_size(m, dtype), dtype=torch.uint8, device=DEV)
+            z.zipccl_compress(x[start:start + m], m, dtype, 1, None, tables[c if name == "each" else 0], alone, alone_cb, ws)
+            assert int(alone_cb.item()) == int(cb[c].item()), (name, c)
+            assert torch.equal(out[int(off[c]):int(off[c]) + int(alone_cb.item())], alone[:int(alone_cb.item())]), (name, c)
+            start += m
