@@ -12,13 +12,8 @@ YARDSTICK = os.path.join(HERE, "libzipccl_yardstick.so")
 SOURCES = ["zipccl_compress.hip", "zipccl_decompress.hip", "zipccl_aux.hip", "zipccl_host.cpp"]
 HEADERS = [os.path.join(CSRC, "zipccl_internal.h"), os.path.join(CSRC, "zipccl_device.h"),
            os.path.join(ROOT, "include", "zipccl.h")]
-# a copy of the compress side whose workgroups do not wait for one another's counts, for the tests of what they do instead
-IMPATIENT = os.path.join(ROOT, "tests", "impatient", "libzipccl_impatient.so")
 TARGETS = {LIB: [os.path.join(CSRC, s) for s in SOURCES],
-           YARDSTICK: [os.path.join(CSRC, "zipccl_yardstick.hip")],
-           IMPATIENT: [os.path.join(CSRC, "zipccl_compress.hip"), os.path.join(CSRC, "zipccl_host.cpp"),
-                       os.path.join(ROOT, "tests", "impatient", "rest.cpp")]}
-FLAGS = {IMPATIENT: ["-DZIPCCL_CHAIN_PATIENCE=0", "-Wl,-Bsymbolic"]}
+           YARDSTICK: [os.path.join(CSRC, "zipccl_yardstick.hip")]}
 
 
 def python_module():
@@ -54,10 +49,16 @@ def _python_command(sources, out):
     return cmd + ["-lc10", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
 
 
+def hip_command(sources, out, flags=()):
+    return [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+            "-Wall", "-Wno-unused-command-line-argument",
+            "-I", os.path.join(ROOT, "include"), "-I", CSRC, *flags, *sources, "-o", out]
+
+
 def build(force=True, verbose=False, lib=None):
     """Compile every target (or the one named); returns the codec library's path.  Without torch the module, which only
     takes its tensors, is left out."""
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     targets = [*TARGETS] if lib is None else [lib]
     if lib is None:
         try:
@@ -69,13 +70,7 @@ def build(force=True, verbose=False, lib=None):
             continue
         sources = _sources(target)
         tmp = target + f".{os.getpid()}.tmp"
-        cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-               "-Wall", "-Wno-unused-command-line-argument",
-               "-I", os.path.join(ROOT, "include"), "-I", CSRC]
-        cmd += FLAGS.get(target, []) + sources + ["-o", tmp]
-        if target not in TARGETS:
-            cmd = _python_command(sources, tmp)
+        cmd = hip_command(sources, tmp) if target in TARGETS else _python_command(sources, tmp)
         if verbose:
             print(" ".join(cmd))
         subprocess.check_call(cmd)

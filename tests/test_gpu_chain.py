@@ -4,6 +4,7 @@ throughout, equal to the oracle's or to those of the captured call, which takes 
 import ctypes
 import os
 
+import impatient_lib
 import numpy as np
 import pytest
 import torch
@@ -17,7 +18,11 @@ if torch.cuda.is_available():
     from gpu_util import DEV, check_parity, gpu_compress, to_device_words
 
 TILE = 8192
-IMPATIENT = os.path.join(os.path.dirname(os.path.abspath(__file__)), "impatient", "libzipccl_impatient.so")
+
+
+@pytest.fixture(scope="module")
+def impatient():
+    return ctypes.CDLL(impatient_lib.LIB if os.path.exists(impatient_lib.LIB) else impatient_lib.build())
 
 
 def _values(n, dtype, seed, sigma=0.02):
@@ -89,9 +94,8 @@ def test_calls_side_by_side_on_several_streams():
     (z.BF16, [3 * TILE]), (z.BF16, [40 * TILE + 3] * 3), (z.BF16, [300 * TILE - 1]), (z.BF16, [100 * TILE + 1] * 8),
     (z.BF16, [2 * TILE * 1160]), (z.FP32, [40 * TILE + 1, 100 * TILE]), (z.FP32, [2 * TILE * 650 + 1]),
 ], ids=str)
-def test_workgroups_that_look_only_once(dtype, sizes):
+def test_workgroups_that_look_only_once(dtype, sizes, impatient):
     """A copy of the library built so that a workgroup looks once for the counts before it and then counts what is missing itself."""
-    lib = ctypes.CDLL(IMPATIENT)
     ce = np.array(sizes, dtype=np.uint64)
     n, C = int(ce.sum()), len(ce)
     print(f"[chain impatient] dtype={dtype} sizes={sizes}", flush=True)
@@ -103,17 +107,16 @@ def test_workgroups_that_look_only_once(dtype, sizes):
     for _ in range(3):
         got = torch.full_like(want, 0xA5)
         got_cb = torch.zeros_like(want_cb)
-        rc = lib.zipccl_compress(vp(d_in.data_ptr()), size(n), ctypes.c_int(dtype), ctypes.c_uint32(C), ce.ctypes.data_as(vp), ctypes.byref(table),
-                                 vp(got.data_ptr()), size(got.numel()), vp(got_cb.data_ptr()), vp(ws.data_ptr()), size(ws.numel()),
-                                 vp(torch.cuda.current_stream().cuda_stream))
+        rc = impatient.zipccl_compress(vp(d_in.data_ptr()), size(n), ctypes.c_int(dtype), ctypes.c_uint32(C), ce.ctypes.data_as(vp), ctypes.byref(table),
+                                       vp(got.data_ptr()), size(got.numel()), vp(got_cb.data_ptr()), vp(ws.data_ptr()), size(ws.numel()),
+                                       vp(torch.cuda.current_stream().cuda_stream))
         torch.cuda.synchronize()
         assert rc == 0 and torch.equal(got, want) and torch.equal(got_cb, want_cb), sizes
 
 
-def test_the_way_back_to_a_total_is_as_short_in_a_long_chunk():
+def test_the_way_back_to_a_total_is_as_short_in_a_long_chunk(impatient):
     """Workgroups that look only once go back to the nearest total that was told, not to the chunk's start: a chunk of 16384 of the larger tiles
     takes them no longer than 16 of 1024 (1.1 times; going back to the start of the chunk it was 4.6)."""
-    lib = ctypes.CDLL(IMPATIENT)
     n = 1 << 28
     print("[chain impatient, long chunk]", flush=True)
     x = (torch.randn(n, device=DEV) * 0.02).bfloat16()
@@ -129,8 +132,8 @@ def test_the_way_back_to_a_total_is_as_short_in_a_long_chunk():
         for _ in range(7):
             start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             start.record()
-            rc = lib.zipccl_compress(vp(x.data_ptr()), size(n), ctypes.c_int(z.BF16), ctypes.c_uint32(C), vp(0), ctypes.byref(table), vp(got.data_ptr()),
-                                     size(got.numel()), vp(got_cb.data_ptr()), vp(ws.data_ptr()), size(ws.numel()), vp(torch.cuda.current_stream().cuda_stream))
+            rc = impatient.zipccl_compress(vp(x.data_ptr()), size(n), ctypes.c_int(z.BF16), ctypes.c_uint32(C), vp(0), ctypes.byref(table), vp(got.data_ptr()),
+                                           size(got.numel()), vp(got_cb.data_ptr()), vp(ws.data_ptr()), size(ws.numel()), vp(torch.cuda.current_stream().cuda_stream))
             end.record()
             torch.cuda.synchronize()
             assert rc == 0
