@@ -205,9 +205,11 @@ constexpr uint32_t kManyTiles = 8192;                /* of 8192 values: chained_
 /*
  * Whether a call that is not captured compresses in the chained form rather than with a stash.  Always where the workspace has no room for
  * a stash, as the form without reads its input twice (us, twice / chained: 8 chunks of 21 * 2^20 values in all 26.4 / 17.6, 64 odd ones of
- * 120 million 117 / 77, 8 odd ones of 537 million 494 / 333).  Not in launches of many bf16
- * tiles whose chunks start off cache lines, where it is no faster (us, with a stash / chained: 8 odd chunks of 67 million
- * normal values 313 / 326, 64 of 4.7 million 179 / 181; of rows with gains among them 336 / 334, 189 / 186).
+ * 120 million 117 / 77, 8 odd ones of 537 million 494 / 333).  Else not in launches of many bf16 tiles whose
+ * chunks start off cache lines, where normal values lose by it, if rows with gains do not (us, with a stash / chained, normal values | rows with gains
+ * among them | Student-t: 8 odd chunks of 70 million in all 48.2 / 50.7 | 53.5 / 52.2 | 49.2 / 50.9, of 120 million 75.7 / 77.1 | 80.3 / 78.7 | 77.0 / 77.2, of
+ * 537 million 320.6 / 331.2 | 348.3 / 341.9 | 332.5 / 334.9; 64 of 120 million 76.5 / 77.1 | 83.4 / 78.7 | 78.6 / 77.5, of 300 million 180.3 / 185.1 |
+ * 190.9 / 188.4 | 183.4 / 183.5).
  */
 inline bool chained_pays(const CompressArgs& a, int dt)
 {
