@@ -21,7 +21,7 @@ TILE = 8192
 
 def split_for_form(data, n_chunks, chunk_elems, form):
     """zipccl_compress takes a launch (128 chunks) in one kernel, whatever the workspace, but for calls that are captured
-    into a graph where a chunk holds more than a few tiles.  by_rule: the call as it is.  stash / reread: a chunk of more
+    into a graph where a chunk holds more than a few tiles, and the largest on chunks that start off cache lines.  by_rule: the call as it is.  stash / reread: a chunk of more
     tiles than that is put behind every 100 chunks that have none, so that the launch, captured (gpu_compress), goes through the
     two-kernel form with a stash, or the one that reads its input twice (which of them, the workspace selects).  Returns
     (data, n_chunks, chunk_elems)."""
@@ -45,8 +45,18 @@ def split_for_form(data, n_chunks, chunk_elems, form):
     return np.concatenate(parts), len(split), np.array(split, dtype=np.uint64)
 
 
+def replayed(call):
+    """The call captured into a graph, which is replayed once."""
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    graph.replay()
+    torch.cuda.synchronize()
+
+
 def gpu_compress(data, dtype, sigma, n_chunks=1, chunk_elems=None, table=None, d_in=None, reread=False,
-                 captured=False):
+                 captured=False, d_ws=None):
     """reread: hand zipccl_compress only its minimum workspace, which selects the form that reads the input
     twice (count, prefix, emit) instead of the single pass with a stash.  captured: the call is captured into a graph, which is
     replayed once (calls that are not, and calls on small chunks, take neither of these forms)."""
@@ -57,16 +67,12 @@ def gpu_compress(data, dtype, sigma, n_chunks=1, chunk_elems=None, table=None, d
     d_in = to_device_words(data) if d_in is None else d_in
     d_out = torch.full((cap,), 0xA5, dtype=torch.uint8, device=DEV)      # poison
     d_cb = torch.full((n_chunks,), -1, dtype=torch.int64, device=DEV)
-    ws = z.zipccl_compress_workspace_size(n, dtype, n_chunks, chunk_elems)
-    d_ws = torch.full((ws,), 0x5A, dtype=torch.uint8, device=DEV)
+    if d_ws is None:
+        d_ws = torch.full((z.zipccl_compress_workspace_size(n, dtype, n_chunks, chunk_elems),), 0x5A, dtype=torch.uint8, device=DEV)
     wsb = z.zipccl_compress_min_workspace_size(n, dtype, n_chunks, chunk_elems) if reread else None
     call = lambda: z.zipccl_compress(d_in, n, dtype, n_chunks, chunk_elems, table, d_out, d_cb, d_ws, workspace_bytes=wsb)
     if captured:
-        torch.cuda.synchronize()
-        graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph):
-            call()
-        graph.replay()
+        replayed(call)
     else:
         call()
     torch.cuda.synchronize()

@@ -15,7 +15,7 @@ from paper_2604_27844_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from gpu_util import DEV, check_parity, gpu_compress, to_device_words
+    from gpu_util import DEV, check_parity, gpu_compress, replayed, to_device_words
 
 TILE = 8192
 
@@ -48,7 +48,8 @@ def test_edges_of_tiles_and_of_what_a_tile_reads(dtype, sizes):
 
 
 def test_a_workspace_that_other_calls_have_left():
-    """The same workspace for calls of several shapes in turn, each twice on other values, and for captured calls between them."""
+    """The same workspace for calls of several shapes in turn, each twice on other values, and for captured calls between them, which leave
+    the counts and prefixes of the form with a stash and of the one that reads twice where the words are."""
     shapes = [[700 * TILE], [40 * TILE + 3] * 8, [9 * TILE], [2 * TILE * 600 + 1], [5 * TILE] * 20]
     ws = torch.full((max(z.zipccl_compress_workspace_size(sum(s), z.BF16, len(s), np.array(s, dtype=np.uint64)) for s in shapes),), 0xFF,
                     dtype=torch.uint8, device=DEV)
@@ -60,7 +61,7 @@ def test_a_workspace_that_other_calls_have_left():
             print(f"[chain workspace] {rep} {s[:2]}", flush=True)
             for seed in (1, 2):
                 data = _values(n, z.BF16, 10 * rep + seed)
-                want, want_cb, _ = gpu_compress(data, z.BF16, 0.02, len(ce), ce, captured=True)
+                want, want_cb, _ = gpu_compress(data, z.BF16, 0.02, len(ce), ce, captured=True, d_ws=ws, reread=seed == 2)
                 got = torch.full_like(want, 0xA5)
                 got_cb = torch.zeros_like(want_cb)
                 z.zipccl_compress(to_device_words(data), n, z.BF16, len(ce), ce, table, got, got_cb, ws)
@@ -154,11 +155,7 @@ def _all_forms(n, dtype, ce, call, label):
         sizes = torch.zeros(C, dtype=torch.int64, device=DEV)
         some = some or z.zipccl_compress_min_workspace_size(n, dtype, C, ce)
         if captured:
-            torch.cuda.synchronize()
-            graph = torch.cuda.CUDAGraph()
-            with torch.cuda.graph(graph):
-                call(out, sizes, ws, some)
-            graph.replay()
+            replayed(lambda: call(out, sizes, ws, some))
         else:
             call(out, sizes, ws, some)
         torch.cuda.synchronize()

@@ -22,7 +22,7 @@ from paper_2604_27844_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from gpu_util import DEV, to_device_words
+    from gpu_util import DEV, replayed, to_device_words
 
 
 def _estimate(d_in, n, dtype):
@@ -207,12 +207,16 @@ def _chunk_tables_case(x, dtype, ce, label):
     assert np.array_equal(np.isnan(got_sig), np.isnan(sig)) and np.array_equal(got_sig[~np.isnan(sig)], sig[~np.isnan(sig)]), label
     cap = z.zipccl_max_compressed_size(n, dtype, C, ce)
     off = z.zipccl_chunk_slot_offsets(n, dtype, C, ce)
-    for reread in (False, True):
+    for captured, reread in ((False, False), (False, True), (True, False), (True, True)):
         d_out = torch.full((cap,), 0xA5, dtype=torch.uint8, device=DEV)
         d_cb = torch.zeros(C, dtype=torch.int64, device=DEV)
         d_ws = torch.empty(z.zipccl_compress_workspace_size(n, dtype, C, ce), dtype=torch.uint8, device=DEV)
         wsb = z.zipccl_compress_min_workspace_size(n, dtype, C, ce) if reread else None
-        z.zipccl_compress_chunk_tables(d_in, n, dtype, C, ce, d_tabs, d_out, d_cb, d_ws, workspace_bytes=wsb)
+        call = lambda: z.zipccl_compress_chunk_tables(d_in, n, dtype, C, ce, d_tabs, d_out, d_cb, d_ws, workspace_bytes=wsb)
+        if captured:
+            replayed(call)
+        else:
+            call()
         torch.cuda.synchronize()
         got, got_cb = d_out.cpu().numpy(), d_cb.cpu().numpy()
         start = 0

@@ -14,7 +14,7 @@ from paper_2604_27844_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from gpu_util import DEV, gpu_compress, to_device_words
+    from gpu_util import DEV, gpu_compress, replayed, to_device_words
 
 
 @pytest.mark.parametrize("name", ["c1", "c2", "c3", "c4", "c5", "c5_fp32"])
@@ -105,7 +105,7 @@ def test_fullsize_reduce_parity(name):
 def test_one_chunk_of_the_largest_sizes(dtype, n, sigma):
     """A single chunk of ZIPCCL_MAX_CHUNK_ELEMS bf16 values (524288 tiles, 2^23 IDX entries, > 2^27 zero-points)
     and an fp32 chunk whose sections start past 4 GiB inside the slot: 64-bit offsets everywhere.  The input
-    repeats a random block (generating 2^32 samples would take minutes); both compress paths."""
+    repeats a random block (generating 2^32 samples would take minutes); all three compress paths."""
     rng = np.random.default_rng(123 + dtype)
     if dtype == z.BF16:
         blk = W.f32_to_bf16_words(rng.standard_normal(2 ** 26, dtype=np.float32) * np.float32(sigma))
@@ -146,12 +146,16 @@ def test_one_chunk_of_the_largest_sizes(dtype, n, sigma):
     assert int(cum[b - 1]) <= (K - 1) // 2 < int(cum[b]), (K, b)
     assert list(d_tab.cpu().numpy()) == list(oracle.build_table(sigma))
     print(f"[huge] robust sigma {float(d_sig.item()):.6g} over {K} magnitudes", flush=True)
-    # full workspace: single pass with a stash; minimum workspace: the input is read twice
-    for wsb in (None, z.zipccl_compress_min_workspace_size(n, dtype, 1)):
-        print(f"[huge] GPU compress, workspace bytes {wsb}", flush=True)
+    # captured, full workspace: single pass with a stash; minimum workspace: the input is read twice; else chained in either
+    for captured, wsb in ((True, None), (True, z.zipccl_compress_min_workspace_size(n, dtype, 1)), (False, None)):
+        print(f"[huge] GPU compress, captured {captured}, workspace bytes {wsb}", flush=True)
         d_out.fill_(0xA5)
-        z.zipccl_compress(d_in, n, dtype, 1, None, z.zipccl_build_table(sigma, dtype), d_out, d_cb, d_ws,
-                          workspace_bytes=wsb)
+        call = lambda: z.zipccl_compress(d_in, n, dtype, 1, None, z.zipccl_build_table(sigma, dtype), d_out, d_cb, d_ws,
+                                         workspace_bytes=wsb)
+        if captured:
+            replayed(call)
+        else:
+            call()
         torch.cuda.synchronize()
         assert int(d_cb.item()) == cb
         for a in range(0, cb, 1 << 30):

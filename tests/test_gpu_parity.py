@@ -16,7 +16,7 @@ from paper_2604_27844_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from gpu_util import DEV, check_parity, gpu_compress, gpu_decompress, to_device_words
+    from gpu_util import DEV, check_parity, gpu_compress, gpu_decompress, replayed, to_device_words
 
 
 def _say(msg):
@@ -177,11 +177,15 @@ def test_small_workspace_takes_the_two_pass_form():
     lo = z.zipccl_compress_min_workspace_size(w.n_elems, w.dtype, w.n_chunks, w.chunk_elems)
     hi = z.zipccl_compress_workspace_size(w.n_elems, w.dtype, w.n_chunks, w.chunk_elems)
     assert lo < hi
-    for ws in (lo, hi - 16, hi):
+    for ws, captured in [(ws, captured) for ws in (lo, hi - 16, hi) for captured in (True, False)]:      # captured: two passes, but for hi
         d_out = torch.full((cap,), 0xA5, dtype=torch.uint8, device=DEV)
         d_cb = torch.zeros(w.n_chunks, dtype=torch.int64, device=DEV)
         d_ws = torch.empty(ws, dtype=torch.uint8, device=DEV)
-        z.zipccl_compress(d_in, w.n_elems, w.dtype, w.n_chunks, w.chunk_elems, table, d_out, d_cb, d_ws)
+        call = lambda: z.zipccl_compress(d_in, w.n_elems, w.dtype, w.n_chunks, w.chunk_elems, table, d_out, d_cb, d_ws)
+        if captured:
+            replayed(call)
+        else:
+            call()
         torch.cuda.synchronize()
         got = d_out.cpu().numpy()
         assert np.array_equal(d_cb.cpu().numpy().astype(np.uint64), ref_cb)

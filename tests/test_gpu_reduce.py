@@ -205,12 +205,13 @@ def test_reduce_into_an_output_that_is_only_element_aligned_and_empty_input():
     assert int(d_st.item()) == 0 and not d_out.cpu().numpy().any()
 
 
-def test_estimate_compress_reduce_chain_replays_inside_a_hip_graph():
+@pytest.mark.parametrize("tiles", [5, 9])                     # the captured compress is one kernel, or two with a stash
+def test_estimate_compress_reduce_chain_replays_inside_a_hip_graph(tiles):
     """Table estimate -> compress with the device table -> fused reduce only launch kernels (no allocation,
     memset or synchronisation), so the chain can be captured; every replay, on fresh input contents and with
     the program's own eager work in between, must equal the oracle's chain."""
     from oracle import sigma as osg
-    P, n = 4, 5 * 8192 + 300                                  # P peer slices = P equal chunks of one tensor
+    P, n = 4, tiles * 8192 + 300                              # P peer slices = P equal chunks of one tensor
     d_in = torch.zeros(P * n, dtype=torch.int16, device=DEV)
     cap = z.zipccl_max_compressed_size(P * n, z.BF16, P)
     d_comp = torch.empty(cap, dtype=torch.uint8, device=DEV)
@@ -253,12 +254,13 @@ def test_estimate_compress_reduce_chain_replays_inside_a_hip_graph():
         assert np.array_equal(d_sum.cpu().numpy().view(np.uint32), want), rep
 
 
+@pytest.mark.parametrize("tiles", [4, 9])                     # as above
 @pytest.mark.parametrize("stride", [1, 4], ids=["every_value", "sampled"])
-def test_chunk_table_estimate_and_compress_chain_replays_inside_a_hip_graph(stride):
+def test_chunk_table_estimate_and_compress_chain_replays_inside_a_hip_graph(stride, tiles):
     """Per-chunk robust tables (from every value, or from a sample) -> compress with them -> fused reduce, captured
     and replayed: the histogram state is zeroed by a kernel of the chain itself, so every replay starts clean."""
     from oracle import sigma as osg
-    P, n = 3, 4 * 8192 + 77
+    P, n = 3, tiles * 8192 + 77
     d_in = torch.zeros(P * n, dtype=torch.int16, device=DEV)
     cap = z.zipccl_max_compressed_size(P * n, z.BF16, P)
     d_comp = torch.empty(cap, dtype=torch.uint8, device=DEV)

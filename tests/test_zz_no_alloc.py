@@ -11,32 +11,37 @@ from paper_2604_27844_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from gpu_util import DEV, to_device_words
+    from gpu_util import DEV, replayed, to_device_words
 
 LIMIT = 32 << 20
 
 
 def _both(data, dtype, sigma, n_chunks, chunk_elems, label):
-    """Compress with the caller-workspace entry point and with the static one into poisoned buffers; everything
-    must be equal: written bytes, untouched bytes, chunk_bytes."""
+    """Compress with the caller-workspace entry point and with the static one, as it is and captured, into poisoned buffers;
+    everything must be equal: written bytes, untouched bytes, chunk_bytes."""
     n = int(data.size)
     print(f"[static] {label}: n={n} chunks={n_chunks}", flush=True)
     table = z.zipccl_build_table(sigma, dtype)
     cap = z.zipccl_max_compressed_size(n, dtype, n_chunks, chunk_elems)
     d_in = to_device_words(data)
     ws = z.zipccl_compress_workspace_size(n, dtype, n_chunks, chunk_elems)
-    # the existing entry point in the form the static one will take: single pass if its workspace fits the array
+    # the existing entry point with as much workspace as the static one has
     d_ws = torch.full((ws,), 0x5A, dtype=torch.uint8, device=DEV)
     wsb = None if ws <= LIMIT else z.zipccl_compress_min_workspace_size(n, dtype, n_chunks, chunk_elems)
     want = torch.full((cap,), 0xA5, dtype=torch.uint8, device=DEV)
     want_cb = torch.full((n_chunks,), -1, dtype=torch.int64, device=DEV)
     z.zipccl_compress(d_in, n, dtype, n_chunks, chunk_elems, table, want, want_cb, d_ws, workspace_bytes=wsb)
-    got = torch.full((cap,), 0xA5, dtype=torch.uint8, device=DEV)
-    got_cb = torch.full((n_chunks,), -1, dtype=torch.int64, device=DEV)
-    z.zipccl_compress_static(d_in, n, dtype, n_chunks, chunk_elems, table, got, got_cb)
-    torch.cuda.synchronize()
-    assert torch.equal(got_cb, want_cb), label
-    assert torch.equal(got, want), label
+    for captured in (False, True):
+        got = torch.full((cap,), 0xA5, dtype=torch.uint8, device=DEV)
+        got_cb = torch.full((n_chunks,), -1, dtype=torch.int64, device=DEV)
+        call = lambda: z.zipccl_compress_static(d_in, n, dtype, n_chunks, chunk_elems, table, got, got_cb)
+        if captured:
+            replayed(call)
+        else:
+            call()
+        torch.cuda.synchronize()
+        assert torch.equal(got_cb, want_cb), (label, captured)
+        assert torch.equal(got, want), (label, captured)
     # and it decodes to the input
     d_back = torch.zeros_like(d_in)
     d_st = torch.zeros(1, dtype=torch.int32, device=DEV)
@@ -47,11 +52,11 @@ def _both(data, dtype, sigma, n_chunks, chunk_elems, label):
 
 def test_static_workspace_compress_equals_compress_on_calls_in_a_row():
     rng = np.random.default_rng(21)
-    # 1: larger than the array holds a stash for (two reads of the input), 8 chunks
+    # 1: larger than the array holds a stash for (captured: two reads of the input), 8 chunks
     big = W.f32_to_bf16_words(rng.standard_normal(40_000_000, dtype=np.float32) * np.float32(0.02))
     big[::3] = 0x7F80                                                  # many zero-points: a busy stash / list
-    _both(big, z.BF16, 0.02, 8, None, "two-read form")
-    # 2: smaller, ragged with an empty chunk, single read with a stash in the same array
+    _both(big, z.BF16, 0.02, 8, None, "no room for a stash")
+    # 2: smaller, ragged with an empty chunk (captured: a chunk of more tiles than a compress without a workspace takes, a stash in the same array)
     ce = np.array([100_000, 0, 8192 * 7 + 5, 1, 300_001], dtype=np.uint64)
     mid = W.f32_to_bf16_words(rng.standard_normal(int(ce.sum()), dtype=np.float32))
     _both(mid, z.BF16, 1.0, len(ce), ce, "ragged, smaller")
