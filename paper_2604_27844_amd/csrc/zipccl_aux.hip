@@ -651,7 +651,7 @@ __global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a,
 {
     constexpr uint32_t ES = DT == ZIPCCL_BF16 ? 2u : 4u;
     constexpr uint32_t NV = DT == ZIPCCL_BF16 ? 1u : 2u;     /* 16-byte pieces per lane and group */
-    constexpr uint32_t NF = 2;                               /* groups in flight per wave (four: 2^27 bf16 values 50 us instead of 48) */
+    constexpr uint32_t NF = 2;                               /* groups in flight per wave (four: one chunk of 2^27 bf16 values 50 us instead of 48) */
     __shared__ __attribute__((aligned(16))) uint32_t s_sample[512];
     __shared__ uint32_t s_cnt[32];
     /* below, window, above (or not counted): outside the window a counter per lane and side, both on the lane's own bank */
@@ -720,7 +720,7 @@ __global__ __launch_bounds__(kHistThreads) void k_window_count(const RobustIo a,
         }
     };
     /* A group's successor is requested as soon as it is counted, not both once both are: one chunk of 2^27 fp32 values 86.3 -> 83.5 us,
-       64 of 2^21 90.3 -> 87.3; bf16 2^25 in 64 20.4 -> 19.6, 2^27 55.8 -> 55.3. */
+       64 of 2^21 90.3 -> 87.3; bf16 64 of 2^19 20.4 -> 19.8, 64 of 2^21 55.7 -> 55.2, one of 2^27 the same (48.3, 48.2). */
     while (k0 < whole) {
 #pragma unroll
         for (uint32_t u = 0; u < NF; ++u) {

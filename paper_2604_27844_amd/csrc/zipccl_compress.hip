@@ -11,16 +11,18 @@
  *              Plane bytes and zero-point exponents are staged in LDS and leave as wide
  *              stores.  The zero-point offsets of section 4.2.3 are an exclusive prefix in
  *              element order (lane -> wave -> tile -> chunk), so the output is deterministic.
- *              The chunk-wide level, which the paper does with a block-level atomic add, has three forms.
- *              k_compress<kModeDirect>, chunks of one or two tiles: a workgroup counts the zero-points of its
- *              chunk's tile before its own itself.
- *              k_compress<kModeChained>, all other calls: a workgroup tells its tile's count as soon as the values are
- *              there, writes everything whose place is known (SM, LO, planes) and then adds up what the tiles
+ *              The chunk-wide level, which the paper does with a block-level atomic add, has four forms.
+ *              k_compress<kModeDirect>, chunks of a few tiles (two at most where the next form can be had): a workgroup counts
+ *              the zero-points of its chunk's tiles before its own itself.
+ *              k_compress<kModeChained>, a scan in one pass by tagged words: a workgroup tells its tile's count as soon as the values
+ *              are there, writes everything whose place is known (SM, LO, planes) and then adds up what the tiles
  *              before have told (chain_prefix, which bounds that wait).  One launch, nothing moved twice.
- *              k_compress<kModeStash>, calls that are captured into a graph (see launch_compress_chained):
+ *              k_compress<kModeStash>, calls that may not chain (launch_compress_chained) or had better not (chained_pays):
  *              the zero-point exponents are parked in a stash; the per-tile counts become per-chunk prefixes inside
  *              k_place (chunks of up to kPlaceScanTiles tiles) or in k_tile_scan; k_place moves each
  *              tile's exponents to their final place and finishes index and header.
+ *              k_compress<kModeCount> and <kModeEmit>, calls that may not chain, without room for a stash: counts,
+ *              k_tile_scan, and everything else from a second read.
  * Everything here is integer work.
  */
 #include <atomic>

@@ -148,8 +148,7 @@ ZIPCCL_HD FewSplit few_split(const ChunkTab& t)
     return f;
 }
 
-/* Where chunk c of a launch lies, and its tiles: how many, and the number of the first among the launch's (not given by a
- * FewSplit, which serves the kernels that do without). */
+/* Where chunk c of a launch lies, and its tiles: how many, and the number of the first among the launch's. */
 struct ChunkPlace {
     uint64_t elem_off, n, slot_off;
     uint32_t tile, tiles;
@@ -310,10 +309,6 @@ struct DecompressArgs {
     ChunkTab tab;
 };
 
-/* kModeStash: single pass over the input; zero-point exponents go to a stash at a position that
- * does not depend on other tiles, and k_place moves them once the tile prefixes are known.
- * kModeCount + kModeEmit: the same without a stash, reading the input twice.
- * kModeDirect: one launch for small chunks; every workgroup counts the zero-points of its chunk's tiles before its own. */
 struct ReduceArgs {
     const uint8_t* comp;     /* n_peers slots of n values each, back to back */
     uint64_t comp_capacity;  /* readable bytes from comp */
@@ -329,6 +324,11 @@ struct ReduceArgs {
     uint32_t gpw_rest;       /* groups per wave in the workgroups after them, which take the rest of the shard */
 };
 
+/* kModeStash: single pass over the input; zero-point exponents go to a stash at a position that
+ * does not depend on other tiles, and k_place moves them once the tile prefixes are known.
+ * kModeCount + kModeEmit: the same without a stash, reading the input twice.
+ * kModeDirect: one launch for small chunks; every workgroup counts the zero-points of its chunk's tiles before its own.
+ * kModeChained: one launch; every workgroup adds up the counts that its chunk's tiles before have told. */
 enum CompressMode { kModeCount = 0, kModeEmit = 1, kModeStash = 2, kModeDirect = 3, kModeChained = 4 };
 
 /* launchers implemented next to their kernels (zipccl_compress.hip, zipccl_decompress.hip, zipccl_aux.hip);
