@@ -84,7 +84,8 @@ uint64_t total_tiles(const std::vector<uint64_t>& ce)
     return t;
 }
 
-/* Workspace layout: header | u32 count per tile | u32 prefix per tile | [stash (one byte per element)]. */
+/* Workspace layout: header | u32 count per tile | u32 prefix per tile, or a 64-bit word per tile where these are (chained form) |
+ * [stash (one byte per element)]. */
 struct WorkspacePlan {
     uint64_t tiles, total_off, prefix_off, stash_off, min_bytes, full_bytes;
 };
